@@ -1,10 +1,13 @@
-"""ctypes binding of libreader_hip.so: argument marshalling only.
+"""Python binding of libreader_hip.so: argument marshalling only.
 
 Every function has the name and argument order of its C entry point in
 ``include/reader.h``; tensors are torch CUDA (ROCm) tensors whose ``data_ptr()`` is
 handed through, and every kernel is enqueued on torch's current stream.  Nothing is
 computed here, and there is no fallback: if the library has not been built, or a
 tensor is not on the GPU, the call raises.
+
+The calls of a decoding loop go through a small extension module (``csrc/torch_binding.cpp``),
+which takes the tensors apart in native code; everything else is ctypes.
 """
 from __future__ import annotations
 
@@ -14,6 +17,7 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libreader_hip.so")
+NATIVE_PATH = os.path.join(_HERE, "_reader_torch.so")
 
 READER_OK = 0
 READER_EINVAL = -1
@@ -61,15 +65,23 @@ class ReaderError(RuntimeError):
 
 
 _lib = None
+_native = None      # the extension module, once it is loaded and knows the library
+
+
+def _load_native():
+    """The extension module (loads the library first)."""
+    load()
+    return _native
 
 
 def load():
     """Load the library; raises if it has not been built (python -m paper_2508_09072_amd.build)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError("HIP library missing: %s (run `python -m paper_2508_09072_amd.build`)" % LIB_PATH)
+    for path in (LIB_PATH, NATIVE_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError("HIP library missing: %s (run `python -m paper_2508_09072_amd.build`)" % path)
     # PyTorch first: it brings its own copy of the HIP runtime, and the tensors and streams handed to
     # the library belong to that one.  Loaded the other way round the process ends up with the
     # library's kernels registered in a runtime that PyTorch's streams do not belong to, and every
@@ -140,6 +152,9 @@ def load():
     lib.reader_profile_collect_each.argtypes = [vp, i32, ctypes.POINTER(i32)]
     lib.reader_tuning_override.restype = ctypes.c_int
     lib.reader_tuning_override.argtypes = [i32, i32]
+    from . import _reader_torch
+    _reader_torch.init(lib._handle)
+    _native = _reader_torch
     _lib = lib
     return lib
 
@@ -219,16 +234,10 @@ def reader_workspace_bytes(dims: ReaderDims, max_seq_len: int) -> int:
 
 def reader_tree_attn(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, out,
                      lse, max_seq_len, workspace, status=None):
-    import torch
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    code = load().reader_tree_attn(
-        ctypes.byref(dims), _dev(q, torch.bfloat16), _dev(k_tree, torch.bfloat16, optional=True),
-        _dev(v_tree, torch.bfloat16, optional=True),
-        _dev(k_cache, torch.bfloat16), _dev(v_cache, torch.bfloat16), _dev(page_table, torch.int32),
-        _dev(seq_lens, torch.int32), _dev(parents, torch.int32), _dev(out, torch.bfloat16),
-        _dev(lse, torch.float32, optional=True), int(max_seq_len), _dev(workspace, optional=True),
-        ws_bytes, _dev(status, torch.int32, optional=True), _stream())
-    _check(code, "reader_tree_attn")
+    code = (_native or _load_native()).tree_attn(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents,
+                                                 out, lse, max_seq_len, workspace, status)
+    if code:
+        _check(code, "reader_tree_attn")
 
 
 NOALLOC_WORKSPACE_BYTES = 40 << 20
@@ -236,49 +245,33 @@ NOALLOC_WORKSPACE_BYTES = 40 << 20
 
 def reader_tree_attn_noalloc(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, out, lse,
                              max_seq_len, status=None):
-    import torch
-    code = load().reader_tree_attn_noalloc(
-        ctypes.byref(dims), _dev(q, torch.bfloat16, optional=dims.B == 0), _dev(k_tree, torch.bfloat16, optional=True),
-        _dev(v_tree, torch.bfloat16, optional=True),
-        _dev(k_cache, torch.bfloat16, optional=dims.B == 0), _dev(v_cache, torch.bfloat16, optional=dims.B == 0),
-        _dev(page_table, torch.int32, optional=dims.B == 0), _dev(seq_lens, torch.int32, optional=dims.B == 0),
-        _dev(parents, torch.int32, optional=dims.B == 0), _dev(out, torch.bfloat16, optional=dims.B == 0),
-        _dev(lse, torch.float32, optional=True), int(max_seq_len), _dev(status, torch.int32, optional=True), _stream())
-    _check(code, "reader_tree_attn_noalloc")
+    code = (_native or _load_native()).tree_attn_noalloc(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens,
+                                                         parents, out, lse, max_seq_len, status)
+    if code:
+        _check(code, "reader_tree_attn_noalloc")
 
 
 def reader_accept_path(dims, draft_tokens, target_tokens, parents, accept_len, path, bonus_token, status=None):
-    import torch
-    code = load().reader_accept_path(
-        ctypes.byref(dims), _dev(draft_tokens, torch.int32), _dev(target_tokens, torch.int32),
-        _dev(parents, torch.int32), _dev(accept_len, torch.int32), _dev(path, torch.int32),
-        _dev(bonus_token, torch.int32), _dev(status, torch.int32, optional=True), _stream())
-    _check(code, "reader_accept_path")
+    code = (_native or _load_native()).accept_path(dims, draft_tokens, target_tokens, parents, accept_len, path, bonus_token,
+                                                   status)
+    if code:
+        _check(code, "reader_accept_path")
 
 
 def reader_kv_compact(dims, k_tree, v_tree, path, accept_len, k_cache, v_cache, page_table, seq_lens, status=None):
-    import torch
-    code = load().reader_kv_compact(
-        ctypes.byref(dims), _dev(k_tree, torch.bfloat16), _dev(v_tree, torch.bfloat16), _dev(path, torch.int32),
-        _dev(accept_len, torch.int32), _dev(k_cache, torch.bfloat16), _dev(v_cache, torch.bfloat16),
-        _dev(page_table, torch.int32), _dev(seq_lens, torch.int32), _dev(status, torch.int32, optional=True),
-        _stream())
-    _check(code, "reader_kv_compact")
+    code = (_native or _load_native()).kv_compact(dims, k_tree, v_tree, path, accept_len, k_cache, v_cache, page_table,
+                                                  seq_lens, status)
+    if code:
+        _check(code, "reader_kv_compact")
 
 
 def reader_verify_step(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, draft_tokens,
                        target_tokens, out, lse, accept_len, path, bonus_token, max_seq_len, workspace, status=None):
-    import torch
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    code = load().reader_verify_step(
-        ctypes.byref(dims), _dev(q, torch.bfloat16), _dev(k_tree, torch.bfloat16, optional=True),
-        _dev(v_tree, torch.bfloat16, optional=True),
-        _dev(k_cache, torch.bfloat16), _dev(v_cache, torch.bfloat16), _dev(page_table, torch.int32),
-        _dev(seq_lens, torch.int32), _dev(parents, torch.int32), _dev(draft_tokens, torch.int32),
-        _dev(target_tokens, torch.int32), _dev(out, torch.bfloat16), _dev(lse, torch.float32, optional=True),
-        _dev(accept_len, torch.int32), _dev(path, torch.int32), _dev(bonus_token, torch.int32), int(max_seq_len),
-        _dev(workspace, optional=True), ws_bytes, _dev(status, torch.int32, optional=True), _stream())
-    _check(code, "reader_verify_step")
+    code = (_native or _load_native()).verify_step(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents,
+                                                   draft_tokens, target_tokens, out, lse, accept_len, path, bonus_token,
+                                                   max_seq_len, workspace, status)
+    if code:
+        _check(code, "reader_verify_step")
 
 
 def reader_kv_rearrange_scratch_bytes(B: int, S: int) -> int:
@@ -288,46 +281,31 @@ def reader_kv_rearrange_scratch_bytes(B: int, S: int) -> int:
 def reader_kv_rearrange(k_pad, v_pad, valid, new_len, scratch):
     """k_pad, v_pad: bf16 [NL, B, S, Hkv, D] device tensors (in place); valid: uint8 [B, S] (in place);
     new_len: int32 [B] (out); scratch: uint8 device tensor of reader_kv_rearrange_scratch_bytes(B, S)."""
-    import torch
-    NL, B, S, Hkv, D = k_pad.shape
-    assert tuple(v_pad.shape) == (NL, B, S, Hkv, D) and tuple(valid.shape) == (B, S) and tuple(new_len.shape) == (B,)
-    code = load().reader_kv_rearrange(
-        NL, B, S, Hkv, D, _dev(k_pad, torch.bfloat16), _dev(v_pad, torch.bfloat16), _dev(valid, torch.uint8),
-        _dev(new_len, torch.int32), _dev(scratch), scratch.numel() * scratch.element_size(), _stream())
-    _check(code, "reader_kv_rearrange")
+    code = (_native or _load_native()).kv_rearrange(k_pad, v_pad, valid, new_len, scratch)
+    if code:
+        _check(code, "reader_kv_rearrange")
 
 
 def reader_target_argmax(logits, target_tokens):
     """logits: bf16 [..., V] device tensor; target_tokens: int32 tensor with one entry per row."""
-    import torch
-    V = logits.shape[-1]
-    rows = logits.numel() // V
-    assert target_tokens.numel() == rows
-    code = load().reader_target_argmax(rows, V, _dev(logits, torch.bfloat16), _dev(target_tokens, torch.int32), _stream())
-    _check(code, "reader_target_argmax")
+    code = (_native or _load_native()).target_argmax(logits, target_tokens)
+    if code:
+        _check(code, "reader_target_argmax")
 
 
 def reader_kv_compact_layers(dims, path, accept_len, k_cache, v_cache, page_table, seq_lens, status=None):
     """k_cache, v_cache: bf16 [num_layers, num_pages, Hkv, page_size, D] device tensors (moved in place)."""
-    import torch
-    NL = k_cache.shape[0]
-    assert tuple(v_cache.shape) == tuple(k_cache.shape) and k_cache.dim() == 5
-    code = load().reader_kv_compact_layers(
-        ctypes.byref(dims), NL, _dev(path, torch.int32), _dev(accept_len, torch.int32), _dev(k_cache, torch.bfloat16),
-        _dev(v_cache, torch.bfloat16), _dev(page_table, torch.int32), _dev(seq_lens, torch.int32),
-        _dev(status, torch.int32, optional=True), _stream())
-    _check(code, "reader_kv_compact_layers")
+    code = (_native or _load_native()).kv_compact_layers(dims, path, accept_len, k_cache, v_cache, page_table, seq_lens,
+                                                         status)
+    if code:
+        _check(code, "reader_kv_compact_layers")
 
 
 def reader_target_sample(logits, parents, uniforms, temperature, target_tokens):
     """logits: bf16 [B, T, V]; parents: int32 [B, T]; uniforms: float32 [B, T]; target_tokens: int32 [B, T]."""
-    import torch
-    B, T, V = logits.shape
-    assert tuple(parents.shape) == (B, T) and tuple(uniforms.shape) == (B, T) and tuple(target_tokens.shape) == (B, T)
-    code = load().reader_target_sample(B, T, V, _dev(logits, torch.bfloat16), _dev(parents, torch.int32),
-                                       _dev(uniforms, torch.float32), float(temperature),
-                                       _dev(target_tokens, torch.int32), _stream())
-    _check(code, "reader_target_sample")
+    code = (_native or _load_native()).target_sample(logits, parents, uniforms, temperature, target_tokens)
+    if code:
+        _check(code, "reader_target_sample")
 
 
 def _host_i32(a):
@@ -355,40 +333,20 @@ class Trie:
         return int(load().reader_trie_nodes(self._h))
 
     def insert(self, tokens):
-        a, p = _host_i32(tokens)
-        _check(load().reader_trie_insert(self._h, p, a.size), "reader_trie_insert")
+        code = _native.trie_insert(self._h or 0, tokens)
+        if code:
+            _check(code, "reader_trie_insert")
 
     def search_path(self, suffix, depth: int):
-        import numpy as np
-        a, p = _host_i32(suffix)
-        out = np.zeros(max(int(depth), 1), dtype=np.int32)
-        k = load().reader_trie_search_path(self._h, p, a.size, int(depth), ctypes.c_void_p(out.ctypes.data))
-        if k < 0:
-            raise ValueError("reader_trie_search_path: bad argument")
-        return out[:k].copy()
+        return _native.trie_search_path(self._h or 0, suffix, depth)
 
     def extract_tree(self, suffix, max_depth: int, budget: int):
-        import numpy as np
-        a, p = _host_i32(suffix)
-        tokens = np.zeros(max(int(budget), 1), dtype=np.int32)
-        parents = np.zeros(max(int(budget), 1), dtype=np.int32)
-        n = load().reader_trie_extract_tree(self._h, p, a.size, int(max_depth), int(budget),
-                                            ctypes.c_void_p(tokens.ctypes.data), ctypes.c_void_p(parents.ctypes.data))
-        if n < 0:
-            raise ValueError("reader_trie_extract_tree: bad argument")
-        return tokens[:n].copy(), parents[:n].copy()
+        return _native.trie_extract_tree(self._h or 0, suffix, max_depth, budget)
 
 
 def reader_tree_attach_path(tokens, parents, n_nodes: int, at_node: int, path_tokens) -> int:
     """tokens, parents: writable numpy int32 arrays of equal capacity; returns the new node count."""
-    import numpy as np
-    assert tokens.dtype == np.int32 and parents.dtype == np.int32 and tokens.size == parents.size
-    a, p = _host_i32(path_tokens)
-    n = load().reader_tree_attach_path(ctypes.c_void_p(tokens.ctypes.data), ctypes.c_void_p(parents.ctypes.data),
-                                       int(n_nodes), tokens.size, int(at_node), p, a.size)
-    if n < 0:
-        raise ValueError("reader_tree_attach_path: bad argument")
-    return int(n)
+    return (_native or _load_native()).tree_attach_path(tokens, parents, n_nodes, at_node, path_tokens)
 
 
 def _host_f32(a):

@@ -1,9 +1,10 @@
-"""Build libreader_hip.so for gfx950 with hipcc (no torch involved).
+"""Build libreader_hip.so for gfx950 with hipcc (no torch involved), and the extension module that
+hands torch tensors and numpy arrays to it.
 
     python -m paper_2508_09072_amd.build
 
-The library is written in-tree next to this file so that it travels with the
-source tree; it is not installed anywhere else.
+Both are written in-tree next to this file so that they travel with the
+source tree; nothing is installed anywhere else.
 """
 from __future__ import annotations
 
@@ -18,6 +19,8 @@ LIB = os.path.join(HERE, "libreader_hip.so")
 # the same library with per-workgroup time stamps in the 128-row attention kernel (python -m ...build --stamps;
 # used by wg_timeline.py only)
 STAMPS_LIB = os.path.join(HERE, "libreader_hip_stamps.so")
+# the extension module binding.py calls the library through (torch tensors and numpy arrays to pointers)
+NATIVE = os.path.join(HERE, "_reader_torch.so")
 SOURCES = ["reader_api.hip", "trie_drafter.cpp", "tree_shape.cpp", "accept_compact.hip", "kv_compact_layers.hip", "kv_rearrange.hip", "target_argmax.hip", "target_sample.hip", "tree_attn_scalar.hip", "tree_attn_mfma.hip", "tree_attn_wide.hip", "peak_probes.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -88,7 +91,40 @@ def check_wide_kernel(hipcc: str, verbose: bool) -> None:
         print("tree_attn_wide.hip: accumulation registers are touched by hand-written instructions only")
 
 
+def build_native(verbose: bool = False) -> str:
+    """The extension module of binding.py (host code: g++, against the installed torch and numpy headers)."""
+    import sysconfig
+
+    import numpy
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    system = [os.path.join(troot, "include"), os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+              os.path.join(rocm, "include"), numpy.get_include(), sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + os.path.join(ROOT, "include")]
+    for d in system:
+        cmd += ["-isystem", d]
+    # (torch is imported before the module: its libraries are in the process already, no search path needed)
+    cmd += [os.path.join(CSRC, "torch_binding.cpp"), "-L" + os.path.join(troot, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+            "-lc10_hip", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building the extension module failed:\n" + res.stdout)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build(verbose: bool = False, stamps: bool = False) -> str:
+    """Both halves: the library (or its profiling variant) and the extension module.  Returns the library's path."""
+    build_native(verbose)
+    return build_library(verbose, stamps)
+
+
+def build_library(verbose: bool = False, stamps: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     lib = STAMPS_LIB if stamps else LIB
     tmp = lib + ".tmp.%d" % os.getpid()
