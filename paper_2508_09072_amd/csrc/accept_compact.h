@@ -96,9 +96,9 @@ __device__ inline void accept_path_body(const AcceptParams &p, int b, int lane, 
         depth_term = best >> 8;
         n_out = min(depth_term, p.max_path - 1);
         if (lane == (term & 63)) {
-            const int s = term >> 6;
-            sh.term[0] = a_lo[s];
-            sh.term[1] = a_hi[s];
+            // (a choice, not an index: an indexed array would live in scratch memory)
+            sh.term[0] = term < 64 ? a_lo[0] : a_lo[1];
+            sh.term[1] = term < 64 ? a_hi[0] : a_hi[1];
         }
         if (lane == 0) sh.accept_len = n_out;
     }
@@ -185,6 +185,8 @@ __device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, i
     // time: their rows are asked for together and stored afterwards (taken one by one, every accepted token
     // costs a trip to memory).  The loads carry no condition (an entry past the path reads the last one
     // again), so that they stay together in front of the stores.
+    // (held in a native vector type: an array of uint4 goes through scratch memory, one more trip)
+    typedef unsigned int held_t __attribute__((ext_vector_type(4)));
     constexpr int kBatch = 8;
     for (int rem = tid; rem < 2 * chunks_per_row; rem += 256) {
         const int which = rem / chunks_per_row;
@@ -194,17 +196,17 @@ __device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, i
         const uint16_t *tree = (which ? p.v_tree : p.k_tree) + ((size_t)b * p.T * p.Hkv + h) * p.D + dc * 8;
         uint16_t *cache = (which ? p.v_cache : p.k_cache) + (size_t)h * READER_PAGE_SIZE * p.D + dc * 8;
         for (int j0 = 0; j0 <= n; j0 += kBatch) {
-            uint4 held[kBatch];
+            held_t held[kBatch];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u)
-                held[u] = *reinterpret_cast<const uint4 *>(tree + (size_t)path[min(j0 + u, n)] * p.Hkv * p.D);
+                held[u] = *reinterpret_cast<const held_t *>(tree + (size_t)path[min(j0 + u, n)] * p.Hkv * p.D);
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
                 const int j = j0 + u;
                 if (j <= n) {
                     const long long page = cs.page[j];
                     const int slot = (L + j) % READER_PAGE_SIZE;
-                    *reinterpret_cast<uint4 *>(cache + ((size_t)page * p.Hkv * READER_PAGE_SIZE + slot) * p.D) = held[u];
+                    *reinterpret_cast<held_t *>(cache + ((size_t)page * p.Hkv * READER_PAGE_SIZE + slot) * p.D) = held[u];
                 }
             }
         }

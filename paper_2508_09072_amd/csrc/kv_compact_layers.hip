@@ -23,6 +23,8 @@ namespace {
 
 constexpr int kMoveThreads = 256;
 constexpr int kMovePerThread = 8;      // 16-byte chunks a thread carries through one pass
+// (a native vector type: an array of uint4 goes through scratch memory, one more trip per pass)
+typedef unsigned int held_t __attribute__((ext_vector_type(4)));
 
 // tickets taken by the workgroups of sequence b in the call that is running (0 between calls)
 __device__ unsigned g_tickets[READER_MAX_B];
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(kMoveThreads) void compact_layers_move_kernel(Compa
     // items: (K or V, head, j = 1..n, chunk), in that order; a pass takes kMoveThreads * kMovePerThread of them
     const int per_stream = n * cpr, total = 2 * p.Hkv * per_stream;
     for (int base = 0; base < total; base += kMoveThreads * kMovePerThread) {
-        uint4 held[kMovePerThread];
+        held_t held[kMovePerThread];
         size_t dst[kMovePerThread];
         uint16_t *cache_of[kMovePerThread];
 #pragma unroll
@@ -100,7 +102,7 @@ __global__ __launch_bounds__(kMoveThreads) void compact_layers_move_kernel(Compa
                     uint16_t *cache = (which ? p.v_cache : p.k_cache) + layer_off;
                     const size_t src = (((size_t)sh.src_page[j] * p.Hkv + h) * READER_PAGE_SIZE + (L + node) % READER_PAGE_SIZE) * p.D + c * 8;
                     dst[r] = (((size_t)sh.dst_page[j] * p.Hkv + h) * READER_PAGE_SIZE + (L + j) % READER_PAGE_SIZE) * p.D + c * 8;
-                    held[r] = *reinterpret_cast<const uint4 *>(cache + src);
+                    held[r] = *reinterpret_cast<const held_t *>(cache + src);
                     cache_of[r] = cache;
                 }
             }
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(kMoveThreads) void compact_layers_move_kernel(Compa
         __syncthreads();   // every row of this pass has been read
 #pragma unroll
         for (int r = 0; r < kMovePerThread; ++r)
-            if (cache_of[r]) *reinterpret_cast<uint4 *>(cache_of[r] + dst[r]) = held[r];
+            if (cache_of[r]) *reinterpret_cast<held_t *>(cache_of[r] + dst[r]) = held[r];
     }
     // the last workgroup of the sequence to get here writes the new length (nobody needs the old one any more)
     if (tid == 0) {
