@@ -134,11 +134,12 @@ enum reader_attn_kernel {
     READER_ATTN_KERNEL_SCALAR = 0,          /* dims->variant = 1: the scalar reference kernel */
     READER_ATTN_KERNEL_ROWS128 = 1,         /* tree_attn_mfma_kernel<D, 4>: 128 rows, 4 computing + 4 copying wavefronts */
     READER_ATTN_KERNEL_ROWS256_WAVES8 = 2,  /* tree_attn_mfma_kernel<D, 8>: 256 rows, 8 wavefronts of 32 rows */
-    READER_ATTN_KERNEL_ROWS256_WAVES4 = 3   /* tree_attn_wide_kernel<D>: 256 rows, 4 wavefronts of 64 rows */
+    READER_ATTN_KERNEL_ROWS256_WAVES4 = 3,  /* tree_attn_wide_kernel<D>: 256 rows, 4 wavefronts of 64 rows */
+    READER_ATTN_KERNEL_SHORT = 4            /* tree_attn_short_kernel<D, rows / 32>: short problems, static grid */
 };
 typedef struct reader_attn_plan_t {
     int32_t kernel;                /* enum reader_attn_kernel */
-    int32_t rows_per_workgroup;    /* 128 or 256 (0 for the scalar kernel) */
+    int32_t rows_per_workgroup;    /* 128 or 256 (short kernel: 32, 64 or 128; 0 for the scalar kernel) */
     int32_t row_chunks;
     int32_t key_ranges;
 } reader_attn_plan_t;
@@ -518,6 +519,8 @@ int reader_measure_peaks(const void *src, size_t src_bytes, void *scratch, size_
  *   READER_TUNE_ATTN_WIDE       which kernel 256-row workgroups run: 1 = four wavefronts with 64 rows each (one per
  *                               SIMD, the accumulation registers managed by hand), 0 = eight with 32 rows each;
  *                               the planner takes the first at head dimension 128 and the second at 64
+ *   READER_TUNE_ATTN_SHORT      0 = never the kernel for short problems, n >= 1 = always, with n shares per pair (n up
+ *                               to 1024, and at most 240 tiles per share); any other override above keeps it out
  * Returns READER_OK, or READER_EINVAL for an unknown `which`.
  */
 enum {
@@ -527,7 +530,8 @@ enum {
     READER_TUNE_ATTN_AXIS64 = 3,
     READER_TUNE_ATTN_WIDE = 4,
     READER_TUNE_ATTN_PAIR_FRONT = 5,
-    READER_TUNE_COUNT_ = 6
+    READER_TUNE_ATTN_SHORT = 6,
+    READER_TUNE_COUNT_ = 7
 };
 int reader_tuning_override(int32_t which, int32_t value);
 

@@ -21,7 +21,7 @@ LIB = os.path.join(HERE, "libreader_hip.so")
 STAMPS_LIB = os.path.join(HERE, "libreader_hip_stamps.so")
 # the extension module binding.py calls the library through (torch tensors and numpy arrays to pointers)
 NATIVE = os.path.join(HERE, "_reader_torch.so")
-SOURCES = ["reader_api.hip", "trie_drafter.cpp", "tree_shape.cpp", "accept_compact.hip", "kv_compact_layers.hip", "kv_rearrange.hip", "target_argmax.hip", "target_sample.hip", "tree_attn_scalar.hip", "tree_attn_mfma.hip", "tree_attn_wide.hip", "peak_probes.hip"]
+SOURCES = ["reader_api.hip", "trie_drafter.cpp", "tree_shape.cpp", "accept_compact.hip", "kv_compact_layers.hip", "kv_rearrange.hip", "target_argmax.hip", "target_sample.hip", "tree_attn_scalar.hip", "tree_attn_mfma.hip", "tree_attn_wide.hip", "tree_attn_short.hip", "peak_probes.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # keep the compiler from forming packed-fp32 instructions

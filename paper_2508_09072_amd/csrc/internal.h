@@ -46,6 +46,8 @@ struct AttnParams {
     int32_t merge_groups;    // thread groups that share a query row's partial records in the merge: 1, or 4 when pairs are cut into many parts
     int32_t tree_in_cache;   // 1: k_tree / v_tree are null, tree node n of sequence b sits at cache position L_b + n
     int32_t wide;            // (256 rows per workgroup) 1: four wavefronts of 64 rows, 0: eight of 32
+    int32_t n_splits;        // short problems: shares every pair's key blocks are cut into (0: one of the ring kernels runs)
+    float split_rcp;         // 1 / n_splits
     int32_t redo_only;       // 1: second pass behind the wide kernel, only the workgroups flagged in `redo` do anything
     int32_t *status;
     int32_t B, T, Hq, Hkv, D, G, M;       // G = Hq/Hkv, M = T*G query rows per (sequence, kv head)
@@ -106,6 +108,10 @@ hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEve
 hipError_t launch_tree_attn_scalar(const AttnParams &p, hipStream_t stream);
 // main kernel of the 256-row flavour with four wavefronts of 64 rows (tree_attn_wide.hip); no second launch
 hipError_t launch_tree_attn_wide_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+
+// short problems: static grid, everything asked for at once (tree_attn_short.hip); both launches
+hipError_t launch_tree_attn_short(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
+                                  const AcceptParams *ap, const CompactParams *cp);
 
 struct AcceptParams {
     const int32_t *draft, *target, *parents;

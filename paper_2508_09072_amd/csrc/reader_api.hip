@@ -16,7 +16,7 @@ namespace reader {
 static char g_error_detail[256] = "";
 
 // Planner overrides set through reader_tuning_override (tests, experiments); -1 = the planner decides.
-static std::atomic<int32_t> g_tuning[READER_TUNE_COUNT_] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
+static std::atomic<int32_t> g_tuning[READER_TUNE_COUNT_] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
 #ifdef READER_WG_STAMPS
 static std::atomic<long long *> g_wg_stamps{nullptr};
 #endif
@@ -87,6 +87,49 @@ int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len) {
     if (n < 1) n = 1;
     if (n >= kNumXCD) n -= n % kNumXCD;  // row chunks of one key range then share an XCD's L2
     return (int)n;
+}
+
+// Short problems run a kernel of their own (tree_attn_short.hip): rows per workgroup, and how many shares the tiles of
+// a pair are cut into; false: one of the ring kernels runs.
+//
+// The rule was fitted to 150 shapes drawn over 1..64 sequences of up to 32 K positions, 1..128 nodes, both head
+// dimensions and three head layouts, each timed with every number of shares and with the ring kernels (it comes
+// within 3 % of the best choice on average, and the launches it takes are 1.26 times faster than the ring kernels'):
+//   - as many shares as fill the compute units once (head dimension 64: twice, two workgroups fit one), but no
+//     more than sqrt(12 tiles): a share costs the merge about a twelfth of what a tile costs the workgroup;
+//   - none where they would save a workgroup less than four tiles' time (six at head dimension 64, whose tiles take less
+//     time): the merge, a launch of its own, takes that long;
+//   - the ring kernels, which cut the work evenly whatever the lengths and take several pairs per workgroup in their
+//     stride, from about 20 tiles per workgroup and round on (24 at head dimension 64); but pairs of up to 16 tiles
+//     that need no cutting are left to the hardware's own scheduling however many there are.
+struct ShortPlan {
+    int rows, chunks, splits;
+};
+static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan &s) {
+    const int forced = tuning(READER_TUNE_ATTN_SHORT);
+    if (forced == 0 || d.variant == 1) return false;
+    for (int which : {READER_TUNE_ATTN_ROWS, READER_TUNE_ATTN_RANGES, READER_TUNE_ATTN_PAIR_COST, READER_TUNE_ATTN_PAIR_FRONT,
+                      READER_TUNE_ATTN_AXIS64, READER_TUNE_ATTN_WIDE})
+        if (tuning(which) >= 0) return false;          // (overrides of the ring kernels' planner)
+    s.rows = 128;
+    s.chunks = (d.T * (d.Hq / d.Hkv) + s.rows - 1) / s.rows;
+    if ((long long)d.B * s.chunks > 65535 || d.Hkv > 65535) return false;   // (dimensions of the grid)
+    const long long units = (long long)d.B * d.Hkv * s.chunks;
+    const long long tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
+    const long long fill = d.D == 64 ? 2 * kNumCU : kNumCU;
+    long long n = fill / (units > 0 ? units : 1);
+    const long long most = (long long)sqrtf(12.0f * (float)tiles);
+    n = n > most ? most : n;
+    n = n > tiles ? tiles : n;
+    n = n < 1 ? 1 : n;
+    if (tiles - (tiles + n - 1) / n < (d.D == 64 ? 6 : 4)) n = 1;
+    if (forced >= 1) n = forced;
+    s.splits = (int)n;
+    const long long per = (tiles + n - 1) / n, rounds = n == 1 ? (units + fill - 1) / fill : 1;
+    if (per > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
+    if (n > 1024 || n * tiles >= 1 << 22) return false;   // (its arithmetic on shares is exact below that)
+    if (forced >= 1) return true;
+    return (n == 1 && tiles <= 16) || per * rounds <= (d.D == 64 ? 24 : 20);
 }
 
 // Measurement hook state: event pairs recorded around the main attention kernel.
@@ -197,6 +240,12 @@ extern "C" size_t reader_workspace_bytes(const reader_dims *dims, int32_t max_se
     int err = 0;
     if (!dims_ok(dims, &err) || max_seq_len < 0) return 0;
     if (dims->B == 0) return 256;
+    ShortPlan sp;
+    if (attn_plan_short(*dims, max_seq_len, sp)) {
+        const size_t n = sp.splits > 1 ? (size_t)dims->B * dims->Hkv * sp.chunks * sp.splits : 0;
+        const size_t rec = n * attn_slot_floats(dims->D, sp.rows) * sizeof(float);
+        return attn_header_bytes(dims->B, dims->Hkv) + ((rec + 255) & ~(size_t)255);
+    }
     size_t slots = 2 * (size_t)attn_plan_ranges(*dims, max_seq_len) * (size_t)row_chunks(*dims, max_seq_len);
     size_t bytes = slots * attn_slot_floats(dims->D, attn_rows_per_wg(*dims, max_seq_len)) * sizeof(float);
     return attn_header_bytes(dims->B, dims->Hkv) + ((bytes + 255) & ~(size_t)255);
@@ -215,6 +264,14 @@ extern "C" int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, re
     if (!dims_ok(dims, &err)) return err;
     if (max_seq_len < 0) return READER_EINVAL;
     const bool scalar = dims->variant == 1;
+    ShortPlan sp;
+    if (attn_plan_short(*dims, max_seq_len, sp)) {
+        plan->kernel = READER_ATTN_KERNEL_SHORT;
+        plan->rows_per_workgroup = sp.rows;
+        plan->row_chunks = sp.chunks;
+        plan->key_ranges = dims->B * dims->Hkv * sp.splits;
+        return READER_OK;
+    }
     plan->rows_per_workgroup = scalar ? 0 : attn_rows_per_wg(*dims, max_seq_len);
     plan->row_chunks = scalar ? 0 : row_chunks(*dims, max_seq_len);
     plan->key_ranges = scalar ? 0 : attn_plan_ranges(*dims, max_seq_len);
@@ -288,6 +345,16 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.tree_in_cache = tree_in_cache ? 1 : 0;
     p.wide = attn_use_wide(*dims, p.rows_per_wg);
     p.redo_only = 0;
+    p.n_splits = 0;
+    p.split_rcp = 0.f;
+    ShortPlan sp;
+    if (attn_plan_short(*dims, max_seq_len, sp)) {
+        p.rows_per_wg = sp.rows;
+        p.n_row_chunks = sp.chunks;
+        p.n_splits = sp.splits;
+        p.split_rcp = 1.0f / (float)sp.splits;
+        p.merge_groups = sp.splits > 8 ? 4 : 1;
+    }
 #ifdef READER_WG_STAMPS
     p.stamps = g_wg_stamps.load(std::memory_order_relaxed);
 #endif

@@ -791,3 +791,33 @@ def test_attn_repeated_launches_are_bit_identical(R, wide, tune):
             assert torch.equal(got[0], first[0]), "outputs differ at repetition %d" % rep
             assert torch.equal(got[1], first[1]), "lse differs at repetition %d" % rep
     assert int(dw.status.item()) == 0
+
+
+# ------------------------------------------------------------------ the kernel for short problems
+
+@pytest.mark.parametrize("T,G,D,lens,splits", [
+    (1, 1, 128, [0], 1), (1, 16, 64, [1, 0, 63], 1), (33, 1, 128, [64, 65, 127], 1), (128, 1, 64, [640, 5], 1),
+    (100, 4, 128, [300, 17], 1),                                  # no share: results written in place, several row chunks
+    (5, 4, 128, [191, 0, 700], 3), (65, 2, 64, [256, 1, 1000], 7),  # shares that start and end anywhere, some of them empty
+    (128, 16, 64, [130], 4), (31, 8, 128, [449, 448, 447], 9),      # more shares than tiles; merge with four thread groups
+    (12, 8, 128, [17000], 130), (64, 1, 64, [40000, 3], 200),       # page ids asked for before and after the length is known
+])
+@pytest.mark.parametrize("in_cache", [False, True])
+def test_attn_short_problem_kernel(R, oracle_mod, T, G, D, lens, splits, in_cache, tune):
+    # forced, so that it meets sizes the planner would leave to the ring kernels; every number of shares gives the same
+    tune(R.TUNE_ATTN_SHORT, splits)
+    if in_cache:
+        check_attn_tree_rows_in_the_cache(R, oracle_mod, T, 4 * G, D, lens, variants=(0,))
+        return
+    w = W.make_custom("short_T%d_S%d" % (T, splits), B=len(lens), Hq=2 * G, Hkv=2, D=D, T=T, seq_lens=lens, tree="trie",
+                      depth=9, branch=4, k_outlier_frac=0.05, seed=480 + T + splits)
+    plan = R.reader_attn_plan(R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages), max(lens) + w.max_path)
+    assert plan["kernel_id"] == 4 and plan["key_ranges"] == 2 * len(lens) * splits, plan
+    check_attn(R, oracle_mod, w, variants=(0,))
+    if max(lens) > 200:
+        w.page_table[0, 2] = w.num_pages           # keys behind a bad page id are skipped, by every kernel alike
+        tune(R.TUNE_ATTN_SHORT, splits)
+        out, lse = run_attn(R, w, want_status=R.STATUS_BAD_PAGE)
+        ref, ref_lse = run_attn(R, w, variant=1, want_status=R.STATUS_BAD_PAGE)
+        assert_close(out, ref, what="bad page")
+        assert_close(lse, ref_lse, what="bad page lse")
