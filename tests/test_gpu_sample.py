@@ -164,3 +164,14 @@ def test_headline_step_shape(R, oracle_mod):
     acc, path, bonus = oracle_mod.accept_path((w.draft_tokens % V).astype(np.int32), got.astype(np.int32), w.parents,
                                               w.max_path)
     assert acc.min() >= 0 and np.all(bonus == got[np.arange(w.B), path[np.arange(w.B), acc]])
+
+
+@pytest.mark.parametrize("B,T,V", [(300, 1, 9000), (1, 128, 2048), (2, 129 - 1, 2049), (9, 120, 5003), (3, 100, 140000)])
+def test_every_number_of_wavefronts_per_row(R, oracle_mod, B, T, V):
+    # four, eight and sixteen wavefronts per row, rows of one slot of 2048 tokens and of more slots than a wavefront has
+    # lanes, deep trees (a node's depth is found from parent pointers beyond the first 64)
+    print("sample parity: B", B, "T", T, "V", V, flush=True)
+    rng = np.random.Generator(np.random.PCG64(B + T * 7 + V))
+    x = rng.standard_normal((B, T, V), dtype=np.float32) * 2.0
+    x[:, :, :: max(1, V // 3)] += 9.0
+    check(R, oracle_mod, W.to_bf16_bits(x), trees(B, T, rng), W.make_uniforms(B, T, rng), 0.8, min_exact=0.9)
