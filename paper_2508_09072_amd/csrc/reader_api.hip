@@ -54,23 +54,29 @@ static bool dims_ok(const reader_dims *d, int *err) {
 // thousand tokens) is over sooner when it is cut into more, lighter workgroups (measured
 // crossover with 256 and with 512 rows per kv head: about 10000 workgroup-tiles, i.e. 40 per
 // workgroup; at a fifth of that the 128-row workgroups are a quarter faster).
-int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
+static int rows_per_wg_by_size(const reader_dims &d, int32_t max_seq_len) {
     const int forced = tuning(READER_TUNE_ATTN_ROWS);
     if (forced == 128 || forced == 256) return forced;
     const int M = d.T * (d.Hq / d.Hkv);
     if (M <= 128) return 128;
-    // three or five chunks of 128 rows: a 256-row workgroup would carry a quarter or a sixth of its rows for nothing
-    // (360 rows per kv head, 24 sequences of 0.3 - 3 K tokens, head dimension 64: step 54 -> 47 us; 320 rows, 48
-    // sequences, head dimension 128: 165 -> 141; from seven chunks on the waste is less than what the 256-row
-    // kernels gain on the fetched bytes)
-    const int chunks = (M + 127) / 128;
-    if (chunks == 3 || chunks == 5) return 128;
     const long long tiles_per_pair = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     const long long units = (long long)d.B * d.Hkv * tiles_per_pair;
     return units * ((M + 127) / 128) <= 10000 ? 128 : 256;
 }
 
-int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len) {
+int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
+    const int forced = tuning(READER_TUNE_ATTN_ROWS);
+    if (forced == 128 || forced == 256) return forced;
+    // three or five chunks of 128 rows: a 256-row workgroup would carry a quarter or a sixth of its rows for nothing
+    // (360 rows per kv head, 24 sequences of 0.3 - 3 K tokens, head dimension 64: step 54 -> 47 us; 320 rows, 48
+    // sequences, head dimension 128: 165 -> 141; from seven chunks on the waste is less than what the 256-row
+    // kernels gain on the fetched bytes)
+    const int chunks = (d.T * (d.Hq / d.Hkv) + 127) / 128;
+    if (chunks == 3 || chunks == 5) return 128;
+    return rows_per_wg_by_size(d, max_seq_len);
+}
+
+static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows) {
     // One range workgroup streams a contiguous run of 64-key tiles of the flattened
     // (sequence, kv head, tile) axis.  One workgroup (8 waves, ~150 KB of LDS) occupies a
     // compute unit, so at most 256 ranges; short problems get fewer so that a range holds
@@ -86,13 +92,25 @@ int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len) {
     if (n > kNumCU) n = kNumCU;
     const int M = d.T * (d.Hq / d.Hkv);
     if (forced <= 0) {
-        const int rows = attn_rows_per_wg(d, max_seq_len), chunks = (M + rows - 1) / rows;
+        const int chunks = (M + rows - 1) / rows;
         if (chunks > 1 && n > kNumCU / chunks) n = kNumCU / chunks;
     }
     if (n > units) n = units;
     if (n < 1) n = 1;
     if (n >= kNumXCD) n -= n % kNumXCD;  // row chunks of one key range then share an XCD's L2
     return (int)n;
+}
+
+int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len) {
+    return plan_ranges(d, max_seq_len, attn_rows_per_wg(d, max_seq_len));
+}
+
+// Bytes set aside for partial records.  They follow from the sizes alone, whichever kernel the planner takes, and never
+// shrink as sequences or positions are added: a workspace that was sized for a program's largest step serves every
+// smaller one, also where that one is cut into more parts.  Every plan stays within them.
+static size_t record_bytes(const reader_dims &d, int32_t max_seq_len) {
+    const int rows = rows_per_wg_by_size(d, max_seq_len), chunks = (d.T * (d.Hq / d.Hkv) + rows - 1) / rows;
+    return 2 * (size_t)plan_ranges(d, max_seq_len, rows) * chunks * attn_slot_floats(d.D, rows) * sizeof(float);
 }
 
 // Short problems run a kernel of their own (tree_attn_short.hip): rows per workgroup, and how many shares the tiles of
@@ -127,6 +145,9 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     const long long most = (long long)sqrtf(12.0f * (float)tiles);
     n = n > most ? most : n;
     n = n > tiles ? tiles : n;
+    // (head dimension 64 would cut some row counts into more records than the workspace holds)
+    const long long held = (long long)(record_bytes(d, max_seq_len) / (attn_slot_floats(d.D, s.rows) * sizeof(float)));
+    if (n > 1 && n * units > held) n = held / units;
     n = n < 1 ? 1 : n;
     if (tiles - (tiles + n - 1) / n < (d.D == 64 ? 6 : 4)) n = 1;
     if (forced >= 1) n = forced;
@@ -246,14 +267,12 @@ extern "C" size_t reader_workspace_bytes(const reader_dims *dims, int32_t max_se
     int err = 0;
     if (!dims_ok(dims, &err) || max_seq_len < 0) return 0;
     if (dims->B == 0) return 256;
+    size_t bytes = record_bytes(*dims, max_seq_len);
     ShortPlan sp;
-    if (attn_plan_short(*dims, max_seq_len, sp)) {
-        const size_t n = sp.splits > 1 ? (size_t)dims->B * dims->Hkv * sp.chunks * sp.splits : 0;
-        const size_t rec = n * attn_slot_floats(dims->D, sp.rows) * sizeof(float);
-        return attn_header_bytes(dims->B, dims->Hkv) + ((rec + 255) & ~(size_t)255);
+    if (tuning(READER_TUNE_ATTN_SHORT) >= 1 && attn_plan_short(*dims, max_seq_len, sp) && sp.splits > 1) {
+        const size_t forced = (size_t)dims->B * dims->Hkv * sp.chunks * sp.splits * attn_slot_floats(dims->D, sp.rows) * sizeof(float);
+        bytes = forced > bytes ? forced : bytes;
     }
-    size_t slots = 2 * (size_t)attn_plan_ranges(*dims, max_seq_len) * (size_t)row_chunks(*dims, max_seq_len);
-    size_t bytes = slots * attn_slot_floats(dims->D, attn_rows_per_wg(*dims, max_seq_len)) * sizeof(float);
     return attn_header_bytes(dims->B, dims->Hkv) + ((bytes + 255) & ~(size_t)255);
 }
 

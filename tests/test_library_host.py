@@ -63,6 +63,24 @@ def test_workspace_bytes_is_pure_and_monotone(R):
     assert R.reader_workspace_bytes(d, 64) <= a
 
 
+def test_a_workspace_for_the_largest_step_serves_every_smaller_one(R):
+    rng = np.random.default_rng(20)
+    for _ in range(3000):
+        Hkv, G, D = int(rng.choice((1, 2, 4, 8, 16))), int(rng.choice((1, 2, 4, 8, 16))), int(rng.choice((64, 128)))
+        T, B, L = int(rng.integers(1, 129)), int(2 ** rng.uniform(0, 7.5)), int(2 ** rng.uniform(0, 15))
+        most = R.reader_workspace_bytes(R.make_dims(B, T, G * Hkv, Hkv, D, 2048, 1, 4096), L)
+        small_b, small_l = int(rng.integers(1, B + 1)), int(rng.integers(0, L + 1))
+        d = R.make_dims(small_b, T, G * Hkv, Hkv, D, 2048, 1, 4096)
+        assert R.reader_workspace_bytes(d, small_l) <= most, (B, T, G, Hkv, D, L, small_b, small_l)
+        # ... and the records of the kernel that is taken fit it (a short problem's pair that is not cut leaves none)
+        plan = R.reader_attn_plan(d, small_l)
+        short = plan["kernel_id"] == 4
+        records = plan["key_ranges"] * plan["row_chunks"] * (1 if short else 2)
+        if short and plan["key_ranges"] == small_b * Hkv:
+            records = 0
+        assert records * plan["rows_per_workgroup"] * (D // 2 + 2) * 4 <= most, (plan, small_b, T, G, Hkv, D, small_l)
+
+
 def test_attention_plan_follows_the_query_rows_and_the_overrides(R):
     # few query rows per kv head: 128-row workgroups with copying wavefronts; many rows on a long context: 256-row
     # workgroups, four wavefronts at head dimension 128 and eight at 64; the override names either
