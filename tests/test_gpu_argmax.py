@@ -48,3 +48,23 @@ def test_odd_row_starts_ties_and_specials(R, oracle_mod):
     bits[5, :] = 0xFF80       # nothing but -inf
     bits[6, 500] = 0x7F80     # +inf
     assert np.array_equal(gpu_argmax(R, bits), oracle_mod.target_argmax(bits))
+
+
+@pytest.mark.parametrize("V", [1, 8, 9, 8192, 8199, 32768, 32776, 65551, 70000, 140001])
+def test_rounds_of_the_stream_and_rows_without_a_finite_logit(R, oracle_mod, V):
+    # rows end within, at and behind a round of a workgroup's loads (8192 logits at 1024 threads); the maximum sits in the
+    # first or last token, appears again later, or the row holds nothing but -inf and NaN
+    print("argmax rounds: V", V, flush=True)
+    rng = np.random.Generator(np.random.PCG64(V))
+    vals = rng.standard_normal((9, V), dtype=np.float32)
+    vals[0, V - 1] = vals[1, 0] = 9.0
+    vals[2, rng.integers(0, V, size=5)] = 9.0
+    bits = W.to_bf16_bits(vals)
+    bits[3, :] = 0xFF80
+    bits[4, :], bits[4, V // 2] = 0x7FC0, 0xFF80
+    bits[5, :], bits[5, 0] = 0xFF80, 0x7FC0
+    bits[6, :], bits[6, V - 1] = 0xFF80, 0x0000
+    bits[7, :] = 0xFFC0
+    assert np.array_equal(gpu_argmax(R, bits), oracle_mod.target_argmax(bits))
+    many = np.tile(bits, (86, 1))                  # 774 rows: 512 threads each
+    assert np.array_equal(gpu_argmax(R, many), np.tile(oracle_mod.target_argmax(bits), 86))
