@@ -48,6 +48,7 @@ struct AttnParams {
     int32_t wide;            // (256 rows per workgroup) 1: four wavefronts of 64 rows, 0: eight of 32
     int32_t n_splits;        // short problems: shares every pair's key blocks are cut into (0: one of the ring kernels runs)
     float split_rcp;         // 1 / n_splits
+    int32_t keep_whole;      // short problems: 1 if pairs that the ring kernels' even cut could leave whole are not cut here either
     int32_t redo_only;       // 1: second pass behind the wide kernel, only the workgroups flagged in `redo` do anything
     int32_t *status;
     int32_t B, T, Hq, Hkv, D, G, M;       // G = Hq/Hkv, M = T*G query rows per (sequence, kv head)

@@ -113,6 +113,25 @@ static size_t record_bytes(const reader_dims &d, int32_t max_seq_len) {
     return 2 * (size_t)plan_ranges(d, max_seq_len, rows) * chunks * attn_slot_floats(d.D, rows) * sizeof(float);
 }
 
+static int attn_use_wide(const reader_dims &d, int rows_per_wg) {
+    // 256-row workgroups: four wavefronts of 64 rows at head dimension 128 (measured 2 to 4 % faster than eight of
+    // 32 rows at the two matrix-bound presets), eight of 32 at head dimension 64 (measured: no difference)
+    const int wide = tuning(READER_TUNE_ATTN_WIDE);
+    return rows_per_wg == 256 && (wide == 1 || (wide < 0 && d.D == 128)) ? 1 : 0;
+}
+
+// What a pair costs the ring kernels beyond its tiles, in tile times, when the ranges are cut.  Mostly the workgroup
+// that finishes it (the ragged last prefix tile, the masks of the tree tiles, normalising and writing the rows; the
+// start has the query rows to fetch): with dedicated copy wavefronts about one tile time in front of the pair's
+// tiles and two behind them; with four wavefronts of 64 rows, whose tiles at the ends of a pair leave the
+// software pipeline and whose accumulators are read out of the other half of the register file, four and
+// four (measured at the large-batch preset: kernel 703 -> 685 us against one in front; 16 and more lose
+// again); otherwise one in front.
+static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
+    const int forced = tuning(READER_TUNE_ATTN_PAIR_COST);
+    return forced >= 0 && forced <= 64 ? forced : (rows_per_wg == 128 ? 3 : (attn_use_wide(d, rows_per_wg) ? 8 : 1));
+}
+
 // Short problems run a kernel of their own (tree_attn_short.hip): rows per workgroup, and how many shares the tiles of
 // a pair are cut into; false: one of the ring kernels runs.
 //
@@ -123,6 +142,9 @@ static size_t record_bytes(const reader_dims &d, int32_t max_seq_len) {
 //     more than sqrt(12 tiles): a share costs the merge about a twelfth of what a tile costs the workgroup;
 //   - none where they would save a workgroup less than four tiles' time (six at head dimension 64, whose tiles take less
 //     time): the merge, a launch of its own, takes that long;
+//   - none where a pair of the longest length is one the ring kernels could have finished in one workgroup: a share's
+//     result is rounded to bf16 in its record and once more in the merge (relative error 2.9e-3 instead of 2.3e-3), and
+//     that is paid only where it was paid before (the kernel asks the same of the actual lengths, pair by pair);
 //   - the ring kernels, which cut the work evenly whatever the lengths and take several pairs per workgroup in their
 //     stride, from about 20 tiles per workgroup and round on (24 at head dimension 64); but pairs of up to 16 tiles
 //     that need no cutting are left to the hardware's own scheduling however many there are.
@@ -150,6 +172,10 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     if (n > 1 && n * units > held) n = held / units;
     n = n < 1 ? 1 : n;
     if (tiles - (tiles + n - 1) / n < (d.D == 64 ? 6 : 4)) n = 1;
+    {
+        const int rows = attn_rows_per_wg(d, max_seq_len);
+        if ((tiles - 1) * plan_ranges(d, max_seq_len, rows) < (long long)d.B * d.Hkv * (tiles + attn_pair_cost(d, rows))) n = 1;
+    }
     if (forced >= 1) n = forced;
     s.splits = (int)n;
     const long long per = (tiles + n - 1) / n, rounds = n == 1 ? (units + fill - 1) / fill : 1;
@@ -276,13 +302,6 @@ extern "C" size_t reader_workspace_bytes(const reader_dims *dims, int32_t max_se
     return attn_header_bytes(dims->B, dims->Hkv) + ((bytes + 255) & ~(size_t)255);
 }
 
-static int attn_use_wide(const reader_dims &d, int rows_per_wg) {
-    // 256-row workgroups: four wavefronts of 64 rows at head dimension 128 (measured 2 to 4 % faster than eight of
-    // 32 rows at the two matrix-bound presets), eight of 32 at head dimension 64 (measured: no difference)
-    const int wide = tuning(READER_TUNE_ATTN_WIDE);
-    return rows_per_wg == 256 && (wide == 1 || (wide < 0 && d.D == 128)) ? 1 : 0;
-}
-
 extern "C" int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, reader_attn_plan_t *plan) {
     int err = 0;
     if (!plan) return READER_EINVAL;
@@ -343,16 +362,8 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.n_row_chunks = row_chunks(*dims, max_seq_len);
     p.n_ranges = attn_plan_ranges(*dims, max_seq_len);
     {
-        // A pair costs the workgroups that start and finish it extra, mostly the one that finishes it (the ragged
-        // last prefix tile, the masks of the tree tiles, normalising and writing the rows; the start has the
-        // query rows to fetch): with dedicated copy wavefronts about one tile time in front of the pair's
-        // tiles and two behind them; with four wavefronts of 64 rows, whose tiles at the ends of a pair leave the
-        // software pipeline and whose accumulators are read out of the other half of the register file, four and
-        // four (measured at the large-batch preset: kernel 703 -> 685 us against one in front; 16 and more lose
-        // again); otherwise one in front.
         const bool wide = attn_use_wide(*dims, p.rows_per_wg);
-        const int forced_cost = tuning(READER_TUNE_ATTN_PAIR_COST);
-        p.pair_cost = forced_cost >= 0 && forced_cost <= 64 ? forced_cost : (p.rows_per_wg == 128 ? 3 : (wide ? 8 : 1));
+        p.pair_cost = attn_pair_cost(*dims, p.rows_per_wg);
         const int forced_front = tuning(READER_TUNE_ATTN_PAIR_FRONT);
         p.pair_front = forced_front >= 0 ? forced_front : (wide ? 4 : 1);
         if (p.pair_front > p.pair_cost) p.pair_front = p.pair_cost;
@@ -372,12 +383,14 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.redo_only = 0;
     p.n_splits = 0;
     p.split_rcp = 0.f;
+    p.keep_whole = 0;
     ShortPlan sp;
     if (attn_plan_short(*dims, max_seq_len, sp)) {
         p.rows_per_wg = sp.rows;
         p.n_row_chunks = sp.chunks;
         p.n_splits = sp.splits;
         p.split_rcp = 1.0f / (float)sp.splits;
+        p.keep_whole = sp.splits > 1 && tuning(READER_TUNE_ATTN_SHORT) < 1;   // (forced: every pair is cut as asked for)
         p.merge_groups = sp.splits > 8 ? 4 : 1;
     }
 #ifdef READER_WG_STAMPS

@@ -83,6 +83,19 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
         L = __builtin_amdgcn_readfirstlane(clamp_len(p, p.seq_lens, b));
         n_pre = (L + kTile - 1) / kTile;
         const int n_all = n_pre + p.n_tree_tiles;
+        if (p.keep_whole) {
+            // The ring kernels give each of n_ranges workgroups an even share of all tiles (and pair_cost positions a
+            // pair).  A pair that fits one such share may have been finished in place there, in fp32 and rounded once: it
+            // is not cut here either.  Its workgroup has no more to do than one of the ring kernels'.
+            int v = 0;
+            for (int i = lane; i < p.B; i += 64) v += (clamp_len(p, p.seq_lens, i) + kTile - 1) / kTile + p.n_tree_tiles + p.pair_cost;
+            const int all = p.Hkv * __builtin_amdgcn_readlane(wave_inclusive_scan(v), 63);   // (below 2^30: at most 256 pairs are cut)
+            if ((n_all - 1) * p.n_ranges < all) {
+                lo = split == 0 ? 0 : n_all;
+                hi = n_all;
+                return;
+            }
+        }
         lo = (int)(((float)(split * n_all) + 0.5f) * p.split_rcp);         // (exact: the host keeps the products below 2^22)
         hi = (int)(((float)((split + 1) * n_all) + 0.5f) * p.split_rcp);
         lo = __builtin_amdgcn_readfirstlane(lo);
@@ -448,7 +461,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
             u32x4 w;
             w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
             const int c = db * 4 + i4 + h;
-            if (row_real) {
+            if (row_real && (whole || lo < hi)) {          // (of an empty share the merge looks at the maxima only)
                 if (whole) *reinterpret_cast<u32x4 *>(orow + c * 8) = w;
                 else __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(rec) + (size_t)c * kShortRows + row_local);
             }
