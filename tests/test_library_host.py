@@ -81,6 +81,18 @@ def test_a_workspace_for_the_largest_step_serves_every_smaller_one(R):
         assert records * plan["rows_per_workgroup"] * (D // 2 + 2) * 4 <= most, (plan, small_b, T, G, Hkv, D, small_l)
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,short", [
+    (16, 16, 32, 8, 128, 1400, True), (16, 16, 32, 8, 128, 1600, False), (16, 16, 32, 8, 128, 2400, False),   # two shares: 12 tiles, 13, 20
+    (8, 64, 32, 8, 64, 2900, True), (8, 64, 32, 8, 64, 4000, False), (32, 64, 8, 2, 128, 2400, False),
+    (1, 64, 32, 8, 128, 16000, True), (1, 16, 8, 8, 64, 32000, True),                      # one sequence: all shares are alike
+    (32, 16, 32, 8, 128, 1200, True), (24, 16, 32, 8, 64, 1400, True)])                    # pairs that are not cut
+def test_long_shares_of_several_sequences_are_left_to_the_ring_kernels(R, B, T, Hq, Hkv, D, bound, short):
+    # every share is as long as the bound makes it: one sequence of 2400 positions among 15 of 64 took 29 us, 23 in the
+    # ring kernels, which cut what there is evenly
+    plan = R.reader_attn_plan(R.make_dims(B, T, Hq, Hkv, D, 2048, 1, 4096), bound)
+    assert (plan["kernel_id"] == 4) == short, plan
+
+
 def test_attention_plan_follows_the_query_rows_and_the_overrides(R):
     # few query rows per kv head: 128-row workgroups with copying wavefronts; many rows on a long context: 256-row
     # workgroups, four wavefronts at head dimension 128 and eight at 64; the override names either
