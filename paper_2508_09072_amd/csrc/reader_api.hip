@@ -67,12 +67,16 @@ static int rows_per_wg_by_size(const reader_dims &d, int32_t max_seq_len) {
 int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     const int forced = tuning(READER_TUNE_ATTN_ROWS);
     if (forced == 128 || forced == 256) return forced;
-    // three or five chunks of 128 rows: a 256-row workgroup would carry a quarter or a sixth of its rows for nothing
-    // (360 rows per kv head, 24 sequences of 0.3 - 3 K tokens, head dimension 64: step 54 -> 47 us; 320 rows, 48
-    // sequences, head dimension 128: 165 -> 141; from seven chunks on the waste is less than what the 256-row
-    // kernels gain on the fetched bytes)
+    // Three or five chunks of 128 rows: a 256-row workgroup would carry a quarter or a sixth of its rows for nothing.
+    // Measured with 264 to 640 query rows per kv head over 1 to 64 sequences of 0.3 to 32 K positions, 128-row over 256-row
+    // workgroups: three chunks 0.87 to 0.93 times as long at head dimension 64, 0.81 to 1.03 at 128 (24 sequences of 0.3 to
+    // 3 K: 70 -> 57 us; even with 32 K), five chunks 0.92 to 0.96 and 0.87 to 1.09.  That last group is ahead up to about 2.5 million tiles x tiles per pair (64
+    // sequences of 1 to 3 K positions: 476 -> 459 us, eight of 2 to 8 K 151 -> 145), behind beyond (two of 32 K 198 -> 203,
+    // 16 of 8 to 32 K 938 -> 1021): with long pairs the four-wavefront kernel has few pair boundaries to pay for, and
+    // in a long launch, whose clock the matrix units' power sets, its fewer operand reads count.
     const int chunks = (d.T * (d.Hq / d.Hkv) + 127) / 128;
-    if (chunks == 3 || chunks == 5) return 128;
+    const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
+    if (chunks == 3 || (chunks == 5 && (d.D == 64 || pairs * tiles <= 2500000 / tiles))) return 128;
     return rows_per_wg_by_size(d, max_seq_len);
 }
 
