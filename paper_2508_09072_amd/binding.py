@@ -153,7 +153,7 @@ def load():
     lib.reader_tuning_override.restype = ctypes.c_int
     lib.reader_tuning_override.argtypes = [i32, i32]
     from . import _reader_torch
-    _reader_torch.init(lib._handle)
+    _reader_torch.init(lib._handle, ReaderDims)
     _native = _reader_torch
     _lib = lib
     return lib

@@ -6,8 +6,9 @@
 // per reader_verify_step and 13 per reader_tree_attn on the machine with the GPU, against 13 to 20 us of kernels);
 // here the same checks cost about a tenth of a microsecond per tensor.
 //
-// The entry points are looked up in the library the ctypes side has loaded (init(handle)), so that both see
-// the same copy of it.  The interpreter lock is released around every call, as ctypes does.
+// The entry points are looked up in the library the ctypes side has loaded (init(handle, dims_type)), so that both see
+// the same copy of it; the ctypes type of the dimensions comes with it.  The interpreter lock is released around
+// every call, as ctypes does.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #define NPY_NO_DEPRECATED_API NPY_1_7_API_VERSION
@@ -34,8 +35,12 @@ struct Api {
     READER_FNS(READER_FN)
 #undef READER_FN
 } api;
+PyTypeObject *dims_type = nullptr;      // binding.ReaderDims
 
-PyObject *py_init(PyObject *, PyObject *arg) {
+PyObject *py_init(PyObject *, PyObject *args) {
+    PyObject *arg;
+    PyTypeObject *type;
+    if (!PyArg_ParseTuple(args, "OO!", &arg, &PyType_Type, &type)) return nullptr;
     void *handle = PyLong_AsVoidPtr(arg);
     if (!handle) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null library handle");
@@ -46,6 +51,9 @@ PyObject *py_init(PyObject *, PyObject *arg) {
     if (!api.name) { PyErr_SetString(PyExc_RuntimeError, "library lacks " #name); return nullptr; }
     READER_FNS(READER_LOOKUP)
 #undef READER_LOOKUP
+    Py_INCREF(type);
+    Py_XDECREF(dims_type);
+    dims_type = type;
     Py_RETURN_NONE;
 }
 
@@ -69,6 +77,11 @@ public:
     const reader_dims *dims() {
         if (!ok_) return nullptr;
         PyObject *o = raw();
+        // (the type itself is asked for: any other object with bytes enough would be read as dimensions)
+        if (!PyObject_TypeCheck(o, dims_type)) {
+            PyErr_Format(PyExc_TypeError, "dims must be a ReaderDims, got %.100s", Py_TYPE(o)->tp_name);
+            return fail();
+        }
         Py_buffer view;
         if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return fail();
         if (view.len < (Py_ssize_t)sizeof dims_) {
@@ -416,7 +429,7 @@ PyObject *py_tree_attach_path(PyObject *const *args, Py_ssize_t n) {   // (token
 
 #define READER_FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(guarded<py_##name>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    {"init", py_init, METH_O, "init(handle): look the entry points up in a loaded library"},
+    {"init", py_init, METH_VARARGS, "init(handle, dims_type): look the entry points up in a loaded library"},
     READER_FAST(tree_attn), READER_FAST(tree_attn_noalloc), READER_FAST(accept_path), READER_FAST(kv_compact),
     READER_FAST(verify_step), READER_FAST(kv_rearrange), READER_FAST(target_argmax), READER_FAST(target_sample),
     READER_FAST(kv_compact_layers), READER_FAST(trie_insert), READER_FAST(trie_search_path), READER_FAST(trie_extract_tree),

@@ -20,6 +20,33 @@ def R():
     return binding
 
 
+def entry_points_with_dims(R):
+    """The calls that take dimensions, with what follows them (tensors on the CPU, which none of them takes)."""
+    import torch
+    i32, bf16 = torch.zeros(1, dtype=torch.int32), torch.zeros(1, dtype=torch.bfloat16)
+    attn = (bf16, bf16, bf16, bf16, bf16, i32, i32, i32)
+    return [(R.reader_tree_attn, attn + (bf16, None, 1, None)), (R.reader_tree_attn_noalloc, attn + (bf16, None, 1)),
+            (R.reader_accept_path, (i32,) * 6), (R.reader_kv_compact, (bf16, bf16, i32, i32, bf16, bf16, i32, i32)),
+            (R.reader_verify_step, attn + (i32, i32, bf16, None, i32, i32, i32, 1, None)),
+            (R.reader_kv_compact_layers, (i32, i32, bf16, bf16, i32, i32))]
+
+
+def test_only_dimensions_are_taken_as_dimensions(R):
+    class Other(ctypes.Structure):
+        _fields_ = R.ReaderDims._fields_
+
+    class Mine(R.ReaderDims):
+        pass
+    size = ctypes.sizeof(R.ReaderDims)
+    for call, rest in entry_points_with_dims(R):
+        for no in (bytes(size), bytearray(2 * size), np.zeros(size, dtype=np.uint8), Other(), None, 7, R.ReaderDims):
+            with pytest.raises(TypeError):
+                call(no, *rest)
+        for yes in (R.make_dims(1, 1, 1, 1, 64, 1, 1, 1), Mine(1, 1, 1, 1, 64)):
+            with pytest.raises(ValueError, match="GPU"):
+                call(yes, *rest)
+
+
 def declared_symbols():
     text = open(os.path.join(ROOT, "include", "reader.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
