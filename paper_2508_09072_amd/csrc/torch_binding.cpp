@@ -19,7 +19,8 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
-#include <vector>
+#include <memory>
+#include <new>
 
 #include "reader.h"
 
@@ -175,6 +176,8 @@ template <PyObject *(*F)(PyObject *const *, Py_ssize_t)>
 PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t n) {
     try {
         return F(args, n);
+    } catch (const std::bad_alloc &) {
+        return PyErr_NoMemory();
     } catch (const std::exception &e) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
         return nullptr;
@@ -353,6 +356,10 @@ bool whole_number(PyObject *o, long long *v) {
     return !(*v == -1 && PyErr_Occurred());
 }
 
+// Room for as many tokens as a caller allows (a depth or budget without an end is an ordinary one): left as it comes, so
+// that only what is written is paid for (filled with zeros, a limit of 2^20 tokens cost 2 ms a call).
+std::unique_ptr<int32_t[]> room(long long n) { return std::unique_ptr<int32_t[]>(new int32_t[(size_t)std::max(n, 1LL)]); }
+
 bool enough(Py_ssize_t n, Py_ssize_t want) {
     if (n == want) return true;
     PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", want, n);
@@ -375,13 +382,13 @@ PyObject *py_trie_search_path(PyObject *const *args, Py_ssize_t n) {   // (trie,
     if (PyErr_Occurred()) return nullptr;
     Ints suffix(args[1]);
     if (!suffix.arr) return nullptr;
-    std::vector<int32_t> out((size_t)std::max(depth, 1LL));
+    const auto out = room(depth);
     int32_t k;
     Py_BEGIN_ALLOW_THREADS
-    k = api.reader_trie_search_path(t, suffix.data(), (int32_t)suffix.size(), (int32_t)depth, out.data());
+    k = api.reader_trie_search_path(t, suffix.data(), (int32_t)suffix.size(), (int32_t)depth, out.get());
     Py_END_ALLOW_THREADS
     if (k < 0) { PyErr_SetString(PyExc_ValueError, "reader_trie_search_path: bad argument"); return nullptr; }
-    return int_array(out.data(), k);
+    return int_array(out.get(), k);
 }
 
 PyObject *py_trie_extract_tree(PyObject *const *args, Py_ssize_t n) {   // (trie, suffix, max_depth, budget)
@@ -392,14 +399,13 @@ PyObject *py_trie_extract_tree(PyObject *const *args, Py_ssize_t n) {   // (trie
     if (PyErr_Occurred()) return nullptr;
     Ints suffix(args[1]);
     if (!suffix.arr) return nullptr;
-    std::vector<int32_t> both(2 * (size_t)std::max(budget, 1LL));
-    int32_t *tokens = both.data(), *parents = tokens + both.size() / 2;
+    const auto tokens = room(budget), parents = room(budget);
     int32_t k;
     Py_BEGIN_ALLOW_THREADS
-    k = api.reader_trie_extract_tree(t, suffix.data(), (int32_t)suffix.size(), (int32_t)depth, (int32_t)budget, tokens, parents);
+    k = api.reader_trie_extract_tree(t, suffix.data(), (int32_t)suffix.size(), (int32_t)depth, (int32_t)budget, tokens.get(), parents.get());
     Py_END_ALLOW_THREADS
     if (k < 0) { PyErr_SetString(PyExc_ValueError, "reader_trie_extract_tree: bad argument"); return nullptr; }
-    PyObject *x = int_array(tokens, k), *y = int_array(parents, k);
+    PyObject *x = int_array(tokens.get(), k), *y = int_array(parents.get(), k);
     if (!x || !y) { Py_XDECREF(x); Py_XDECREF(y); return nullptr; }
     return Py_BuildValue("(NN)", x, y);
 }

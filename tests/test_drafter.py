@@ -150,3 +150,22 @@ def test_an_unbounded_tree_accepts_what_the_metric_counts(R):
         ptr += step
         stops += 1
     assert len(resp) / stops == pytest.approx(D.self_repetition(prompt, resp), rel=1e-12)
+
+
+def test_a_limit_that_is_never_reached_costs_nothing(R):
+    # a depth and a budget far beyond what the trie holds: the memory set aside for the results is not filled beforehand
+    import os
+    import subprocess
+    import sys
+    code = ("import resource; from paper_2508_09072_amd import binding as R; t = R.Trie(4); t.insert([1, 2, 3]);"
+            "rss = lambda: resource.getrusage(resource.RUSAGE_SELF).ru_maxrss; a = rss();"
+            "assert t.search_path([1], 1 << 26).tolist() == [2, 3];"
+            "assert t.extract_tree([1], 8, 1 << 26)[0].tolist() == [1, 2, 3]; print(rss() - a)")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120, cwd=root)
+    assert res.returncode == 0, res.stderr
+    assert int(res.stdout) < 64 << 10, "%s KB" % res.stdout          # (filled: 256 MB a result)
+    trie = R.Trie(4)
+    for call in (lambda: trie.search_path([1], 1 << 60), lambda: trie.extract_tree([1], 2, 1 << 60)):
+        with pytest.raises(MemoryError):
+            call()
