@@ -139,11 +139,19 @@ public:
         if (v == -1 && PyErr_Occurred()) ok_ = false;
         return (int32_t)v;
     }
+    // anything Python's float() takes
     double number() {
         if (!ok_) return 0.0;
-        const double v = PyFloat_AsDouble(raw());
-        if (v == -1.0 && PyErr_Occurred()) ok_ = false;
+        PyObject *as_float = PyNumber_Float(raw());
+        if (!as_float) { ok_ = false; return 0.0; }
+        const double v = PyFloat_AS_DOUBLE(as_float);
+        Py_DECREF(as_float);
         return v;
+    }
+    void want_dims(const at::Tensor *t, int64_t n, const char *what) {
+        if (!ok_ || t->dim() == n) return;
+        PyErr_Format(PyExc_ValueError, "%s needs %lld dimensions, got %lld", what, (long long)n, (long long)t->dim());
+        ok_ = false;
     }
     void reject(PyObject *type, const char *why) {
         if (!ok_) return;
@@ -265,8 +273,9 @@ PyObject *py_verify_step(PyObject *const *args, Py_ssize_t n) {
 PyObject *py_kv_rearrange(PyObject *const *args, Py_ssize_t n) {
     Args a(args, n, 5);
     const at::Tensor *k = a.tensor(kBf16), *v = a.tensor(kBf16), *valid = a.tensor(kU8), *len = a.tensor(kI32), *scratch = a.tensor(kAny);
+    a.want_dims(k, 5, "k_pad");
     if (!a.ok()) return nullptr;
-    if (k->dim() != 5 || v->sizes() != k->sizes() || valid->dim() != 2 || valid->size(0) != k->size(1) ||
+    if (v->sizes() != k->sizes() || valid->dim() != 2 || valid->size(0) != k->size(1) ||
         valid->size(1) != k->size(2) || len->dim() != 1 || len->size(0) != k->size(1)) {
         a.reject(PyExc_AssertionError, "k_pad, v_pad [NL, B, S, Hkv, D], valid [B, S] and new_len [B] do not fit each other");
         return nullptr;
@@ -296,8 +305,9 @@ PyObject *py_target_sample(PyObject *const *args, Py_ssize_t n) {
     const at::Tensor *logits = a.tensor(kBf16), *parents = a.tensor(kI32), *uniforms = a.tensor(kF32);
     const double temperature = a.number();
     const at::Tensor *out = a.tensor(kI32);
+    a.want_dims(logits, 3, "logits");
     if (!a.ok()) return nullptr;
-    if (logits->dim() != 3 || parents->sizes() != logits->sizes().slice(0, 2) || uniforms->sizes() != parents->sizes() ||
+    if (parents->sizes() != logits->sizes().slice(0, 2) || uniforms->sizes() != parents->sizes() ||
         out->sizes() != parents->sizes()) {
         a.reject(PyExc_AssertionError, "logits [B, T, V], parents, uniforms and target_tokens [B, T] do not fit each other");
         return nullptr;
