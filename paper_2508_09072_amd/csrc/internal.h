@@ -37,7 +37,7 @@ struct AttnParams {
     int32_t *range_tiles;    // header: per range workgroup the number of tiles it holds (0: it wrote no record)
     int32_t *redo;           // header: per workgroup of the wide kernel 1 if its range has to be computed again (kMaxAttnWorkgroups entries)
 #ifdef READER_WG_STAMPS
-    long long *stamps;       // profiling build only: kWgStamps time stamps per workgroup (100 MHz counter), or null
+    long long *stamps;       // profiling build only: kWgStamps time stamps (100 MHz counter) of each of the first kStampedWgs workgroups, or null
 #endif
     int32_t pair_cost;       // what a pair costs beyond its tiles, in tile times, when the ranges are cut
     int32_t pair_front;      // the part of it booked in front of the pair's tiles (the rest behind them)
@@ -87,7 +87,8 @@ enum WgStamp {
     kStampLoopIssued = 12,  // ... that item asked for
     kStampTileLanded = 13,  // first key tile complete in LDS (past the barrier that says so)
     kStampTileDone = 14,    // first key tile computed by this wavefront (before the next barrier)
-    kWgStamps = 15
+    kWgStamps = 15,
+    kStampedWgs = 2048       // workgroups that note anything: the buffer holds this many
 };
 #endif
 constexpr int kMaxRowChunks = 8;                           // ceil(READER_MAX_T * 16 grouped heads / 256 rows)

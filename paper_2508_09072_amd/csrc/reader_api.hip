@@ -275,8 +275,8 @@ extern "C" const char *reader_strerror(int code) {
 extern "C" const char *reader_last_error_detail(void) { return g_error_detail; }
 
 #ifdef READER_WG_STAMPS
-// Profiling build only (not declared in the public header): device buffer of kWgStamps 64-bit stamps per
-// workgroup of the attention main kernel, at least 2048 workgroups; null switches the stamps off.
+// Profiling build only (not declared in the public header): device buffer of kWgStamps 64-bit stamps for
+// each of the first kStampedWgs workgroups of the attention main kernel; null switches the stamps off.
 extern "C" int reader_profile_wg_stamps(void *device_buffer) {
     g_wg_stamps.store(static_cast<long long *>(device_buffer), std::memory_order_relaxed);
     return READER_OK;

@@ -71,7 +71,7 @@ namespace reader {
 #ifdef READER_WG_STAMPS
 #define READER_STAMP(k, who)                                                                              \
     do {                                                                                                  \
-        if (p.stamps && threadIdx.x == (who))                                                             \
+        if (p.stamps && threadIdx.x == (who) && blockIdx.x < kStampedWgs)                                 \
             p.stamps[(size_t)blockIdx.x * kWgStamps + (k)] = (long long)__builtin_amdgcn_s_memrealtime(); \
     } while (0)
 #else

@@ -6,7 +6,8 @@
 // for: scan of all lengths, cut of the tile axis, tile list in LDS, barriers in between.  Here everything that can
 // be is fixed by the host, and the rest is asked for at once:
 //   - a static grid: workgroup (split s, kv head, sequence and row chunk) takes the s-th of n_splits equal shares of
-//     its pair's tiles, so nothing is searched for and no other sequence's length is needed;
+//     its pair's tiles, so nothing is searched for (of the other sequences' lengths only the sum is wanted, where pairs
+//     are cut: a pair that the ring kernels could leave whole stays whole);
 //   - one trip to memory brings the length, the page ids of the sequence (into registers of the wavefronts that
 //     copy, asked for before the length is known), the parent pointers and the query rows; a second one the keys;
 //   - no list and no barrier in front of the main loop.
@@ -38,11 +39,11 @@ constexpr int kPageRegs = 4;              // page ids a copying wavefront holds:
 
 // Profiling build (-DREADER_WG_STAMPS): thread `who` of the workgroup notes the time at point k
 #ifdef READER_WG_STAMPS
-#define READER_STAMP(k, who)                                                                                      \
-    do {                                                                                                          \
-        if (p.stamps && threadIdx.x == (who))                                                                     \
-            p.stamps[(((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kWgStamps + (k)] = \
-                (long long)__builtin_amdgcn_s_memrealtime();                                                      \
+#define READER_STAMP(k, who)                                                                              \
+    do {                                                                                                  \
+        const unsigned wg = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;               \
+        if (p.stamps && threadIdx.x == (who) && wg < kStampedWgs)                                         \
+            p.stamps[(size_t)wg * kWgStamps + (k)] = (long long)__builtin_amdgcn_s_memrealtime();         \
     } while (0)
 #else
 #define READER_STAMP(k, who) do { } while (0)
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
     int *s_hole = s_par + 4 * READER_MAX_T;                                          // [kS][4]: quarter of the tile behind a bad page id
     const unsigned ring_lds = (unsigned)(size_t)(lds_char *)ring;
 
-    READER_STAMP(0, 0);
+    READER_STAMP(kStampEntry, 0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int split = blockIdx.x, hkv = blockIdx.y;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
         }
 #pragma unroll
         for (int i = 0; i < kPageRegs; ++i) asm volatile("" : "+v"(page[i]));   // (waited for in front of the copies)
-        READER_STAMP(1, 256);
+        READER_STAMP(kStampRange, 256);
         auto issue = [&](int t) {
             const unsigned at = (unsigned)(t - lo) % kS;
             const unsigned dst = ring_lds + at * G::kStageBytes + cw * G::kRowsPerWave * G::kRowBytes;
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
 #pragma unroll 1
         for (int i = 0; i < kS - 1 && lo + i < hi; ++i) {
             issue(lo + i);
-            if (i == 0) READER_STAMP(2, 256);
+            if (i == 0) READER_STAMP(kStampItem0Issued, 256);
         }
 #pragma unroll 1
         for (int t = lo; t < hi; ++t) {
@@ -282,8 +283,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
         const unsigned at = (unsigned)(t - lo) % kS;
         const char *stage = ring + at * G::kStageBytes;
         __syncthreads();       // tile t is complete in LDS
-        if (t == lo) READER_STAMP(3, 0);
-        if (t == lo + 1) READER_STAMP(4, 0);
+        if (t == lo) READER_STAMP(kStampTileLanded, 0);
+        if (t == lo + 1) READER_STAMP(kStampFirstTile, 0);
         if (!wave_active) continue;
         const int4 hole = *reinterpret_cast<const int4 *>(s_hole + at * 4);
         // S^T = K.Q^T: two 32-key blocks, two independent chains.  All operand fragments are asked for before they are
@@ -433,7 +434,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
             __builtin_amdgcn_sched_group_barrier(0x008, 4 * G::kOBlocks, 0);
         }
     }
-    READER_STAMP(5, 0);
+    READER_STAMP(kStampLastTile, 0);
 
     // ---- a pair that was not split is normalised and written out, a share leaves a record for the merge
     if (!wave_active) return;
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
             p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_run * c2 + __builtin_amdgcn_logf(l_run)) * kLn2;
         }
     }
-    READER_STAMP(7, 0);
+    READER_STAMP(kStampExit, 0);
     if (p.status && bad) atomicOr(p.status, bad);
 }
 

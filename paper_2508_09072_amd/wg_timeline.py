@@ -1,16 +1,18 @@
 """Where the attention main kernel's time goes, workgroup by workgroup, on one MI355X.
 
 The profiling build of the library (python -m paper_2508_09072_amd.build --stamps, a second .so next to the
-normal one) has thread 0 of every workgroup of the 128-row attention kernel note the GPU's constant-rate
-counter (100 MHz) at these points: kernel entry, share of the tile axis known, tile list written, copy
-constants made, first key tile asked for, first two asked for, first item complete in LDS, first key tile computed, last tile computed, exit.  This
-script runs one preset with it and prints, over all workgroups and over the last launches of the run,
+normal one) has one thread of each of the first 2048 workgroups of the 128-row and short-problem attention
+kernels note the GPU's constant-rate counter (100 MHz) at these points: kernel entry, share of the tile axis
+known, tile list written, copy constants made, first key tile asked for, first two asked for, first item complete
+in LDS, first key tile computed, last tile computed, exit (the short-problem kernel has no list and fewer
+points).  This script runs one preset with it and prints, over all workgroups and over the last launches of the run,
 when each point is reached (relative to the first workgroup's entry), how long a workgroup takes per
 tile in between, and how far apart the workgroups finish:
 
     python -m paper_2508_09072_amd.wg_timeline [--config 2] [--steps 40] [--tune ATTN_PAIR_COST=3]
 
-The stamps cost a few stores per workgroup; the kernel is otherwise the one the benchmark times.
+The stamps cost a few stores per workgroup; the kernel is otherwise the one the benchmark times, except that the
+short-problem kernel at head dimension 64 runs one workgroup per compute unit here and two there.
 Inputs are seeded and synthetic (the benchmark presets).
 """
 from __future__ import annotations
@@ -82,11 +84,13 @@ def main():
     lib.reader_profile_wg_stamps(None)
     assert int(dw.status.item()) == 0
 
+    plan = R.reader_attn_plan(dw.dims, dw.max_seq_len)
+    short = plan["kernel_id"] == 4                                       # (its workgroups leave no tile counts)
     ranges = dw.workspace[:256 * 4].view(torch.int32).cpu().numpy()    # tiles per range, first words of the workspace
     use = rows[len(rows) // 2:]                                          # the second half of the launches
     n_wg = int((use[0][:, 0] != 0).sum())
-    print("preset %s: %d workgroups with stamps, %d launches summarised; times in us from the first workgroup's entry"
-          % (w.name, n_wg, len(use)))
+    print("preset %s, %s: %d workgroups with stamps, %d launches summarised; times in us from the first workgroup's entry"
+          % (w.name, plan["kernel"], n_wg, len(use)))
     rel = []
     for s in use:
         live = s[s[:, 0] != 0].astype(np.float64)
@@ -101,9 +105,11 @@ def main():
             continue
         print("%-38s %8.2f %8.2f %8.2f %8.2f %8.2f" % (name, v.min(), np.percentile(v, 10), np.median(v),
                                                         np.percentile(v, 90), v.max()))
-    tiles = ranges[:n_wg].astype(np.float64) if n_wg <= 256 else None
+    tiles = ranges[:n_wg].astype(np.float64) if n_wg <= 256 and not short else None
     stream_us = rel[:, :, 6] - rel[:, :, 5]
-    print("first tile computed -> last tile computed: median %.2f us per workgroup" % np.median(stream_us))
+    reached = (rel[:, :, 5] >= 0) & (rel[:, :, 6] >= 0)                  # (workgroups of at least two tiles)
+    if reached.any():
+        print("first tile computed -> last tile computed: median %.2f us per workgroup" % np.median(stream_us[reached]))
     if tiles is not None and (tiles > 1).all():
         per_tile = np.median(stream_us, axis=0) / (tiles - 1)
         print("  per tile: median %.3f us, p10 %.3f, p90 %.3f   (tiles per workgroup: %d..%d)"

@@ -843,3 +843,34 @@ def test_attn_short_plan_rounds_no_result_once_more_than_the_ring_kernels(R, ora
     err, err_ring = np.linalg.norm(out - ref), np.linalg.norm(ring - ref)
     print("relative error", err / np.linalg.norm(ref), "ring kernels", err_ring / np.linalg.norm(ref), flush=True)
     assert err <= 1.05 * err_ring
+
+
+def test_profiling_build_notes_no_more_workgroups_than_its_buffer_holds(R):
+    # 64 sequences x 8 kv heads x 8 row chunks = 4096 workgroups; the time stamps of the first 2048 are kept
+    import ctypes
+    import os
+    import torch
+    from paper_2508_09072_amd import build, wg_timeline
+    assert os.path.exists(build.STAMPS_LIB), "profiling build missing"
+    w = W.make_custom("stamps", B=64, Hq=64, Hkv=8, D=64, T=128, seq_lens=[20] * 64, tree="trie", depth=6, seed=491)
+    dw = R.to_device(w)
+    assert R.reader_attn_plan(dw.dims, dw.max_seq_len)["kernel_id"] == 4
+    lib = ctypes.CDLL(build.STAMPS_LIB)
+    lib.reader_tree_attn.argtypes = R.load().reader_tree_attn.argtypes
+    lib.reader_profile_wg_stamps.argtypes = [ctypes.c_void_p]
+    n = wg_timeline.MAX_WG
+    buf = torch.zeros((2 * n + 64, wg_timeline.N_STAMPS), dtype=torch.int64, device="cuda")   # (room for all 4096 besides)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    lib.reader_profile_wg_stamps(p(buf))
+    try:
+        assert lib.reader_tree_attn(ctypes.byref(dw.dims), p(dw.q), p(dw.k_tree), p(dw.v_tree), p(dw.k_cache), p(dw.v_cache),
+                                    p(dw.page_table), p(dw.seq_lens), p(dw.parents), p(dw.out), None, dw.max_seq_len,
+                                    p(dw.workspace), dw.workspace.numel(), p(dw.status),
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+    finally:
+        lib.reader_profile_wg_stamps(None)
+    assert bool((buf[:n, 0] > 0).all()) and bool((buf[:n, 7] > 0).all())
+    assert int(buf[n:].count_nonzero()) == 0
+    got = bf16_to_np(dw.out)
+    assert_close(got, run_attn(R, w)[0], what="profiling build against the normal one")
