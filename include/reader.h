@@ -135,11 +135,11 @@ enum reader_attn_kernel {
     READER_ATTN_KERNEL_ROWS128 = 1,         /* tree_attn_mfma_kernel<D, 4>: 128 rows, 4 computing + 4 copying wavefronts */
     READER_ATTN_KERNEL_ROWS256_WAVES8 = 2,  /* tree_attn_mfma_kernel<D, 8>: 256 rows, 8 wavefronts of 32 rows */
     READER_ATTN_KERNEL_ROWS256_WAVES4 = 3,  /* tree_attn_wide_kernel<D>: 256 rows, 4 wavefronts of 64 rows */
-    READER_ATTN_KERNEL_SHORT = 4            /* tree_attn_short_kernel<D, rows / 32>: short problems, static grid */
+    READER_ATTN_KERNEL_SHORT = 4            /* tree_attn_short_kernel<D>: short problems, 128 rows, static grid */
 };
 typedef struct reader_attn_plan_t {
     int32_t kernel;                /* enum reader_attn_kernel */
-    int32_t rows_per_workgroup;    /* 128 or 256 (short kernel: 32, 64 or 128; 0 for the scalar kernel) */
+    int32_t rows_per_workgroup;    /* 128 or 256 (short kernel: 128; 0 for the scalar kernel) */
     int32_t row_chunks;
     int32_t key_ranges;
 } reader_attn_plan_t;

@@ -207,15 +207,14 @@ def reader_validate_tree(parents_host) -> int:
 
 
 ATTN_KERNEL_NAMES = {0: "tree_attn_scalar_kernel", 1: "tree_attn_mfma_kernel<D, 4>", 2: "tree_attn_mfma_kernel<D, 8>",
-                     3: "tree_attn_wide_kernel<D>", 4: "tree_attn_short_kernel<D, R>"}
+                     3: "tree_attn_wide_kernel<D>", 4: "tree_attn_short_kernel<D>"}
 
 
 def reader_attn_plan(dims: ReaderDims, max_seq_len: int) -> dict:
     """Kernel, rows per workgroup, row chunks and key ranges reader_tree_attn would use (host only)."""
     plan = ReaderAttnPlan()
     _check(load().reader_attn_plan(ctypes.byref(dims), int(max_seq_len), ctypes.byref(plan)), "reader_attn_plan")
-    return {"kernel": ATTN_KERNEL_NAMES[int(plan.kernel)].replace("D", str(int(dims.D)))
-            .replace("R", str(int(plan.rows_per_workgroup) // 32)), "kernel_id": int(plan.kernel),
+    return {"kernel": ATTN_KERNEL_NAMES[int(plan.kernel)].replace("D", str(int(dims.D))), "kernel_id": int(plan.kernel),
             "rows_per_workgroup": int(plan.rows_per_workgroup), "row_chunks": int(plan.row_chunks),
             "key_ranges": int(plan.key_ranges)}
 

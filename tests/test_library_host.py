@@ -150,6 +150,9 @@ def test_attention_plan_follows_the_query_rows_and_the_overrides(R):
     finally:
         R.reader_tuning_override(R.TUNE_ATTN_WIDE, -1)
         R.reader_tuning_override(R.TUNE_ATTN_ROWS, -1)
+    for D in (64, 128):                    # the name is the one a kernel trace shows
+        short = R.reader_attn_plan(R.make_dims(1, 64, 32, 8, D, 260, 7, 300), 4096)
+        assert short["kernel"] == "tree_attn_short_kernel<%d>" % D and short["rows_per_workgroup"] == 128
     scalar = R.reader_attn_plan(R.make_dims(2, 8, 8, 2, 64, 10, 4, 20, variant=1), 100)
     assert scalar["kernel_id"] == 0
     with pytest.raises(RuntimeError):
