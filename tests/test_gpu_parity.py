@@ -34,6 +34,31 @@ def tune(R):
         R.reader_tuning_override(which, -1)
 
 
+@pytest.fixture(params=["planned", "ring"])
+def kernels(request, R, tune):
+    """Runs a test with the planner's choice, which for small shapes is the kernel for short problems, and with the ring
+    kernels, which take the large ones."""
+    if request.param == "ring":
+        tune(R.TUNE_ATTN_SHORT, 0)
+    return request.param
+
+
+def plan_of(R, w):
+    dims = R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages)
+    return R.reader_attn_plan(dims, int(w.seq_lens.max()) + w.max_path)
+
+
+def check_kernel(R, w, kernels):
+    """The kernel that the test means is the one that runs: 4 is the one for short problems."""
+    plan = plan_of(R, w)
+    assert (plan["kernel_id"] == 4) == (kernels == "planned"), plan
+    return plan
+
+
+def variants_of(kernels):
+    return (0, 1) if kernels == "planned" else (0,)       # (the scalar kernel is the same both times)
+
+
 def bf16_to_np(t):
     return t.float().cpu().numpy().astype(np.float64)
 
@@ -63,49 +88,60 @@ def check_attn(R, oracle_mod, w, variants=(0, 1), sm_scale=0.0):
 # ------------------------------------------------------------------ attention, whole outputs
 
 @pytest.mark.parametrize("index,scale", [(0, 1.0), (1, 1.0), (2, 0.25), (3, 0.03), (4, 0.04)])
-def test_attn_presets_element_by_element(R, oracle_mod, index, scale):
+def test_attn_presets_element_by_element(R, oracle_mod, index, scale, kernels):
     # presets 0 and 1 at full size; 2-4 with shortened prefixes (still several 64-key tiles,
     # ragged tails, several workgroups per pair) so that the oracle finishes in seconds
     w = W.make_config(index, length_scale=scale)
-    check_attn(R, oracle_mod, w, variants=(0, 1) if index < 2 else (0,))
+    assert kernels == "planned" or plan_of(R, w)["kernel_id"] != 4
+    check_attn(R, oracle_mod, w, variants=variants_of(kernels) if index < 2 else (0,))
 
 
 @pytest.mark.parametrize("L", [0, 1, 15, 16, 63, 64, 65, 127, 129, 500])
-def test_attn_prefix_length_edges(R, oracle_mod, L):
+def test_attn_prefix_length_edges(R, oracle_mod, L, kernels):
     w = W.make_custom("edge_L%d" % L, B=2, Hq=8, Hkv=2, D=128, T=20, seq_lens=[L, max(0, L - 1)],
                       tree="uniform", depth=5, seed=100 + L)
-    check_attn(R, oracle_mod, w)
+    plan = check_kernel(R, w, kernels)
+    assert kernels == "planned" or plan["kernel_id"] == 1, plan
+    check_attn(R, oracle_mod, w, variants=variants_of(kernels))
 
 
 @pytest.mark.parametrize("T,tree", [(1, "chain"), (2, "chain"), (31, "uniform"), (64, "trie"), (65, "uniform"),
                                     (128, "chain"), (128, "star"), (128, "trie")])
-def test_attn_tree_shapes(R, oracle_mod, T, tree):
+def test_attn_tree_shapes(R, oracle_mod, T, tree, kernels):
     w = W.make_custom("tree_%s_T%d" % (tree, T), B=2, Hq=4, Hkv=2, D=128, T=T, seq_lens=[70, 200],
                       tree=tree, depth=12, branch=8, seed=200 + T)
-    check_attn(R, oracle_mod, w)
+    plan = check_kernel(R, w, kernels)
+    assert kernels == "planned" or plan["kernel_id"] == 1, plan
+    check_attn(R, oracle_mod, w, variants=variants_of(kernels))
 
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(8, 8, 64), (8, 2, 64), (16, 2, 64), (4, 4, 128), (16, 2, 128), (32, 2, 128)])
-def test_attn_head_layouts(R, oracle_mod, Hq, Hkv, D):
+def test_attn_head_layouts(R, oracle_mod, Hq, Hkv, D, kernels):
     w = W.make_custom("heads_%d_%d_%d" % (Hq, Hkv, D), B=3, Hq=Hq, Hkv=Hkv, D=D, T=24,
                       seq_lens=[130, 5, 321], tree="trie", depth=6, branch=3, seed=300 + Hq + D)
-    check_attn(R, oracle_mod, w)
+    plan = check_kernel(R, w, kernels)
+    assert kernels == "planned" or plan["kernel_id"] == 1, plan
+    check_attn(R, oracle_mod, w, variants=variants_of(kernels))
 
 
-def test_attn_many_short_sequences(R, oracle_mod):
-    # more pairs than a workgroup range holds tiles: ranges cover several whole pairs
+def test_attn_many_short_sequences(R, oracle_mod, kernels):
+    # more pairs than a workgroup range holds tiles: the ring kernels' ranges cover several whole pairs
     rng = np.random.Generator(np.random.PCG64(5))
     w = W.make_custom("many_short", B=40, Hq=8, Hkv=4, D=128, T=8, seq_lens=rng.integers(0, 90, size=40),
                       tree="uniform", depth=4, seed=401)
-    check_attn(R, oracle_mod, w)
+    plan = check_kernel(R, w, kernels)
+    assert kernels == "planned" or plan["kernel_id"] == 1, plan
+    check_attn(R, oracle_mod, w, variants=variants_of(kernels))
 
 
-def test_attn_more_sequences_than_lengths_fit_in_lds(R, oracle_mod):
-    # above 1024 sequences the clamped lengths are re-read from memory while the tile list is written
+def test_attn_more_sequences_than_lengths_fit_in_lds(R, oracle_mod, kernels):
+    # above 1024 sequences the ring kernels re-read the clamped lengths from memory while the tile list is written
     rng = np.random.Generator(np.random.PCG64(6))
     w = W.make_custom("very_many", B=1100, Hq=4, Hkv=2, D=64, T=4, seq_lens=rng.integers(0, 40, size=1100),
                       tree="uniform", depth=3, seed=404)
-    check_attn(R, oracle_mod, w)
+    plan = check_kernel(R, w, kernels)
+    assert kernels == "planned" or plan["kernel_id"] == 1, plan
+    check_attn(R, oracle_mod, w, variants=variants_of(kernels))
 
 
 @pytest.mark.parametrize("T,Hq", [(16, 8), (48, 16)])
@@ -144,7 +180,7 @@ def test_attn_pair_cost_in_front_of_and_behind_the_tiles(R, oracle_mod, cost, fr
 
 
 @pytest.mark.parametrize("lens", [[300, 40], [2500]])
-def test_attn_most_query_rows_per_kv_head(R, oracle_mod, lens):
+def test_attn_most_query_rows_per_kv_head(R, oracle_mod, lens, kernels):
     # 128 nodes x 16 grouped heads = 2048 query rows per kv head: sixteen 128-row chunks (short contexts) or
     # eight 256-row chunks per key range, and so few ranges that all workgroups run at once
     w = W.make_custom("rows2048", B=len(lens), Hq=32, Hkv=2, D=128, T=128, seq_lens=lens, tree="trie", depth=9,
@@ -152,11 +188,12 @@ def test_attn_most_query_rows_per_kv_head(R, oracle_mod, lens):
     plan = R.reader_attn_plan(R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.page_table.shape[1], w.max_path, w.k_cache.shape[0]),
                               int(max(lens)))
     assert plan["row_chunks"] * plan["key_ranges"] <= 256, plan
+    check_kernel(R, w, kernels)
     check_attn(R, oracle_mod, w, variants=(0,))
 
 
 @pytest.mark.parametrize("case", range(16))
-def test_attn_seeded_random_shapes(R, oracle_mod, case):
+def test_attn_seeded_random_shapes(R, oracle_mod, case, kernels):
     # a seeded sweep over batch, tree size, head layout and length mix (empty sequences included), both
     # kernel flavours (up to 128 query rows per kv head, and more)
     rng = np.random.Generator(np.random.PCG64(9000 + case))
@@ -177,6 +214,7 @@ def test_attn_seeded_random_shapes(R, oracle_mod, case):
     w = W.make_custom("rand%d" % case, B=B, Hq=Hkv * G, Hkv=Hkv, D=D, T=T, seq_lens=[int(x) for x in L],
                       tree=str(rng.choice(["trie", "uniform", "chain", "star"])), depth=int(rng.integers(2, 12)),
                       branch=int(rng.integers(1, 6)), seed=9100 + case)
+    check_kernel(R, w, kernels)
     check_attn(R, oracle_mod, w, variants=(0,))
 
 
@@ -197,8 +235,8 @@ def test_attn_more_than_128_query_rows_both_decompositions(R, oracle_mod, rows, 
 @pytest.mark.parametrize("T,Hq,D,lens", [(16, 8, 128, [0, 1, 15, 16, 200]), (32, 32, 128, [333, 1024, 77]),
                                          (64, 16, 128, [500, 31]), (128, 16, 128, [260]), (100, 32, 128, [64, 129]),
                                          (16, 8, 64, [5, 700]), (1, 8, 128, [40, 0])])
-def test_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens):
-    check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants=(0, 1))
+def test_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, kernels):
+    check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants=variants_of(kernels), kernels=kernels)
 
 
 @pytest.mark.parametrize("T,Hq,D,lens", [(64, 16, 128, [500, 31]), (128, 16, 128, [260, 1500]), (100, 32, 128, [64, 129]),
@@ -213,7 +251,21 @@ def test_attn_tree_rows_in_the_cache_with_256_row_workgroups(R, oracle_mod, T, H
     check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants=(0,))
 
 
-def check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants):
+@pytest.mark.parametrize("T,in_cache", [(45, False), (45, True), (73, False), (73, True)])
+def test_attn_three_and_five_chunks_of_128_rows_on_the_ring_kernel(R, oracle_mod, T, in_cache, kernels):
+    # eight query rows per node and head dimension 64: 360 and 584 rows per kv head, the last chunk not full
+    lens = [301, 64, 777, 15]
+    if in_cache:
+        plan = check_attn_tree_rows_in_the_cache(R, oracle_mod, T, 32, 64, lens, variants=(0,), kernels=kernels)
+    else:
+        w = W.make_custom("chunks_T%d" % T, B=len(lens), Hq=32, Hkv=4, D=64, T=T, seq_lens=lens, tree="trie", depth=8, seed=412)
+        plan = check_kernel(R, w, kernels)
+        check_attn(R, oracle_mod, w, variants=(0,))
+    assert plan["rows_per_workgroup"] == 128 and plan["row_chunks"] == (3 if T == 45 else 5), plan
+    assert kernels == "planned" or plan["kernel"] == "tree_attn_mfma_kernel<64, 4>", plan
+
+
+def check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants, kernels=None):
     # the in-cache layout: no tree tensors, node n of sequence b sits at cache position L_b + n (any alignment
     # to the 16-position pages); the result must be what the oracle gives for the separate-tensor layout
     import torch
@@ -228,6 +280,8 @@ def check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants):
     dims = R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, table.shape[1], w.max_path, kc.shape[0])
     bound = int(max(lens))
     ws = torch.empty(max(R.reader_workspace_bytes(dims, bound), 256), dtype=torch.uint8, device="cuda")
+    plan = R.reader_attn_plan(dims, bound)
+    assert kernels is None or (plan["kernel_id"] == 4) == (kernels == "planned"), plan
     for variant in variants:
         dims.variant = variant
         dw.out.fill_(float("nan"))
@@ -245,6 +299,7 @@ def check_attn_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, variants):
     with pytest.raises(R.ReaderError):
         R.reader_tree_attn(dims, dw.q, None, None, bf16(kc), bf16(vc), torch.from_numpy(table).cuda(), dw.seq_lens,
                            dw.parents, dw.out, dw.lse, table.shape[1] * 16, ws, dw.status)
+    return plan
 
 
 def test_attn_custom_scale_and_peaked_scores(R, oracle_mod):
@@ -370,9 +425,10 @@ def test_attn_full_size_head_dim_64_with_256_row_workgroups(R, oracle_mod):
 
 # ------------------------------------------------------------------ device-side input errors
 
-def test_malformed_tree_and_bad_page_set_status_without_faulting(R, oracle_mod):
+def test_malformed_tree_and_bad_page_set_status_without_faulting(R, oracle_mod, kernels):
     w = W.make_custom("status", B=2, Hq=4, Hkv=2, D=128, T=10, seq_lens=[40, 90], tree="uniform", depth=4, seed=404)
     w.parents[1, 5] = 7                    # parent after child
+    check_kernel(R, w, kernels)
     for variant in (0, 1):
         run_attn(R, w, variant=variant, want_status=R.STATUS_BAD_TREE)
     w = W.make_custom("status2", B=2, Hq=4, Hkv=2, D=128, T=10, seq_lens=[40, 90], tree="uniform", depth=4, seed=405)
@@ -399,6 +455,7 @@ def test_malformed_tree_and_bad_page_set_status_without_faulting(R, oracle_mod):
     w.page_table[0, 9] = -1
     w.page_table[1, 4] = w.num_pages + 1      # a whole tile of sequence 1 (pages 4..7)
     w.page_table[1, 5] = w.page_table[1, 6] = w.page_table[1, 7] = -1
+    check_kernel(R, w, kernels)
     outs = [run_attn(R, w, variant=v, want_status=R.STATUS_BAD_PAGE) for v in (0, 1)]
     assert np.isfinite(outs[0][0]).all() and np.isfinite(outs[0][1]).all()
     assert_close(outs[0][0], outs[1][0], what="bad pages in the middle: matrix-core kernel against the scalar one")
@@ -550,10 +607,11 @@ def random_step_workload(case):
 
 @pytest.mark.parametrize("index,scale", [(0, 1.0), (1, 0.1), (2, 0.1), (2, 1.0), (3, 0.02), (4, 0.05)] +
                          [(-1 - c, 1.0) for c in range(10)])
-def test_verify_step_equals_the_three_calls_and_the_oracle(R, oracle_mod, index, scale):
+def test_verify_step_equals_the_three_calls_and_the_oracle(R, oracle_mod, index, scale, kernels):
     import torch
     # the presets, and a seeded sweep of random shapes (negative index)
     w = W.make_config(index, length_scale=scale) if index >= 0 else random_step_workload(-1 - index)
+    assert kernels == "planned" or plan_of(R, w)["kernel_id"] != 4
     # the three entry points, one after the other
     dw3 = run_step(R, w)
     # the fused entry point on a fresh upload of the same workload
@@ -580,7 +638,7 @@ def test_verify_step_equals_the_three_calls_and_the_oracle(R, oracle_mod, index,
 
 @pytest.mark.parametrize("T,Hq,D,lens", [(16, 8, 128, [0, 1, 15, 16, 200]), (40, 16, 64, [333, 1024, 77, 5]),
                                          (128, 16, 128, [50, 700])])
-def test_verify_step_with_the_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens):
+def test_verify_step_with_the_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens, kernels):
     check_verify_step_with_the_tree_rows_in_the_cache(R, oracle_mod, T, Hq, D, lens)
 
 

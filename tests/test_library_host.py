@@ -99,13 +99,36 @@ def test_a_workspace_for_the_largest_step_serves_every_smaller_one(R):
         small_b, small_l = int(rng.integers(1, B + 1)), int(rng.integers(0, L + 1))
         d = R.make_dims(small_b, T, G * Hkv, Hkv, D, 2048, 1, 4096)
         assert R.reader_workspace_bytes(d, small_l) <= most, (B, T, G, Hkv, D, L, small_b, small_l)
-        # ... and the records of the kernel that is taken fit it (a short problem's pair that is not cut leaves none)
-        plan = R.reader_attn_plan(d, small_l)
-        short = plan["kernel_id"] == 4
-        records = plan["key_ranges"] * plan["row_chunks"] * (1 if short else 2)
-        if short and plan["key_ranges"] == small_b * Hkv:
-            records = 0
-        assert records * plan["rows_per_workgroup"] * (D // 2 + 2) * 4 <= most, (plan, small_b, T, G, Hkv, D, small_l)
+        # ... and the records of the kernel that is taken fit the workspace of the call itself, behind its header
+        check_records_fit(R, d, small_l)
+
+
+def check_records_fit(R, d, bound):
+    plan = R.reader_attn_plan(d, bound)
+    header = -(-(256 * 4 + 256 * 8 * 4 + d.B * d.Hkv * 8) // 256) * 256
+    short = plan["kernel_id"] == 4
+    records = plan["key_ranges"] * plan["row_chunks"] * (1 if short else 2)
+    if short and plan["key_ranges"] == d.B * d.Hkv:
+        records = 0                                     # (a short problem's pair that is not cut leaves none)
+    need = records * plan["rows_per_workgroup"] * (d.D // 2 + 2) * 4
+    have = R.reader_workspace_bytes(d, bound) - header
+    assert need <= have, (plan, need, have, d.B, d.T, d.Hq, d.Hkv, d.D, bound)
+    return plan
+
+
+def test_records_fit_the_calls_own_workspace_on_every_route(R):
+    # three and five chunks of 128 rows and their neighbours, where the plan and the size of the records follow
+    # different rules, and the lengths around which a pair is cut
+    rng = np.random.default_rng(21)
+    met = set()
+    for _ in range(20000):
+        D, Hkv, G = int(rng.choice((64, 128))), int(rng.choice((1, 2, 4, 8))), int(rng.choice((1, 3, 4, 5, 8, 16)))
+        rows = int(rng.choice((100, 128, 129, 250, 256, 257, 300, 384, 385, 512, 513, 600, 640, 641, 800, 1000)))
+        T, B, L = min(128, -(-rows // G)), int(2 ** rng.uniform(0, 7)), int(2 ** rng.uniform(4, 17))
+        plan = check_records_fit(R, R.make_dims(B, T, G * Hkv, Hkv, D, 1 << 14, 1, 1 << 20), L)
+        met.add((D, plan["kernel_id"], plan["row_chunks"]))
+    assert {(D, k, c) for D in (64, 128) for k in (1, 4) for c in (1, 2, 3, 4, 5)} <= met
+    assert {(128, 3, 2), (128, 3, 3), (64, 2, 2), (64, 2, 4)} <= met
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,short", [
