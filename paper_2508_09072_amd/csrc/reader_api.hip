@@ -69,14 +69,18 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     if (forced == 128 || forced == 256) return forced;
     // Three or five chunks of 128 rows: a 256-row workgroup would carry a quarter or a sixth of its rows for nothing.
     // Measured with 264 to 640 query rows per kv head over 1 to 64 sequences of 0.3 to 32 K positions, 128-row over 256-row
-    // workgroups: three chunks 0.87 to 0.93 times as long at head dimension 64, 0.81 to 1.03 at 128 (24 sequences of 0.3 to
-    // 3 K: 70 -> 57 us; even with 32 K), five chunks 0.92 to 0.96 and 0.87 to 1.09.  That last group is ahead up to about 2.5 million tiles x tiles per pair (64
-    // sequences of 1 to 3 K positions: 476 -> 459 us, eight of 2 to 8 K 151 -> 145), behind beyond (two of 32 K 198 -> 203,
-    // 16 of 8 to 32 K 938 -> 1021): with long pairs the four-wavefront kernel has few pair boundaries to pay for, and
-    // in a long launch, whose clock the matrix units' power sets, its fewer operand reads count.
-    const int chunks = (d.T * (d.Hq / d.Hkv) + 127) / 128;
+    // workgroups: 0.87 to 0.96 at head dimension 64.  At 128 it is 0.81 to 0.99 while the product of the tiles of all
+    // pairs and the tiles of one stays small (24 sequences of 0.3 to 3 K and three chunks: 70 -> 57 us; 64 of 1 to 3 K and
+    // five: 459 -> 449) and more beyond: with long pairs the four-wavefront kernel has few pair boundaries to pay for, and
+    // in a long launch, whose clock the matrix units' power sets, its fewer operand reads count, the more so where most
+    // wavefronts of the last chunk have no rows.  Five chunks cross over at 2.5 million (two sequences of 32 K 191 -> 199,
+    // 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in the last 256 at about 6 (two of 32 K 129 -> 128,
+    // eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31 million).
+    const int M = d.T * (d.Hq / d.Hkv), chunks = (M + 127) / 128;
     const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
-    if (chunks == 3 || (chunks == 5 && (d.D == 64 || pairs * tiles <= 2500000 / tiles))) return 128;
+    const bool odd = chunks == 3 || chunks == 5;
+    const long long most = chunks == 5 ? 2500000 : 6000000;
+    if (odd && (d.D == 64 || (M > 320 && M <= 384) || pairs * tiles <= most / tiles)) return 128;
     return rows_per_wg_by_size(d, max_seq_len);
 }
 

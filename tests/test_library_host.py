@@ -146,8 +146,9 @@ def test_long_shares_of_several_sequences_are_left_to_the_ring_kernels(R, B, T, 
 @pytest.mark.parametrize("T,D,B,bound,rows", [
     (72, 128, 2, 32768, 256), (72, 128, 16, 32768, 256), (80, 128, 64, 8192, 256),        # five chunks, long pairs
     (72, 128, 64, 3000, 128), (72, 128, 8, 8192, 128), (72, 64, 16, 32768, 128),          # shorter ones; head dimension 64
-    (40, 128, 16, 32768, 128), (48, 128, 64, 8192, 128)])                                 # three chunks
-def test_five_chunks_of_128_rows_are_for_shorter_pairs(R, T, D, B, bound, rows):
+    (40, 128, 16, 32768, 256), (33, 128, 8, 32768, 256), (40, 128, 2, 32768, 128), (40, 64, 16, 32768, 128),   # three chunks, the last
+    (41, 128, 16, 32768, 128), (48, 128, 64, 8192, 128)])                                 # ... 256 rows up to a quarter full, and more
+def test_three_and_five_chunks_of_128_rows_are_for_shorter_pairs(R, T, D, B, bound, rows):
     # eight query rows per node; 16 sequences of 8 to 32 K positions: 1021 us in 128-row workgroups, 938 in 256-row ones
     plan = R.reader_attn_plan(R.make_dims(B, T, 64, 8, D, 2100, 1, 200000), bound)
     assert plan["rows_per_workgroup"] == rows, plan
