@@ -132,7 +132,7 @@ def roofline_of(w, each):
                 "frac": tflops / MFMA_BF16_PEAK_TFLOPS}
     from paper_2508_09072_amd import binding as R
     plan = R.reader_attn_plan(R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages),
-                              int(w.seq_lens.max()))
+                              int(w.seq_lens.max()) + w.max_path)       # (the bound the launches have, see to_device)
     roof.update({"kernel": plan["kernel"], "workgroups": plan["key_ranges"] * plan["row_chunks"],
                  "rows_per_workgroup": plan["rows_per_workgroup"], "kernel_ms": kernel_ms, "launches_timed": n,
                  "kernel_ms_median": float(np.median(each)) if n else None,
