@@ -76,6 +76,7 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     // wavefronts of the last chunk have no rows.  Five chunks cross over at 2.5 million (two sequences of 32 K 191 -> 199,
     // 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in the last 256 at about 6 (two of 32 K 129 -> 128,
     // eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31 million).
+    // Seven chunks go by size like the even ones: 1.02 to 1.20, but 0.97 with 24 sequences of 0.3 to 3 K.
     const int M = d.T * (d.Hq / d.Hkv), chunks = (M + 127) / 128;
     const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     const bool odd = chunks == 3 || chunks == 5;
@@ -143,9 +144,10 @@ static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
 // Short problems run a kernel of their own (tree_attn_short.hip): rows per workgroup, and how many shares the tiles of
 // a pair are cut into; false: one of the ring kernels runs.
 //
-// The rule was fitted to 150 shapes drawn over 1..64 sequences of up to 32 K positions, 1..128 nodes, both head
-// dimensions and three head layouts, each timed with every number of shares and with the ring kernels (it comes
-// within 3 % of the best choice on average, and the launches it takes are 1.26 times faster than the ring kernels'):
+// The rule was fitted to shapes drawn over 1..64 sequences of up to 32 K positions, 1..128 nodes, both head
+// dimensions and three head layouts, each timed with every number of shares and with the ring kernels.  On 150 others
+// it comes within 3 % of the best choice (geometric mean; worst 1.43 times it, launches of 10 to 20 us), and the ring kernels
+// take 1.6 times as long (geometric mean; least 0.94 times):
 //   - as many shares as fill the compute units once (head dimension 64: twice, two workgroups fit one), but no
 //     more than sqrt(12 tiles): a share costs the merge about a twelfth of what a tile costs the workgroup;
 //   - none where they would save a workgroup less than four tiles' time (six at head dimension 64, whose tiles take less
