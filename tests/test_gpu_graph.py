@@ -116,8 +116,12 @@ def test_measured_peaks_are_plausible_and_bad_sizes_are_refused():
     assert 2000.0 < got["hbm_read_gbs"] < 8000.0
     assert 800.0 < got["mfma_bf16_tflops"] < 2600.0
     assert 900.0 < got["mfma_clock_mhz"] < 2600.0
-    # the rate is what 1024 matrix pipes do at that clock, one 32-cycle instruction after the other
-    assert abs(got["mfma_bf16_tflops"] - 1024 * 32768 / 32 * got["mfma_clock_mhz"] * 1e-6) < 0.05 * got["mfma_bf16_tflops"]
+    # The rate is what 1024 matrix pipes do at that clock, one 32-cycle instruction after the other.  The clock is read by
+    # the first workgroup, on one XCD, and the launch ends with the slowest: never above that clock's rate (1 % for the
+    # event's resolution), and below it by up to what XCDs differ by under matrix load, a tenth (160 against 176 us
+    # for equal work), and 1 % for the launch.  (Seen on fresh boxes: 0.2 to 5.3 % below.)
+    at_clock = 1024 * 32768 / 32 * got["mfma_clock_mhz"] * 1e-6
+    assert 0.89 * at_clock < got["mfma_bf16_tflops"] < 1.01 * at_clock
     with pytest.raises(RuntimeError):
         R.reader_measure_peaks(src[: 1 << 20], scratch)
     with pytest.raises(RuntimeError):
