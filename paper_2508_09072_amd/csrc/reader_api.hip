@@ -158,12 +158,14 @@ static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
 //   - the ring kernels, which cut the work evenly whatever the lengths and take several pairs per workgroup in their
 //     stride, from about 20 tiles per workgroup and round on (24 at head dimension 64); but pairs of up to 16 tiles
 //     that need no cutting are left to the hardware's own scheduling however many there are;
-//   - and from 13 tiles per workgroup on where the pairs of several sequences would be cut: the shares are as long as the
-//     longest sequence makes them, whatever the others' lengths, and the host knows no more than that bound.  Measured
-//     against the ring kernels at 13 to 24 tiles per workgroup (how many times faster; geometric mean and worst of 130
-//     shapes): equal lengths 1.10 (0.98), lengths between a quarter of the bound and all of it 0.99 (0.84), one
-//     sequence that long among others of 64 positions 1.03 (0.69); at 9 to 12 tiles 1.09 (0.95), 1.05 (0.90) and 1.16
-//     (0.87).
+//   - sooner where the pairs of several sequences would be cut: the shares are as long as the longest sequence makes
+//     them, whatever the others' lengths, and the host knows no more than that bound.  From more than 14 tiles per
+//     workgroup on (20 at head dimension 64), and four less where there are two shares.  Measured against the ring
+//     kernels on 420 shapes of 8 to 24 tiles, how many times faster (geometric mean and worst), for lengths from a tenth, a
+//     quarter and half of the bound to all of it, all equal, and one of the bound among others of 64 positions: below
+//     the line 1.08 (0.93), 1.09 (0.96), 1.10 (0.98), 1.11 (1.01) and 1.21 (0.88), head dimension 64 1.11 (0.91), 1.11
+//     (0.95), 1.13 (1.00), 1.16 (1.03) and 1.27 (0.78); beyond it 0.98 (0.84), 1.00 (0.88), 1.03 (0.85), 1.07 (0.95) and
+//     0.98 (0.73), and 1.03 (0.92), 1.04 (0.91), 1.08 (0.95), 1.14 (1.04) and 1.07 (0.70).
 struct ShortPlan {
     int rows, chunks, splits;
 };
@@ -198,7 +200,7 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     if (per > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
     if (n > 1024 || n * tiles >= 1 << 22) return false;   // (its arithmetic on shares is exact below that)
     if (forced >= 1) return true;
-    if (n > 1 && d.B > 1) return per <= 12;
+    if (n > 1 && d.B > 1) return per <= (d.D == 64 ? 20 : 14) - (n == 2 ? 4 : 0);
     return (n == 1 && tiles <= 16) || per * rounds <= (d.D == 64 ? 24 : 20);
 }
 

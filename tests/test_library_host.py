@@ -132,8 +132,10 @@ def test_records_fit_the_calls_own_workspace_on_every_route(R):
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,short", [
-    (16, 16, 32, 8, 128, 1400, True), (16, 16, 32, 8, 128, 1600, False), (16, 16, 32, 8, 128, 2400, False),   # two shares: 12 tiles, 13, 20
-    (8, 64, 32, 8, 64, 2900, True), (8, 64, 32, 8, 64, 4000, False), (32, 64, 8, 2, 128, 2400, False),
+    (16, 16, 32, 8, 128, 1200, True), (16, 16, 32, 8, 128, 1400, False), (16, 16, 32, 8, 128, 2400, False),   # two shares: 10 tiles, 12, 20
+    (8, 16, 32, 8, 128, 3500, True), (8, 16, 32, 8, 128, 3700, False), (32, 64, 8, 2, 128, 2400, False),       # four: 14, 15; two: 20
+    (8, 64, 32, 8, 64, 5000, True), (8, 64, 32, 8, 64, 5300, False),                       # head dimension 64, four: 20, 21
+    (13, 64, 32, 8, 64, 1900, True), (13, 64, 32, 8, 64, 2100, False),                     # two: 16, 17
     (1, 64, 32, 8, 128, 16000, True), (1, 16, 8, 8, 64, 32000, True),                      # one sequence: all shares are alike
     (32, 16, 32, 8, 128, 1200, True), (24, 16, 32, 8, 64, 1400, True)])                    # pairs that are not cut
 def test_long_shares_of_several_sequences_are_left_to_the_ring_kernels(R, B, T, Hq, Hkv, D, bound, short):
