@@ -63,7 +63,7 @@ struct AttnParams {
 
 // Size of one partial record in 4-byte units: `rows` rows of D bf16 outputs (normalised by the
 // record's own sum), then the rows' running maxima and running sums as fp32.
-__host__ __device__ inline size_t attn_slot_floats(int D, int rows) { return (size_t)rows * (size_t)(D / 2 + 2); }
+__host__ __device__ constexpr size_t attn_slot_floats(int D, int rows) { return (size_t)rows * (size_t)(D / 2 + 2); }
 
 // The workspace starts with a header the main kernel leaves for the kernels after it: one int per
 // range workgroup (kNumCU of them at most), one int per workgroup of the 256-row kernels (the

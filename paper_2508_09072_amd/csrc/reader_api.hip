@@ -410,7 +410,7 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
         p.n_splits = sp.splits;
         p.split_rcp = 1.0f / (float)sp.splits;
         p.keep_whole = sp.splits > 1 && tuning(READER_TUNE_ATTN_SHORT) < 1;   // (forced: every pair is cut as asked for)
-        p.merge_groups = sp.splits > 8 ? 4 : 1;
+        p.merge_groups = sp.splits > 4 ? 4 : 1;
     }
 #ifdef READER_WG_STAMPS
     p.stamps = g_wg_stamps.load(std::memory_order_relaxed);

@@ -479,86 +479,105 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
     if (p.status && bad) atomicOr(p.status, bad);
 }
 
-// Merge of the n_splits records of every query row: one thread per 8-wide chunk of a row, all records of a row (eight
-// at a time) asked for together.  With many splits four thread groups (one wavefront each) share a row's records.
-template <int D>
-__device__ inline void merge_short_body(const AttnParams &p, int pair, int block_y) {
-    constexpr int kC = D / 8;
-    const int groups = p.merge_groups, group_threads = 256 / groups;
-    const int tid = threadIdx.x, grp = tid / group_threads, t2 = tid - grp * group_threads;
-    const int m = block_y * (group_threads / kC) + t2 / kC, c = t2 % kC;
-    const bool live = m < p.M;
-    const int rows = p.rows_per_wg, chunk = m / rows, r = m - chunk * rows, n_splits = p.n_splits;
-    const size_t rec_floats = attn_slot_floats(D, rows);
-    const float *rec = p.workspace + ((size_t)pair * p.n_row_chunks + chunk) * n_splits * rec_floats;
-    const int share = (n_splits + groups - 1) / groups, first = grp * share, last = min(n_splits, first + share);
-    float m_all = -INFINITY, l_all = 0.f, acc[8];
+// Merge of the n_splits records of every query row.  A record is laid out [chunk of 8 values][row], so a wavefront takes 16
+// consecutive rows of four chunks: its loads fetch 256 contiguous bytes per chunk.  With more than four shares the four
+// wavefronts of a workgroup take a quarter of the shares each and fold their states through LDS in the order of the shares.
+//
+// What bounds it: a launch, one trip to memory for the records (other compute units have just written them past the
+// caches) and the way back; loads are few and asked for together, four records at a time.  As one thread per row and chunk
+// in row order, eight records at a time whether there were that many or not, it took 6.6 us where this takes 4.2 (three
+// sequences of 0.7 - 2.5 K tokens, ten shares of 24 pairs with 100 rows; four wavefronts per row from nine shares on there).
+struct MergeState {
+    float m, l, acc[8];
+    __device__ __forceinline__ void fold(float m2, float l2, const float (&v)[8]) {     // another state, its sum of weights l2
+        const float m_new = fmaxf(m, m2);
+        const float fa = __builtin_amdgcn_exp2f(m - m_new), fb = __builtin_amdgcn_exp2f(m2 - m_new);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    constexpr int kBatch = 8;
-    for (int s0 = first; s0 < last && live; s0 += kBatch) {
+        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * fa + v[e] * fb;
+        l = l * fa + l2 * fb;
+        m = m_new;
+    }
+};
+
+template <int D>
+__device__ __forceinline__ void merge_short_body(const AttnParams &p, int b, int hkv, int block) {
+    constexpr int kQuads = D / 32;                           // sets of four chunks in a row
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_splits = p.n_splits;
+    const bool four = p.merge_groups == 4;
+    const int unit = four ? block : block * 4 + wave;        // 16 rows x 4 chunks
+    const int m = (unit / kQuads) * 16 + (lane & 15), c = (unit % kQuads) * 4 + (lane >> 4);
+    const bool live = m < p.M;
+    const int chunk = m / kShortRows, r = m % kShortRows;
+    constexpr size_t kRec = attn_slot_floats(D, kShortRows);
+    const float *rec = p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + (live ? chunk : 0)) * n_splits * kRec;
+    const int share = four ? (n_splits + 3) >> 2 : n_splits, first = four ? wave * share : 0, last = min(n_splits, first + share);
+    MergeState st;
+    st.m = -INFINITY;
+    st.l = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st.acc[e] = 0.f;
+    constexpr int kBatch = 4;
+    for (int s0 = first; s0 < last; s0 += kBatch) {
         float ms[kBatch], ls[kBatch];
         uint4 v[kBatch];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            const float *part = rec + (size_t)min(s0 + j, last - 1) * rec_floats;
-            ms[j] = part[rows * (D / 2) + r];
-            ls[j] = part[rows * (D / 2 + 1) + r];
-            v[j] = reinterpret_cast<const uint4 *>(part)[(size_t)c * rows + r];
+            const float *part = rec + (size_t)min(s0 + j, last - 1) * kRec;
+            v[j] = reinterpret_cast<const uint4 *>(part)[c * kShortRows + r];
+            ms[j] = part[kShortRows * (D / 2) + r];
+            ls[j] = part[kShortRows * (D / 2 + 1) + r];
         }
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             if (s0 + j >= last || ms[j] == -INFINITY) continue;      // (no key of that share for this row)
-            const float m_new = fmaxf(m_all, ms[j]);
-            const float fa = __builtin_amdgcn_exp2f(m_all - m_new), fb = __builtin_amdgcn_exp2f(ms[j] - m_new) * ls[j];
             const uint32_t u[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+            float x[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                acc[2 * e] = acc[2 * e] * fa + fb * __uint_as_float(u[e] << 16);
-                acc[2 * e + 1] = acc[2 * e + 1] * fa + fb * __uint_as_float(u[e] & 0xffff0000u);
+                x[2 * e] = ls[j] * __uint_as_float(u[e] << 16);
+                x[2 * e + 1] = ls[j] * __uint_as_float(u[e] & 0xffff0000u);
             }
-            l_all = l_all * fa + fb;
-            m_all = m_new;
+            st.fold(ms[j], ls[j], x);
         }
     }
-    if (groups > 1) {
-        __shared__ float s_state[3][64][10];
-        if (grp > 0) {
-            float *st = s_state[grp - 1][t2];
-            st[0] = m_all; st[1] = l_all;
+    if (four) {
+        __shared__ float s_state[3][10][64];
+        if (wave > 0) {
+            float *o = &s_state[wave - 1][0][lane];
+            o[0] = st.m;
+            o[64] = st.l;
 #pragma unroll
-            for (int d = 0; d < 8; ++d) st[2 + d] = acc[d];
+            for (int e = 0; e < 8; ++e) o[(2 + e) * 64] = st.acc[e];
         }
         __syncthreads();
-        if (grp > 0) return;
-        for (int g = 0; g < groups - 1; ++g) {
-            const float *st = s_state[g][t2];
-            const float m_g = st[0];
-            if (m_g == -INFINITY) continue;
-            const float m_new = fmaxf(m_all, m_g);
-            const float fa = __builtin_amdgcn_exp2f(m_all - m_new), fb = __builtin_amdgcn_exp2f(m_g - m_new);
+        if (wave > 0) return;
 #pragma unroll
-            for (int d = 0; d < 8; ++d) acc[d] = acc[d] * fa + st[2 + d] * fb;
-            l_all = l_all * fa + st[1] * fb;
-            m_all = m_new;
+        for (int g = 0; g < 3; ++g) {
+            const float *o = &s_state[g][0][lane];
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = o[(2 + e) * 64];
+            if (o[0] != -INFINITY) st.fold(o[0], o[64], x);
         }
     }
     if (!live) return;
-    const int b = pair / p.Hkv, hkv = pair - b * p.Hkv, node = m / p.G, group = m - node * p.G;
-    const float inv = 1.f / l_all;                                    // (> 0: every row sees its own tree node)
+    // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
+    const int node = (int)(((float)m + 0.5f) * (1.0f / (float)p.G)), group = m - node * p.G;
+    const float inv = 1.f / st.l;                                     // (> 0: every row sees its own tree node)
     uint4 w;
-    w.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-    w.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-    w.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
-    w.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
+    w.x = pack_bf16x2(st.acc[0] * inv, st.acc[1] * inv);
+    w.y = pack_bf16x2(st.acc[2] * inv, st.acc[3] * inv);
+    w.z = pack_bf16x2(st.acc[4] * inv, st.acc[5] * inv);
+    w.w = pack_bf16x2(st.acc[6] * inv, st.acc[7] * inv);
     *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = w;
     if (p.lse && c == 0)
-        p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_all + __builtin_amdgcn_logf(l_all)) * kLn2;
+        p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (st.m + __builtin_amdgcn_logf(st.l)) * kLn2;
 }
 
 template <int D>
 __global__ __launch_bounds__(256) void merge_short_kernel(AttnParams p) {
-    merge_short_body<D>(p, blockIdx.x, blockIdx.y);
+    merge_short_body<D>(p, blockIdx.z, blockIdx.y, blockIdx.x);
 }
 
 // Tail of the fused step: one workgroup per sequence that accepts a path and appends its rows, then the merge
@@ -566,8 +585,8 @@ __global__ __launch_bounds__(256) void merge_short_kernel(AttnParams p) {
 template <int D>
 __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks_y) {
     if ((int)blockIdx.x >= p.B) {
-        const int m = blockIdx.x - p.B;
-        merge_short_body<D>(p, m / merge_blocks_y, m % merge_blocks_y);
+        const int m = blockIdx.x - p.B, pair = m / merge_blocks_y, seq = pair / p.Hkv;
+        merge_short_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks_y);
         return;
     }
     __shared__ AcceptShared sh;
@@ -609,14 +628,14 @@ hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_sta
                       const CompactParams *cp) {
     const hipError_t e = launch_main<D>(p, stream, ev_start, ev_stop);
     if (e != hipSuccess) return e;
-    const int rows_per_block = 256 / p.merge_groups / (D / 8);
-    const int merge_y = p.n_splits > 1 ? (p.M + rows_per_block - 1) / rows_per_block : 0;
+    const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
+    const int merge_y = p.n_splits == 1 ? 0 : p.merge_groups == 4 ? units : (units + 3) / 4;
     if (ap && cp) {
         hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * merge_y), dim3(256), 0, stream, p, *ap, *cp, merge_y);
         return note_hip_error("launch verify_tail_short_kernel", hipGetLastError());
     }
     if (merge_y == 0) return hipSuccess;
-    hipLaunchKernelGGL(merge_short_kernel<D>, dim3(p.B * p.Hkv, merge_y), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(merge_short_kernel<D>, dim3(merge_y, p.Hkv, p.B), dim3(256), 0, stream, p);
     return note_hip_error("launch merge_short_kernel", hipGetLastError());
 }
 

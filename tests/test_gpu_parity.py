@@ -881,6 +881,18 @@ def test_attn_short_problem_kernel(R, oracle_mod, T, G, D, lens, splits, in_cach
         assert_close(lse, ref_lse, what="bad page lse")
 
 
+@pytest.mark.parametrize("T,G,D,splits", [
+    (15, 1, 64, 4), (16, 1, 128, 5),         # the merge takes 16 rows x 4 chunks per wavefront: one block of rows, full or not;
+    (17, 1, 128, 4), (17, 1, 64, 5),         # up to four shares one wavefront reads all of them, from five on four share them out
+    (127, 1, 64, 8), (43, 3, 128, 9),        # edges of the record (128 rows); shares per wavefront that come out even or not
+])
+def test_attn_short_problem_merge_edges(R, oracle_mod, T, G, D, splits, tune):
+    tune(R.TUNE_ATTN_SHORT, splits)
+    w = W.make_custom("merge_T%d_S%d" % (T, splits), B=2, Hq=2 * G, Hkv=2, D=D, T=T, seq_lens=[900, 70], tree="trie", depth=6,
+                      branch=3, k_outlier_frac=0.05, seed=520 + T + splits)
+    check_attn(R, oracle_mod, w, variants=(0,))
+
+
 @pytest.mark.parametrize("B,Hkv,D,lens", [(32, 8, 64, [1000] * 32),                   # 256 equal pairs: one range each
                                           (8, 8, 64, [2400] + [64] * 7), (8, 8, 128, [2400] + [64] * 7),   # one long among short
                                           (70, 2, 64, [40 + 13 * b for b in range(70)])])     # more sequences than lanes
