@@ -412,6 +412,59 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// Eight output values of a query row while its partial records are merged: running maximum (exponent of two), sum of
+// weights relative to it, weighted sum of the records' outputs.
+struct MergeState {
+    float m = -INFINITY, l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+    __device__ __forceinline__ void fold(float m2, float l2, const float (&v)[8]) {
+        const float m_new = fmaxf(m, m2);
+        const float fa = __builtin_amdgcn_exp2f(m - m_new), fb = __builtin_amdgcn_exp2f(m2 - m_new);   // (fa = 0 the first time)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * fa + v[e] * fb;
+        l = l * fa + l2 * fb;
+        m = m_new;
+    }
+    // a record: eight bf16 outputs normalised by the record's own sum l2
+    __device__ __forceinline__ void fold_record(float m2, float l2, const uint4 &w) {
+        const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = l2 * __uint_as_float(u[e] << 16);
+            v[2 * e + 1] = l2 * __uint_as_float(u[e] & 0xffff0000u);
+        }
+        fold(m2, l2, v);
+    }
+    // The states of the four wavefronts of a workgroup, folded into the first one's in their order.  All threads call this;
+    // true for the first wavefront.
+    __device__ __forceinline__ bool gather(float (&s_state)[3][10][64], int wave, int lane) {
+        if (wave > 0) {
+            float *o = &s_state[wave - 1][0][lane];
+            o[0] = m;
+            o[64] = l;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[(2 + e) * 64] = acc[e];
+        }
+        __syncthreads();
+        if (wave > 0) return false;
+#pragma unroll
+        for (int g = 0; g < 3; ++g) {
+            const float *o = &s_state[g][0][lane];
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = o[(2 + e) * 64];
+            if (o[0] != -INFINITY) fold(o[0], o[64], v);
+        }
+        return true;
+    }
+    __device__ __forceinline__ uint4 result() const {
+        const float inv = 1.f / l;                               // (> 0: every row sees its own tree node)
+        return make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
+                          pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
+    }
+};
+
 // Transposing LDS load of gfx950: within each group of 16 lanes the 16 x 4 block of
 // 16-bit elements the lanes point at (lane k supplies 4 consecutive elements) is read
 // as 4 rows of 16, and lane i receives element i of each row.

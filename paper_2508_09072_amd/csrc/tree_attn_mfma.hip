@@ -775,132 +775,71 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
 }
 
 // Merge the partial records of every pair that was cut between workgroups.
-// A record holds [D / 8 chunks][rows][8 bf16] of output normalised by the record's own sum, then
-// the rows' running maxima, then their running sums.  One thread takes one 8-wide chunk of one
-// query row: D / 8 threads per row, 256 / (D / 8) rows per workgroup; grid = (B * Hkv, rows / that).
-// Which workgroups hold a pair's records, and which ranges are empty, come from the header the
-// main kernel wrote.
+// A record holds [D / 8 chunks][rows][8 bf16] of output normalised by the record's own sum, then the rows' running maxima,
+// then their running sums.  A wavefront takes 16 consecutive rows of four chunks (256 contiguous bytes per chunk and
+// load, 64 of an output row).  With few pairs and many ranges a pair is cut into dozens of parts: the four wavefronts of a
+// workgroup then take a quarter of the parts each and fold their states through LDS in the order of the ranges.
+// Which workgroups hold a pair's records, and which ranges are empty, come from the header the main kernel wrote.
+// Measured against one thread per row and chunk in row order, eight records at a time, behind integer divisions: alone
+// 6.0 -> 5.0 us (24 sequences of 0.3 - 3 K, head dimension 64, 360 rows), as tail of a step 7.4 -> 6.9 (16 of 1 - 4 K) and
+// 18.9 -> 16.3 (64 of 2 - 8 K, 100 MB of records and rows).
 template <int D>
-__device__ inline void merge_body(const AttnParams &p, int pair, int block_y) {
-    const int b = pair / p.Hkv, hkv = pair - b * p.Hkv;
-    const int2 info = reinterpret_cast<const int2 *>(p.pair_info)[pair];
-    const int w_first = info.x, w_last = info.y;
+__device__ __forceinline__ void merge_body(const AttnParams &p, int b, int hkv, int block) {
+    const int2 info = reinterpret_cast<const int2 *>(p.pair_info)[b * p.Hkv + hkv];
+    constexpr int kQuads = D / 32;                           // sets of four chunks in a row
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool four = p.merge_groups == 4;
+    const int unit = four ? block : block * 4 + wave;        // 16 rows x 4 chunks
+    const int m_row = (unit / kQuads) * 16 + (lane & 15), c = (unit % kQuads) * 4 + (lane >> 4);
+    const bool live = m_row < p.M;
+    const int rows = p.rows_per_wg, row_chunk = live ? (rows == 128 ? m_row / 128 : m_row / 256) : 0;
+    const int row_local = live ? m_row - row_chunk * rows : 0;
+    const size_t rec_floats = attn_slot_floats(D, rows);
+    const int w_first = __builtin_amdgcn_readfirstlane(info.x), w_last = __builtin_amdgcn_readfirstlane(info.y);
     if (w_first == w_last) return;   // finished in place by one workgroup (the whole workgroup leaves)
 
-    // p.merge_groups (1 or 4) thread groups share a query row's records: with few pairs and many
-    // ranges a pair is cut into dozens of parts, and the groups fetch theirs side by side.
-    constexpr int kC = D / 8;                   // chunks (threads) per row
-    const int groups = p.merge_groups, group_threads = 256 / groups;
-    const int rows_per_block = group_threads / kC;
-    const int tid = threadIdx.x, grp = tid / group_threads, t2 = tid - grp * group_threads;
-    const int blocks_per_chunk = p.rows_per_wg / rows_per_block;
-    const int row_chunk = block_y / blocks_per_chunk;
-    const int block_in_chunk = block_y - row_chunk * blocks_per_chunk;
-    // Thread -> (row, 8-wide chunk).  One group: a workgroup takes rows_per_block whole rows, a row's chunks on
-    // neighbouring threads.  Four groups (one wavefront each): a record is laid out [chunk][row], so a wavefront
-    // takes 16 consecutive rows of four chunks (256 contiguous bytes per chunk and load) instead of four whole
-    // rows (64), and the workgroups of a row block take a quarter of the chunks each; same number of workgroups.
-    int row_local, c;
-    if (groups == 1) {
-        row_local = block_in_chunk * rows_per_block + t2 / kC;
-        c = t2 % kC;
-    } else {
-        constexpr int kQuarters = kC / 4;
-        row_local = (block_in_chunk / kQuarters) * 16 + (t2 & 15);
-        c = (block_in_chunk % kQuarters) * 4 + (t2 >> 4);
-    }
-    const int m_row = row_chunk * p.rows_per_wg + row_local;
-    const bool live = m_row < p.M;
-    const int node = live ? m_row / p.G : 0, group = live ? m_row - node * p.G : 0;
-    const size_t rows = p.rows_per_wg;
-    const size_t rec_floats = attn_slot_floats(D, p.rows_per_wg);
-    // this group's share of the parts, in range order
-    const int n_parts = w_last - w_first + 1, share = (n_parts + groups - 1) / groups;
-    const int my_first = w_first + grp * share, my_last = min(w_last, my_first + share - 1);
-
-    // online merge: every part's loads are independent of the other parts' values
-    float m_all = -INFINITY, l_all = 0.f;
-    float acc[8];
-#pragma unroll
-    for (int d = 0; d < 8; ++d) acc[d] = 0.f;
-    // Records are fetched eight at a time (all their loads in flight together) and folded in in range order.
-    constexpr int kBatch = 8;
-    for (int w0 = my_first; w0 <= my_last && live; w0 += kBatch) {
+    // this wavefront's share of the parts, in range order
+    const int n_parts = w_last - w_first + 1, share = four ? (n_parts + 3) >> 2 : n_parts;
+    const int my_first = four ? w_first + wave * share : w_first, my_last = min(w_last, my_first + share - 1);
+    MergeState st;
+    // Records are fetched four at a time (all their loads in flight together) and folded in in range order.
+    constexpr int kBatch = 4;
+    for (int w0 = my_first; w0 <= my_last; w0 += kBatch) {
         float mw[kBatch], lw[kBatch];
         uint4 v[kBatch];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            const int w = w0 + j;
-            mw[j] = -INFINITY;
-            if (w <= my_last) {
-                // A range that holds no tile (more workgroups than tiles) wrote no record: its slot
-                // holds stale bytes.  The slot is read all the same, next to the range's tile count and
-                // not behind it (one round trip less), and dropped afterwards.
-                const int n_here = p.range_tiles[w];
-                const size_t slot = ((size_t)(2 * w + (w == w_first ? 1 : 0)) * p.n_row_chunks + row_chunk);
-                const float *rec = p.workspace + slot * rec_floats;
-                const float m_rec = rec[rows * (D / 2) + row_local];
-                lw[j] = rec[rows * (D / 2 + 1) + row_local];
-                v[j] = reinterpret_cast<const uint4 *>(rec)[(size_t)c * rows + row_local];
-                mw[j] = n_here != 0 ? m_rec : -INFINITY;
-            }
+            // A range that holds no tile (more workgroups than tiles) wrote no record: its slot holds stale bytes.  The
+            // slot is read all the same, next to the range's tile count and not behind it (one round trip less), and
+            // dropped afterwards.
+            const int w = min(w0 + j, my_last);
+            const int n_here = p.range_tiles[w];
+            const size_t slot = ((size_t)(2 * w + (w == w_first ? 1 : 0)) * p.n_row_chunks + row_chunk);
+            const float *rec = p.workspace + slot * rec_floats;
+            v[j] = reinterpret_cast<const uint4 *>(rec)[c * rows + row_local];
+            const float m_rec = rec[rows * (D / 2) + row_local];
+            lw[j] = rec[rows * (D / 2 + 1) + row_local];
+            mw[j] = n_here != 0 && w0 + j <= my_last ? m_rec : -INFINITY;
         }
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (mw[j] == -INFINITY) continue;   // no record, or this row saw no key of that part
-            const float m_new = fmaxf(m_all, mw[j]);
-            const float fa = __builtin_amdgcn_exp2f(m_all - m_new);      // 0 for the first part
-            const float fb = __builtin_amdgcn_exp2f(mw[j] - m_new) * lw[j];
-            const uint32_t u[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc[2 * e] = acc[2 * e] * fa + fb * __uint_as_float(u[e] << 16);
-                acc[2 * e + 1] = acc[2 * e + 1] * fa + fb * __uint_as_float(u[e] & 0xffff0000u);
-            }
-            l_all = l_all * fa + fb;
-            m_all = m_new;
-        }
+        for (int j = 0; j < kBatch; ++j)
+            if (mw[j] != -INFINITY) st.fold_record(mw[j], lw[j], v[j]);   // (else no record, or this row saw no key of that part)
     }
-    if (groups > 1) {
-        // groups 1.. leave their state in LDS; group 0 folds them in, in range order
-        __shared__ float s_state[3][64][10];
-        if (grp > 0) {
-            float *st = s_state[grp - 1][t2];
-            st[0] = m_all; st[1] = l_all;
-#pragma unroll
-            for (int d = 0; d < 8; ++d) st[2 + d] = acc[d];
-        }
-        __syncthreads();
-        if (grp > 0) return;
-        for (int g = 0; g < groups - 1; ++g) {
-            const float *st = s_state[g][t2];
-            const float m_g = st[0];
-            if (m_g == -INFINITY) continue;
-            const float m_new = fmaxf(m_all, m_g);
-            const float fa = __builtin_amdgcn_exp2f(m_all - m_new), fb = __builtin_amdgcn_exp2f(m_g - m_new);
-#pragma unroll
-            for (int d = 0; d < 8; ++d) acc[d] = acc[d] * fa + st[2 + d] * fb;
-            l_all = l_all * fa + st[1] * fb;
-            m_all = m_new;
-        }
+    if (four) {
+        __shared__ float s_state[3][10][64];
+        if (!st.gather(s_state, wave, lane)) return;
     }
     if (!live) return;
-    // l_all > 0: every query row sees at least its own tree node
-    const float inv = 1.f / l_all;
-    uint16_t *orow = p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8;
-    uint4 w;
-    w.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-    w.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-    w.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
-    w.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
-    *reinterpret_cast<uint4 *>(orow) = w;
+    // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
+    const int node = (int)(((float)m_row + 0.5f) * (1.0f / (float)p.G)), group = m_row - node * p.G;
+    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = st.result();
     if (p.lse && c == 0)
-        p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_all + __builtin_amdgcn_logf(l_all)) * kLn2;
+        p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (st.m + __builtin_amdgcn_logf(st.l)) * kLn2;
 }
 
 template <int D>
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnParams p) {
-    merge_body<D>(p, blockIdx.x, blockIdx.y);
+    merge_body<D>(p, blockIdx.z, blockIdx.x, blockIdx.y);
 }
 
 // Tail of the fused step: one workgroup per sequence that accepts a path and appends its rows
@@ -913,8 +852,8 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(AttnParams p, AcceptPa
     // the per-sequence workgroups come first in the grid: theirs is the longest chain of
     // dependent memory accesses, so they should start first
     if ((int)blockIdx.x >= p.B) {
-        const int m = blockIdx.x - p.B;
-        merge_body<D>(p, m / merge_blocks_y, m % merge_blocks_y);
+        const int m = blockIdx.x - p.B, pair = m / merge_blocks_y, seq = pair / p.Hkv;
+        merge_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks_y);
         return;
     }
     __shared__ AcceptShared sh;
@@ -963,13 +902,14 @@ static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_
 // Second launch: merge of the partial records, and in the fused step acceptance and compaction.
 template <int D>
 static hipError_t launch_tail(const AttnParams &p, hipStream_t stream, const AcceptParams *ap, const CompactParams *cp) {
-    const int merge_y = p.n_row_chunks * (p.rows_per_wg / (256 / p.merge_groups / (D / 8)));
+    const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
+    const int merge_y = p.merge_groups == 4 ? units : (units + 3) / 4;
     if (ap && cp) {
         const int n_merge = p.B * p.Hkv * merge_y;
         hipLaunchKernelGGL(verify_tail_kernel<D>, dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
         return note_hip_error("launch verify_tail_kernel", hipGetLastError());
     }
-    hipLaunchKernelGGL(tree_attn_merge_kernel<D>, dim3(p.B * p.Hkv, merge_y), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(tree_attn_merge_kernel<D>, dim3(p.Hkv, merge_y, p.B), dim3(256), 0, stream, p);
     return note_hip_error("launch tree_attn_merge_kernel", hipGetLastError());
 }
 

@@ -487,18 +487,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
 // caches) and the way back; loads are few and asked for together, four records at a time.  As one thread per row and chunk
 // in row order, eight records at a time whether there were that many or not, it took 6.6 us where this takes 4.2 (three
 // sequences of 0.7 - 2.5 K tokens, ten shares of 24 pairs with 100 rows; four wavefronts per row from nine shares on there).
-struct MergeState {
-    float m, l, acc[8];
-    __device__ __forceinline__ void fold(float m2, float l2, const float (&v)[8]) {     // another state, its sum of weights l2
-        const float m_new = fmaxf(m, m2);
-        const float fa = __builtin_amdgcn_exp2f(m - m_new), fb = __builtin_amdgcn_exp2f(m2 - m_new);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * fa + v[e] * fb;
-        l = l * fa + l2 * fb;
-        m = m_new;
-    }
-};
-
 template <int D>
 __device__ __forceinline__ void merge_short_body(const AttnParams &p, int b, int hkv, int block) {
     constexpr int kQuads = D / 32;                           // sets of four chunks in a row
@@ -513,10 +501,6 @@ __device__ __forceinline__ void merge_short_body(const AttnParams &p, int b, int
     const float *rec = p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + (live ? chunk : 0)) * n_splits * kRec;
     const int share = four ? (n_splits + 3) >> 2 : n_splits, first = four ? wave * share : 0, last = min(n_splits, first + share);
     MergeState st;
-    st.m = -INFINITY;
-    st.l = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) st.acc[e] = 0.f;
     constexpr int kBatch = 4;
     for (int s0 = first; s0 < last; s0 += kBatch) {
         float ms[kBatch], ls[kBatch];
@@ -531,46 +515,17 @@ __device__ __forceinline__ void merge_short_body(const AttnParams &p, int b, int
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             if (s0 + j >= last || ms[j] == -INFINITY) continue;      // (no key of that share for this row)
-            const uint32_t u[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x[2 * e] = ls[j] * __uint_as_float(u[e] << 16);
-                x[2 * e + 1] = ls[j] * __uint_as_float(u[e] & 0xffff0000u);
-            }
-            st.fold(ms[j], ls[j], x);
+            st.fold_record(ms[j], ls[j], v[j]);
         }
     }
     if (four) {
         __shared__ float s_state[3][10][64];
-        if (wave > 0) {
-            float *o = &s_state[wave - 1][0][lane];
-            o[0] = st.m;
-            o[64] = st.l;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[(2 + e) * 64] = st.acc[e];
-        }
-        __syncthreads();
-        if (wave > 0) return;
-#pragma unroll
-        for (int g = 0; g < 3; ++g) {
-            const float *o = &s_state[g][0][lane];
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = o[(2 + e) * 64];
-            if (o[0] != -INFINITY) st.fold(o[0], o[64], x);
-        }
+        if (!st.gather(s_state, wave, lane)) return;
     }
     if (!live) return;
     // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
     const int node = (int)(((float)m + 0.5f) * (1.0f / (float)p.G)), group = m - node * p.G;
-    const float inv = 1.f / st.l;                                     // (> 0: every row sees its own tree node)
-    uint4 w;
-    w.x = pack_bf16x2(st.acc[0] * inv, st.acc[1] * inv);
-    w.y = pack_bf16x2(st.acc[2] * inv, st.acc[3] * inv);
-    w.z = pack_bf16x2(st.acc[4] * inv, st.acc[5] * inv);
-    w.w = pack_bf16x2(st.acc[6] * inv, st.acc[7] * inv);
-    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = w;
+    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = st.result();
     if (p.lse && c == 0)
         p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (st.m + __builtin_amdgcn_logf(st.l)) * kLn2;
 }
