@@ -28,109 +28,171 @@ struct AcceptShared {
     int accept_len;
 };
 
-// Called by every thread of the workgroup (it contains barriers); the work is done by the
-// first wavefront (`active`: threadIdx.x < 64, lane = threadIdx.x).
-__device__ inline void accept_path_body(const AcceptParams &p, int b, int lane, bool active, AcceptShared &sh) {
-    const int T = p.T;
-    const int32_t *par = p.parents + (size_t)b * T;
-    const int32_t *draft = p.draft + (size_t)b * T;
-    const int32_t *target = p.target + (size_t)b * T;
+// Orders a wavefront's LDS accesses for the compiler; the hardware executes those of one wavefront in order.
+__device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-    bool bad_tree = false;
-    bool match[2] = {false, false};
-    int my_target[2] = {0, 0}, my_draft[2] = {0, 0}, my_par[2] = {-1, -1};
-    bool my_valid[2] = {false, false};
-    unsigned long long m_lo = 0ull, m_hi = 0ull;
-    if (active) {
-        // one trip to memory for the three token/parent rows; target[parent] then comes from LDS
+// The tokens and parents of a lane's two nodes, asked for ahead of the acceptance.
+struct AcceptTokens {
+    int par[2], draft[2], target[2];
+};
+__device__ __forceinline__ AcceptTokens accept_load(const AcceptParams &p, int b, int lane) {
+    AcceptTokens a;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int i = lane + 64 * s;
-            if (i < T) {
-                int pi = par[i];
-                my_draft[s] = draft[i];
-                my_target[s] = target[i];
-                my_valid[s] = (i == 0) ? (pi == -1) : (pi >= 0 && pi < i);
-                if (!my_valid[s]) { bad_tree = true; pi = -1; }
-                my_par[s] = pi;
-                sh.par[i] = pi;
-                sh.target[i] = my_target[s];
-            }
+    for (int s = 0; s < 2; ++s) {
+        const int i = lane + 64 * s;
+        const bool in = i < p.T;
+        a.par[s] = in ? p.parents[(size_t)b * p.T + i] : -1;
+        a.draft[s] = in ? p.draft[(size_t)b * p.T + i] : 0;
+        a.target[s] = in ? p.target[(size_t)b * p.T + i] : 0;
+    }
+    return a;
+}
+
+// Acceptance of sequence b by one wavefront, without barriers, in three parts, so that a caller can put other work between
+// them: the tokens go into LDS, the path is chosen from there (LDS only), the results are written out.
+struct AcceptNodes {
+    int draft[2], par[2];      // drafted token and parent of the lane's two nodes (-1: none, or a bad link)
+    bool valid[2];
+};
+__device__ __forceinline__ AcceptNodes accept_stage(const AcceptParams &p, int lane, const AcceptTokens &tok, AcceptShared &sh) {
+    AcceptNodes nd;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int i = lane + 64 * s, pi = tok.par[s];
+        nd.draft[s] = tok.draft[s];
+        nd.valid[s] = i < p.T && ((i == 0) ? (pi == -1) : (pi >= 0 && pi < i));
+        nd.par[s] = nd.valid[s] ? pi : -1;
+        if (i < p.T) {
+            sh.par[i] = nd.par[s];
+            sh.target[i] = tok.target[s];
         }
     }
-    __syncthreads();
-    if (active) {
+    wave_lds_order();
+    return nd;
+}
+
+// Returns the number of accepted nodes, leaves the path in sh.path and the status bits to report in `bits`.
+__device__ inline int accept_choose(const AcceptParams &p, int lane, const AcceptNodes &nd, AcceptShared &sh, int &bits) {
+    const int T = p.T;
+    bool match[2] = {false, false}, bad_tree = false;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int i = lane + 64 * s;
-            if (i < T) match[s] = (i == 0) || (my_valid[s] && my_draft[s] == sh.target[my_par[s]]);
+    for (int s = 0; s < 2; ++s) {
+        const int i = lane + 64 * s;
+        if (i < T) {
+            match[s] = (i == 0) || (nd.valid[s] && nd.draft[s] == sh.target[nd.par[s]]);   // (target[parent] comes from LDS)
+            bad_tree |= !nd.valid[s];
         }
-        m_lo = __ballot(match[0]);
-        m_hi = __ballot(match[1]);
     }
+    const unsigned long long m_lo = __ballot(match[0]), m_hi = __ballot(match[1]);
 
     // ancestor-or-self sets by walking the parent chain (at most T steps, always ends)
     unsigned long long a_lo[2] = {0ull, 0ull}, a_hi[2] = {0ull, 0ull};
-    int n_out = 0, depth_term = 0;
-    if (active) {
-        int key[2] = {-1, -1};
+    int key[2] = {-1, -1};
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int i = lane + 64 * s;
-            if (i < T) {
-                int t = i;
-                for (int step = 0; step < T && t >= 0; ++step) {
-                    if (t < 64) a_lo[s] |= 1ull << t; else a_hi[s] |= 1ull << (t - 64);
-                    t = sh.par[t];
-                }
-                const bool ok = ((a_lo[s] & ~m_lo) == 0) && ((a_hi[s] & ~m_hi) == 0);
-                const int depth = __popcll(a_lo[s]) + __popcll(a_hi[s]) - 1;
-                if (ok) key[s] = depth * 256 + (255 - i);   // deeper first, then lower node id
+    for (int s = 0; s < 2; ++s) {
+        const int i = lane + 64 * s;
+        if (i < T) {
+            int t = i;
+            for (int step = 0; step < T && t >= 0; ++step) {
+                if (t < 64) a_lo[s] |= 1ull << t; else a_hi[s] |= 1ull << (t - 64);
+                t = sh.par[t];
             }
-        }
-        int best = max(key[0], key[1]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off));
-        // the root always qualifies, so best >= 255
-        const int term = 255 - (best & 255);
-        depth_term = best >> 8;
-        n_out = min(depth_term, p.max_path - 1);
-        if (lane == (term & 63)) {
-            // (a choice, not an index: an indexed array would live in scratch memory)
-            sh.term[0] = term < 64 ? a_lo[0] : a_lo[1];
-            sh.term[1] = term < 64 ? a_hi[0] : a_hi[1];
-        }
-        if (lane == 0) sh.accept_len = n_out;
-    }
-    __syncthreads();
-
-    if (active) {
-        const unsigned long long t_lo = sh.term[0], t_hi = sh.term[1];
-        int32_t *path = p.path + (size_t)b * p.max_path;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int i = lane + 64 * s;
-            if (i < T) {
-                const bool on_path = (s == 0) ? ((t_lo >> lane) & 1ull) : ((t_hi >> lane) & 1ull);
-                if (on_path) {
-                    const int depth = __popcll(a_lo[s]) + __popcll(a_hi[s]) - 1;
-                    if (depth < p.max_path) { path[depth] = i; sh.path[depth] = i; }
-                    if (depth == n_out) {
-                        p.accept_len[b] = n_out;
-                        p.bonus[b] = my_target[s];
-                    }
-                }
-            }
-        }
-        for (int j = n_out + 1 + lane; j < p.max_path; j += 64) path[j] = -1;
-
-        const bool any_bad_tree = __ballot(bad_tree) != 0ull;
-        if (p.status && lane == 0) {
-            int bits = (any_bad_tree ? READER_STATUS_BAD_TREE : 0) |
-                       (depth_term > n_out ? READER_STATUS_BAD_PATH : 0);
-            if (bits) atomicOr(p.status, bits);
+            const bool ok = ((a_lo[s] & ~m_lo) == 0) && ((a_hi[s] & ~m_hi) == 0);
+            const int depth = __popcll(a_lo[s]) + __popcll(a_hi[s]) - 1;
+            if (ok) key[s] = depth * 256 + (255 - i);   // deeper first, then lower node id
         }
     }
+    int best = max(key[0], key[1]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off));
+    // the root always qualifies, so best >= 255
+    const int term = 255 - (best & 255), depth_term = best >> 8;
+    const int n_out = min(depth_term, p.max_path - 1);
+    if (lane == (term & 63)) {
+        // (a choice, not an index: an indexed array would live in scratch memory)
+        sh.term[0] = term < 64 ? a_lo[0] : a_lo[1];
+        sh.term[1] = term < 64 ? a_hi[0] : a_hi[1];
+    }
+    wave_lds_order();
+    const unsigned long long t_lo = sh.term[0], t_hi = sh.term[1];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int i = lane + 64 * s;
+        const bool on_path = ((s == 0 ? t_lo : t_hi) >> lane) & 1ull;
+        if (i < T && on_path) {
+            const int depth = __popcll(a_lo[s]) + __popcll(a_hi[s]) - 1;
+            if (depth < p.max_path) sh.path[depth] = i;
+        }
+    }
+    if (lane == 0) sh.accept_len = n_out;
+    wave_lds_order();
+    bits = (__ballot(bad_tree) != 0ull ? READER_STATUS_BAD_TREE : 0) | (depth_term > n_out ? READER_STATUS_BAD_PATH : 0);
+    return n_out;
+}
+
+__device__ __forceinline__ void accept_report(const AcceptParams &p, int b, int lane, int n, int bits, const AcceptShared &sh) {
+    for (int j = lane; j < p.max_path; j += 64) p.path[(size_t)b * p.max_path + j] = j <= n ? sh.path[j] : -1;
+    if (lane == 0) {
+        p.accept_len[b] = n;
+        p.bonus[b] = sh.target[sh.path[n]];
+        if (p.status && bits) atomicOr(p.status, bits);
+    }
+}
+
+// all of it; the number of accepted nodes and the path are left in `sh` too
+__device__ inline void accept_path_wave(const AcceptParams &p, int b, int lane, AcceptShared &sh) {
+    const AcceptNodes nd = accept_stage(p, lane, accept_load(p, b, lane), sh);
+    int bits;
+    const int n = accept_choose(p, lane, nd, sh, bits);
+    accept_report(p, b, lane, n, bits, sh);
+}
+
+// One kv head's part of the compaction of sequence b (old length L) by one wavefront: the rows of path[0..n] (LDS) of the
+// tree tensors are appended behind position L - 1.  Every item is checked before anything is written, and every head of a
+// sequence comes to the same verdict.  Returns by how much the sequence grows: n + 1, or 0 where it was refused, with the
+// reason in `bits`.
+template <int D>
+__device__ inline int kv_compact_head_wave(const CompactParams &p, int b, int hkv, int lane, int n, int L, const int *path, int &bits) {
+    if (L < 0 || (long long)L + n + 1 > (long long)p.max_pages * READER_PAGE_SIZE) {
+        bits |= READER_STATUS_BAD_PATH;
+        return 0;
+    }
+    // A lane keeps its place inside a position (K or V, 16-byte chunk) and takes every kPer-th path entry, eight at a time:
+    // their page ids and rows are asked for together (one trip to memory) and stored afterwards.  The loads carry no
+    // condition: an entry past the path reads the last one again.
+    constexpr int kChunks = D / 8, kPer = 64 / (2 * kChunks), kBatch = 8;
+    const int at = lane / (2 * kChunks), which = (lane / kChunks) & 1, dc = lane % kChunks;
+    typedef unsigned int held_t __attribute__((ext_vector_type(4)));
+    const uint16_t *tree = (which ? p.v_tree : p.k_tree) + ((size_t)b * p.T * p.Hkv + hkv) * D + dc * 8;
+    uint16_t *cache = (which ? p.v_cache : p.k_cache) + (size_t)hkv * READER_PAGE_SIZE * D + dc * 8;
+    const int32_t *table = p.page_table + (size_t)b * p.max_pages;
+    // (positions L .. L + n: inside the table, by the check above)
+    bool bad_page = false;
+    for (int j = lane; j <= n; j += 64) {
+        const int page = table[(L + j) / READER_PAGE_SIZE];
+        bad_page |= page < 0 || page >= p.num_pages;
+    }
+    for (int j0 = 0; j0 <= n; j0 += kPer * kBatch) {
+        held_t held[kBatch];
+        int page[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = min(j0 + u * kPer + at, n);
+            page[u] = table[(L + j) / READER_PAGE_SIZE];
+            held[u] = *reinterpret_cast<const held_t *>(tree + (size_t)path[j] * p.Hkv * D);
+        }
+        if (j0 == 0 && __any(bad_page)) {
+            bits |= READER_STATUS_BAD_PAGE;
+            return 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = j0 + u * kPer + at;
+            if (j <= n)
+                *reinterpret_cast<held_t *>(cache + ((size_t)page[u] * p.Hkv * READER_PAGE_SIZE + (L + j) % READER_PAGE_SIZE) * D) = held[u];
+        }
+    }
+    return n + 1;
 }
 
 // What compaction needs that does not depend on the accepted path: the old length and the page

@@ -5,7 +5,7 @@ namespace reader {
 
 __global__ __launch_bounds__(64) void accept_path_kernel(AcceptParams p) {
     __shared__ AcceptShared sh;
-    accept_path_body(p, blockIdx.x, threadIdx.x, true, sh);
+    accept_path_wave(p, blockIdx.x, threadIdx.x, sh);
 }
 
 hipError_t launch_accept_path(const AcceptParams &p, hipStream_t stream) {

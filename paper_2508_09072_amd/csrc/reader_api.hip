@@ -395,8 +395,9 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
             if (p.n_ranges == (1 << sh)) p.ranges_shift = sh;
     }
     p.num_pages = dims->num_pages;
-    // few pairs, many ranges: a pair is cut into eight parts or more on average, the merge fetches them four abreast
-    p.merge_groups = (long long)dims->B * dims->Hkv * 8 <= p.n_ranges ? 4 : 1;
+    // Few pairs, many ranges: a pair is cut into six parts or more on average, and four wavefronts share them out (nine
+    // sequences of 12 K positions, 7 parts: 48.8 -> 47.4 us; four of 32 K with 512 rows, 4 parts: tail 11.0 -> 12.1, so not those).
+    p.merge_groups = (long long)dims->B * dims->Hkv * 6 <= p.n_ranges ? 4 : 1;
     p.tree_in_cache = tree_in_cache ? 1 : 0;
     p.wide = attn_use_wide(*dims, p.rows_per_wg);
     p.redo_only = 0;

@@ -802,29 +802,33 @@ __device__ __forceinline__ void merge_body(const AttnParams &p, int b, int hkv, 
     const int n_parts = w_last - w_first + 1, share = four ? (n_parts + 3) >> 2 : n_parts;
     const int my_first = four ? w_first + wave * share : w_first, my_last = min(w_last, my_first + share - 1);
     MergeState st;
-    // Records are fetched four at a time (all their loads in flight together) and folded in in range order.
-    constexpr int kBatch = 4;
-    for (int w0 = my_first; w0 <= my_last; w0 += kBatch) {
-        float mw[kBatch], lw[kBatch];
-        uint4 v[kBatch];
+    // Records are fetched four or eight at a time (all their loads in flight together) and folded in in range order.
+    auto take = [&](auto batch_c) __attribute__((always_inline)) {
+        constexpr int kBatch = decltype(batch_c)::value;
+        for (int w0 = my_first; w0 <= my_last; w0 += kBatch) {
+            float mw[kBatch], lw[kBatch];
+            uint4 v[kBatch];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            // A range that holds no tile (more workgroups than tiles) wrote no record: its slot holds stale bytes.  The
-            // slot is read all the same, next to the range's tile count and not behind it (one round trip less), and
-            // dropped afterwards.
-            const int w = min(w0 + j, my_last);
-            const int n_here = p.range_tiles[w];
-            const size_t slot = ((size_t)(2 * w + (w == w_first ? 1 : 0)) * p.n_row_chunks + row_chunk);
-            const float *rec = p.workspace + slot * rec_floats;
-            v[j] = reinterpret_cast<const uint4 *>(rec)[c * rows + row_local];
-            const float m_rec = rec[rows * (D / 2) + row_local];
-            lw[j] = rec[rows * (D / 2 + 1) + row_local];
-            mw[j] = n_here != 0 && w0 + j <= my_last ? m_rec : -INFINITY;
+            for (int j = 0; j < kBatch; ++j) {
+                // A range that holds no tile (more workgroups than tiles) wrote no record: its slot holds stale bytes.  The
+                // slot is read all the same, next to the range's tile count and not behind it (one round trip less), and
+                // dropped afterwards.
+                const int w = min(w0 + j, my_last);
+                const int n_here = p.range_tiles[w];
+                const size_t slot = ((size_t)(2 * w + (w == w_first ? 1 : 0)) * p.n_row_chunks + row_chunk);
+                const float *rec = p.workspace + slot * rec_floats;
+                v[j] = reinterpret_cast<const uint4 *>(rec)[c * rows + row_local];
+                const float m_rec = rec[rows * (D / 2) + row_local];
+                lw[j] = rec[rows * (D / 2 + 1) + row_local];
+                mw[j] = n_here != 0 && w0 + j <= my_last ? m_rec : -INFINITY;
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+                if (mw[j] != -INFINITY) st.fold_record(mw[j], lw[j], v[j]);   // (else no record, or this row saw no key of that part)
         }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j)
-            if (mw[j] != -INFINITY) st.fold_record(mw[j], lw[j], v[j]);   // (else no record, or this row saw no key of that part)
-    }
+    };
+    if (share > 4) take(std::integral_constant<int, 8>{});
+    else take(std::integral_constant<int, 4>{});
     if (four) {
         __shared__ float s_state[3][10][64];
         if (!st.gather(s_state, wave, lane)) return;
@@ -862,7 +866,7 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(AttnParams p, AcceptPa
     // (in-cache layout, no tree tensors: the in-place move of the accepted rows follows as a launch of its own)
     const bool append = cp.k_tree != nullptr;
     if (append) kv_compact_prefetch(cp, b, tid, cs);   // on its way while the path is being chosen
-    accept_path_body(ap, b, tid, tid < 64, sh);
+    if (tid < 64) accept_path_wave(ap, b, tid, sh);
     if (!append) return;
     __syncthreads();
     kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);

@@ -60,8 +60,16 @@ constexpr int kWavesPerSimd64 = 2;        // (the time stamps take registers)
 constexpr int kWavesPerSimd64 = 4;
 #endif
 
-template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(AttnParams p) {
+// kStep: the fused step where no pair is cut.  Acceptance needs tokens and compaction rows that nobody else in this launch
+// writes, and neither has anything to do with the attention's results: the first copying wavefront of a pair (first row
+// chunk) does both for its kv head, the choice of the path while the first tiles are on their way, the rest when it has no
+// more tiles to ask for and the computing wavefronts are at their last ones.  Every kv head's wavefront finds the path by
+// itself, the first head's reports it.  Only the new lengths have to wait for the next launch, because this one reads the
+// old ones.  (Cut pairs need a second launch for their merge anyway, and their workgroups are over so soon that the
+// side job would make them longer: two nodes on a prompt of 4 K tokens 13.1 -> 14.2 us.  Uncut: five sequences of 100
+// tokens 13.4 -> 11.0, 55 of 14 - 144 tokens 43.0 -> 40.3.)
+template <int D, bool kStep>
+__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const AcceptParams &ap, const CompactParams &cp) {
     constexpr bool kDeep = D == 128;
     constexpr int CW = 4, kS = kShortStages;
     using G = Geometry<D, CW>;
@@ -70,6 +78,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
     char *ring = smem;                                                               // [kS][kStageBytes]
     int *s_par = reinterpret_cast<int *>(smem + kS * G::kStageBytes);                // [4][READER_MAX_T]: one copy per computing wavefront
     int *s_hole = s_par + 4 * READER_MAX_T;                                          // [kS][4]: quarter of the tile behind a bad page id
+    AcceptShared *s_accept = reinterpret_cast<AcceptShared *>(s_hole + 4 * kS);      // (the fused step only)
     const unsigned ring_lds = (unsigned)(size_t)(lds_char *)ring;
 
     READER_STAMP(kStampEntry, 0);
@@ -119,6 +128,13 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
         };
         const bool early = n_table <= kPageRegs * 64 * 4;   // all the sequence can have: asked for before its length is known
         if (early) fetch_pages();
+        const bool side = kStep && cw == 0 && chunk == 0;
+        AcceptTokens tok;
+        int old_len = 0;
+        if (side) {
+            tok = accept_load(ap, b, lane);
+            old_len = cp.seq_lens[b];
+        }
         share();
         if (!early) {
             page_base = lo;
@@ -136,6 +152,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
         }
 #pragma unroll
         for (int i = 0; i < kPageRegs; ++i) asm volatile("" : "+v"(page[i]));   // (waited for in front of the copies)
+        AcceptNodes nodes;
+        if (side) nodes = accept_stage(ap, lane, tok, *s_accept);    // (here with the page ids: a wait behind the copies would be for those too)
         READER_STAMP(kStampRange, 256);
         auto issue = [&](int t) {
             const unsigned at = (unsigned)(t - lo) % kS;
@@ -195,6 +213,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
             issue(lo + i);
             if (i == 0) READER_STAMP(kStampItem0Issued, 256);
         }
+        int accepted = 0, step_bits = 0;
+        if (side) accepted = accept_choose(ap, lane, nodes, *s_accept, step_bits);
 #pragma unroll 1
         for (int t = lo; t < hi; ++t) {
             // this wavefront's part of tile t has landed once at most its copies of the tiles behind it are outstanding
@@ -206,6 +226,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
             if (t + kS - 1 < hi) issue(t + kS - 1);
         }
         if (p.status && bad) atomicOr(p.status, bad);
+        if (side) {
+            const bool report = hkv == 0;
+            if (cp.k_tree) {                      // (in-cache layout: the rows move in a launch of their own)
+                const int grown = kv_compact_head_wave<D>(cp, b, hkv, lane, accepted, old_len, s_accept->path, step_bits);
+                if (report && lane == 0) p.pair_info[b] = grown;
+            }
+            if (report) accept_report(ap, b, lane, accepted, step_bits, *s_accept);
+        }
         return;
     }
 
@@ -479,12 +507,26 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
     if (p.status && bad) atomicOr(p.status, bad);
 }
 
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(AttnParams p) {
+    tree_attn_short_body<D, false>(p, AcceptParams(), CompactParams());
+}
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp) {
+    tree_attn_short_body<D, true>(p, ap, cp);
+}
+// ... and behind it the lengths: it has left by how much every sequence grows
+__global__ __launch_bounds__(256) void lengths_short_kernel(const int32_t *grown, int32_t *seq_lens, int B) {
+    const int b = blockIdx.x * 256 + threadIdx.x;
+    if (b < B) seq_lens[b] += grown[b];
+}
+
 // Merge of the n_splits records of every query row.  A record is laid out [chunk of 8 values][row], so a wavefront takes 16
 // consecutive rows of four chunks: its loads fetch 256 contiguous bytes per chunk.  With more than four shares the four
 // wavefronts of a workgroup take a quarter of the shares each and fold their states through LDS in the order of the shares.
 //
 // What bounds it: a launch, one trip to memory for the records (other compute units have just written them past the
-// caches) and the way back; loads are few and asked for together, four records at a time.  As one thread per row and chunk
+// caches) and the way back; loads are few and asked for together, four or eight records at a time.  As one thread per row and chunk
 // in row order, eight records at a time whether there were that many or not, it took 6.6 us where this takes 4.2 (three
 // sequences of 0.7 - 2.5 K tokens, ten shares of 24 pairs with 100 rows; four wavefronts per row from nine shares on there).
 template <int D>
@@ -501,23 +543,28 @@ __device__ __forceinline__ void merge_short_body(const AttnParams &p, int b, int
     const float *rec = p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + (live ? chunk : 0)) * n_splits * kRec;
     const int share = four ? (n_splits + 3) >> 2 : n_splits, first = four ? wave * share : 0, last = min(n_splits, first + share);
     MergeState st;
-    constexpr int kBatch = 4;
-    for (int s0 = first; s0 < last; s0 += kBatch) {
-        float ms[kBatch], ls[kBatch];
-        uint4 v[kBatch];
+    auto take = [&](auto batch_c) __attribute__((always_inline)) {
+        constexpr int kBatch = decltype(batch_c)::value;
+        for (int s0 = first; s0 < last; s0 += kBatch) {
+            float ms[kBatch], ls[kBatch];
+            uint4 v[kBatch];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const float *part = rec + (size_t)min(s0 + j, last - 1) * kRec;
-            v[j] = reinterpret_cast<const uint4 *>(part)[c * kShortRows + r];
-            ms[j] = part[kShortRows * (D / 2) + r];
-            ls[j] = part[kShortRows * (D / 2 + 1) + r];
-        }
+            for (int j = 0; j < kBatch; ++j) {
+                const float *part = rec + (size_t)min(s0 + j, last - 1) * kRec;
+                v[j] = reinterpret_cast<const uint4 *>(part)[c * kShortRows + r];
+                ms[j] = part[kShortRows * (D / 2) + r];
+                ls[j] = part[kShortRows * (D / 2 + 1) + r];
+            }
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (s0 + j >= last || ms[j] == -INFINITY) continue;      // (no key of that share for this row)
-            st.fold_record(ms[j], ls[j], v[j]);
+            for (int j = 0; j < kBatch; ++j) {
+                if (s0 + j >= last || ms[j] == -INFINITY) continue;      // (no key of that share for this row)
+                st.fold_record(ms[j], ls[j], v[j]);
+            }
         }
-    }
+    };
+    // (a second round is a second trip to memory, a record read twice only a load)
+    if (share > 4) take(std::integral_constant<int, 8>{});
+    else take(std::integral_constant<int, 4>{});
     if (four) {
         __shared__ float s_state[3][10][64];
         if (!st.gather(s_state, wave, lane)) return;
@@ -535,13 +582,13 @@ __global__ __launch_bounds__(256) void merge_short_kernel(AttnParams p) {
     merge_short_body<D>(p, blockIdx.z, blockIdx.y, blockIdx.x);
 }
 
-// Tail of the fused step: one workgroup per sequence that accepts a path and appends its rows, then the merge
-// blocks (none where no pair was split).  The jobs touch disjoint data.
+// Tail of the fused step where pairs were cut: one workgroup per sequence that accepts a path and appends its rows, then the
+// merge blocks.  The jobs touch disjoint data.
 template <int D>
-__global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks_y) {
+__global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks) {
     if ((int)blockIdx.x >= p.B) {
-        const int m = blockIdx.x - p.B, pair = m / merge_blocks_y, seq = pair / p.Hkv;
-        merge_short_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks_y);
+        const int m = blockIdx.x - p.B, pair = m / merge_blocks, seq = pair / p.Hkv;
+        merge_short_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks);
         return;
     }
     __shared__ AcceptShared sh;
@@ -549,48 +596,59 @@ __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, Ac
     const int b = blockIdx.x, tid = threadIdx.x;
     const bool append = cp.k_tree != nullptr;       // (in-cache layout: the rows move in a launch of their own)
     if (append) kv_compact_prefetch(cp, b, tid, cs);
-    accept_path_body(ap, b, tid, tid < 64, sh);
+    if (tid < 64) accept_path_wave(ap, b, tid, sh);
     if (!append) return;
     __syncthreads();
     kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
 }
 
-template <int D>
-hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+template <int D, bool kStep>
+hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
+                       const CompactParams *cp) {
     using G = Geometry<D, 4>;
-    constexpr size_t lds = (size_t)kShortStages * G::kStageBytes + (4 * READER_MAX_T + 4 * kShortStages) * sizeof(int);
+    constexpr size_t lds = (size_t)kShortStages * G::kStageBytes + (4 * READER_MAX_T + 4 * kShortStages) * sizeof(int) +
+                           (kStep ? sizeof(AcceptShared) : 0);
     {
         static std::mutex guard;             // host threads may call in at the same time
         static bool allowed = false;
         std::lock_guard<std::mutex> lock(guard);
         if (!allowed) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_short_kernel<D>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            const void *kernel = kStep ? reinterpret_cast<const void *>(&verify_short_kernel<D>) : reinterpret_cast<const void *>(&tree_attn_short_kernel<D>);
+            const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) { (void)hipGetLastError(); return note_hip_error("hipFuncSetAttribute(short attention LDS size)", e); }
             allowed = true;
         }
     }
     const dim3 grid(p.n_splits, p.Hkv, p.B * p.n_row_chunks);
-    if (ev_start && ev_stop)
-        hipExtLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p);
-    else
-        hipLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, p);
+    const bool timed = ev_start && ev_stop;
+    if constexpr (kStep) {
+        if (timed) hipExtLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p, *ap, *cp);
+        else hipLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, p, *ap, *cp);
+    } else {
+        if (timed) hipExtLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p);
+        else hipLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, p);
+    }
     return note_hip_error("launch tree_attn_short_kernel", hipGetLastError());
 }
 
 template <int D>
 hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
                       const CompactParams *cp) {
-    const hipError_t e = launch_main<D>(p, stream, ev_start, ev_stop);
-    if (e != hipSuccess) return e;
+    if (ap && cp && p.n_splits == 1) {
+        const hipError_t e = launch_main<D, true>(p, stream, ev_start, ev_stop, ap, cp);
+        if (e != hipSuccess || !cp->k_tree) return e;
+        hipLaunchKernelGGL(lengths_short_kernel, dim3((p.B + 255) / 256), dim3(256), 0, stream, p.pair_info, cp->seq_lens, p.B);
+        return note_hip_error("launch lengths_short_kernel", hipGetLastError());
+    }
+    const hipError_t e = launch_main<D, false>(p, stream, ev_start, ev_stop, nullptr, nullptr);
+    if (e != hipSuccess || p.n_splits == 1) return e;
     const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
-    const int merge_y = p.n_splits == 1 ? 0 : p.merge_groups == 4 ? units : (units + 3) / 4;
+    const int blocks = p.merge_groups == 4 ? units : (units + 3) / 4;
     if (ap && cp) {
-        hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * merge_y), dim3(256), 0, stream, p, *ap, *cp, merge_y);
+        hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * blocks), dim3(256), 0, stream, p, *ap, *cp, blocks);
         return note_hip_error("launch verify_tail_short_kernel", hipGetLastError());
     }
-    if (merge_y == 0) return hipSuccess;
-    hipLaunchKernelGGL(merge_short_kernel<D>, dim3(merge_y, p.Hkv, p.B), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(merge_short_kernel<D>, dim3(blocks, p.Hkv, p.B), dim3(256), 0, stream, p);
     return note_hip_error("launch merge_short_kernel", hipGetLastError());
 }
 

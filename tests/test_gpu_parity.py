@@ -881,6 +881,57 @@ def test_attn_short_problem_kernel(R, oracle_mod, T, G, D, lens, splits, in_cach
         assert_close(lse, ref_lse, what="bad page lse")
 
 
+@pytest.mark.parametrize("Hkv,D,T,max_path,fault", [
+    (1, 64, 1, 1, None), (3, 128, 2, 2, None),         # the root alone; two positions per wavefront instruction, one filled
+    (2, 128, 17, 17, None), (8, 64, 33, 33, None),     # one position more than a round of eight instructions takes (16, 32)
+    (2, 64, 128, 128, None), (2, 128, 128, 128, None), # every lane holds two nodes
+    (2, 128, 40, 7, None),                             # paths cut to max_path: BAD_PATH, and the cut path is appended
+    (2, 64, 40, 40, "page"), (2, 128, 40, 40, "end"), (2, 128, 40, 40, "tree"), (2, 64, 40, 40, "length"),
+])
+def test_verify_step_of_whole_pairs_does_the_rest_in_the_same_launch(R, Hkv, D, T, max_path, fault, tune):
+    # where no pair is cut, a copying wavefront of the attention kernel accepts and appends: same results, same refusals and
+    # status bits as the three calls
+    import torch
+    w = W.make_custom("side_T%d_D%d" % (T, D), B=3, Hq=2 * Hkv, Hkv=Hkv, D=D, T=T, seq_lens=[70, 0, 31], tree="chain", p_match=1.0,
+                      max_path=max_path, seed=640 + T + D)
+    if fault == "page":
+        w.page_table[0, 70 // 16 + 1] = w.num_pages + 5     # a page that only appended rows would need
+    elif fault == "end":
+        w.page_table = np.ascontiguousarray(w.page_table[:, :5])   # 80 positions: the first sequence's path runs past the table
+    elif fault == "tree":
+        w.parents[1, 9] = 30
+    elif fault == "length":
+        w.seq_lens[2] = -4
+
+    def run(fused):
+        tune(R.TUNE_ATTN_SHORT, 1)
+        dw = R.to_device(w)
+        dims = R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.page_table.shape[1], w.max_path, w.num_pages)
+        limit = 75
+        assert R.reader_attn_plan(dims, limit)["kernel_id"] == 4
+        if fused:
+            R.reader_verify_step(dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
+                                 dw.draft_tokens, dw.target_tokens, dw.out, dw.lse, dw.accept_len, dw.path, dw.bonus, limit,
+                                 dw.workspace, dw.status)
+        else:
+            R.reader_tree_attn(dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
+                               dw.out, dw.lse, limit, dw.workspace, dw.status)
+            R.reader_accept_path(dims, dw.draft_tokens, dw.target_tokens, dw.parents, dw.accept_len, dw.path, dw.bonus, dw.status)
+            R.reader_kv_compact(dims, dw.k_tree, dw.v_tree, dw.path, dw.accept_len, dw.k_cache, dw.v_cache, dw.page_table,
+                                dw.seq_lens, dw.status)
+        torch.cuda.synchronize()
+        return dw
+
+    a, b = run(True), run(False)
+    expected = {None: 0 if max_path >= T else R.STATUS_BAD_PATH, "page": R.STATUS_BAD_PAGE, "end": R.STATUS_BAD_PATH,
+                "tree": R.STATUS_BAD_TREE, "length": R.STATUS_BAD_PATH}[fault]
+    assert int(a.status.item()) == int(b.status.item()) == expected
+    for name in ("out", "lse", "accept_len", "path", "bonus", "seq_lens"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    for name in ("k_cache", "v_cache"):
+        assert np.array_equal(cache_bits(getattr(a, name)), cache_bits(getattr(b, name))), name
+
+
 @pytest.mark.parametrize("T,G,D,splits", [
     (15, 1, 64, 4), (16, 1, 128, 5),         # the merge takes 16 rows x 4 chunks per wavefront: one block of rows, full or not;
     (17, 1, 128, 4), (17, 1, 64, 5),         # up to four shares one wavefront reads all of them, from five on four share them out
