@@ -359,10 +359,14 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
         constexpr int nb = e == 31 ? 1 - wkb : wkb, ne = (e + 1) & 31;
         w_x = weight_arg(s[nb][ne / 16][ne % 16], mc[ne / 16]);
         constexpr int pe = (e + 31) & 31;                     // the weight of one slot ago
-        lsum[pe / 16][pe & 1] += w_p1;
+        // (these too: the compiler takes a result of inline asm for one that may not be ready, and puts a wait state in
+        // front of every use of its own, some forty per tile)
+        asm volatile("v_add_f32 %0, %0, %1" : "+v"(lsum[pe / 16][pe & 1]) : "v"(w_p1));
         if constexpr ((e & 1) == 0) {
             constexpr int pb = e == 0 ? 1 - wkb : wkb, p2 = (e + 30) & 31, r = p2 / 16, i = p2 % 16;
-            pk[pb][r][i >> 3][(i >> 1) & 3] = pack_bf16x2(w_p2, w_p1);
+            uint32_t both;
+            asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(both) : "v"(w_p2), "v"(w_p1));
+            pk[pb][r][i >> 3][(i >> 1) & 3] = both;
         }
         w_p2 = w_p1;
         w_p1 = p_cur;
@@ -381,10 +385,6 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
     //                             of each, so a slot has room for about four of them).
     // Every operand fragment is read from LDS once, two groups of four matrix instructions ahead of
     // its use, and serves both row blocks back to back.
-    auto v_frag = [&](const char *stage, int ks, int db) {
-        return __builtin_shufflevector(v_half(stage, ks, db, 0), v_half(stage, ks, db, 1), 0, 1, 2, 3, 4, 5, 6, 7);
-    };
-
     // S = K.Q^T of a tile
     auto scores = [&](const char *stage) {
         constexpr int kK = G::kKSteps;
@@ -457,21 +457,23 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
         constexpr int kK = G::kKSteps, kOB = G::kOBlocks;
         static_assert(kK == 2 * kOB, "a half step has as many score as product instructions");
         bf16x8 kf[3];
-        s16x8 vf[3];
-        // fragments of group g of half step kb: K rows of key block kb, k-step g; V^T of 16-key step 2 kb + g / kOB, output block g % kOB
-        auto load_group = [&](auto kbc, auto gc) {
-            constexpr int kb = decltype(kbc)::value, g = decltype(gc)::value;
-            kf[(kb * kK + g) % 3] = k_frag(next_stage, kb, g);
-            vf[(kb * kK + g) % 3] = v_frag(stage, 2 * kb + g / kOB, g % kOB);
+        s16x4 vf[3][2];
+        // fragments of group g of half step kb: K rows of key block kb, k-step g; V^T of 16-key step 2 kb + g / kOB, output
+        // block g % kOB.  Three reads, one in each of three slots of a group (part): a slot then has an instruction of the
+        // compiler's own between the argument of a weight and its exponential, which takes the place of a wait state that
+        // the compiler would put between two pieces of inline asm.
+        auto load_part = [&](auto kbc, auto gc, auto part) {
+            constexpr int kb = decltype(kbc)::value, g = decltype(gc)::value, w3 = (kb * kK + g) % 3;
+            if constexpr (decltype(part)::value == 0) kf[w3] = k_frag(next_stage, kb, g);
+            else vf[w3][decltype(part)::value - 1] = v_half(stage, 2 * kb + g / kOB, g % kOB, decltype(part)::value - 1);
         };
-        load_group(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-        load_group(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+        static_for<3>([&](auto part) {
+            load_part(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, part);
+            load_part(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, part);
+        });
         __builtin_amdgcn_sched_barrier(0);
         static_for<2 * kK>([&](auto gg) {
             constexpr int kb = decltype(gg)::value / kK, g = decltype(gg)::value % kK;
-            // two groups ahead, into the registers the group before this one has left
-            if constexpr (g + 2 < kK) load_group(std::integral_constant<int, kb>{}, std::integral_constant<int, g + 2>{});
-            else if constexpr (kb == 0) load_group(std::integral_constant<int, 1>{}, std::integral_constant<int, g + 2 - kK>{});
             static_for<4>([&](auto mc4) {
                 constexpr int m = decltype(mc4)::value, j = g * 4 + m;      // slot j of 4 kK in this half step
                 // Half step 0: P S P S (the first K fragment is the last to arrive); half step 1: S S P P.  Either
@@ -482,10 +484,16 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
                 constexpr int r = kb == 0 ? m >> 1 : m & 1;
                 constexpr int w3 = (kb * kK + g) % 3;                        // this group's place in the window of three
                 if constexpr (is_p) {
-                    mfma_o<Acc::o(r, g % kOB)>(__builtin_bit_cast(bf16x8, vf[w3]), p_frag(kb, r, g / kOB));
+                    const s16x8 a8 = __builtin_shufflevector(vf[w3][0], vf[w3][1], 0, 1, 2, 3, 4, 5, 6, 7);
+                    mfma_o<Acc::o(r, g % kOB)>(__builtin_bit_cast(bf16x8, a8), p_frag(kb, r, g / kOB));
                 } else {
                     if constexpr (g == 0) mfma_s0<Acc::q(r, g)>(s[kb][r], kf[w3]);
                     else mfma_s<Acc::q(r, g)>(s[kb][r], kf[w3]);
+                }
+                // two groups ahead, into the registers the group before this one has left
+                if constexpr (m < 3) {
+                    if constexpr (g + 2 < kK) load_part(std::integral_constant<int, kb>{}, std::integral_constant<int, g + 2>{}, mc4);
+                    else if constexpr (kb == 0) load_part(std::integral_constant<int, 1>{}, std::integral_constant<int, g + 2 - kK>{}, mc4);
                 }
                 // Copies of the tile three ahead: spread evenly over the tile, so that the copy instructions reach
                 // the memory pipeline as a trickle: issued together they fill its queue, and a wavefront that
@@ -696,6 +704,10 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
         if (I.pair_ends && !I.last_iter) prefetch_q(desc_b(it + 1), desc_hkv(it + 1));
         return I;
     };
+    auto whole_at = [&](int i) {
+        const int2 d = *reinterpret_cast<const int2 *>(&desc_of(i)->n_valid);
+        return is_whole(__builtin_amdgcn_readfirstlane(d.x), __builtin_amdgcn_readfirstlane(d.y));
+    };
     auto stage_of = [&](int it) { return ring + ((unsigned)it % kS) * G::kStageBytes; };   // (unsigned: a mask, not a signed remainder)
 
     for (int it = 0; it < n_iter; ++it) {
@@ -722,12 +734,37 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
             scores(stage_of(it));
             begin_run();
             while (I.pipelined) {
-                const size_t boff = (size_t)(I.c_blk >= 0 ? I.c_blk : 0) * (16 * G::kRowBytes);
-                const char *kbase = reinterpret_cast<const char *>(p.k_cache) + boff;
-                const char *vbase = reinterpret_cast<const char *>(p.v_cache) + boff;
-                if (I.copy_inside) tile_pipelined(std::true_type{}, stage_of(it), stage_of(it + 1), kbase, vbase, I.copy_stage_lds);
-                else tile_pipelined(std::false_type{}, stage_of(it), stage_of(it + 1), kbase, vbase, I.copy_stage_lds);
-                ++it;
+                if (I.copy_inside) {
+                    // The middle of a run: as long as the tile after next and the tile to copy are whole too, a loop of its
+                    // own with one path through it, so that no register moves at a join, and with nothing between two tiles
+                    // but the wait, the barrier and the words of the next tile to copy.  Issue bounds this kernel (one
+                    // wavefront per SIMD; a tile is 2048 cycles of matrix work and some 3000 of instruction issue), and
+                    // the general loop head costs every tile some 850 cycles more, 35 register moves among them.  Whole
+                    // steps, before and after: 4 sequences of 32 K positions, 128 nodes, 288 -> 258 us; 64 of 2 to 8 K,
+                    // 64 nodes, 64 query heads, 747 -> 670 us.
+                    int blk = I.c_blk;
+                    unsigned whole = (whole_at(it + 2) ? 1u : 0u) | (whole_at(it + 3) ? 2u : 0u);   // bit k: tile it + 2 + k
+                    const int end = min(n_iter - kS + 1, (it | (kDescSlots / 2 - 1)) + 1);            // (the list is extended by the general head)
+                    for (;;) {
+                        const size_t boff = (size_t)(unsigned)blk * (16 * G::kRowBytes);
+                        tile_pipelined(std::true_type{}, stage_of(it), stage_of(it + 1), reinterpret_cast<const char *>(p.k_cache) + boff,
+                                       reinterpret_cast<const char *>(p.v_cache) + boff, ring_lds + ((unsigned)(it + kS - 1) % kS) * G::kStageBytes);
+                        ++it;
+                        blk = __builtin_amdgcn_readfirstlane(d_blk);
+                        const int c_valid = __builtin_amdgcn_readfirstlane(d_cpy.x), c_flags = __builtin_amdgcn_readfirstlane(d_cpy.y);
+                        if (it >= end || (whole & 1u) == 0 || !is_whole(c_valid, c_flags)) break;
+                        whole = (whole >> 1) | 2u;
+                        wait_vmcnt<kCopiesPerTile>();
+                        __syncthreads();        // tiles it and it + 1 are complete in LDS; every wavefront is done with tile it - 1
+                        d_cpy = *reinterpret_cast<const int2 *>(&desc_of(it + kS)->n_valid);
+                        d_blk = desc_of(it + kS)->blk[cw];
+                    }
+                    d_cur = *reinterpret_cast<const int2 *>(&desc_of(it)->n_valid);
+                    d_nxt = *reinterpret_cast<const int2 *>(&desc_of(it + 1)->n_valid);
+                } else {
+                    tile_pipelined(std::false_type{}, stage_of(it), stage_of(it + 1), nullptr, nullptr, 0u);
+                    ++it;
+                }
                 I = begin_iteration(it);    // (a whole tile that starts no segment: nothing else to prepare)
             }
             end_run();

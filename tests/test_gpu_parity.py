@@ -154,6 +154,34 @@ def test_attn_ranges_longer_than_the_tile_list(R, oracle_mod, T, Hq, tune):
     check_attn(R, oracle_mod, w)
 
 
+@pytest.mark.parametrize("ranges,D,lens", [
+    (1, 128, [64 * n + r for n in range(2, 9) for r in (0, 1)]),   # runs of one to eight whole tiles in one range
+    (1, 64, [64 * n + r for n in range(2, 9) for r in (0, 63)]),
+    (1, 128, [64 * 124, 64 * 131 + 5, 64 * 6, 64 * 7]),     # runs that end, start and go on where the list is extended
+    (1, 128, [64 * 127, 64 * 126, 64 * 4]),
+    (3, 128, [64 * 400 + 17]), (2, 128, [64 * 257, 640]),   # and that go over it more than once, cut between workgroups
+    (1, 128, [-960]), (1, 64, [-1344])])                    # negative: with page ids outside the pool along the way
+def test_attn_runs_of_whole_tiles_with_256_row_workgroups(R, oracle_mod, ranges, D, lens, tune):
+    # the kernel of four 64-row wavefronts runs the middle of a run in a loop of its own, which looks three tiles ahead
+    tune(R.TUNE_ATTN_ROWS, 256)
+    tune(R.TUNE_ATTN_WIDE, 1)
+    tune(R.TUNE_ATTN_RANGES, ranges)
+    w = W.make_custom("runs_D%d_%d" % (D, len(lens)), B=len(lens), Hq=4, Hkv=1, D=D, T=33, seq_lens=[abs(n) for n in lens],
+                      tree="trie", depth=6, seed=408 + len(lens))
+    assert plan_of(R, w)["kernel_id"] == 3, plan_of(R, w)
+    if lens[0] > 0:
+        check_attn(R, oracle_mod, w, variants=(0,))
+        return
+    for tile in range(1, 14):                  # the bad tile meets the loop as the tile to copy, at every place of the run
+        bad = w.page_table.copy()
+        w.page_table[0, 4 * tile + tile % 4] = w.num_pages
+        out, lse = run_attn(R, w, want_status=R.STATUS_BAD_PAGE)
+        ref, ref_lse = run_attn(R, w, variant=1, want_status=R.STATUS_BAD_PAGE)
+        assert_close(out, ref, what="bad page in tile %d" % tile)
+        assert_close(lse, ref_lse, what="bad page in tile %d, lse" % tile)
+        w.page_table[:] = bad
+
+
 @pytest.mark.parametrize("T,Hq", [(16, 8), (48, 16)])
 def test_attn_ranges_cut_with_64_bit_arithmetic(R, oracle_mod, T, Hq, tune):
     # the kernel cuts its ranges in 32-bit arithmetic when the host can show that nothing
