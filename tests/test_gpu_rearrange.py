@@ -86,3 +86,38 @@ def test_second_pass_changes_nothing(R, oracle_mod):
     k2, v2, valid2, new_len2 = run_gpu(R, c2)
     assert np.array_equal(k2, k) and np.array_equal(v2, v) and np.array_equal(valid2, valid)
     assert np.array_equal(new_len2, new_len)
+
+
+@pytest.mark.parametrize("S", [1, 7, 8, 63, 64, 65, 511, 513, 4100, 8191, 8192, 8193, 16390])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_flags_of_any_length_and_alignment(R, oracle_mod, S, shift):
+    # the scan reads the flags of 8 positions as one word where they are aligned, and byte by byte at a ragged end
+    # and for flags at an odd address; rounds of 8192 positions; any nonzero byte is a token
+    import torch
+    rng = np.random.Generator(np.random.PCG64(S + shift))
+    B = 8
+    valid = np.zeros((B, S), dtype=np.uint8)
+    valid[0] = rng.integers(2, 256, size=S)
+    valid[1] = (rng.random(S) < 0.5) * 255
+    valid[2, S - 1] = 1
+    valid[3, 0] = 128
+    valid[4, : S // 2] = 1
+    valid[5, S // 3 :] = 1
+    valid[6, : max(1, S - 9)] = rng.random(max(1, S - 9)) < 0.97
+    k = W.to_bf16_bits(rng.standard_normal((1, B, S, 1, 64), dtype=np.float32))
+    v = W.to_bf16_bits(rng.standard_normal((1, B, S, 1, 64), dtype=np.float32))
+    k_ref, v_ref, valid_ref = k.copy(), v.copy(), valid.copy()
+    len_ref = oracle_mod.kv_rearrange(k_ref, v_ref, valid_ref)
+    print("rearrange flags: S", S, "shift", shift, flush=True)
+    dk, dv = (torch.from_numpy(t.view(np.int16)).cuda().view(torch.bfloat16) for t in (k, v))
+    room = torch.full((B * S + 16,), 77, dtype=torch.uint8, device="cuda")
+    flags = room[shift: shift + B * S].view(B, S)
+    flags.copy_(torch.from_numpy(valid))
+    new_len = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    scratch = torch.empty(max(R.reader_kv_rearrange_scratch_bytes(B, S), 256), dtype=torch.uint8, device="cuda")
+    R.reader_kv_rearrange(dk, dv, flags, new_len, scratch)
+    torch.cuda.synchronize()
+    assert np.array_equal(new_len.cpu().numpy(), len_ref) and np.array_equal(flags.cpu().numpy(), valid_ref)
+    assert bool((room[:shift] == 77).all()) and bool((room[shift + B * S:] == 77).all())
+    for got, ref, what in ((dk, k_ref, "K"), (dv, v_ref, "V")):
+        assert np.array_equal(got.view(torch.int16).cpu().numpy().view(np.uint16), ref), what
