@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256) void lengths_short_kernel(const int32_t *grown
 }
 
 // Merge of the n_splits records of every query row.  A record is laid out [chunk of 8 values][row], so a wavefront takes 16
-// consecutive rows of four chunks: its loads fetch 256 contiguous bytes per chunk.  With more than four shares the four
+// consecutive rows of four chunks: its loads fetch 256 contiguous bytes per chunk.  With more than eight shares the four
 // wavefronts of a workgroup take a quarter of the shares each and fold their states through LDS in the order of the shares.
 //
 // What bounds it: a launch, one trip to memory for the records (other compute units have just written them past the

@@ -962,7 +962,7 @@ def test_verify_step_of_whole_pairs_does_the_rest_in_the_same_launch(R, Hkv, D, 
 
 @pytest.mark.parametrize("T,G,D,splits", [
     (15, 1, 64, 4), (16, 1, 128, 5),         # the merge takes 16 rows x 4 chunks per wavefront: one block of rows, full or not;
-    (17, 1, 128, 4), (17, 1, 64, 5),         # up to four shares one wavefront reads all of them, from five on four share them out
+    (17, 1, 128, 4), (17, 1, 64, 5),         # up to eight shares one wavefront reads all of them, four or eight at a time, from nine on four share them out
     (127, 1, 64, 8), (43, 3, 128, 9),        # edges of the record (128 rows); shares per wavefront that come out even or not
 ])
 def test_attn_short_problem_merge_edges(R, oracle_mod, T, G, D, splits, tune):
