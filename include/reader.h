@@ -295,10 +295,12 @@ int reader_kv_compact_layers(const reader_dims *dims, int32_t num_layers,
  * accepted path; Section 4.3 / Algorithm 4: the accepted rows join the cache), with the
  * arguments, layouts, results and status bits of
  *     reader_tree_attn -> reader_accept_path -> reader_kv_compact
- * called in that order on one stream, but in two kernel launches instead of four: the
- * second launch merges the attention partials, accepts a path per sequence and compacts
- * it.  target_tokens are an input here too (the base model's tokens come from outside
- * this library), so the attention output is not consulted by the acceptance.
+ * called in that order on one stream, but in two kernel launches instead of four (three
+ * where the four-wavefront kernel runs): the last launch merges the attention partials, accepts
+ * a path per sequence and compacts it; where a short problem's pairs are not cut, the first
+ * launch does all of that as well and the second only writes the new lengths.  target_tokens
+ * are an input here too (the base model's tokens come from outside this library), so the
+ * attention output is not consulted by the acceptance.
  * k_cache, v_cache and seq_lens are read by the attention and then updated by the
  * compaction.  dims->variant must be 0.  Errors as for the three calls.
  *

@@ -76,6 +76,7 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     // wavefronts of the last chunk have no rows.  Five chunks cross over at 2.5 million (two sequences of 32 K 191 -> 199,
     // 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in the last 256 at about 6 (two of 32 K 129 -> 128,
     // eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31 million).
+    // (All of these with a four-wavefront kernel that took a ninth longer than it does now: the two lines lie a little high.)
     // Seven chunks go by size like the even ones: 1.02 to 1.20, but 0.97 with 24 sequences of 0.3 to 3 K.
     const int M = d.T * (d.Hq / d.Hkv), chunks = (M + 127) / 128;
     const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
@@ -151,7 +152,7 @@ static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
 //   - as many shares as fill the compute units once (head dimension 64: twice, two workgroups fit one), but no
 //     more than sqrt(12 tiles): a share costs the merge about a twelfth of what a tile costs the workgroup;
 //   - none where they would save a workgroup less than four tiles' time (six at head dimension 64, whose tiles take less
-//     time): the merge, a launch of its own, takes that long;
+//     time): the merge, a launch of its own, takes that long (both as fitted with a merge of 6.6 us where it takes 4.2 now);
 //   - none where a pair of the longest length is one the ring kernels could have finished in one workgroup: a share's
 //     result is rounded to bf16 in its record and once more in the merge (relative error 2.9e-3 instead of 2.3e-3), and
 //     that is paid only where it was paid before (the kernel asks the same of the actual lengths, pair by pair);
