@@ -25,7 +25,6 @@
 //           step); as plain stores it runs at the rate of a fill, with the movers underneath.
 #include "internal.h"
 
-
 namespace reader {
 
 namespace {
