@@ -76,13 +76,21 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     // wavefronts of the last chunk have no rows.  Five chunks cross over at 2.5 million (two sequences of 32 K 191 -> 199,
     // 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in the last 256 at about 6 (two of 32 K 129 -> 128,
     // eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31 million).
-    // (All of these with a four-wavefront kernel that took a ninth longer than it does now: the two lines lie a little high.)
+    // These lines were drawn with a four-wavefront kernel that took a ninth longer than it does now.  Where pairs are so few (25
+    // at most, a half or a third of the 128-row side's ranges) that both sides cut every one of them, two lines lie where
+    // today's kernel crosses over: five chunks at 1 million (one sequence of 23 K 88 -> 80 us, of 32 K 114 -> 97), three with
+    // more than 320 rows at 2 (two of 23 K 110 -> 100, of 32 K 150 -> 126; two of 8 K would lose, 46 -> 51).  Three with up to 320
+    // rows would gain as much above 2, and still have the old line.  With more pairs the lines stay: the 256-row side has
+    // more ranges, cuts more pairs and rounds those once more (five of 1 to 14 K, 384 rows: 2.82e-3 -> 2.87e-3 off 64 bits, 24 of
+    // 2 to 8 K 2.52e-3 -> 2.62e-3; with up to 25 pairs 0.99 to 1.004 times).
     // Seven chunks go by size like the even ones: 1.02 to 1.20, but 0.97 with 24 sequences of 0.3 to 3 K.
     const int M = d.T * (d.Hq / d.Hkv), chunks = (M + 127) / 128;
     const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     const bool odd = chunks == 3 || chunks == 5;
-    const long long most = chunks == 5 ? 2500000 : 6000000;
-    if (odd && (d.D == 64 || (M > 320 && M <= 384) || pairs * tiles <= most / tiles)) return 128;
+    const bool few = pairs * 10 <= kNumCU;
+    const bool filled = M > 320 && M <= 384;
+    const long long most = chunks == 5 ? (few ? 1000000 : 2500000) : few && filled ? 2000000 : 6000000;
+    if (odd && (d.D == 64 || (filled && !few) || pairs * tiles <= most / tiles)) return 128;
     return rows_per_wg_by_size(d, max_seq_len);
 }
 

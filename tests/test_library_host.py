@@ -156,6 +156,17 @@ def test_three_and_five_chunks_of_128_rows_are_for_shorter_pairs(R, T, D, B, bou
     assert plan["rows_per_workgroup"] == rows, plan
 
 
+@pytest.mark.parametrize("T,D,B,bound,rows", [
+    (72, 128, 1, 22000, 128), (72, 128, 1, 23000, 256), (80, 128, 3, 13300, 256), (80, 128, 4, 13300, 128),   # five chunks
+    (41, 128, 1, 31000, 128), (41, 128, 1, 32768, 256), (48, 128, 3, 19200, 256), (48, 128, 4, 32768, 128),   # three, more than 320 rows
+    (40, 128, 1, 32768, 128), (72, 64, 1, 32768, 128), (48, 64, 1, 32768, 128)])
+def test_few_long_pairs_cross_over_sooner(R, T, D, B, bound, rows):
+    # up to 25 pairs of a sequence and a kv head are all cut on either side of the line
+    dims = R.make_dims(B, T, 64, 8, D, 2100, 1, 200000)
+    assert R.reader_attn_plan(dims, bound)["rows_per_workgroup"] == rows
+    check_records_fit(R, dims, bound)
+
+
 def test_attention_plan_follows_the_query_rows_and_the_overrides(R):
     # few query rows per kv head: 128-row workgroups with copying wavefronts; many rows on a long context: 256-row
     # workgroups, four wavefronts at head dimension 128 and eight at 64; the override names either
