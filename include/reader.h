@@ -298,13 +298,13 @@ int reader_kv_compact_layers(const reader_dims *dims, int32_t num_layers,
  * called in that order on one stream, but in two kernel launches instead of four (three
  * where the four-wavefront kernel runs): the last launch merges the attention partials, accepts
  * a path per sequence and compacts it; where a short problem's pairs are not cut, the first
- * launch does all of that as well and the second only writes the new lengths.  target_tokens
- * are an input here too (the base model's tokens come from outside this library), so the
- * attention output is not consulted by the acceptance.
+ * launch accepts as well and the second only compacts.  target_tokens are an input here too
+ * (the base model's tokens come from outside this library), so the attention output is not
+ * consulted by the acceptance.
  * k_cache, v_cache and seq_lens are read by the attention and then updated by the
- * compaction; a slot that accepted rows are appended to must not lie inside the prefix of another
- * sequence that shares the page (its next step would find them there in any case; here it may be
- * this one).  dims->variant must be 0.  Errors as for the three calls.
+ * compaction: nothing is appended before the attention of every sequence has been computed, so
+ * sequences may share pages as the three calls let them, a partly filled one among forks of
+ * unequal length too.  dims->variant must be 0.  Errors as for the three calls.
  *
  * k_tree and v_tree both NULL: the in-cache layout of reader_tree_attn, one layer.  The step
  * is then reader_tree_attn -> reader_accept_path -> reader_kv_compact_layers(num_layers = 1)

@@ -23,7 +23,7 @@ namespace reader {
 struct AcceptShared {
     int par[READER_MAX_T];
     int target[READER_MAX_T];        // the base model's tokens, so that target[parent] is an LDS read
-    int path[READER_MAX_T];          // the accepted path, for a compaction that follows in the same workgroup
+    int path[READER_MAX_T];          // the accepted path, to report and for a compaction that follows in the same workgroup
     unsigned long long term[2];
     int accept_len;
 };
@@ -145,54 +145,6 @@ __device__ inline void accept_path_wave(const AcceptParams &p, int b, int lane, 
     int bits;
     const int n = accept_choose(p, lane, nd, sh, bits);
     accept_report(p, b, lane, n, bits, sh);
-}
-
-// One kv head's part of the compaction of sequence b (old length L) by one wavefront: the rows of path[0..n] (LDS) of the
-// tree tensors are appended behind position L - 1.  Every item is checked before anything is written, and every head of a
-// sequence comes to the same verdict.  Returns by how much the sequence grows: n + 1, or 0 where it was refused, with the
-// reason in `bits`.
-template <int D>
-__device__ inline int kv_compact_head_wave(const CompactParams &p, int b, int hkv, int lane, int n, int L, const int *path, int &bits) {
-    if (L < 0 || (long long)L + n + 1 > (long long)p.max_pages * READER_PAGE_SIZE) {
-        bits |= READER_STATUS_BAD_PATH;
-        return 0;
-    }
-    // A lane keeps its place inside a position (K or V, 16-byte chunk) and takes every kPer-th path entry, eight at a time:
-    // their page ids and rows are asked for together (one trip to memory) and stored afterwards.  The loads carry no
-    // condition: an entry past the path reads the last one again.
-    constexpr int kChunks = D / 8, kPer = 64 / (2 * kChunks), kBatch = 8;
-    const int at = lane / (2 * kChunks), which = (lane / kChunks) & 1, dc = lane % kChunks;
-    typedef unsigned int held_t __attribute__((ext_vector_type(4)));
-    const uint16_t *tree = (which ? p.v_tree : p.k_tree) + ((size_t)b * p.T * p.Hkv + hkv) * D + dc * 8;
-    uint16_t *cache = (which ? p.v_cache : p.k_cache) + (size_t)hkv * READER_PAGE_SIZE * D + dc * 8;
-    const int32_t *table = p.page_table + (size_t)b * p.max_pages;
-    // (positions L .. L + n: inside the table, by the check above)
-    bool bad_page = false;
-    for (int j = lane; j <= n; j += 64) {
-        const int page = table[(L + j) / READER_PAGE_SIZE];
-        bad_page |= page < 0 || page >= p.num_pages;
-    }
-    for (int j0 = 0; j0 <= n; j0 += kPer * kBatch) {
-        held_t held[kBatch];
-        int page[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int j = min(j0 + u * kPer + at, n);
-            page[u] = table[(L + j) / READER_PAGE_SIZE];
-            held[u] = *reinterpret_cast<const held_t *>(tree + (size_t)path[j] * p.Hkv * D);
-        }
-        if (j0 == 0 && __any(bad_page)) {
-            bits |= READER_STATUS_BAD_PAGE;
-            return 0;
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int j = j0 + u * kPer + at;
-            if (j <= n)
-                *reinterpret_cast<held_t *>(cache + ((size_t)page[u] * p.Hkv * READER_PAGE_SIZE + (L + j) % READER_PAGE_SIZE) * D) = held[u];
-        }
-    }
-    return n + 1;
 }
 
 // What compaction needs that does not depend on the accepted path: the old length and the page

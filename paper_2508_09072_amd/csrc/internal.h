@@ -104,7 +104,7 @@ int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len);
 struct AcceptParams;
 struct CompactParams;
 // ev_start / ev_stop: optional events recorded around the main kernel only.  With `ap` and
-// `cp` the second launch also accepts a path per sequence and compacts it (the fused step).
+// `cp` a path per sequence is accepted and compacted too (the fused step).
 hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
                                  const AcceptParams *ap = nullptr, const CompactParams *cp = nullptr);
 hipError_t launch_tree_attn_scalar(const AttnParams &p, hipStream_t stream);

@@ -60,16 +60,16 @@ constexpr int kWavesPerSimd64 = 2;        // (the time stamps take registers)
 constexpr int kWavesPerSimd64 = 4;
 #endif
 
-// kStep: the fused step where no pair is cut.  Acceptance needs tokens and compaction rows that nobody else in this launch
-// writes, and neither has anything to do with the attention's results: the first copying wavefront of a pair (first row
-// chunk) does both for its kv head, the choice of the path while the first tiles are on their way, the rest when it has no
-// more tiles to ask for and the computing wavefronts are at their last ones.  Every kv head's wavefront finds the path by
-// itself, the first head's reports it.  Only the new lengths have to wait for the next launch, because this one reads the
-// old ones.  (Cut pairs need a second launch for their merge anyway, and their workgroups are over so soon that the
-// side job would make them longer: two nodes on a prompt of 4 K tokens 13.1 -> 14.2 us.  Uncut: five sequences of 100
-// tokens 13.4 -> 11.0, 55 of 14 - 144 tokens 43.0 -> 40.3.)
+// kStep: the fused step where no pair is cut.  Acceptance reads tokens only and writes nothing that an attention launch
+// reads, so the first copying wavefront of a sequence's first workgroup chooses the path while the first tiles are on their
+// way and reports it when it has no more tiles to ask for.  The accepted rows wait for the next launch: a slot behind one
+// sequence's end may lie inside the prefix of another one that this launch still reads (forks of unequal length that share a
+// partly filled page), and so do the lengths, which every workgroup reads.  Whole steps, against acceptance in the second
+// launch too: five sequences of 100 tokens, 32 nodes, 15.8 -> 14.6 us; 44 of 237, 24 nodes, 28.3 -> 27.3, at head dimension
+// 64 14.9 -> 14.3; 64 of 300 to 500, 20 nodes, 40.7 -> 40.3.  (Cut pairs need a second launch for their merge anyway, which
+// accepts as well.)
 template <int D, bool kStep>
-__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const AcceptParams &ap, const CompactParams &cp) {
+__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const AcceptParams &ap) {
     constexpr bool kDeep = D == 128;
     constexpr int CW = 4, kS = kShortStages;
     using G = Geometry<D, CW>;
@@ -128,13 +128,9 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
         };
         const bool early = n_table <= kPageRegs * 64 * 4;   // all the sequence can have: asked for before its length is known
         if (early) fetch_pages();
-        const bool side = kStep && cw == 0 && chunk == 0;
+        const bool side = kStep && cw == 0 && chunk == 0 && hkv == 0;
         AcceptTokens tok;
-        int old_len = 0;
-        if (side) {
-            tok = accept_load(ap, b, lane);
-            old_len = cp.seq_lens[b];
-        }
+        if (side) tok = accept_load(ap, b, lane);
         share();
         if (!early) {
             page_base = lo;
@@ -226,14 +222,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             if (t + kS - 1 < hi) issue(t + kS - 1);
         }
         if (p.status && bad) atomicOr(p.status, bad);
-        if (side) {
-            const bool report = hkv == 0;
-            if (cp.k_tree) {                      // (in-cache layout: the rows move in a launch of their own)
-                const int grown = kv_compact_head_wave<D>(cp, b, hkv, lane, accepted, old_len, s_accept->path, step_bits);
-                if (report && lane == 0) p.pair_info[b] = grown;
-            }
-            if (report) accept_report(ap, b, lane, accepted, step_bits, *s_accept);
-        }
+        if (side) accept_report(ap, b, lane, accepted, step_bits, *s_accept);
         return;
     }
 
@@ -509,16 +498,11 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
 
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(AttnParams p) {
-    tree_attn_short_body<D, false>(p, AcceptParams(), CompactParams());
+    tree_attn_short_body<D, false>(p, AcceptParams());
 }
 template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp) {
-    tree_attn_short_body<D, true>(p, ap, cp);
-}
-// ... and behind it the lengths: it has left by how much every sequence grows
-__global__ __launch_bounds__(256) void lengths_short_kernel(const int32_t *grown, int32_t *seq_lens, int B) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b < B) seq_lens[b] += grown[b];
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(AttnParams p, AcceptParams ap) {
+    tree_attn_short_body<D, true>(p, ap);
 }
 
 // Merge of the n_splits records of every query row.  A record is laid out [chunk of 8 values][row], so a wavefront takes 16
@@ -603,8 +587,7 @@ __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, Ac
 }
 
 template <int D, bool kStep>
-hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
-                       const CompactParams *cp) {
+hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap) {
     using G = Geometry<D, 4>;
     constexpr size_t lds = (size_t)kShortStages * G::kStageBytes + (4 * READER_MAX_T + 4 * kShortStages) * sizeof(int) +
                            (kStep ? sizeof(AcceptShared) : 0);
@@ -622,8 +605,8 @@ hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_st
     const dim3 grid(p.n_splits, p.Hkv, p.B * p.n_row_chunks);
     const bool timed = ev_start && ev_stop;
     if constexpr (kStep) {
-        if (timed) hipExtLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p, *ap, *cp);
-        else hipLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, p, *ap, *cp);
+        if (timed) hipExtLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p, *ap);
+        else hipLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, p, *ap);
     } else {
         if (timed) hipExtLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p);
         else hipLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, p);
@@ -635,12 +618,11 @@ template <int D>
 hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
                       const CompactParams *cp) {
     if (ap && cp && p.n_splits == 1) {
-        const hipError_t e = launch_main<D, true>(p, stream, ev_start, ev_stop, ap, cp);
-        if (e != hipSuccess || !cp->k_tree) return e;
-        hipLaunchKernelGGL(lengths_short_kernel, dim3((p.B + 255) / 256), dim3(256), 0, stream, p.pair_info, cp->seq_lens, p.B);
-        return note_hip_error("launch lengths_short_kernel", hipGetLastError());
+        const hipError_t e = launch_main<D, true>(p, stream, ev_start, ev_stop, ap);
+        if (e != hipSuccess || !cp->k_tree) return e;      // (in-cache layout: the rows move in a launch of their own)
+        return launch_kv_compact(*cp, stream);
     }
-    const hipError_t e = launch_main<D, false>(p, stream, ev_start, ev_stop, nullptr, nullptr);
+    const hipError_t e = launch_main<D, false>(p, stream, ev_start, ev_stop, nullptr);
     if (e != hipSuccess || p.n_splits == 1) return e;
     const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
     const int blocks = p.merge_groups == 4 ? units : (units + 3) / 4;

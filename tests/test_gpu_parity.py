@@ -917,8 +917,8 @@ def test_attn_short_problem_kernel(R, oracle_mod, T, G, D, lens, splits, in_cach
     (2, 64, 40, 40, "page"), (2, 128, 40, 40, "end"), (2, 128, 40, 40, "tree"), (2, 64, 40, 40, "length"),
 ])
 def test_verify_step_of_whole_pairs_does_the_rest_in_the_same_launch(R, Hkv, D, T, max_path, fault, tune):
-    # where no pair is cut, a copying wavefront of the attention kernel accepts and appends: same results, same refusals and
-    # status bits as the three calls
+    # where no pair is cut, a copying wavefront of the attention kernel accepts and the second launch appends: same results,
+    # same refusals and status bits as the three calls
     import torch
     w = W.make_custom("side_T%d_D%d" % (T, D), B=3, Hq=2 * Hkv, Hkv=Hkv, D=D, T=T, seq_lens=[70, 0, 31], tree="chain", p_match=1.0,
                       max_path=max_path, seed=640 + T + D)
@@ -955,6 +955,44 @@ def test_verify_step_of_whole_pairs_does_the_rest_in_the_same_launch(R, Hkv, D, 
                 "tree": R.STATUS_BAD_TREE, "length": R.STATUS_BAD_PATH}[fault]
     assert int(a.status.item()) == int(b.status.item()) == expected
     for name in ("out", "lse", "accept_len", "path", "bonus", "seq_lens"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    for name in ("k_cache", "v_cache"):
+        assert np.array_equal(cache_bits(getattr(a, name)), cache_bits(getattr(b, name))), name
+
+
+@pytest.mark.parametrize("D,short", [(64, 1), (128, 1), (64, 4), (128, 4), (64, 0), (128, 0)])
+def test_verify_step_appends_behind_every_reading_of_a_shared_page(R, D, short, tune):
+    # forks of unequal length: the page that the shorter one appends to is the last page of the longer ones' prefixes.  The
+    # step is attention, then acceptance, then compaction, so the longer ones see the page as it was, whichever kernel runs
+    # (whole pairs, cut pairs, ring kernels).
+    import torch
+    tune(R.TUNE_ATTN_SHORT, short)
+    w = W.make_custom("forks_D%d" % D, B=3, Hq=8, Hkv=4, D=D, T=14, seq_lens=[2, 960, 512], tree="chain", p_match=1.0, seed=660 + D)
+    shared = w.page_table[0, 0]
+    w.page_table[1, 959 // 16] = w.page_table[2, 511 // 16] = shared
+    rng = np.random.Generator(np.random.PCG64(661))
+    for cache in (w.k_cache, w.v_cache):
+        cache[shared] = W.to_bf16_bits(rng.standard_normal(cache[shared].shape, dtype=np.float32))
+    dims = R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages)
+    results = []
+    for fused in (True, False):
+        dw = R.to_device(w)
+        assert (R.reader_attn_plan(dims, dw.max_seq_len)["kernel_id"] == 4) == (short > 0)
+        if fused:
+            R.reader_verify_step(dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
+                                 dw.draft_tokens, dw.target_tokens, dw.out, dw.lse, dw.accept_len, dw.path, dw.bonus,
+                                 dw.max_seq_len, dw.workspace, dw.status)
+        else:
+            R.reader_tree_attn(dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
+                               dw.out, dw.lse, dw.max_seq_len, dw.workspace, dw.status)
+            R.reader_accept_path(dims, dw.draft_tokens, dw.target_tokens, dw.parents, dw.accept_len, dw.path, dw.bonus, dw.status)
+            R.reader_kv_compact(dims, dw.k_tree, dw.v_tree, dw.path, dw.accept_len, dw.k_cache, dw.v_cache, dw.page_table,
+                                dw.seq_lens, dw.status)
+        torch.cuda.synchronize()
+        assert int(dw.status.item()) == 0 and dw.accept_len.tolist() == [13, 13, 13]
+        results.append(dw)
+    a, b = results
+    for name in ("out", "lse", "path", "bonus", "seq_lens"):
         assert torch.equal(getattr(a, name), getattr(b, name)), name
     for name in ("k_cache", "v_cache"):
         assert np.array_equal(cache_bits(getattr(a, name)), cache_bits(getattr(b, name))), name
