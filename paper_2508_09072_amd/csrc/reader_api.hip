@@ -64,6 +64,9 @@ static int rows_per_wg_by_size(const reader_dims &d, int32_t max_seq_len) {
     return units * ((M + 127) / 128) <= 10000 ? 128 : 256;
 }
 
+static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows);
+static int attn_pair_cost(const reader_dims &d, int rows_per_wg);
+
 int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     const int forced = tuning(READER_TUNE_ATTN_ROWS);
     if (forced == 128 || forced == 256) return forced;
@@ -76,21 +79,26 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     // wavefronts of the last chunk have no rows.  Five chunks cross over at 2.5 million (two sequences of 32 K 191 -> 199,
     // 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in the last 256 at about 6 (two of 32 K 129 -> 128,
     // eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31 million).
-    // These lines were drawn with a four-wavefront kernel that took a ninth longer than it does now.  Where pairs are so few (25
-    // at most, a half or a third of the 128-row side's ranges) that both sides cut every one of them, two lines lie where
-    // today's kernel crosses over: five chunks at 1 million (one sequence of 23 K 88 -> 80 us, of 32 K 114 -> 97), three with
-    // more than 320 rows at 2 (two of 23 K 110 -> 100, of 32 K 150 -> 126; two of 8 K would lose, 46 -> 51).  Three with up to 320
-    // rows would gain as much above 2, and still have the old line.  With more pairs the lines stay: the 256-row side has
-    // more ranges, cuts more pairs and rounds those once more (five of 1 to 14 K, 384 rows: 2.82e-3 -> 2.87e-3 off 64 bits, 24 of
-    // 2 to 8 K 2.52e-3 -> 2.62e-3; with up to 25 pairs 0.99 to 1.004 times).
+    // These lines were drawn with a four-wavefront kernel that took a ninth longer than it does now.  With one sequence of
+    // few kv heads two lines lie where today's kernel crosses over: five chunks at 1 million (23 K positions, 576 rows
+    // 88 -> 80 us; 32 K 114 -> 97), three with more than 320 rows at 2 (32 K, 384 rows 83 -> 76).  They hold for that one only
+    // because the host can show there that nothing is rounded oftener: all pairs are equally long, and while pairs x (2 +
+    // pair cost) fit the 128-row side's ranges, no range is longer than a pair's tiles less one, so that side cuts every pair
+    // of two tiles or more, whatever the length turns out to be (error against 64 bits 0.99 to 1.001 times).  Several sequences keep the old lines:
+    // they would gain as much where their lengths are about equal (two of 32 K with 384 rows 150 -> 126), but the 256-row side has
+    // more ranges and cuts short pairs among long ones that the 128-row side leaves whole (of 24 pairs of one sequence of
+    // 18 K and two of 1.5 K 20 instead of 13; five of 1 to 14 K, 384 rows: 2.82e-3 -> 2.87e-3 off 64 bits).  Three chunks of up
+    // to 320 rows keep the line at 6 million also for one sequence, whose pairs of 32 K would gain 5 %.
+    // Like every line here these go by the bound on the lengths.  Where a sequence stays far below it, the side that wins
+    // at the bound can lose: 8 K under a bound of 32 K, 576 rows, 39 us with 128 rows and 44 with 256.
     // Seven chunks go by size like the even ones: 1.02 to 1.20, but 0.97 with 24 sequences of 0.3 to 3 K.
     const int M = d.T * (d.Hq / d.Hkv), chunks = (M + 127) / 128;
     const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     const bool odd = chunks == 3 || chunks == 5;
-    const bool few = pairs * 10 <= kNumCU;
     const bool filled = M > 320 && M <= 384;
-    const long long most = chunks == 5 ? (few ? 1000000 : 2500000) : few && filled ? 2000000 : 6000000;
-    if (odd && (d.D == 64 || (filled && !few) || pairs * tiles <= most / tiles)) return 128;
+    const bool cut_anyway = odd && d.B == 1 && pairs * (2 + attn_pair_cost(d, 128)) <= plan_ranges(d, max_seq_len, 128);
+    const long long most = chunks == 5 ? (cut_anyway ? 1000000 : 2500000) : cut_anyway && filled ? 2000000 : 6000000;
+    if (odd && (d.D == 64 || (filled && !cut_anyway) || pairs * tiles <= most / tiles)) return 128;
     return rows_per_wg_by_size(d, max_seq_len);
 }
 

@@ -157,14 +157,68 @@ def test_three_and_five_chunks_of_128_rows_are_for_shorter_pairs(R, T, D, B, bou
 
 
 @pytest.mark.parametrize("T,D,B,bound,rows", [
-    (72, 128, 1, 22000, 128), (72, 128, 1, 23000, 256), (80, 128, 3, 13300, 256), (80, 128, 4, 13300, 128),   # five chunks
-    (41, 128, 1, 31000, 128), (41, 128, 1, 32768, 256), (48, 128, 3, 19200, 256), (48, 128, 4, 32768, 128),   # three, more than 320 rows
+    (72, 128, 1, 22000, 128), (72, 128, 1, 23000, 256), (80, 128, 2, 16400, 128), (80, 128, 3, 13300, 128),   # five chunks
+    (41, 128, 1, 31000, 128), (41, 128, 1, 32768, 256), (48, 128, 2, 32768, 128), (48, 128, 4, 32768, 128),   # three, more than 320 rows
     (40, 128, 1, 32768, 128), (72, 64, 1, 32768, 128), (48, 64, 1, 32768, 128)])
-def test_few_long_pairs_cross_over_sooner(R, T, D, B, bound, rows):
-    # up to 25 pairs of a sequence and a kv head are all cut on either side of the line
+def test_one_long_sequence_crosses_over_sooner(R, T, D, B, bound, rows):
     dims = R.make_dims(B, T, 64, 8, D, 2100, 1, 200000)
     assert R.reader_attn_plan(dims, bound)["rows_per_workgroup"] == rows
     check_records_fit(R, dims, bound)
+
+
+def whole_pairs(lens, T, Hkv, ranges, front, cost):
+    """The (sequence, kv head) pairs that no start of a range falls into, by the cut that the ring kernels make: a pair is
+    `front` positions, its tiles, and the rest of `cost` positions behind them; all positions are shared out evenly."""
+    tiles = [-(-n // 64) + -(-T // 64) for n in lens]
+    pairs = [(b, h) for b in range(len(lens)) for h in range(Hkv)]
+    begin = np.concatenate(([0], np.cumsum([tiles[b] + cost for b, _ in pairs])))
+    starts = np.arange(1, ranges) * begin[-1] // ranges
+    at = np.searchsorted(begin, starts, side="right") - 1
+    tile = starts - begin[at] - front                        # the first tile at or behind the start of the range
+    n = np.asarray([tiles[b] for b, _ in pairs])
+    return {pairs[i] for i in range(len(pairs))} - {pairs[i] for i, t in zip(at, tile) if 0 < t < n[i]}
+
+
+def test_the_model_of_the_cut():
+    # one pair of ten tiles over two ranges is cut in its middle; as long as there are as many ranges as equal pairs none is
+    assert whole_pairs([600], 16, 1, 2, 1, 3) == set()
+    assert whole_pairs([600], 16, 8, 8, 1, 3) == {(0, h) for h in range(8)}
+    assert whole_pairs([18000, 1500, 1500], 72, 8, 48, 1, 3) - whole_pairs([18000, 1500, 1500], 72, 8, 80, 4, 8)
+
+
+def test_odd_row_chunks_change_over_early_only_where_no_pair_is_newly_cut(R):
+    # a cut pair's result is rounded once more.  Below the lines that were drawn by speed alone 256-row workgroups may run
+    # only where they leave every pair whole that 128-row workgroups would, whatever the lengths below the bound.
+    rng = np.random.default_rng(22)
+    shapes = [(72, 8, [18000, 1500, 1500]), (72, 4, [18000] + [1500] * 5), (72, 2, [18000] + [600] * 11), (48, 8, [32768, 3000, 3000])]
+    shapes += [(T, Hkv, [n]) for T in (41, 48, 65, 80) for Hkv in (1, 2, 4, 8, 9, 10, 16, 17, 25) for n in (20000, 23000, 32768, 65536)]
+    for _ in range(400):
+        B, Hkv = int(rng.integers(1, 26)), int(rng.choice((1, 2, 4, 8, 16, 25)))
+        longest = int(2 ** rng.uniform(13, 17))
+        lens = [longest] + [int(longest * 2 ** -rng.uniform(0, 7)) for _ in range(B - 1)]
+        shapes.append((int(rng.choice((41, 44, 48, 65, 72, 80))), Hkv, lens))
+    early = 0
+    for T, Hkv, lens in shapes:
+        M, bound, B = 8 * T, max(lens), len(lens)
+        chunks, tiles = -(-M // 128), -(-bound // 64) + -(-T // 64)
+        if B * Hkv * tiles * tiles > (2500000 if chunks == 5 else 1 << 62):
+            continue                                           # (beyond the lines by speed)
+        dims = R.make_dims(B, T, 8 * Hkv, Hkv, 128, 1 << 13, 1, 1 << 20)
+        plan = R.reader_attn_plan(dims, bound)
+        if plan["kernel_id"] == 4 or plan["rows_per_workgroup"] == 128:
+            continue
+        early += 1
+        R.reader_tuning_override(R.TUNE_ATTN_ROWS, 128)
+        try:
+            narrow = R.reader_attn_plan(dims, bound)
+        finally:
+            R.reader_tuning_override(R.TUNE_ATTN_ROWS, -1)
+        assert narrow["kernel_id"] == 1 and plan["kernel_id"] == 3
+        below = [lens] + [[max(0, n * k // 64 - 5) for n in lens] for k in range(64)] + [[k] * B for k in range(0, 1400, 31)]
+        for actual in below:
+            new = whole_pairs(actual, T, Hkv, plan["key_ranges"], 4, 8)
+            assert whole_pairs(actual, T, Hkv, narrow["key_ranges"], 1, 3) <= new, (T, Hkv, actual[:4])
+    assert early >= 20
 
 
 def test_attention_plan_follows_the_query_rows_and_the_overrides(R):
