@@ -473,7 +473,8 @@ int32_t reader_tree_select(const int32_t *parents, const float *alpha, const flo
  * Measurement hooks for benchmarks (not operations of the method).  While enabled,
  * every reader_tree_attn / reader_verify_step call launches its main streaming kernel
  * with a HIP event pair that takes the kernel's own start and end time stamps (the
- * second launch of the call is outside the pair).
+ * later launches of the call are outside the pair; in a fused step whose first launch
+ * accepts as well, the pair spans that too).
  * reader_profile_collect waits for the recorded events (it synchronises the host with
  * them), adds up the elapsed times of all pairs recorded since the last collect into
  * *kernel_ms_sum, stores their count in *launches, and forgets them.  The event

@@ -611,7 +611,7 @@ hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_st
         if (timed) hipExtLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p);
         else hipLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, p);
     }
-    return note_hip_error("launch tree_attn_short_kernel", hipGetLastError());
+    return note_hip_error(kStep ? "launch verify_short_kernel" : "launch tree_attn_short_kernel", hipGetLastError());
 }
 
 template <int D>
