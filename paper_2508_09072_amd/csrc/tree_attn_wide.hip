@@ -738,10 +738,11 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
                     // The middle of a run: as long as the tile after next and the tile to copy are whole too, a loop of its
                     // own with one path through it, so that no register moves at a join, and with nothing between two tiles
                     // but the wait, the barrier and the words of the next tile to copy.  Issue bounds this kernel (one
-                    // wavefront per SIMD; a tile is 2048 cycles of matrix work and some 3000 of instruction issue), and
-                    // the general loop head costs every tile some 850 cycles more, 35 register moves among them.  Whole
-                    // steps, before and after: 4 sequences of 32 K positions, 128 nodes, 288 -> 258 us; 64 of 2 to 8 K,
-                    // 64 nodes, 64 query heads, 747 -> 670 us.
+                    // wavefront per SIMD; 2048 cycles of a tile are matrix work).  4 sequences of 32 K positions, 128 nodes,
+                    // cycles of the whole launch per tile, clock and kernel time: with the general loop head and a group's
+                    // operand reads in one place 4250 at 2.05 GHz, 267 us; this loop alone 3850 at 1.98, 255; the spread
+                    // operand reads with the written-out sums alone 3970 at 1.99, 261; both 3300 at 1.80, 234.  Whole steps,
+                    // neither and both: 285 -> 255 us; 64 sequences of 2 to 8 K, 64 nodes, 64 query heads, 728 -> 642.
                     int blk = I.c_blk;
                     unsigned whole = (whole_at(it + 2) ? 1u : 0u) | (whole_at(it + 3) ? 2u : 0u);   // bit k: tile it + 2 + k
                     const int end = min(n_iter - kS + 1, (it | (kDescSlots / 2 - 1)) + 1);            // (the list is extended by the general head)
