@@ -916,7 +916,7 @@ def test_attn_short_problem_kernel(R, oracle_mod, T, G, D, lens, splits, in_cach
     (2, 128, 40, 7, None),                             # paths cut to max_path: BAD_PATH, and the cut path is appended
     (2, 64, 40, 40, "page"), (2, 128, 40, 40, "end"), (2, 128, 40, 40, "tree"), (2, 64, 40, 40, "length"),
 ])
-def test_verify_step_of_whole_pairs_does_the_rest_in_the_same_launch(R, Hkv, D, T, max_path, fault, tune):
+def test_verify_step_of_whole_pairs_accepts_in_the_same_launch(R, Hkv, D, T, max_path, fault, tune):
     # where no pair is cut, a copying wavefront of the attention kernel accepts and the second launch appends: same results,
     # same refusals and status bits as the three calls
     import torch
@@ -1002,6 +1002,10 @@ def test_verify_step_appends_behind_every_reading_of_a_shared_page(R, D, short, 
     (15, 1, 64, 4), (16, 1, 128, 5),         # the merge takes 16 rows x 4 chunks per wavefront: one block of rows, full or not;
     (17, 1, 128, 4), (17, 1, 64, 5),         # up to eight shares one wavefront reads all of them, four or eight at a time, from nine on four share them out
     (127, 1, 64, 8), (43, 3, 128, 9),        # edges of the record (128 rows); shares per wavefront that come out even or not
+    (15, 1, 64, 9), (16, 1, 128, 9),         # nine: three each for three wavefronts, none for the fourth
+    (17, 1, 128, 10), (17, 1, 64, 12),       # one for the fourth; as many for each
+    (127, 1, 64, 13), (127, 1, 128, 16), (128, 1, 64, 11),
+    (17, 1, 128, 17), (127, 1, 64, 25),      # five and seven each: eight at a time
 ])
 def test_attn_short_problem_merge_edges(R, oracle_mod, T, G, D, splits, tune):
     tune(R.TUNE_ATTN_SHORT, splits)
