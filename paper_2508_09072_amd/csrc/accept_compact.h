@@ -1,5 +1,5 @@
-// Device code of the acceptance and compaction steps, shared by their own kernels and by the
-// fused tail kernel of reader_verify_step.
+// Device code of the acceptance and compaction steps, shared by their own kernels and by the launches of
+// reader_verify_step: the tails do both, the attention launch of short pairs that are not cut accepts.
 //
 // Acceptance (Algorithm 5; Appendix C invariants 2-3): one 64-lane wavefront per
 // sequence.  Each lane owns up to two tree nodes.  A node "matches" when its drafted

@@ -72,23 +72,26 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     if (forced == 128 || forced == 256) return forced;
     // Three or five chunks of 128 rows: a 256-row workgroup would carry a quarter or a sixth of its rows for nothing.
     // Measured with 264 to 640 query rows per kv head over 1 to 64 sequences of 0.3 to 32 K positions, 128-row over 256-row
-    // workgroups: 0.87 to 0.96 at head dimension 64.  At 128 it is 0.81 to 0.99 while the product of the tiles of all
-    // pairs and the tiles of one stays small (24 sequences of 0.3 to 3 K and three chunks: 70 -> 57 us; 64 of 1 to 3 K and
-    // five: 459 -> 449) and more beyond: with long pairs the four-wavefront kernel has few pair boundaries to pay for, and
-    // in a long launch, whose clock the matrix units' power sets, its fewer operand reads count, the more so where most
-    // wavefronts of the last chunk have no rows.  Five chunks cross over at 2.5 million (two sequences of 32 K 191 -> 199,
-    // 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in the last 256 at about 6 (two of 32 K 129 -> 128,
-    // eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31 million).
+    // workgroups: 0.87 to 0.96 at head dimension 64 (of eight wavefronts; four, which do not run there, would beat the 128
+    // rows on long contexts by now: 16 sequences of 8 to 32 K with 360 rows 217 -> 187 us, 24 of 0.3 to 3 K 44 -> 48).
+    // At 128 it is 0.81 to 0.99 while the product of the tiles of all pairs and the tiles of one stays small (24 sequences
+    // of 0.3 to 3 K and three chunks: 70 -> 57 us; 64 of 1 to 3 K and five: 459 -> 449) and more beyond: with long pairs the
+    // four-wavefront kernel has few pair boundaries to pay for, and in a long launch, whose clock the matrix units' power
+    // sets, its fewer operand reads count, the more so where most wavefronts of the last chunk have no rows.  Five chunks
+    // cross over at 2.5 million (two sequences of 32 K 191 -> 199, 16 of 8 to 32 K 944 -> 1034), three with up to 64 rows in
+    // the last 256 at about 6 (two of 32 K 129 -> 128, eight 475 -> 501), three with more do not (0.97 to 1.00 up to 31
+    // million).
     // These lines were drawn with a four-wavefront kernel that took a ninth longer than it does now.  With one sequence of
-    // few kv heads two lines lie where today's kernel crosses over: five chunks at 1 million (23 K positions, 576 rows
-    // 88 -> 80 us; 32 K 114 -> 97), three with more than 320 rows at 2 (32 K, 384 rows 83 -> 76).  They hold for that one only
+    // few kv heads two lines lie where today's kernel crosses over: five chunks at 1 million (23 K positions, 576 rows 88 ->
+    // 80 us; 32 K 114 -> 97), three with more than 320 rows at 2 (32 K, 384 rows 83 -> 76).  They hold for that one only
     // because the host can show there that nothing is rounded oftener: all pairs are equally long, and while pairs x (2 +
-    // pair cost) fit the 128-row side's ranges, no range is longer than a pair's tiles less one, so that side cuts every pair
-    // of two tiles or more, whatever the length turns out to be (error against 64 bits 0.99 to 1.001 times).  Several sequences keep the old lines:
-    // they would gain as much where their lengths are about equal (two of 32 K with 384 rows 150 -> 126), but the 256-row side has
-    // more ranges and cuts short pairs among long ones that the 128-row side leaves whole (of 24 pairs of one sequence of
-    // 18 K and two of 1.5 K 20 instead of 13; five of 1 to 14 K, 384 rows: 2.82e-3 -> 2.87e-3 off 64 bits).  Three chunks of up
-    // to 320 rows keep the line at 6 million also for one sequence, whose pairs of 32 K would gain 5 %.
+    // pair cost) fit the 128-row side's ranges, no range is longer than a pair's tiles less one, so that side cuts every
+    // pair of two tiles or more, whatever the length turns out to be (error against 64 bits 0.99 to 1.001 times).  Several
+    // sequences keep the old lines: they would gain as much where their lengths are about equal (two of 32 K with 384 rows
+    // 150 -> 126), but the 256-row side has more ranges and cuts short pairs among long ones that the 128-row side leaves
+    // whole (of 24 pairs of one sequence of 18 K and two of 1.5 K 20 instead of 13; five of 1 to 14 K, 384 rows: 2.82e-3 ->
+    // 2.87e-3 off 64 bits).  Three chunks of up to 320 rows keep the line at 6 million also for one sequence, whose pairs of
+    // 32 K would gain 5 %.
     // Like every line here these go by the bound on the lengths.  Where a sequence stays far below it, the side that wins
     // at the bound can lose: 8 K under a bound of 32 K, 576 rows, 39 us with 128 rows and 44 with 256.
     // Seven chunks go by size like the even ones: 1.02 to 1.20, but 0.97 with 24 sequences of 0.3 to 3 K.
@@ -140,8 +143,11 @@ static size_t record_bytes(const reader_dims &d, int32_t max_seq_len) {
 }
 
 static int attn_use_wide(const reader_dims &d, int rows_per_wg) {
-    // 256-row workgroups: four wavefronts of 64 rows at head dimension 128 (measured 2 to 4 % faster than eight of
-    // 32 rows at the two matrix-bound presets), eight of 32 at head dimension 64 (measured: no difference)
+    // 256-row workgroups: four wavefronts of 64 rows at head dimension 128 (eight of 32 rows take 1.08 to 1.29 times as long over
+    // six shapes of 1 to 64 sequences of 1 to 32 K positions: two matrix-bound presets 310 against 241 us, 772 against 642), eight
+    // of 32 at head dimension 64.  There the line is older than the four wavefronts' loop for the middle of a run: the two were
+    // equal then.  Now four would take 120 us instead of 142 (16 sequences of 4 to 16 K, 256 rows), 414 instead of 493 (64 of 2 to
+    // 8 K, 512 rows), but 37 instead of 33 where pairs are short (24 of 0.3 to 3 K, 256 rows); not moved yet.
     const int wide = tuning(READER_TUNE_ATTN_WIDE);
     return rows_per_wg == 256 && (wide == 1 || (wide < 0 && d.D == 128)) ? 1 : 0;
 }
@@ -163,8 +169,8 @@ static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
 //
 // The rule was fitted to shapes drawn over 1..64 sequences of up to 32 K positions, 1..128 nodes, both head
 // dimensions and three head layouts, each timed with every number of shares and with the ring kernels.  On 150 others
-// it comes within 3 % of the best choice (geometric mean; worst 1.43 times it, launches of 10 to 20 us), and the ring kernels
-// take 1.6 times as long (geometric mean; least 0.94 times):
+// it comes within 3 % of the best choice (geometric mean; worst 1.29 times it, launches of 10 to 20 us), and the ring kernels
+// take 1.54 times as long (geometric mean; least 0.98 times), both with today's merges:
 //   - as many shares as fill the compute units once (head dimension 64: twice, two workgroups fit one), but no
 //     more than sqrt(12 tiles): a share costs the merge about a twelfth of what a tile costs the workgroup;
 //   - none where they would save a workgroup less than four tiles' time (six at head dimension 64, whose tiles take less
@@ -178,11 +184,11 @@ static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
 //   - sooner where the pairs of several sequences would be cut: the shares are as long as the longest sequence makes
 //     them, whatever the others' lengths, and the host knows no more than that bound.  From more than 14 tiles per
 //     workgroup on (20 at head dimension 64), and four less where there are two shares.  Measured against the ring
-//     kernels on 420 shapes of 8 to 24 tiles, how many times faster (geometric mean and worst), for lengths from a tenth, a
+//     kernels on 420 shapes of 8 to 25 tiles, how many times faster (geometric mean and worst), for lengths from a tenth, a
 //     quarter and half of the bound to all of it, all equal, and one of the bound among others of 64 positions: below
-//     the line 1.08 (0.93), 1.09 (0.96), 1.10 (0.98), 1.11 (1.01) and 1.21 (0.88), head dimension 64 1.11 (0.91), 1.11
-//     (0.95), 1.13 (1.00), 1.16 (1.03) and 1.27 (0.78); beyond it 0.98 (0.84), 1.00 (0.88), 1.03 (0.85), 1.07 (0.95) and
-//     0.98 (0.73), and 1.03 (0.92), 1.04 (0.91), 1.08 (0.95), 1.14 (1.04) and 1.07 (0.70).
+//     the line 1.02 (0.90), 1.04 (0.94), 1.06 (0.98), 1.10 (1.02) and 0.96 (0.78), head dimension 64 1.09 (0.91), 1.08
+//     (0.90), 1.10 (0.90), 1.15 (1.03) and 1.06 (0.70); beyond it 0.93 (0.82), 0.96 (0.87), 1.01 (0.95), 1.08 (1.00) and
+//     0.81 (0.67), and 1.00 (0.91), 1.01 (0.90), 1.04 (0.93), 1.12 (1.07) and 0.78 (0.66).
 struct ShortPlan {
     int rows, chunks, splits;
 };
