@@ -297,8 +297,10 @@ int reader_kv_compact_layers(const reader_dims *dims, int32_t num_layers,
  *     reader_tree_attn -> reader_accept_path -> reader_kv_compact
  * called in that order on one stream, but in two kernel launches instead of four (three
  * where the four-wavefront kernel runs): the last launch merges the attention partials, accepts
- * a path per sequence and compacts it; where a short problem's pairs are not cut, the first
- * launch accepts as well and the second only compacts.  target_tokens are an input here too
+ * a path per sequence and compacts it.  A short problem that fits the chip at once is one launch, whose
+ * workgroups wait for one another (never without bound, and never for a workgroup that may not
+ * run: whoever arrives last does what others have left); on a stream that is being captured it is
+ * two, with the same results.  target_tokens are an input here too
  * (the base model's tokens come from outside this library), so the attention output is not
  * consulted by the acceptance.
  * k_cache, v_cache and seq_lens are read by the attention and then updated by the
@@ -309,7 +311,7 @@ int reader_kv_compact_layers(const reader_dims *dims, int32_t num_layers,
  * k_tree and v_tree both NULL: the in-cache layout of reader_tree_attn, one layer.  The step
  * is then reader_tree_attn -> reader_accept_path -> reader_kv_compact_layers(num_layers = 1)
  * on k_cache, v_cache [num_pages, Hkv, page_size, D]: the accepted rows move in place (one
- * more small launch).  A model with several layers runs the attention of each layer, and
+ * more small launch, except where the step is one).  A model with several layers runs the attention of each layer, and
  * after the last one reader_accept_path and one reader_kv_compact_layers over all of them.
  */
 int reader_verify_step(const reader_dims *dims,
@@ -474,7 +476,7 @@ int32_t reader_tree_select(const int32_t *parents, const float *alpha, const flo
  * every reader_tree_attn / reader_verify_step call launches its main streaming kernel
  * with a HIP event pair that takes the kernel's own start and end time stamps (the
  * later launches of the call are outside the pair; in a fused step whose first launch
- * accepts as well, the pair spans that too).
+ * does more than attend, the pair spans that too).
  * reader_profile_collect waits for the recorded events (it synchronises the host with
  * them), adds up the elapsed times of all pairs recorded since the last collect into
  * *kernel_ms_sum, stores their count in *launches, and forgets them.  The event
@@ -526,6 +528,8 @@ int reader_measure_peaks(const void *src, size_t src_bytes, void *scratch, size_
  *                               the planner takes the first at head dimension 128 and the second at 64
  *   READER_TUNE_ATTN_SHORT      0 = never the kernel for short problems, n >= 1 = always, with n shares per pair (n up
  *                               to 1024, and at most 240 tiles per share); any other override above keeps it out
+ *   READER_TUNE_JOIN            0 = reader_verify_step of a short problem never waits inside a launch, n >= 1 = it waits for
+ *                               (n - 1) / 100 us at most (1: whoever finds another workgroup missing leaves at once)
  * Returns READER_OK, or READER_EINVAL for an unknown `which`.
  */
 enum {
@@ -536,7 +540,8 @@ enum {
     READER_TUNE_ATTN_WIDE = 4,
     READER_TUNE_ATTN_PAIR_FRONT = 5,
     READER_TUNE_ATTN_SHORT = 6,
-    READER_TUNE_COUNT_ = 7
+    READER_TUNE_JOIN = 7,
+    READER_TUNE_COUNT_ = 8
 };
 int reader_tuning_override(int32_t which, int32_t value);
 

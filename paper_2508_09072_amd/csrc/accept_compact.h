@@ -1,5 +1,5 @@
 // Device code of the acceptance and compaction steps, shared by their own kernels and by the launches of
-// reader_verify_step: the tails do both, the attention launch of short pairs that are not cut accepts.
+// reader_verify_step: the tails do both, and so do workgroups of the attention launch of short problems (or it accepts only).
 //
 // Acceptance (Algorithm 5; Appendix C invariants 2-3): one 64-lane wavefront per
 // sequence.  Each lane owns up to two tree nodes.  A node "matches" when its drafted
@@ -226,6 +226,72 @@ __device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, i
         }
     }
     if (tid == 0) p.seq_lens[b] = L + n + 1;
+}
+
+// The accepted rows of a sequence, moved by wavefronts that share no barrier (inside the attention launch of a fused step).
+// Every wavefront checks for itself what the sequence would touch, one path entry per lane and half, and notes where each
+// entry's row is and goes.  A thread keeps its column of a position (K or V, head, chunk) and walks the entries in order,
+// eight loads ahead of eight stores.  Tree tensors: row path[j] goes to position L + j.  Rows in the cache already (k_tree
+// null): position L + path[j] moves to L + j; path[j] >= j, so a destination is never the source of a later entry, and an
+// earlier one of the column has been read.
+struct TailShared {
+    AcceptShared accept;
+    long long src[READER_MAX_T], dst[READER_MAX_T];   // in values, of head 0 and chunk 0; dst < 0: in place already
+};
+struct TailLane {
+    int L, bad;             // old length, status bits (0: go); the same in all lanes
+};
+__device__ __forceinline__ TailLane tail_check(const CompactParams &p, int b, int lane, TailShared &sh) {
+    TailLane t;
+    t.L = __builtin_amdgcn_readfirstlane(p.seq_lens[b]);
+    t.bad = READER_STATUS_BAD_PATH;
+    const int n = sh.accept.accept_len;
+    const bool move = p.k_tree == nullptr;
+    const long long mapped = (long long)p.max_pages * READER_PAGE_SIZE, page_values = (long long)p.Hkv * READER_PAGE_SIZE * p.D;
+    const int32_t *table = p.page_table + (size_t)b * p.max_pages;
+    if (t.L < 0 || (long long)t.L + n + 1 > mapped) return t;
+    int bad = 0;
+    for (int j = lane; j <= n; j += 64) {
+        const int node = sh.accept.path[j], to = t.L + j;
+        const long long from = (long long)t.L + node;
+        if (move && from >= mapped) { bad |= READER_STATUS_BAD_PATH; continue; }
+        const int dst_page = table[to / READER_PAGE_SIZE], src_page = move ? table[from / READER_PAGE_SIZE] : 0;
+        if (dst_page < 0 || dst_page >= p.num_pages || src_page < 0 || src_page >= p.num_pages) { bad |= READER_STATUS_BAD_PAGE; continue; }
+        sh.src[j] = move ? src_page * page_values + from % READER_PAGE_SIZE * p.D : ((long long)b * p.T + node) * p.Hkv * p.D;
+        sh.dst[j] = move && node == j ? -1 : dst_page * page_values + to % READER_PAGE_SIZE * p.D;
+    }
+    wave_lds_order();
+    t.bad = (__ballot(bad & READER_STATUS_BAD_PATH) != 0ull ? READER_STATUS_BAD_PATH : 0) |
+            (__ballot(bad & READER_STATUS_BAD_PAGE) != 0ull ? READER_STATUS_BAD_PAGE : 0);
+    return t;
+}
+constexpr int kTailBatch = 8;
+typedef unsigned int tail_held_t __attribute__((ext_vector_type(4)));
+// A thread's column `col` (below 2 Hkv D / 8): where its 16 bytes of a row of the source and of the cache are.
+struct TailColumn {
+    const uint16_t *src;
+    uint16_t *dst;
+};
+__device__ __forceinline__ TailColumn tail_column(const CompactParams &p, int col) {
+    const int chunks = p.D / 8, per_row = p.Hkv * chunks, which = col >= per_row ? 1 : 0, c = col - which * per_row;
+    const int h = c / chunks, dc = c - h * chunks;
+    TailColumn t;
+    t.dst = (which ? p.v_cache : p.k_cache) + (size_t)h * READER_PAGE_SIZE * p.D + dc * 8;
+    t.src = p.k_tree ? (which ? p.v_tree : p.k_tree) + (size_t)h * p.D + dc * 8 : t.dst;
+    return t;
+}
+__device__ __forceinline__ void tail_load(const TailColumn &col, const TailShared &sh, int j0, tail_held_t (&held)[kTailBatch]) {
+    const int n = sh.accept.accept_len;
+#pragma unroll
+    for (int u = 0; u < kTailBatch; ++u) held[u] = *reinterpret_cast<const tail_held_t *>(col.src + sh.src[min(j0 + u, n)]);
+}
+__device__ __forceinline__ void tail_store(const TailColumn &col, const TailShared &sh, int j0, const tail_held_t (&held)[kTailBatch]) {
+    const int n = sh.accept.accept_len;
+#pragma unroll
+    for (int u = 0; u < kTailBatch; ++u) {
+        const long long to = j0 + u <= n ? sh.dst[j0 + u] : -1;
+        if (to >= 0) *reinterpret_cast<tail_held_t *>(col.dst + to) = held[u];
+    }
 }
 
 }  // namespace reader

@@ -36,6 +36,7 @@ struct AttnParams {
     int32_t *pair_info;      // header: per (sequence, kv head) the first and the last workgroup that hold its tiles
     int32_t *range_tiles;    // header: per range workgroup the number of tiles it holds (0: it wrote no record)
     int32_t *redo;           // header: per workgroup of the wide kernel 1 if its range has to be computed again (kMaxAttnWorkgroups entries)
+                             // (a fused step that waits inside its launch keeps its marks in these three arrays: arrivals.h)
 #ifdef READER_WG_STAMPS
     long long *stamps;       // profiling build only: kWgStamps time stamps (100 MHz counter) of each of the first kStampedWgs workgroups, or null
 #endif
@@ -43,12 +44,17 @@ struct AttnParams {
     int32_t pair_front;      // the part of it booked in front of the pair's tiles (the rest behind them)
     int32_t axis32;          // 1: every position of the cost axis times n_ranges fits in an int
     int32_t ranges_shift;    // log2(n_ranges) when it is a power of two (the even cut is then a shift), else -1
-    int32_t merge_groups;    // thread groups that share a query row's partial records in the merge: 1, or 4 when pairs are cut into many parts
+    int32_t merge_groups;    // (ring kernels) thread groups that share a query row's partial records in the merge: 1, or 4 when pairs are cut into many parts
     int32_t tree_in_cache;   // 1: k_tree / v_tree are null, tree node n of sequence b sits at cache position L_b + n
     int32_t wide;            // (256 rows per workgroup) 1: four wavefronts of 64 rows, 0: eight of 32
     int32_t n_splits;        // short problems: shares every pair's key blocks are cut into (0: one of the ring kernels runs)
     float split_rcp;         // 1 / n_splits
     int32_t keep_whole;      // short problems: 1 if pairs that the ring kernels' even cut could leave whole are not cut here either
+    int32_t wait_ticks;      // ... how long a workgroup waits for others at most (100 MHz)
+    int32_t join;            // ... 1: the fused step's launch may wait inside, token permitting
+    int32_t units_per_xcd;   // ... and how many pairs' chunks of 128 rows every XCD takes (the last of some of them: none)
+    float units_per_xcd_rcp, pairs_rcp, hkv_rcp;   // 1 / units_per_xcd, 1 / (B Hkv), 1 / Hkv
+    unsigned long long token;   // short problems: what marks this launch's arrivals in the header (0: nothing waits inside the launch)
     int32_t redo_only;       // 1: second pass behind the wide kernel, only the workgroups flagged in `redo` do anything
     int32_t *status;
     int32_t B, T, Hq, Hkv, D, G, M;       // G = Hq/Hkv, M = T*G query rows per (sequence, kv head)
@@ -58,6 +64,7 @@ struct AttnParams {
     int32_t n_row_chunks;                  // ceil(M / rows_per_wg)
     int32_t n_ranges;                      // workgroups along the flattened (pair, tile) axis
     int64_t num_pages;
+    float g_rcp;                           // 1 / G
     float scale_log2;                      // sm_scale * log2(e)
 };
 
@@ -111,7 +118,7 @@ hipError_t launch_tree_attn_scalar(const AttnParams &p, hipStream_t stream);
 // main kernel of the 256-row flavour with four wavefronts of 64 rows (tree_attn_wide.hip); no second launch
 hipError_t launch_tree_attn_wide_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
-// short problems: static grid, everything asked for at once (tree_attn_short.hip); both launches
+// short problems: static grid, everything asked for at once (tree_attn_short.hip); all launches of the call
 hipError_t launch_tree_attn_short(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
                                   const AcceptParams *ap, const CompactParams *cp);
 

@@ -3,6 +3,8 @@
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
+#include <time.h>
+#include <unistd.h>
 
 #include <atomic>
 #include <mutex>
@@ -16,7 +18,8 @@ namespace reader {
 static char g_error_detail[256] = "";
 
 // Planner overrides set through reader_tuning_override (tests, experiments); -1 = the planner decides.
-static std::atomic<int32_t> g_tuning[READER_TUNE_COUNT_] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
+static std::atomic<int32_t> g_tuning[READER_TUNE_COUNT_] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
+static_assert(READER_TUNE_COUNT_ == 8, "every override starts at -1");
 #ifdef READER_WG_STAMPS
 static std::atomic<long long *> g_wg_stamps{nullptr};
 #endif
@@ -191,7 +194,17 @@ static int attn_pair_cost(const reader_dims &d, int rows_per_wg) {
 //     0.81 (0.67), and 1.00 (0.91), 1.01 (0.90), 1.04 (0.93), 1.12 (1.07) and 0.78 (0.66).
 struct ShortPlan {
     int rows, chunks, splits;
+    bool join;                 // all shares of a pair fit one XCD, side by side with all others and the fused step's keepers
 };
+// Workgroups of the short kernel that an XCD runs at once.
+static int short_wgs_per_xcd(int D) {
+#ifdef READER_WG_STAMPS
+    (void)D;
+    return kNumCU / kNumXCD;                             // (the time stamps take registers)
+#else
+    return (D == 64 ? 2 : 1) * kNumCU / kNumXCD;
+#endif
+}
 static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan &s) {
     const int forced = tuning(READER_TUNE_ATTN_SHORT);
     if (forced == 0 || d.variant == 1) return false;
@@ -218,10 +231,18 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
         if ((tiles - 1) * plan_ranges(d, max_seq_len, rows) < (long long)d.B * d.Hkv * (tiles + attn_pair_cost(d, rows))) n = 1;
     }
     if (forced >= 1) n = forced;
-    s.splits = (int)n;
     const long long per = (tiles + n - 1) / n, rounds = n == 1 ? (units + fill - 1) / fill : 1;
-    if (per > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
-    if (n > 1024 || n * tiles >= 1 << 22) return false;   // (its arithmetic on shares is exact below that)
+    // The fused step merges, accepts and appends inside the launch if all shares of a pair fit one XCD, with room for a
+    // workgroup more per sequence.  (Both entry points take the same number of shares: the same bits.)  A share or two fewer are
+    // well worth the launch that is saved, as long as no share gets more than two tiles longer.
+    const long long per_xcd = (units + kNumXCD - 1) / kNumXCD;
+    const long long most_here = (short_wgs_per_xcd(d.D) - (d.B + kNumXCD - 1) / kNumXCD) / (per_xcd > 0 ? per_xcd : 1);
+    const long long fewer = n < most_here ? n : most_here;
+    s.join = fewer >= (n > 1 ? 2 : 1) && (forced < 1 || fewer == n) && (tiles + fewer - 1) / fewer <= per + 2;
+    if (s.join) n = fewer;
+    s.splits = (int)n;                                 // (the lines below are about the number of shares that fill the chip)
+    if ((tiles + n - 1) / n > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
+    if (n > 1024 || n * (tiles + 1) >= 1 << 22) return false;   // (its arithmetic on shares is exact below that)
     if (forced >= 1) return true;
     if (n > 1 && d.B > 1) return per <= (d.D == 64 ? 20 : 14) - (n == 2 ? 4 : 0);
     return (n == 1 && tiles <= 16) || per * rounds <= (d.D == 64 ? 24 : 20);
@@ -397,7 +418,7 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.pair_info = workspace ? (int32_t *)((char *)workspace + kNumCU * 4 + kMaxAttnWorkgroups * 4) : nullptr;
     p.workspace = workspace ? (float *)((char *)workspace + attn_header_bytes(dims->B, dims->Hkv)) : nullptr;
     p.B = dims->B; p.T = dims->T; p.Hq = dims->Hq; p.Hkv = dims->Hkv; p.D = dims->D;
-    p.G = dims->Hq / dims->Hkv; p.M = p.T * p.G;
+    p.G = dims->Hq / dims->Hkv; p.M = p.T * p.G; p.g_rcp = 1.0f / (float)p.G;
     p.max_pages = dims->max_pages_per_seq; p.max_seq_len = max_seq_len;
     p.n_tree_tiles = (dims->T + kTile - 1) / kTile;
     p.rows_per_wg = attn_rows_per_wg(*dims, max_seq_len);
@@ -424,6 +445,9 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.tree_in_cache = tree_in_cache ? 1 : 0;
     p.wide = attn_use_wide(*dims, p.rows_per_wg);
     p.redo_only = 0;
+    p.token = 0;
+    p.wait_ticks = p.units_per_xcd = p.join = 0;
+    p.units_per_xcd_rcp = p.pairs_rcp = p.hkv_rcp = 0.f;
     p.n_splits = 0;
     p.split_rcp = 0.f;
     p.keep_whole = 0;
@@ -433,11 +457,8 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
         p.n_row_chunks = sp.chunks;
         p.n_splits = sp.splits;
         p.split_rcp = 1.0f / (float)sp.splits;
+        p.join = sp.join;
         p.keep_whole = sp.splits > 1 && tuning(READER_TUNE_ATTN_SHORT) < 1;   // (forced: every pair is cut as asked for)
-        // up to eight records fit one batch of a wavefront's loads, and four wavefronts on them gain nothing for their fold.
-        // Whole steps, one wavefront against four: 5 shares 18.1 (18.5) and 18.6 (19.1) us, 6 shares 16.8 (17.1), 8 shares
-        // 15.7 (16.5), 15.4 (15.7) and 15.9 (16.1).
-        p.merge_groups = sp.splits > 8 ? 4 : 1;
     }
 #ifdef READER_WG_STAMPS
     p.stamps = g_wg_stamps.load(std::memory_order_relaxed);
@@ -445,6 +466,41 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     float scale = dims->sm_scale > 0.f ? dims->sm_scale : 1.0f / sqrtf((float)dims->D);
     p.scale_log2 = scale * 1.44269504088896340736f;
     return READER_OK;
+}
+
+// Marks of a launch inside which workgroups wait (arrivals.h): never twice the same in a process, and no two processes alike.
+static unsigned long long next_token() {
+    static std::atomic<unsigned long long> serial{[] {
+        timespec t = {};
+        (void)clock_gettime(CLOCK_REALTIME, &t);
+        unsigned long long z = (unsigned long long)t.tv_sec * 1000000000ull + (unsigned long long)t.tv_nsec + ((unsigned long long)getpid() << 40);
+        z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;         // (splitmix64's finalizer)
+        z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+        return (z ^ (z >> 31)) & ~63ull;
+    }()};
+    unsigned long long token;
+    do token = serial.fetch_add(64, std::memory_order_relaxed);
+    while (token == 0);
+    return token;
+}
+
+// Short problems: does the launch merge its records, accept and append by itself, its workgroups waiting for one another?
+// Not while the stream is being captured, whose launches would carry the same token at every replay.
+static void attn_join(AttnParams &p, hipStream_t stream) {
+    const int forced = tuning(READER_TUNE_JOIN);
+    if (forced == 0) return;
+    if (!p.join) return;
+    if (stream) {                                        // (the null stream cannot be captured)
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return;
+    }
+    p.token = next_token();
+    p.wait_ticks = forced > 0 ? forced - 1 : 3000;       // 30 us
+    const int pairs = p.B * p.Hkv;
+    p.units_per_xcd = (pairs * p.n_row_chunks + kNumXCD - 1) / kNumXCD;
+    p.units_per_xcd_rcp = 1.0f / (float)p.units_per_xcd;
+    p.pairs_rcp = 1.0f / (float)pairs;
+    p.hkv_rcp = 1.0f / (float)p.Hkv;
 }
 
 static void accept_fill(const reader_dims *dims, const int32_t *draft_tokens, const int32_t *target_tokens,
@@ -555,9 +611,10 @@ extern "C" int reader_verify_step(const reader_dims *dims, const void *q, const 
     compact_fill(dims, k_tree, v_tree, path, accept_len, k_cache, v_cache, page_table, seq_lens, status, cp);
     hipEvent_t ev_a, ev_b;
     profile_next(&ev_a, &ev_b);
+    attn_join(p, (hipStream_t)stream);
     forget_stale_error();
     if (launch_tree_attn_mfma(p, (hipStream_t)stream, ev_a, ev_b, &ap, &cp) != hipSuccess) return READER_EHIP;
-    if (p.tree_in_cache) {
+    if (p.tree_in_cache && !p.token) {
         // the tree rows are in the cache already: the accepted ones move in place (this layer's cache)
         CompactLayersParams lp;
         compact_layers_fill(dims, 1, path, accept_len, k_cache, v_cache, page_table, seq_lens, status, lp);

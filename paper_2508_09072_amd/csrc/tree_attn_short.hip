@@ -10,7 +10,8 @@
 //     are cut: a pair that the ring kernels could leave whole stays whole);
 //   - one trip to memory brings the length, the page ids of the sequence (into registers of the wavefronts that
 //     copy, asked for before the length is known), the parent pointers and the query rows; a second one the keys;
-//   - no list and no barrier in front of the main loop.
+//   - no list and no barrier in front of the main loop;
+//   - the fused step is this one launch where all its workgroups fit the chip (see kJoin below).
 // The main loop is that of the 128-row ring kernel: wavefronts 0..3 compute 32 query rows each, 4..7 copy 64-key
 // tiles HBM -> LDS into a ring of four buffers, one barrier per tile.
 //
@@ -26,6 +27,7 @@
 #include <mutex>
 
 #include "accept_compact.h"
+#include "arrivals.h"
 #include "internal.h"
 #include "tree_attn_common.h"
 
@@ -35,15 +37,18 @@ namespace {
 
 constexpr int kShortRows = 128;
 constexpr int kShortStages = 4;
+// what the tree tiles of a cut pair cost beyond themselves, in tiles (16-layer decoding step of three users 276 -> 273 us; at head
+// dimension 64, where a tile takes half the time, it costs the step on 512 tokens 0.1 us)
+template <int D> constexpr int kTreeCost = D == 128 ? 1 : 0;
 constexpr int kPageRegs = 4;              // page ids a copying wavefront holds: one per lane and register, i.e. 256 tiles
 
 // Profiling build (-DREADER_WG_STAMPS): thread `who` of the workgroup notes the time at point k
 #ifdef READER_WG_STAMPS
 #define READER_STAMP(k, who)                                                                              \
     do {                                                                                                  \
-        const unsigned wg = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;               \
-        if (p.stamps && threadIdx.x == (who) && wg < kStampedWgs)                                         \
-            p.stamps[(size_t)wg * kWgStamps + (k)] = (long long)__builtin_amdgcn_s_memrealtime();         \
+        const unsigned at_ = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;              \
+        if (p.stamps && threadIdx.x == (who) && at_ < kStampedWgs)                                        \
+            p.stamps[(size_t)at_ * kWgStamps + (k)] = (long long)__builtin_amdgcn_s_memrealtime();         \
     } while (0)
 #else
 #define READER_STAMP(k, who) do { } while (0)
@@ -60,16 +65,242 @@ constexpr int kWavesPerSimd64 = 2;        // (the time stamps take registers)
 constexpr int kWavesPerSimd64 = 4;
 #endif
 
-// kStep: the fused step where no pair is cut.  Acceptance reads tokens only and writes nothing that an attention launch
-// reads, so the first copying wavefront of a sequence's first workgroup chooses the path while the first tiles are on their
-// way and reports it when it has no more tiles to ask for.  The accepted rows wait for the next launch: a slot behind one
-// sequence's end may lie inside the prefix of another one that this launch still reads (forks of unequal length that share a
-// partly filled page), and so do the lengths, which every workgroup reads.  Whole steps, against acceptance in the second
-// launch too: five sequences of 100 tokens, 32 nodes, 15.8 -> 14.6 us; 44 of 237, 24 nodes, 28.3 -> 27.3, at head dimension
-// 64 14.9 -> 14.3; 64 of 300 to 500, 20 nodes, 40.7 -> 40.3.  (Cut pairs need a second launch for their merge anyway, which
-// accepts as well.)
-template <int D, bool kStep>
-__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const AcceptParams &ap) {
+// Merge of the n_splits records of every query row.  A record is laid out [chunk of 8 values][row]; a wavefront takes four rows
+// of four chunks (64 contiguous bytes per chunk of a record, 64 of an output row), and its four groups of 16 lanes every fourth
+// record each, four or eight of them asked for together: up to 32 records are one trip to memory.  Weights against the largest of the
+// lane's references, then against that of all four groups: two swaps and a maximum, two swaps and additions.
+//
+// What bounds it: alone, a launch; inside the attention launch, one wavefront's instructions, each waiting for the one before.
+// Before, a thread per row and chunk folded one record after the other into its state (two exponentials and 36 instructions
+// per record, four wavefronts' states through LDS): inside the launch, 24 pairs of 100 rows in ten shares, 3.5 us where this takes
+// 2.2; as a launch of its own, 16-layer decoding step of three users 265 -> 255 us.
+//
+// kAgent: the records are read past the caches of this XCD.
+template <int D, bool kAgent>
+__device__ __forceinline__ void merge_rows(const AttnParams &p, int b, int hkv, int unit) {
+    constexpr int kQuads = D / 32;                           // sets of four chunks in a row
+    constexpr size_t kRec = attn_slot_floats(D, kShortRows);   // (64 records stay below 2^32 bytes)
+    const int lane = threadIdx.x & 63, g = lane >> 4, n = p.n_splits;
+    // (four wavefronts side by side: eight rows of eight chunks, so that the halves of a line of 128 bytes are fetched together)
+    const int in8 = unit % (2 * kQuads), quad = (in8 >> 2) * 2 + (in8 & 1), block = unit / (2 * kQuads) * 2 + ((in8 >> 1) & 1);
+    const int chunk = block / (kShortRows / 4), r = block % (kShortRows / 4) * 4 + (lane & 3);
+    const int c = quad * 4 + ((lane >> 2) & 3), m_row = chunk * kShortRows + r;
+    if (block * 4 >= p.M) return;                            // (a wavefront too many of the grid)
+    // (rows past the last one of a block are in the records too, with whatever bytes)
+    const char *rec = reinterpret_cast<const char *>(p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + chunk) * n * kRec);
+    const unsigned row_at = (c * kShortRows + r) * 16, m_at = (kShortRows * (D / 2) + r) * 4, l_at = m_at + kShortRows * 4;
+    float m = -INFINITY, l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto take = [&](auto batch_c) __attribute__((always_inline)) {
+        constexpr int kBatch = decltype(batch_c)::value;         // records a lane asks for together
+#pragma unroll 1
+        for (int j0 = g; j0 - g < n; j0 += 4 * kBatch) {
+            float ms[kBatch], ls[kBatch];
+            uint4 v[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                const unsigned at = (unsigned)min(j0 + 4 * i, n - 1) * (unsigned)(kRec * sizeof(float));   // (a record read twice is only a load)
+                const uint4 *row = reinterpret_cast<const uint4 *>(rec + (at + row_at));
+                const float *m_rec = reinterpret_cast<const float *>(rec + (at + m_at)), *l_rec = reinterpret_cast<const float *>(rec + (at + l_at));
+                v[i] = kAgent ? agent_load16(row) : *row;
+                ms[i] = kAgent ? agent_load(m_rec) : *m_rec;
+                ls[i] = kAgent ? agent_load(l_rec) : *l_rec;
+            }
+            float m_new = m;
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                if (j0 + 4 * i >= n) ms[i] = -INFINITY;
+                m_new = fmaxf(m_new, ms[i]);
+            }
+            const float ref = m_new == -INFINITY ? 0.f : m_new, old = __builtin_amdgcn_exp2f(m - ref);
+            l *= old;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] *= old;
+            m = m_new;
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                // (a share that saw no key of this row wrote no values: whatever is there is dropped, not weighted)
+                const bool none = ms[i] == -INFINITY;
+                const float w = none ? 0.f : ls[i] * __builtin_amdgcn_exp2f(ms[i] - ref);
+                const uint32_t u[4] = {none ? 0u : v[i].x, none ? 0u : v[i].y, none ? 0u : v[i].z, none ? 0u : v[i].w};
+                l += w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[2 * e] = __builtin_fmaf(w, __uint_as_float(u[e] << 16), acc[2 * e]);
+                    acc[2 * e + 1] = __builtin_fmaf(w, __uint_as_float(u[e] & 0xffff0000u), acc[2 * e + 1]);
+                }
+            }
+        }
+    };
+    if (n > 16) take(std::integral_constant<int, 8>{});
+    else take(std::integral_constant<int, 4>{});
+    // over the four groups of lanes
+    float m_all = m;
+    {
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
+        m_all = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        const auto b2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
+        m_all = fmaxf(__uint_as_float(b2[0]), __uint_as_float(b2[1]));
+    }
+    const float mine = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_all);
+    auto total = [&](float x) {
+        x *= mine;
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+        const auto b2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return __uint_as_float(b2[0]) + __uint_as_float(b2[1]);
+    };
+    l = total(l);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = total(acc[e]);
+    if (m_row >= p.M || g != 0) return;
+    const float inv = 1.f / l;                               // (> 0: every row sees its own tree node)
+    // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
+    const int node = (int)(((float)m_row + 0.5f) * p.g_rcp), group = m_row - node * p.G;
+    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) =
+        make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
+                   pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
+    if (p.lse && c == 0) p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_all + __builtin_amdgcn_logf(l)) * kLn2;
+}
+
+// Inside the attention launch: the rows that fall to share s of the pair's chunk, by the eight wavefronts of a workgroup.
+// Records that were all written on this XCD are in its L2 (and in no first-level cache: nobody has read them in this launch before
+// all of them were there, and no line of 128 bytes holds two pairs' records); others are read past it (kAgent).
+template <int D, bool kAgent>
+__device__ __forceinline__ void merge_share(const AttnParams &p, int b, int hkv, int chunk, int s) {
+    constexpr int kQuads = D / 32;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first = chunk * (kShortRows / 4) * kQuads, n_units = (min(kShortRows, p.M - chunk * kShortRows) + 7) / 8 * 2 * kQuads;
+#pragma unroll 1
+    for (int u = s * 8 + wave; u < n_units; u += p.n_splits * 8) merge_rows<D, kAgent>(p, b, hkv, first + u);
+}
+
+// The argument of the fused step's kernels, and a part of it read where it is used: read at the kernel's entry, as the compiler
+// would, what is only needed behind the main loop sits in scalar registers all the way and pushes others out.
+struct StepParams {
+    AttnParams attn;
+    AcceptParams accept;
+    CompactParams compact;
+};
+template <typename T, size_t kOffset>
+__device__ __forceinline__ T late_argument() {
+    typedef const __attribute__((address_space(4))) char arg_char;
+    arg_char *at = (arg_char *)__builtin_amdgcn_kernarg_segment_ptr() + kOffset;
+    asm volatile("" : "+s"(at));
+    T t;
+    __builtin_memcpy(&t, (const char *)at, sizeof(T));
+    return t;
+}
+
+// This launch's marks in the workspace header: of every workgroup that works on a share whether its part of the records is
+// written, and whether it reads nothing of the cache and the lengths any more; of those that keep a sequence's cache whether
+// they have left, and whether any of them has.
+struct Marks {
+    mark_t *written, *landed, *keepers, *any_left, token;
+    int n_wg;
+    __device__ __forceinline__ explicit Marks(const AttnParams &p) {
+        written = reinterpret_cast<mark_t *>(p.redo);
+        landed = written + kMaxMarks;
+        keepers = reinterpret_cast<mark_t *>(p.pair_info);
+        any_left = reinterpret_cast<mark_t *>(p.range_tiles);
+        token = p.token;
+        n_wg = p.B * p.Hkv * p.n_row_chunks * p.n_splits;
+    }
+};
+
+// Compaction of sequence b by NT threads (`t` of them this one) that share no barrier, behind a path that is in sh.accept:
+// the rows that were asked for ahead are in `held`.
+template <int NT>
+__device__ __forceinline__ void keep_rows(const CompactParams &cp, int b, int t, const TailLane &tail, const TailShared &sh,
+                                          bool held_first, tail_held_t (&held)[kTailBatch]) {
+    if (tail.bad == 0) {
+#pragma unroll 1
+        for (int c = t; c < 2 * cp.Hkv * (cp.D / 8); c += NT) {
+            const TailColumn column = tail_column(cp, c);
+#pragma unroll 1
+            for (int j0 = 0; j0 <= sh.accept.accept_len; j0 += kTailBatch) {
+                if (!held_first || c != t || j0 != 0) tail_load(column, sh, j0, held);
+                tail_store(column, sh, j0, held);
+            }
+        }
+    }
+    if (t == 0) {
+        if (tail.bad == 0) cp.seq_lens[b] = tail.L + sh.accept.accept_len + 1;
+        else if (cp.status) atomicOr(cp.status, tail.bad);
+    }
+}
+
+// The sequences whose own workgroup has left, by one wavefront of a workgroup that has seen every other one land.
+__device__ __forceinline__ void keep_for_others(const AttnParams &p, const Marks &marks, int lane, TailShared &sh) {
+    const AcceptParams ap = late_argument<AcceptParams, offsetof(StepParams, accept)>();
+    const CompactParams cp = late_argument<CompactParams, offsetof(StepParams, compact)>();
+#pragma unroll 1
+    for (int b = 0; b < p.B; ++b) {
+        if (agent_load(marks.keepers + b) != (marks.token | kLeft) || !take_over(marks.keepers + b, marks.token, lane)) continue;
+        int bits;
+        const AcceptNodes nodes = accept_stage(ap, lane, accept_load(ap, b, lane), sh.accept);
+        (void)accept_choose(ap, lane, nodes, sh.accept, bits);          // (reported by the workgroup that left)
+        const TailLane tail = tail_check(cp, b, lane, sh);
+        tail_held_t held[kTailBatch];
+        keep_rows<64>(cp, b, lane, tail, sh, false, held);
+        wave_lds_order();                                               // (before the next one's nodes go where these were)
+    }
+}
+
+// A workgroup that keeps one sequence's cache in a fused step: it accepts while the others attend, has the accepted rows ready,
+// and when every one of the others has read its keys and the lengths it appends them (a slot behind one sequence's end may
+// lie inside the prefix of another: forks of unequal length that share a partly filled page).
+constexpr int kKeeperThreads = 256;
+__device__ __forceinline__ void keep_sequence(const AttnParams &p, int b, TailShared &sh, int &s_append) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid >= kKeeperThreads) return;
+    const Marks marks(p);
+    const CompactParams cp = late_argument<CompactParams, offsetof(StepParams, compact)>();
+    if (tid < 64) accept_path_wave(late_argument<AcceptParams, offsetof(StepParams, accept)>(), b, lane, sh.accept);
+    __syncthreads();
+    const TailLane tail = tail_check(cp, b, lane, sh);
+    tail_held_t held[kTailBatch];
+    const bool ahead = tail.bad == 0 && tid < 2 * cp.Hkv * (cp.D / 8);
+    if (ahead) tail_load(tail_column(cp, tid), sh, 0, held);
+    if (tid < 64) {
+        auto seen = [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); };
+        bool go = wait_until(seen, 4 * p.wait_ticks);       // (for the longest share, and it keeps nobody from running)
+        if (!go) {
+            if (lane == 0) agent_store(marks.keepers + b, marks.token | kLeft);
+            wait_vmcnt<0>();
+            if (lane == 0) agent_store(marks.any_left, marks.token);
+            wait_vmcnt<0>();
+            go = seen() && take_over(marks.keepers + b, marks.token, lane);
+        }
+        if (lane == 0) s_append = go ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_append) keep_rows<kKeeperThreads>(cp, b, tid, tail, sh, ahead, held);
+}
+
+// What a workgroup whose launch waits inside keeps in LDS for its wavefronts.
+struct JoinShared {
+    mark_t left;        // shares of the pair whose workgroups have left, one bit each
+    int complete;       // all shares have written their records
+    int local;          // ... on this workgroup's XCD
+    int append;         // (a keeper's) the rows may be appended
+};
+
+// kStep, kJoin: the fused step in one launch.  Workgroups that keep a sequence's cache each (keep_sequence) accept meanwhile, and
+// append when everybody's keys have landed; the shares of a cut pair wait for one another and merge its rows together, on one
+// XCD.  A second launch costs 4 to 5 us, of which 2.2 are the launch.  What takes its place: 0.3 us until a share's records are
+// written through, 0.7 until their marks are seen, 2 for the merge; and an append that ends with the last share's rows.
+// Whole steps: 512 tokens 10.0 -> 8.2 us, one prompt of 4 K tokens 17.7 -> 16.3, five sequences of 100 tokens, whole pairs,
+// 12.8 -> 8.9; with the tree in the cache (three launches before) 19.7 -> 12.5.  Acceptance by the first copying wavefront of an
+// attention workgroup instead made that workgroup's first keys 0.9 us late and its append 1.7; merging inside the launches
+// of reader_tree_attn as well gains nothing (16.1 -> 15.8 us at most, 7.4 -> 8.4 on 512 tokens).
+//
+// kStep alone: where the workgroups of a step do not fit the chip at once, or the stream is being captured, and no pair is cut.
+// Acceptance reads tokens only and writes nothing that an attention launch reads, so the first copying wavefront of a sequence's
+// first workgroup chooses the path while the first tiles are on their way and reports it when it has no more tiles to ask for;
+// the accepted rows wait for the next launch, as everybody reads the lengths (64 sequences of 300 to 500 tokens, 20 nodes, 40.7
+// us with acceptance in the second launch, 40.3).  Where pairs are cut the second launch merges, accepts and appends.
+template <int D, bool kStep, bool kJoin>
+__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
     constexpr bool kDeep = D == 128;
     constexpr int CW = 4, kS = kShortStages;
     using G = Geometry<D, CW>;
@@ -78,15 +309,37 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
     char *ring = smem;                                                               // [kS][kStageBytes]
     int *s_par = reinterpret_cast<int *>(smem + kS * G::kStageBytes);                // [4][READER_MAX_T]: one copy per computing wavefront
     int *s_hole = s_par + 4 * READER_MAX_T;                                          // [kS][4]: quarter of the tile behind a bad page id
-    AcceptShared *s_accept = reinterpret_cast<AcceptShared *>(s_hole + 4 * kS);      // (the fused step only)
+    JoinShared *s_join = reinterpret_cast<JoinShared *>(s_hole + 4 * kS);            // (where the launch waits inside)
+    TailShared *s_tail = reinterpret_cast<TailShared *>(s_join + (kJoin ? 1 : 0));   // (the fused step; not all of it where the launch does not wait)
+    AcceptShared *s_accept = &s_tail->accept;
     const unsigned ring_lds = (unsigned)(size_t)(lds_char *)ring;
 
     READER_STAMP(kStampEntry, 0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int split = blockIdx.x, hkv = blockIdx.y;
-    const int chunk = p.n_row_chunks == 1 ? 0 : blockIdx.z / p.B, b = blockIdx.z - chunk * p.B;
+    int split, hkv, chunk, b, wg = 0;
+    if constexpr (kJoin) {
+        // All shares of a pair's chunk get ids that are equal modulo 8: one XCD, whose L2 then holds the records to be merged.
+        const int k = blockIdx.x >> 3, pairs = p.B * p.Hkv, units = pairs * p.n_row_chunks;
+        if (k >= p.units_per_xcd * p.n_splits) {
+            keep_sequence(p, blockIdx.x - kNumXCD * p.units_per_xcd * p.n_splits, *s_tail, s_join->append);
+            return;
+        }
+        // (quotients of small numbers by way of floats: exact)
+        split = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * p.units_per_xcd_rcp));
+        const int unit = (blockIdx.x & 7) + 8 * (k - split * p.units_per_xcd);
+        if (unit >= units) return;
+        chunk = p.n_row_chunks == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)unit + 0.5f) * p.pairs_rcp));
+        const int pair = unit - chunk * pairs;
+        b = p.B == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)pair + 0.5f) * p.hkv_rcp));
+        hkv = pair - b * p.Hkv;
+        wg = unit * p.n_splits + split;
+    } else {
+        split = blockIdx.x, hkv = blockIdx.y;
+        chunk = p.n_row_chunks == 1 ? 0 : blockIdx.z / p.B, b = blockIdx.z - chunk * p.B;
+    }
     const int32_t *table = p.page_table + (size_t)b * p.max_pages;
+    bool whole = p.n_splits == 1;      // the pair's tiles are all this workgroup's (or all another one's): no record
     // this workgroup's tiles [lo, hi) of the pair (prefix tiles, then tree tiles), once the length is there
     int L, n_pre, lo, hi;
     auto share = [&]() {
@@ -103,15 +356,19 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             if ((n_all - 1) * p.n_ranges < all) {
                 lo = split == 0 ? 0 : n_all;
                 hi = n_all;
+                whole = kJoin;
                 return;
             }
         }
-        lo = (int)(((float)(split * n_all) + 0.5f) * p.split_rcp);         // (exact: the host keeps the products below 2^22)
-        hi = (int)(((float)((split + 1) * n_all) + 0.5f) * p.split_rcp);
-        lo = __builtin_amdgcn_readfirstlane(lo);
-        hi = __builtin_amdgcn_readfirstlane(hi);
+        // (the last share, which makes the tree's masks before its first tile, gets a tile less to do)
+        const int cost = n_all + kTreeCost<D>;
+        lo = (int)(((float)(split * cost) + 0.5f) * p.split_rcp);          // (exact: the host keeps the products below 2^22)
+        hi = (int)(((float)((split + 1) * cost) + 0.5f) * p.split_rcp);
+        lo = __builtin_amdgcn_readfirstlane(min(lo, n_all));
+        hi = __builtin_amdgcn_readfirstlane(min(hi, n_all));
     };
     int bad = 0;
+    bool some_left = false;            // a keeper has left before this workgroup's keys had landed
 
     if (wave >= 4) {
         // ---------------- wavefronts that only move data ----------------
@@ -128,9 +385,9 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
         };
         const bool early = n_table <= kPageRegs * 64 * 4;   // all the sequence can have: asked for before its length is known
         if (early) fetch_pages();
-        const bool side = kStep && cw == 0 && chunk == 0 && hkv == 0;
+        const bool side = kStep && !kJoin && cw == 0 && chunk == 0 && hkv == 0;
         AcceptTokens tok;
-        if (side) tok = accept_load(ap, b, lane);
+        if (side) tok = accept_load(late_argument<AcceptParams, offsetof(StepParams, accept)>(), b, lane);
         share();
         if (!early) {
             page_base = lo;
@@ -149,7 +406,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
 #pragma unroll
         for (int i = 0; i < kPageRegs; ++i) asm volatile("" : "+v"(page[i]));   // (waited for in front of the copies)
         AcceptNodes nodes;
-        if (side) nodes = accept_stage(ap, lane, tok, *s_accept);    // (here with the page ids: a wait behind the copies would be for those too)
+        if (side) nodes = accept_stage(late_argument<AcceptParams, offsetof(StepParams, accept)>(), lane, tok, *s_accept);    // (here with the page ids: a wait behind the copies would be for those too)
         READER_STAMP(kStampRange, 256);
         auto issue = [&](int t) {
             const unsigned at = (unsigned)(t - lo) % kS;
@@ -210,7 +467,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             if (i == 0) READER_STAMP(kStampItem0Issued, 256);
         }
         int accepted = 0, step_bits = 0;
-        if (side) accepted = accept_choose(ap, lane, nodes, *s_accept, step_bits);
+        if (side) accepted = accept_choose(late_argument<AcceptParams, offsetof(StepParams, accept)>(), lane, nodes, *s_accept, step_bits);
 #pragma unroll 1
         for (int t = lo; t < hi; ++t) {
             // this wavefront's part of tile t has landed once at most its copies of the tiles behind it are outstanding
@@ -222,19 +479,29 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             if (t + kS - 1 < hi) issue(t + kS - 1);
         }
         if (p.status && bad) atomicOr(p.status, bad);
-        if (side) accept_report(ap, b, lane, accepted, step_bits, *s_accept);
-        return;
+        if (side) accept_report(late_argument<AcceptParams, offsetof(StepParams, accept)>(), b, lane, accepted, step_bits, *s_accept);
+        if constexpr (!kJoin) {
+            return;
+        } else {
+            if (lo >= hi) __syncthreads();     // (no tile, so no barrier yet: now every wavefront has read the lengths)
+            if (cw == 0) {
+                const Marks marks(p);          // (the keys of the last tile are in LDS)
+                if (lane == 0) agent_store(marks.landed + wg, marks.token);
+                wait_vmcnt<0>();
+                some_left = agent_load(marks.any_left) == marks.token;
+            }
+        }
     }
 
     // ---------------- wavefronts that only compute ----------------
+    if (wave < 4) {
     const int n = lane & 31, h = lane >> 5;
     const int row_local = wave * 32 + n;
     const int m_row = chunk * kShortRows + row_local;                        // query row inside the pair
     const bool row_real = m_row < p.M;
     const bool wave_active = chunk * kShortRows + wave * 32 < p.M;
-    const float g_rcp = 1.0f / (float)p.G;
     // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
-    const int node = row_real ? (int)(((float)m_row + 0.5f) * g_rcp) : 0;
+    const int node = row_real ? (int)(((float)m_row + 0.5f) * p.g_rcp) : 0;
     const int group = row_real ? m_row - node * p.G : 0;
     // (the length first: the page ids, which the first keys wait for, are then in front of the query rows)
     share();
@@ -454,116 +721,124 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
     READER_STAMP(kStampLastTile, 0);
 
     // ---- a pair that was not split is normalised and written out, a share leaves a record for the merge
-    if (!wave_active) return;
-    {
+    if (wave_active) {
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
         l_run = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
-    const bool whole = gridDim.x == 1;
-    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;                       // (a row may see no key of a share)
-    const size_t slot = ((((size_t)b * p.Hkv + hkv) * p.n_row_chunks + chunk) * gridDim.x + split);
-    float *rec = p.workspace + slot * attn_slot_floats(D, kShortRows);
-    uint16_t *orow = p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D;
-    // A lane holds, per 8-wide chunk of the row, 4 values and its partner lane (lane ^ 32) the other 4: one half-wave
-    // swap per pair of chunks gives every lane whole 16-byte chunks.  Records are [D / 8 chunks][rows][8 values].
+        const float inv = l_run > 0.f ? 1.f / l_run : 0.f;                   // (a row may see no key of a share)
+        const size_t slot = ((((size_t)b * p.Hkv + hkv) * p.n_row_chunks + chunk) * p.n_splits + split);
+        float *rec = p.workspace + slot * attn_slot_floats(D, kShortRows);
+        uint16_t *orow = p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D;
+        // A lane holds, per 8-wide chunk of the row, 4 values and its partner lane (lane ^ 32) the other 4: one half-wave
+        // swap per pair of chunks gives every lane whole 16-byte chunks.  Records are [D / 8 chunks][rows][8 values].
 #pragma unroll
-    for (int db = 0; db < G::kOBlocks; ++db)
+        for (int db = 0; db < G::kOBlocks; ++db)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; i4 += 2) {
-            const uint32_t a0 = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
-            const uint32_t a1 = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
-            const uint32_t b0 = pack_bf16x2(o[db][4 * i4 + 4] * inv, o[db][4 * i4 + 5] * inv);
-            const uint32_t b1 = pack_bf16x2(o[db][4 * i4 + 6] * inv, o[db][4 * i4 + 7] * inv);
-            const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-            const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-            u32x4 w;
-            w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
-            const int c = db * 4 + i4 + h;
-            if (row_real && (whole || lo < hi)) {          // (of an empty share the merge looks at the maxima only)
-                if (whole) *reinterpret_cast<u32x4 *>(orow + c * 8) = w;
-                else __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(rec) + (size_t)c * kShortRows + row_local);
+            for (int i4 = 0; i4 < 4; i4 += 2) {
+                const uint32_t a0 = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
+                const uint32_t a1 = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
+                const uint32_t b0 = pack_bf16x2(o[db][4 * i4 + 4] * inv, o[db][4 * i4 + 5] * inv);
+                const uint32_t b1 = pack_bf16x2(o[db][4 * i4 + 6] * inv, o[db][4 * i4 + 7] * inv);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+                u32x4 w;
+                w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
+                const int c = db * 4 + i4 + h;
+                if (row_real && lo < hi) {                 // (of an empty share the merge looks at the maxima only)
+                    u32x4 *rec16 = reinterpret_cast<u32x4 *>(rec) + (size_t)c * kShortRows + row_local;
+                    if (whole) *reinterpret_cast<u32x4 *>(orow + c * 8) = w;
+                    else if (kJoin) agent_store16(rec16, w);
+                    else __builtin_nontemporal_store(w, rec16);
+                }
+            }
+        if (row_real && h == 0) {
+            float m_exp2 = m_run * c2;
+            asm volatile("" : "+v"(m_exp2));      // (rounded here in every kernel: the lse of a whole pair has the bits of one from a record)
+            if (!whole) {
+                float *m_rec = rec + kShortRows * (D / 2) + row_local, *l_rec = m_rec + kShortRows;
+                if constexpr (kJoin) {
+                    agent_store(m_rec, m_exp2);
+                    agent_store(l_rec, l_run);
+                } else {
+                    *m_rec = m_exp2;
+                    *l_rec = l_run;
+                }
+            } else if (p.lse && lo < hi) {
+                p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_exp2 + __builtin_amdgcn_logf(l_run)) * kLn2;
             }
         }
-    if (row_real && h == 0) {
-        if (!whole) {
-            rec[kShortRows * (D / 2) + row_local] = m_run * c2;
-            rec[kShortRows * (D / 2 + 1) + row_local] = l_run;
-        } else if (p.lse) {
-            p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_run * c2 + __builtin_amdgcn_logf(l_run)) * kLn2;
+        READER_STAMP(kStampExit, 0);
+    }
+    if (p.status && bad) atomicOr(p.status, bad);
+    if constexpr (kJoin) {
+        if (lo >= hi) __syncthreads();
+        wait_vmcnt<0>();                       // this wavefront's part of the record is where the others will look for it
+    }
+    }
+    if constexpr (kJoin) {
+        auto merge = [&]() __attribute__((always_inline)) {
+            __syncthreads();                   // the records are written
+            if (wave == 0) {
+                const Marks marks(p);
+                const mark_t xcc = my_xcc();
+                const mark_t *of_pair = marks.written + (wg - split);
+                mark_t seen = 0;
+                auto look = [&] {
+                    seen = agent_load(of_pair + min(lane, p.n_splits - 1));
+                    return (bool)__all((seen & ~kMarkBits) == marks.token);
+                };
+                if (lane == 0) agent_store(marks.written + wg, marks.token | xcc);
+                bool complete = wait_until(look, p.wait_ticks);
+                if (!complete) {
+                    if (lane == 0) agent_store(marks.written + wg, marks.token | xcc | kLeft);
+                    wait_vmcnt<0>();
+                    complete = look();
+                }
+                const mark_t have_left = __ballot((seen & kStateBits) == kLeft);
+                const bool here = __all((seen & (kMarkBits & ~kStateBits)) == xcc);
+                if (lane == 0) {
+                    s_join->complete = complete ? 1 : 0;
+                    s_join->local = here ? 1 : 0;
+                    s_join->left = have_left;
+                }
+            }
+            __syncthreads();
+            if (!__builtin_amdgcn_readfirstlane(s_join->complete)) return;
+            const mark_t left = s_join->left;
+            const int local = __builtin_amdgcn_readfirstlane(s_join->local);
+            // The rows of the pair's chunk are shared out among its shares' workgroups; those of the ones that have left are
+            // done by everybody who is there (twice the same bytes, if by several).
+#pragma unroll 1
+            for (int s = 0; s < p.n_splits; ++s) {
+                if (s != split && !__builtin_amdgcn_readfirstlane((int)((left >> s) & 1))) continue;
+                if (local) merge_share<D, false>(p, b, hkv, chunk, s);
+                else merge_share<D, true>(p, b, hkv, chunk, s);
+            }
+        };
+        if (!whole) merge();
+        if (some_left) {              // (one wavefront)
+            const Marks marks(p);
+            if (all_here(marks.landed, marks.n_wg, marks.token, lane)) keep_for_others(p, marks, lane, *s_tail);
         }
     }
-    READER_STAMP(kStampExit, 0);
-    if (p.status && bad) atomicOr(p.status, bad);
 }
 
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(AttnParams p) {
-    tree_attn_short_body<D, false>(p, AcceptParams());
+    tree_attn_short_body<D, false, false>(p);
 }
 template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(AttnParams p, AcceptParams ap) {
-    tree_attn_short_body<D, true>(p, ap);
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(StepParams p) {
+    tree_attn_short_body<D, true, false>(p.attn);
 }
-
-// Merge of the n_splits records of every query row.  A record is laid out [chunk of 8 values][row], so a wavefront takes 16
-// consecutive rows of four chunks: its loads fetch 256 contiguous bytes per chunk.  With more than eight shares the four
-// wavefronts of a workgroup take a quarter of the shares each and fold their states through LDS in the order of the shares.
-//
-// What bounds it: a launch, one trip to memory for the records (other compute units have just written them past the
-// caches) and the way back; loads are few and asked for together, four or eight records at a time.  As one thread per row and chunk
-// in row order, eight records at a time whether there were that many or not, it took 6.6 us where this takes 4.2 (three
-// sequences of 0.7 - 2.5 K tokens, ten shares of 24 pairs with 100 rows; four wavefronts per row from nine shares on there).
 template <int D>
-__device__ __forceinline__ void merge_short_body(const AttnParams &p, int b, int hkv, int block) {
-    constexpr int kQuads = D / 32;                           // sets of four chunks in a row
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_splits = p.n_splits;
-    const bool four = p.merge_groups == 4;
-    const int unit = four ? block : block * 4 + wave;        // 16 rows x 4 chunks
-    const int m = (unit / kQuads) * 16 + (lane & 15), c = (unit % kQuads) * 4 + (lane >> 4);
-    const bool live = m < p.M;
-    const int chunk = m / kShortRows, r = m % kShortRows;
-    constexpr size_t kRec = attn_slot_floats(D, kShortRows);
-    const float *rec = p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + (live ? chunk : 0)) * n_splits * kRec;
-    const int share = four ? (n_splits + 3) >> 2 : n_splits, first = four ? wave * share : 0, last = min(n_splits, first + share);
-    MergeState st;
-    auto take = [&](auto batch_c) __attribute__((always_inline)) {
-        constexpr int kBatch = decltype(batch_c)::value;
-        for (int s0 = first; s0 < last; s0 += kBatch) {
-            float ms[kBatch], ls[kBatch];
-            uint4 v[kBatch];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const float *part = rec + (size_t)min(s0 + j, last - 1) * kRec;
-                v[j] = reinterpret_cast<const uint4 *>(part)[c * kShortRows + r];
-                ms[j] = part[kShortRows * (D / 2) + r];
-                ls[j] = part[kShortRows * (D / 2 + 1) + r];
-            }
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                if (s0 + j >= last || ms[j] == -INFINITY) continue;      // (no key of that share for this row)
-                st.fold_record(ms[j], ls[j], v[j]);
-            }
-        }
-    };
-    // (a second round is a second trip to memory, a record read twice only a load)
-    if (share > 4) take(std::integral_constant<int, 8>{});
-    else take(std::integral_constant<int, 4>{});
-    if (four) {
-        __shared__ float s_state[3][10][64];
-        if (!st.gather(s_state, wave, lane)) return;
-    }
-    if (!live) return;
-    // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
-    const int node = (int)(((float)m + 0.5f) * (1.0f / (float)p.G)), group = m - node * p.G;
-    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = st.result();
-    if (p.lse && c == 0)
-        p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (st.m + __builtin_amdgcn_logf(st.l)) * kLn2;
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_join_kernel(StepParams p) {
+    tree_attn_short_body<D, true, true>(p.attn);
 }
 
 template <int D>
 __global__ __launch_bounds__(256) void merge_short_kernel(AttnParams p) {
-    merge_short_body<D>(p, blockIdx.z, blockIdx.y, blockIdx.x);
+    const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    merge_rows<D, false>(p, blockIdx.z, blockIdx.y, unit);
 }
 
 // Tail of the fused step where pairs were cut: one workgroup per sequence that accepts a path and appends its rows, then the
@@ -572,7 +847,7 @@ template <int D>
 __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks) {
     if ((int)blockIdx.x >= p.B) {
         const int m = blockIdx.x - p.B, pair = m / merge_blocks, seq = pair / p.Hkv;
-        merge_short_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks);
+        merge_rows<D, false>(p, seq, pair - seq * p.Hkv, (m - pair * merge_blocks) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
         return;
     }
     __shared__ AcceptShared sh;
@@ -586,47 +861,51 @@ __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, Ac
     kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
 }
 
-template <int D, bool kStep>
-hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap) {
+template <int D, bool kStep, bool kJoin>
+hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
+                       const CompactParams *cp) {
     using G = Geometry<D, 4>;
     constexpr size_t lds = (size_t)kShortStages * G::kStageBytes + (4 * READER_MAX_T + 4 * kShortStages) * sizeof(int) +
-                           (kStep ? sizeof(AcceptShared) : 0);
+                           (kJoin ? sizeof(JoinShared) : 0) + (kStep ? (kJoin ? sizeof(TailShared) : sizeof(AcceptShared)) : 0);
+    static_assert(kStep || !kJoin, "only the fused step waits inside a launch");
+    const void *kernel = kJoin ? reinterpret_cast<const void *>(&verify_short_join_kernel<D>)
+                       : kStep ? reinterpret_cast<const void *>(&verify_short_kernel<D>) : reinterpret_cast<const void *>(&tree_attn_short_kernel<D>);
     {
         static std::mutex guard;             // host threads may call in at the same time
         static bool allowed = false;
         std::lock_guard<std::mutex> lock(guard);
         if (!allowed) {
-            const void *kernel = kStep ? reinterpret_cast<const void *>(&verify_short_kernel<D>) : reinterpret_cast<const void *>(&tree_attn_short_kernel<D>);
             const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) { (void)hipGetLastError(); return note_hip_error("hipFuncSetAttribute(short attention LDS size)", e); }
             allowed = true;
         }
     }
-    const dim3 grid(p.n_splits, p.Hkv, p.B * p.n_row_chunks);
+    const dim3 grid = kJoin ? dim3(kNumXCD * p.units_per_xcd * p.n_splits + p.B) : dim3(p.n_splits, p.Hkv, p.B * p.n_row_chunks);
     const bool timed = ev_start && ev_stop;
-    if constexpr (kStep) {
-        if (timed) hipExtLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p, *ap);
-        else hipLaunchKernelGGL(verify_short_kernel<D>, grid, dim3(kThreads), lds, stream, p, *ap);
-    } else {
-        if (timed) hipExtLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, p);
-        else hipLaunchKernelGGL(tree_attn_short_kernel<D>, grid, dim3(kThreads), lds, stream, p);
-    }
-    return note_hip_error(kStep ? "launch verify_short_kernel" : "launch tree_attn_short_kernel", hipGetLastError());
+    auto go = [&](auto *fn, const char *name, auto... args) {
+        if (timed) hipExtLaunchKernelGGL(fn, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, args...);
+        else hipLaunchKernelGGL(fn, grid, dim3(kThreads), lds, stream, args...);
+        return note_hip_error(name, hipGetLastError());
+    };
+    if constexpr (kJoin) return go(verify_short_join_kernel<D>, "launch verify_short_join_kernel", StepParams{p, *ap, *cp});
+    else if constexpr (kStep) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{p, *ap, *cp});
+    else return go(tree_attn_short_kernel<D>, "launch tree_attn_short_kernel", p);
 }
 
 template <int D>
 hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
                       const CompactParams *cp) {
-    if (ap && cp && p.n_splits == 1) {
-        const hipError_t e = launch_main<D, true>(p, stream, ev_start, ev_stop, ap);
+    const bool step = ap && cp;
+    if (step && p.token) return launch_main<D, true, true>(p, stream, ev_start, ev_stop, ap, cp);
+    if (step && p.n_splits == 1) {
+        const hipError_t e = launch_main<D, true, false>(p, stream, ev_start, ev_stop, ap, cp);
         if (e != hipSuccess || !cp->k_tree) return e;      // (in-cache layout: the rows move in a launch of their own)
         return launch_kv_compact(*cp, stream);
     }
-    const hipError_t e = launch_main<D, false>(p, stream, ev_start, ev_stop, nullptr);
+    const hipError_t e = launch_main<D, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr);
     if (e != hipSuccess || p.n_splits == 1) return e;
-    const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
-    const int blocks = p.merge_groups == 4 ? units : (units + 3) / 4;
-    if (ap && cp) {
+    const int blocks = (p.M + 7) / 8 * (D / 64);           // of 8 rows x 8 chunks, four wavefronts
+    if (step) {
         hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * blocks), dim3(256), 0, stream, p, *ap, *cp, blocks);
         return note_hip_error("launch verify_tail_short_kernel", hipGetLastError());
     }
