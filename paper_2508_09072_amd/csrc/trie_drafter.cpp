@@ -3,16 +3,14 @@
 // and the depth-first extraction of a draft tree.  Plain C++ on host memory; no GPU involved.
 // It produces the token / parent arrays that the verification step takes.
 //
-// What bounds it is finding a node's child, a probe of the edge table each time: a prompt of 4096 tokens in a trie of
-// depth 8 takes 32768 of them.  Nodes are therefore plain records in one array, linked to their siblings by number, and all
-// edges share one open-addressing table of 8 bytes per slot; and the n-grams of a text are followed by where they
-// end, not by where they begin, so that the lookups of one token (one per n-gram length) do not wait for each
-// other.  Measured on one core against a hash map of edges and a vector of children per node, walked n-gram by
-// n-gram: 4096 tokens inserted in 0.4 instead of 2.1 ms (65536: 7 instead of 60), a path of 8 tokens found in 0.7
-// instead of 2.6 us, the trie given back in 1 instead of 640 us.
-// Most of these probes could be spared: of the 17 to 18 thousand nodes of such a trie 3.4 have no child and 13.3 a single
-// one, which is found through its parent.  A trial that gives edges slots only from a node's second child on built the
-// same tries and trees in 0.58 to 0.66 of the time (one request 593 -> 392 us on a slower core); not built in yet.
+// What bounds it is finding a node's child: a prompt of 4096 tokens in a trie of depth 8 takes 32768 lookups.  Nodes are
+// therefore plain records in one array, linked to their siblings by number, and the n-grams of a text are followed by where
+// they end, not by where they begin, so that the lookups of one token (one per n-gram length) do not wait for each other.
+// Of the 17 to 18 thousand nodes of such a trie 3.4 have no child and 13.3 a single one, which its parent leads to: only
+// the children of nodes with two or more are in a table (one for all, open addressing, 8 bytes per slot).  Measured on one
+// core: one request (prompt of 4096 tokens, 64 draft trees and search paths) 226 us, 351 when every edge had a slot, 2560
+// with a hash map of edges and a vector of children per node, walked n-gram by n-gram; 65536 tokens of text that repeats
+// little inserted in 7.8 ms, 40 when every edge had a slot.
 #include <algorithm>
 #include <cstdint>
 #include <cstdlib>
@@ -35,48 +33,56 @@ struct reader_trie {
     };
     int32_t max_depth;
     std::vector<Node> nodes;              // nodes[0] is the root (empty n-gram)
-    std::vector<Slot> slots;              // edges (parent, token) -> child; a power of two of them, at most three quarters in use
+    std::vector<Slot> slots;              // edges (parent, token) -> child of nodes with several; a power of two of them, at most three quarters in use
+    size_t used = 0;                      // slots in use
     int shift;                            // 64 - log2(slots)
 
     size_t slot_of(int32_t node, int32_t token) const {
         const uint64_t key = ((uint64_t)(uint32_t)node << 32) | (uint32_t)token;
         return (size_t)((key * 0x9e3779b97f4a7c15ull) >> shift);     // multiplicative hashing, the golden ratio's bits
     }
-    // Child of `node` along `token`, or 0; *at is its slot, or the free one where it belongs.
-    int32_t find(int32_t node, int32_t token, size_t *at) const {
+    int32_t child(int32_t node, int32_t token) const {
+        const int32_t newest = nodes[node].newest;
+        if (newest == 0 || nodes[newest].token == token) return newest;
+        if (nodes[newest].older == 0) return 0;
         const size_t mask = slots.size() - 1;
         size_t i = slot_of(node, token);
         while (slots[i].child != 0 && !(slots[i].token == token && nodes[slots[i].child].parent == node)) i = (i + 1) & mask;
-        *at = i;
         return slots[i].child;
     }
-    int32_t child(int32_t node, int32_t token) const {
-        size_t at;
-        return find(node, token, &at);
+    void enter(int32_t c) {
+        const size_t mask = slots.size() - 1;
+        size_t i = slot_of(nodes[c].parent, nodes[c].token);
+        while (slots[i].child != 0) i = (i + 1) & mask;
+        slots[i] = {nodes[c].token, c};
+        ++used;
     }
-    // Room for `more` further nodes.
+    // Room for `more` further nodes: the records, and a slot for each and for the only child that it may make one of two.
     void make_room(size_t more) {
         const size_t need = nodes.size() + more;
         if (need > nodes.capacity()) nodes.reserve(std::max(need, 2 * nodes.capacity()));
-        const size_t want = need + need / 3 + 1;
+        const size_t edges = std::min(used + 2 * more, need);
+        grow_table(edges + edges / 3 + 1);
+    }
+    void grow_table(size_t want) {
         if (want <= slots.size()) return;
         int log2 = 64 - shift;
         while (((size_t)1 << log2) < want) ++log2;
         std::vector<Slot> fresh((size_t)1 << log2, Slot{0, 0});
         slots.swap(fresh);
         shift = 64 - log2;
-        const size_t mask = slots.size() - 1;
-        for (size_t c = 1; c < nodes.size(); ++c) {
-            size_t i = slot_of(nodes[c].parent, nodes[c].token);
-            while (slots[i].child != 0) i = (i + 1) & mask;
-            slots[i] = {nodes[c].token, (int32_t)c};
-        }
+        used = 0;
+        for (size_t c = 1; c < nodes.size(); ++c)
+            if (nodes[nodes[nodes[c].parent].newest].older != 0) enter((int32_t)c);
     }
-    int32_t add(int32_t node, int32_t token, size_t at) {
-        const int32_t c = (int32_t)nodes.size();
-        nodes.push_back({token, 0, node, 0, nodes[node].newest});
+    int32_t add(int32_t node, int32_t token) {
+        const int32_t c = (int32_t)nodes.size(), newest = nodes[node].newest;
+        nodes.push_back({token, 0, node, 0, newest});
         nodes[node].newest = c;
-        slots[at] = {token, c};
+        if (newest != 0) {
+            if (nodes[newest].older == 0) enter(newest);
+            enter(c);
+        }
         return c;
     }
     // the most frequent continuation, the earliest of equals (which is met last)
@@ -161,16 +167,18 @@ extern "C" int reader_trie_insert(reader_trie *t, const int32_t *tokens, int64_t
         // at[d]: the node of the n-gram of d tokens that ends in front of the current token (at[0]: the root)
         const int32_t D = t->max_depth;
         std::vector<int32_t> at((size_t)std::min<int64_t>(D, n) + 1, 0);
-        // (more than half of the n-grams of a text are new: growing by doubling would move and fault in all of it again)
-        t->make_room((size_t)std::min<int64_t>(std::min<int64_t>(n, D) * (n / 8) * 5, 1 << 20));
+        // (more than half of the n-grams of a text are new: growing by doubling would move and fault in all of it again; a
+        // quarter of them need a slot)
+        const size_t fresh = (size_t)std::min<int64_t>(std::min<int64_t>(n, D) * (n / 8) * 5, 1 << 20);
+        if (t->nodes.size() + fresh > t->nodes.capacity()) t->nodes.reserve(std::max(t->nodes.size() + fresh, 2 * t->nodes.capacity()));
+        t->grow_table(t->used + fresh / 2);
         for (int64_t j = 0; j < n; ++j) {
             const int32_t token = tokens[j], longest = (int32_t)std::min<int64_t>(j, D - 1);
             if (t->nodes.size() + (size_t)longest + 1 > 0x7fffffffu) return READER_EUNSUPPORTED;
             t->make_room((size_t)longest + 1);
             for (int32_t d = longest; d >= 0; --d) {
-                size_t slot;
-                int32_t c = t->find(at[d], token, &slot);
-                if (c == 0) c = t->add(at[d], token, slot);
+                int32_t c = t->child(at[d], token);
+                if (c == 0) c = t->add(at[d], token);
                 ++t->nodes[c].count;
                 at[d + 1] = c;
             }
