@@ -297,10 +297,9 @@ int reader_kv_compact_layers(const reader_dims *dims, int32_t num_layers,
  *     reader_tree_attn -> reader_accept_path -> reader_kv_compact
  * called in that order on one stream, but in two kernel launches instead of four (three
  * where the four-wavefront kernel runs): the last launch merges the attention partials, accepts
- * a path per sequence and compacts it.  A short problem that fits the chip at once is one launch, whose
- * workgroups wait for one another (never without bound, and never for a workgroup that may not
- * run: whoever arrives last does what others have left); on a stream that is being captured it is
- * two, with the same results.  target_tokens are an input here too
+ * a path per sequence and compacts it.  A short problem is one launch, whose workgroups wait for one
+ * another (never without bound: whoever arrives last does what others have left), except on a stream
+ * that is being captured: two there, with the same results.  target_tokens are an input here too
  * (the base model's tokens come from outside this library), so the attention output is not
  * consulted by the acceptance.
  * k_cache, v_cache and seq_lens are read by the attention and then updated by the

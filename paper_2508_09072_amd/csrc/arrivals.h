@@ -21,6 +21,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "internal.h"
+
 namespace reader {
 
 // The low bits of a mark, which a token leaves free: kLeft, kTaken, and the XCD its workgroup runs on.
@@ -28,7 +30,7 @@ typedef unsigned long long mark_t;
 constexpr mark_t kLeft = 1, kTaken = 3, kStateBits = 3, kMarkBits = 63;
 constexpr int kXccShift = 2;
 constexpr mark_t kTokenStep = kMarkBits + 1;
-constexpr int kMaxMarks = 512;                   // working workgroups of a launch that waits
+constexpr int kMaxMarks = kMaxAttnWorkgroups * 4 / 8;   // the workspace header holds so many
 
 __device__ __forceinline__ mark_t agent_load(const mark_t *m) { return __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void agent_store(mark_t *m, mark_t v) { __hip_atomic_store(m, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -45,12 +47,12 @@ __device__ __forceinline__ mark_t my_xcc() {
 __device__ __forceinline__ bool all_here(const mark_t *marks, int n, mark_t token, int lane) {
     bool here = true;
 #pragma unroll 1
-    for (int base = 0; base < n; base += 256) {
-        mark_t v[4];
+    for (int base = 0; base < n; base += 512) {
+        mark_t v[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = agent_load(marks + min(base + i * 64 + lane, n - 1));   // (asked for together)
+        for (int i = 0; i < 8; ++i) v[i] = agent_load(marks + min(base + i * 64 + lane, n - 1));   // (asked for together)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) here &= (v[i] & ~kMarkBits) == token;
+        for (int i = 0; i < 8; ++i) here &= (v[i] & ~kMarkBits) == token;
     }
     return __all(here);
 }

@@ -11,7 +11,7 @@
 //   - one trip to memory brings the length, the page ids of the sequence (into registers of the wavefronts that
 //     copy, asked for before the length is known), the parent pointers and the query rows; a second one the keys;
 //   - no list and no barrier in front of the main loop;
-//   - the fused step is this one launch where all its workgroups fit the chip (see kJoin below).
+//   - the fused step is this one launch (see kJoin below).
 // The main loop is that of the 128-row ring kernel: wavefronts 0..3 compute 32 query rows each, 4..7 copy 64-key
 // tiles HBM -> LDS into a ring of four buffers, one barrier per tile.
 //
@@ -199,7 +199,7 @@ struct Marks {
     int n_wg;
     __device__ __forceinline__ explicit Marks(const AttnParams &p) {
         written = reinterpret_cast<mark_t *>(p.redo);
-        landed = written + kMaxMarks;
+        landed = written + (p.n_splits > 1 ? kMaxMarks / 2 : 0);      // (whole pairs leave no record)
         keepers = reinterpret_cast<mark_t *>(p.pair_info);
         any_left = reinterpret_cast<mark_t *>(p.range_tiles);
         token = p.token;
@@ -294,7 +294,10 @@ struct JoinShared {
 // attention workgroup instead made that workgroup's first keys 0.9 us late and its append 1.7; merging inside the launches
 // of reader_tree_attn as well gains nothing (16.1 -> 15.8 us at most, 7.4 -> 8.4 on 512 tokens).
 //
-// kStep alone: where the workgroups of a step do not fit the chip at once, or the stream is being captured, and no pair is cut.
+// Whole pairs of more sequences than run at once: the keepers, last in the grid, come to run when nobody waits for a place
+// any more (44 sequences of 237 tokens, 24 nodes, 29.8 -> 24.2 us, at head dimension 64 17.5 -> 14.0).
+//
+// kStep alone: whole pairs, on a stream that is being captured or of more workgroups than there are marks for.
 // Acceptance reads tokens only and writes nothing that an attention launch reads, so the first copying wavefront of a sequence's
 // first workgroup chooses the path while the first tiles are on their way and reports it when it has no more tiles to ask for;
 // the accepted rows wait for the next launch, as everybody reads the lengths (64 sequences of 300 to 500 tokens, 20 nodes, 40.7

@@ -47,7 +47,7 @@ NAMES = ("out", "lse", "accept_len", "path", "bonus", "seq_lens", "k_cache", "v_
     (5, 3, 1, 128, 7, [64, 1, 300, 65, 0], 1), (40, 4, 1, 64, 20, list(range(3, 203, 5)), 1),   # pairs that are not cut
     (2, 1, 16, 128, 128, [900, 333], 7), (1, 2, 1, 64, 128, [4000], 64),   # sixteen row chunks; as many shares as may be
     (1, 1, 1, 64, 1, [0], 1), (1, 1, 1, 128, 1, [0], 4),               # a root alone; more shares than tiles
-    (56, 8, 1, 64, 12, [40] * 56, 1), (28, 8, 1, 128, 12, [40] * 28, 1), (9, 3, 1, 128, 12, [240] * 9, 5),   # as many workgroups as may wait (448 and 56 keepers, 224 and 28); no multiple of the XCDs
+    (64, 8, 2, 64, 12, [40] * 64, 1), (128, 8, 1, 128, 12, [40] * 128, 1), (129, 8, 1, 64, 3, [40] * 129, 1), (9, 3, 1, 128, 12, [240] * 9, 5),   # more workgroups than run at once, as many as there are marks, and more; no multiple of the XCDs
     (4, 1, 1, 64, 60, [2400, 64, 64, 64], None), (2, 16, 1, 128, 60, [1100, 64], None),   # the planner's choice: pairs that stay whole among cut ones
 ])
 @pytest.mark.parametrize("in_cache", [False, True])
