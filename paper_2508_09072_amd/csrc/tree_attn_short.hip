@@ -75,103 +75,142 @@ constexpr int kWavesPerSimd64 = 4;
 // per record, four wavefronts' states through LDS): inside the launch, 24 pairs of 100 rows in ten shares, 3.5 us where this takes
 // 2.2; as a launch of its own, 16-layer decoding step of three users 265 -> 255 us.
 //
-// kAgent: the records are read past the caches of this XCD.
-template <int D, bool kAgent>
-__device__ __forceinline__ void merge_rows(const AttnParams &p, int b, int hkv, int unit) {
+// kAgent: the records are read past the caches of this XCD.  kUnits: sets of four rows and four chunks that the wavefront takes
+// together, `unit` and every `step`-th behind it below `end` (few records leave a lane room for several).
+template <int D, bool kAgent, int kUnits, int kBatch>
+__device__ __forceinline__ void merge_rows(const AttnParams &p, int b, int hkv, int unit, int step, int end) {
     constexpr int kQuads = D / 32;                           // sets of four chunks in a row
     constexpr size_t kRec = attn_slot_floats(D, kShortRows);   // (64 records stay below 2^32 bytes)
     const int lane = threadIdx.x & 63, g = lane >> 4, n = p.n_splits;
     // (four wavefronts side by side: eight rows of eight chunks, so that the halves of a line of 128 bytes are fetched together)
-    const int in8 = unit % (2 * kQuads), quad = (in8 >> 2) * 2 + (in8 & 1), block = unit / (2 * kQuads) * 2 + ((in8 >> 1) & 1);
-    const int chunk = block / (kShortRows / 4), r = block % (kShortRows / 4) * 4 + (lane & 3);
-    const int c = quad * 4 + ((lane >> 2) & 3), m_row = chunk * kShortRows + r;
-    if (block * 4 >= p.M) return;                            // (a wavefront too many of the grid)
-    // (rows past the last one of a block are in the records too, with whatever bytes)
-    const char *rec = reinterpret_cast<const char *>(p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + chunk) * n * kRec);
-    const unsigned row_at = (c * kShortRows + r) * 16, m_at = (kShortRows * (D / 2) + r) * 4, l_at = m_at + kShortRows * 4;
-    float m = -INFINITY, l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    auto take = [&](auto batch_c) __attribute__((always_inline)) {
-        constexpr int kBatch = decltype(batch_c)::value;         // records a lane asks for together
+    int m_row[kUnits], c[kUnits];
+    const char *rec[kUnits];
+    unsigned row_at[kUnits], m_at[kUnits];
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+        const int at = min(unit + u * step, end - 1);        // (a unit too many is the last one again, and not written)
+        const int in8 = at % (2 * kQuads), quad = (in8 >> 2) * 2 + (in8 & 1), block = at / (2 * kQuads) * 2 + ((in8 >> 1) & 1);
+        const int chunk = block / (kShortRows / 4), r = block % (kShortRows / 4) * 4 + (lane & 3);
+        c[u] = quad * 4 + ((lane >> 2) & 3);
+        m_row[u] = unit + u * step < end ? chunk * kShortRows + r : p.M;
+        // (rows past the last one of a block are in the records too, with whatever bytes)
+        rec[u] = reinterpret_cast<const char *>(p.workspace + ((size_t)(b * p.Hkv + hkv) * p.n_row_chunks + chunk) * n * kRec);
+        row_at[u] = (c[u] * kShortRows + r) * 16;
+        m_at[u] = (kShortRows * (D / 2) + r) * 4;
+    }
+    float m[kUnits], l[kUnits], acc[kUnits][8];
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+        m[u] = -INFINITY;
+        l[u] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[u][e] = 0.f;
+    }
 #pragma unroll 1
-        for (int j0 = g; j0 - g < n; j0 += 4 * kBatch) {
-            float ms[kBatch], ls[kBatch];
-            uint4 v[kBatch];
+    for (int j0 = g; j0 - g < n; j0 += 4 * kBatch) {
+        float ms[kUnits][kBatch], ls[kUnits][kBatch];
+        uint4 v[kUnits][kBatch];
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u)
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) {
                 const unsigned at = (unsigned)min(j0 + 4 * i, n - 1) * (unsigned)(kRec * sizeof(float));   // (a record read twice is only a load)
-                const uint4 *row = reinterpret_cast<const uint4 *>(rec + (at + row_at));
-                const float *m_rec = reinterpret_cast<const float *>(rec + (at + m_at)), *l_rec = reinterpret_cast<const float *>(rec + (at + l_at));
-                v[i] = kAgent ? agent_load16(row) : *row;
-                ms[i] = kAgent ? agent_load(m_rec) : *m_rec;
-                ls[i] = kAgent ? agent_load(l_rec) : *l_rec;
+                const uint4 *row = reinterpret_cast<const uint4 *>(rec[u] + (at + row_at[u]));
+                const float *m_rec = reinterpret_cast<const float *>(rec[u] + (at + m_at[u]));
+                const float *l_rec = reinterpret_cast<const float *>(rec[u] + (at + m_at[u] + kShortRows * 4));
+                v[u][i] = kAgent ? agent_load16(row) : *row;
+                ms[u][i] = kAgent ? agent_load(m_rec) : *m_rec;
+                ls[u][i] = kAgent ? agent_load(l_rec) : *l_rec;
             }
-            float m_new = m;
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            float m_new = m[u];
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) {
-                if (j0 + 4 * i >= n) ms[i] = -INFINITY;
-                m_new = fmaxf(m_new, ms[i]);
+                if (j0 + 4 * i >= n) ms[u][i] = -INFINITY;
+                m_new = fmaxf(m_new, ms[u][i]);
             }
-            const float ref = m_new == -INFINITY ? 0.f : m_new, old = __builtin_amdgcn_exp2f(m - ref);
-            l *= old;
+            const float ref = m_new == -INFINITY ? 0.f : m_new, old = __builtin_amdgcn_exp2f(m[u] - ref);
+            l[u] *= old;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] *= old;
-            m = m_new;
+            for (int e = 0; e < 8; ++e) acc[u][e] *= old;
+            m[u] = m_new;
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) {
                 // (a share that saw no key of this row wrote no values: whatever is there is dropped, not weighted)
-                const bool none = ms[i] == -INFINITY;
-                const float w = none ? 0.f : ls[i] * __builtin_amdgcn_exp2f(ms[i] - ref);
-                const uint32_t u[4] = {none ? 0u : v[i].x, none ? 0u : v[i].y, none ? 0u : v[i].z, none ? 0u : v[i].w};
-                l += w;
+                const bool none = ms[u][i] == -INFINITY;
+                const float w = none ? 0.f : ls[u][i] * __builtin_amdgcn_exp2f(ms[u][i] - ref);
+                const uint32_t x[4] = {none ? 0u : v[u][i].x, none ? 0u : v[u][i].y, none ? 0u : v[u][i].z, none ? 0u : v[u][i].w};
+                l[u] += w;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    acc[2 * e] = __builtin_fmaf(w, __uint_as_float(u[e] << 16), acc[2 * e]);
-                    acc[2 * e + 1] = __builtin_fmaf(w, __uint_as_float(u[e] & 0xffff0000u), acc[2 * e + 1]);
+                    acc[u][2 * e] = __builtin_fmaf(w, __uint_as_float(x[e] << 16), acc[u][2 * e]);
+                    acc[u][2 * e + 1] = __builtin_fmaf(w, __uint_as_float(x[e] & 0xffff0000u), acc[u][2 * e + 1]);
                 }
             }
         }
-    };
-    if (n > 16) take(std::integral_constant<int, 8>{});
-    else take(std::integral_constant<int, 4>{});
-    // over the four groups of lanes
-    float m_all = m;
-    {
-        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
-        m_all = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-        const auto b2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
-        m_all = fmaxf(__uint_as_float(b2[0]), __uint_as_float(b2[1]));
     }
-    const float mine = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_all);
-    auto total = [&](float x) {
-        x *= mine;
-        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-        const auto b2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        return __uint_as_float(b2[0]) + __uint_as_float(b2[1]);
-    };
-    l = total(l);
+    // over the four groups of lanes
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = total(acc[e]);
-    if (m_row >= p.M || g != 0) return;
-    const float inv = 1.f / l;                               // (> 0: every row sees its own tree node)
-    // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
-    const int node = (int)(((float)m_row + 0.5f) * p.g_rcp), group = m_row - node * p.G;
-    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) =
-        make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
-                   pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
-    if (p.lse && c == 0) p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_all + __builtin_amdgcn_logf(l)) * kLn2;
+    for (int u = 0; u < kUnits; ++u) {
+        float m_all = m[u];
+        {
+            const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
+            m_all = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+            const auto b2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
+            m_all = fmaxf(__uint_as_float(b2[0]), __uint_as_float(b2[1]));
+        }
+        const float mine = m[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[u] - m_all);
+        auto total = [&](float x) {
+            x *= mine;
+            const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+            x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+            const auto b2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+            return __uint_as_float(b2[0]) + __uint_as_float(b2[1]);
+        };
+        l[u] = total(l[u]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[u][e] = total(acc[u][e]);
+        if (m_row[u] < p.M && g == 0) {
+            const float inv = 1.f / l[u];                    // (> 0: every row sees its own tree node)
+            // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
+            const int node = (int)(((float)m_row[u] + 0.5f) * p.g_rcp), group = m_row[u] - node * p.G;
+            *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c[u] * 8) =
+                make_uint4(pack_bf16x2(acc[u][0] * inv, acc[u][1] * inv), pack_bf16x2(acc[u][2] * inv, acc[u][3] * inv),
+                           pack_bf16x2(acc[u][4] * inv, acc[u][5] * inv), pack_bf16x2(acc[u][6] * inv, acc[u][7] * inv));
+            if (p.lse && c[u] == 0)
+                p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_all + __builtin_amdgcn_logf(l[u])) * kLn2;
+        }
+    }
+}
+
+// As a launch of its own: a wavefront per unit, blocks of four.
+template <int D>
+__device__ __forceinline__ void merge_block(const AttnParams &p, int b, int hkv, int block) {
+    const int unit = block * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (p.n_splits > 16) merge_rows<D, false, 1, 8>(p, b, hkv, unit, 1, unit + 1);
+    else merge_rows<D, false, 1, 4>(p, b, hkv, unit, 1, unit + 1);
 }
 
 // Inside the attention launch: the rows that fall to share s of the pair's chunk, by the eight wavefronts of a workgroup.
 // Records that were all written on this XCD are in its L2 (and in no first-level cache: nobody has read them in this launch before
 // all of them were there, and no line of 128 bytes holds two pairs' records); others are read past it (kAgent).
+// With few shares a wavefront has several units to do, and takes up to four of them together: one trip to memory,
+// not one each (64 pairs' chunks of 128 rows, two shares each 21.2 -> 18.2 us, three 17.7 -> 16.8).
 template <int D, bool kAgent>
 __device__ __forceinline__ void merge_share(const AttnParams &p, int b, int hkv, int chunk, int s) {
     constexpr int kQuads = D / 32;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int first = chunk * (kShortRows / 4) * kQuads, n_units = (min(kShortRows, p.M - chunk * kShortRows) + 7) / 8 * 2 * kQuads;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = p.n_splits, step = n * 8;
+    const int first = chunk * (kShortRows / 4) * kQuads, end = first + (min(kShortRows, p.M - chunk * kShortRows) + 7) / 8 * 2 * kQuads;
+    auto all = [&](auto units_c, auto batch_c) __attribute__((always_inline)) {
+        constexpr int kUnits = decltype(units_c)::value, kBatch = decltype(batch_c)::value;
 #pragma unroll 1
-    for (int u = s * 8 + wave; u < n_units; u += p.n_splits * 8) merge_rows<D, kAgent>(p, b, hkv, first + u);
+        for (int u = first + s * 8 + wave; u < end; u += step * kUnits) merge_rows<D, kAgent, kUnits, kBatch>(p, b, hkv, u, step, end);
+    };
+    if (!kAgent && n <= 4) all(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+    else if (!kAgent && n <= 8) all(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
+    else if (n <= 16) all(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    else all(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
 }
 
 // The argument of the fused step's kernels, and a part of it read where it is used: read at the kernel's entry, as the compiler
@@ -840,8 +879,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verif
 
 template <int D>
 __global__ __launch_bounds__(256) void merge_short_kernel(AttnParams p) {
-    const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    merge_rows<D, false>(p, blockIdx.z, blockIdx.y, unit);
+    merge_block<D>(p, blockIdx.z, blockIdx.y, blockIdx.x);
 }
 
 // Tail of the fused step where pairs were cut: one workgroup per sequence that accepts a path and appends its rows, then the
@@ -850,7 +888,7 @@ template <int D>
 __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks) {
     if ((int)blockIdx.x >= p.B) {
         const int m = blockIdx.x - p.B, pair = m / merge_blocks, seq = pair / p.Hkv;
-        merge_rows<D, false>(p, seq, pair - seq * p.Hkv, (m - pair * merge_blocks) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+        merge_block<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks);
         return;
     }
     __shared__ AcceptShared sh;
