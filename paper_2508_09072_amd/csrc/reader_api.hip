@@ -234,13 +234,15 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     const long long per = (tiles + n - 1) / n, rounds = n == 1 ? (units + fill - 1) / fill : 1;
     // The fused step merges, accepts and appends inside the launch if all shares of a pair fit one XCD, with room for a
     // workgroup more per sequence; whole pairs, whose workgroups wait for nobody, as long as there are marks for them: the
-    // keepers come last in the grid and take no place from the others.  (Both entry points take the same number of shares: the same bits.)  A share or two fewer are
-    // well worth the launch that is saved, as long as no share gets more than two tiles longer.
+    // keepers come last in the grid and take no place from the others.  (Both entry points take the same number of shares: the same bits.)  Up to an eighth
+    // fewer are well worth the launch that is saved (one prompt of 4 K tokens, 30 instead of 32, 17.9 -> 16.3 us).  More are
+    // not taken: the longer a share, the less exactly bf16 holds its mean of many values (error against 64 bits of 8 x 8 pairs
+    // of seven tiles, three shares for four, 2.72e-3 -> 2.76e-3; 10 pairs of up to 49 tiles, 15 for 23, 2.73e-3 -> 2.78e-3).
     const long long per_xcd = (units + kNumXCD - 1) / kNumXCD;
     const long long most_here = (short_wgs_per_xcd(d.D) - (d.B + kNumXCD - 1) / kNumXCD) / (per_xcd > 0 ? per_xcd : 1);
     const long long fewer = n < most_here ? n : most_here;
     if (n == 1) s.join = units <= kMaxAttnWorkgroups / 2;
-    else s.join = fewer >= 2 && (forced < 1 || fewer == n) && (tiles + fewer - 1) / fewer <= per + 2;
+    else s.join = fewer >= 2 && (forced < 1 || fewer == n) && fewer * 8 >= n * 7 && (tiles + fewer - 1) / fewer <= per + 2;
     if (s.join && n > 1) n = fewer;
     s.splits = (int)n;                                 // (the lines below are about the number of shares that fill the chip)
     if ((tiles + n - 1) / n > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
