@@ -235,7 +235,7 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     // The fused step merges, accepts and appends inside the launch if all shares of a pair fit one XCD, with room for a
     // workgroup more per sequence; whole pairs, whose workgroups wait for nobody, as long as there are marks for them: the
     // keepers come last in the grid and take no place from the others.  (Both entry points take the same number of shares: the same bits.)  Up to an eighth
-    // fewer are well worth the launch that is saved (one prompt of 4 K tokens, 30 instead of 32, 17.9 -> 16.3 us).  More are
+    // fewer are well worth the launch that is saved (one prompt of 4 K tokens, 15 instead of 16, 18.2 -> 15.9 us).  More are
     // not taken: the longer a share, the less exactly bf16 holds its mean of many values (error against 64 bits of 8 x 8 pairs
     // of seven tiles, three shares for four, 2.72e-3 -> 2.76e-3; 10 pairs of up to 49 tiles, 15 for 23, 2.73e-3 -> 2.78e-3).
     const long long per_xcd = (units + kNumXCD - 1) / kNumXCD;

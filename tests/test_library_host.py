@@ -347,3 +347,15 @@ def test_layered_compaction_arguments_are_checked_on_the_host(R):
     assert f(ctypes.byref(dims), 2, one, one, None, one, one, one, None, None) == R.READER_EINVAL
     empty = R.make_dims(0, 16, 8, 2, 128, 8, 8, 40)
     assert f(ctypes.byref(empty), 2, None, None, None, None, None, None, None, None) == R.READER_OK
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,shares", [
+    (1, 64, 32, 8, 128, 4160, 15),      # 16 would fill the chip; 15 fit an XCD beside the workgroup that appends
+    (8, 32, 8, 8, 128, 444, 4),         # three would fit: a quarter fewer
+    (5, 83, 2, 2, 128, 3020, 24),       # fifteen would fit
+    (1, 16, 8, 8, 64, 568, 10),         # nothing in the way
+])
+def test_a_short_problem_gives_up_at_most_an_eighth_of_its_shares_for_one_launch(R, B, T, Hq, Hkv, D, bound, shares):
+    plan = R.reader_attn_plan(R.make_dims(B, T, Hq, Hkv, D, 300, 4 if T > 3 else 1, 5000), bound)
+    assert plan["kernel_id"] == 4
+    assert plan["key_ranges"] == B * Hkv * shares
