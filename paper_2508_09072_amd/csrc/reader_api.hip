@@ -232,21 +232,17 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     }
     if (forced >= 1) n = forced;
     const long long per = (tiles + n - 1) / n, rounds = n == 1 ? (units + fill - 1) / fill : 1;
-    // The fused step merges, accepts and appends inside the launch if all shares of a pair fit one XCD, with room for a
-    // workgroup more per sequence; whole pairs, whose workgroups wait for nobody, as long as there are marks for them: the
-    // keepers come last in the grid and take no place from the others.  (Both entry points take the same number of shares: the same bits.)  Up to an eighth
-    // fewer are well worth the launch that is saved (one prompt of 4 K tokens, 15 instead of 16, 18.2 -> 15.9 us).  More are
-    // not taken: the longer a share, the less exactly bf16 holds its mean of many values (error against 64 bits of 8 x 8 pairs
-    // of seven tiles, three shares for four, 2.72e-3 -> 2.76e-3; 10 pairs of up to 49 tiles, 15 for 23, 2.73e-3 -> 2.78e-3).
-    const long long per_xcd = (units + kNumXCD - 1) / kNumXCD;
-    const long long most_here = (short_wgs_per_xcd(d.D) - (d.B + kNumXCD - 1) / kNumXCD) / (per_xcd > 0 ? per_xcd : 1);
-    const long long fewer = n < most_here ? n : most_here;
-    if (n == 1) s.join = units <= kMaxAttnWorkgroups / 2;
-    else s.join = fewer >= 2 && (forced < 1 || fewer == n) && fewer * 8 >= n * 7 && (tiles + fewer - 1) / fewer <= per + 2;
-    if (s.join && n > 1) n = fewer;
-    s.splits = (int)n;                                 // (the lines below are about the number of shares that fill the chip)
-    if ((tiles + n - 1) / n > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
-    if (n > 1024 || n * (tiles + 1) >= 1 << 22) return false;   // (its arithmetic on shares is exact below that)
+    // The fused step merges, accepts and appends inside the launch if all shares of an XCD's pairs run there side by side with
+    // its part of the keepers, a workgroup per sequence; whole pairs, whose workgroups wait for nobody, as long as there are
+    // marks for them: the keepers come last in the grid and take no place from the others.  Keepers that have to wait for a
+    // place beside cut pairs make it slower than two launches (one prompt of 4 K tokens, 16 shares of 16 pairs' chunks, 18.2 us,
+    // with the keeper behind them 19.7).  Fewer shares are not taken to make room: the longer a share, the less exactly bf16
+    // holds its mean of many values (15 instead of 16 there 15.9 us, but up to 1.011 times the error against 64 bits).
+    const long long per_xcd = (units + kNumXCD - 1) / kNumXCD, keepers = (d.B + kNumXCD - 1) / kNumXCD;
+    s.join = n == 1 ? units <= kMaxAttnWorkgroups / 2 : n * per_xcd + keepers <= short_wgs_per_xcd(d.D);
+    s.splits = (int)n;
+    if (per > 240) return false;                       // (the kernel keeps the page ids of a share at hand)
+    if (n > 1024 || n * tiles >= 1 << 22) return false;   // (its arithmetic on shares is exact below that)
     if (forced >= 1) return true;
     if (n > 1 && d.B > 1) return per <= (d.D == 64 ? 20 : 14) - (n == 2 ? 4 : 0);
     return (n == 1 && tiles <= 16) || per * rounds <= (d.D == 64 ? 24 : 20);

@@ -37,9 +37,6 @@ namespace {
 
 constexpr int kShortRows = 128;
 constexpr int kShortStages = 4;
-// what the tree tiles of a cut pair cost beyond themselves, in tiles (16-layer decoding step of three users 276 -> 273 us; at head
-// dimension 64, where a tile takes half the time, it costs the step on 512 tokens 0.1 us)
-template <int D> constexpr int kTreeCost = D == 128 ? 1 : 0;
 constexpr int kPageRegs = 4;              // page ids a copying wavefront holds: one per lane and register, i.e. 256 tiles
 
 // Profiling build (-DREADER_WG_STAMPS): thread `who` of the workgroup notes the time at point k
@@ -402,12 +399,10 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
                 return;
             }
         }
-        // (the last share, which makes the tree's masks before its first tile, gets a tile less to do)
-        const int cost = n_all + kTreeCost<D>;
-        lo = (int)(((float)(split * cost) + 0.5f) * p.split_rcp);          // (exact: the host keeps the products below 2^22)
-        hi = (int)(((float)((split + 1) * cost) + 0.5f) * p.split_rcp);
-        lo = __builtin_amdgcn_readfirstlane(min(lo, n_all));
-        hi = __builtin_amdgcn_readfirstlane(min(hi, n_all));
+        lo = (int)(((float)(split * n_all) + 0.5f) * p.split_rcp);         // (exact: the host keeps the products below 2^22)
+        hi = (int)(((float)((split + 1) * n_all) + 0.5f) * p.split_rcp);
+        lo = __builtin_amdgcn_readfirstlane(lo);
+        hi = __builtin_amdgcn_readfirstlane(hi);
     };
     int bad = 0;
     bool some_left = false;            // a keeper has left before this workgroup's keys had landed

@@ -1065,3 +1065,36 @@ def test_profiling_build_notes_no_more_workgroups_than_its_buffer_holds(R):
     assert int(buf[n:].count_nonzero()) == 0
     got = bf16_to_np(dw.out)
     assert_close(got, run_attn(R, w)[0], what="profiling build against the normal one")
+
+
+@pytest.mark.parametrize("D,splits,L", [(64, 5, 700), (128, 5, 700), (128, 15, 4096), (64, 7, 321)])
+@pytest.mark.parametrize("entry", ["attn", "step"])
+def test_the_shares_of_a_cut_pair_are_even(R, D, splits, L, entry, tune):
+    # with keys of zeros every weight is 1, and the sum in a row's record is the number of keys that the share has for it:
+    # tiles [s n / shares, (s + 1) n / shares) of 64 keys, whichever entry point asks
+    import torch
+    w = W.make_custom("even", B=1, Hq=4, Hkv=2, D=D, T=20, seq_lens=[L], tree="trie", depth=6, seed=492)
+    w.k_cache[:] = 0
+    w.k_tree[:] = 0
+    tune(R.TUNE_ATTN_SHORT, splits)
+    dw = R.to_device(w)
+    args = (dw.dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents)
+    if entry == "attn":
+        R.reader_tree_attn(*args, dw.out, dw.lse, L, dw.workspace, dw.status)
+    else:
+        R.reader_verify_step(*args, dw.draft_tokens, dw.target_tokens, dw.out, dw.lse, dw.accept_len, dw.path, dw.bonus, L, dw.workspace,
+                             dw.status)
+    torch.cuda.synchronize()
+    rows, header, slot = 128, (256 * 4 + 2048 * 4 + 1 * 2 * 8 + 255) & ~255, 128 * (D // 2 + 2)
+    records = dw.workspace[header:header + 2 * splits * slot * 4].view(torch.float32).cpu().numpy().reshape(2, splits, slot)
+    sums = records[:, :, rows * (D // 2 + 1):][:, :, :40]                # (two grouped heads: row 2 n + g)
+    prefix = (L + 63) // 64
+    n = prefix + 1
+    depth = [0] * 20
+    for i in range(20):
+        depth[i] = 1 if w.parents[0, i] < 0 else depth[w.parents[0, i]] + 1
+    for s in range(splits):
+        lo, hi = s * n // splits, (s + 1) * n // splits
+        keys = min(hi * 64, L) - min(lo * 64, L) + (np.repeat(depth, 2) if lo <= prefix < hi else 0)
+        assert np.array_equal(sums[0, s], np.broadcast_to(keys, 40).astype(np.float32)), (s, lo, hi, sums[0, s], keys)
+        assert np.array_equal(sums[1, s], sums[0, s]), s

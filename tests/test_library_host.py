@@ -350,12 +350,14 @@ def test_layered_compaction_arguments_are_checked_on_the_host(R):
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,shares", [
-    (1, 64, 32, 8, 128, 4160, 15),      # 16 would fill the chip; 15 fit an XCD beside the workgroup that appends
-    (8, 32, 8, 8, 128, 444, 4),         # three would fit: a quarter fewer
-    (5, 83, 2, 2, 128, 3020, 24),       # fifteen would fit
-    (1, 16, 8, 8, 64, 568, 10),         # nothing in the way
+    (1, 64, 32, 8, 128, 4160, 16),      # sixteen pairs' chunks: all compute units
+    (8, 32, 8, 8, 128, 444, 4),
+    (5, 83, 2, 2, 128, 3020, 24),
+    (3, 25, 32, 8, 128, 2556, 10),
+    (1, 16, 8, 8, 64, 568, 10),         # sqrt(12 tiles)
 ])
-def test_a_short_problem_gives_up_at_most_an_eighth_of_its_shares_for_one_launch(R, B, T, Hq, Hkv, D, bound, shares):
+def test_a_short_problem_has_as_many_shares_as_the_rule_says(R, B, T, Hq, Hkv, D, bound, shares):
+    # none are given up for the sake of one launch: longer shares are rounded worse
     plan = R.reader_attn_plan(R.make_dims(B, T, Hq, Hkv, D, 300, 4 if T > 3 else 1, 5000), bound)
     assert plan["kernel_id"] == 4
     assert plan["key_ranges"] == B * Hkv * shares
