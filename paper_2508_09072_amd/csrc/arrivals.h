@@ -7,29 +7,23 @@
 // the launches stay apart.
 //
 // Marks, and what they vouch for, pass the XCDs' caches: stores are written through, marks are looked at past them (agent
-// scope), and a wavefront waits for its own stores (vmcnt 0) before the mark is set.  No cache is written back or invalidated
-// (an invalidation by every wavefront took 17 us).  What workgroups of one XCD have written (their marks say where they run) is in
-// the L2 that all its compute units share, and plain loads find it there, of lines that this compute unit has not read before
-// in the launch.  Plain stores would be there sooner too, but the launch would end with that much more to write back (one
+// scope), and a wavefront waits for its own stores (vmcnt 0) before the mark is set, and for the mark before it looks at another's.
+// No cache is written back or invalidated (an invalidation by every wavefront took 17 us).  What workgroups of one XCD have
+// written (their marks say where they run) is in the L2 that all its compute units share, and plain loads find it there, of
+// lines that this compute unit has not read before in the launch.  Plain stores would be there sooner too, but the launch would end with that much more to write back (one
 // prompt of 4 K tokens: 11.7 instead of 12.5 us until the last row is merged, but 19.0 instead of 17.0 for the step).
 //
-// No wait is unbounded, and none relies on all workgroups running at the same time (another stream's kernel may keep some of
-// them out for as long as it likes).  A waiter whose time is up says so in a mark and looks once more; if somebody is still
-// missing it leaves, and whoever arrives last finds that mark and does its work: the mark was set before that last look, the
-// missing arrival came after it, and looks at the marks behind its own arrival.
+// Who waits for whom, and what happens to the work of those who leave: handshake.h.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include "handshake.h"
 #include "internal.h"
+#include "tree_attn_common.h"
 
 namespace reader {
 
-// The low bits of a mark, which a token leaves free: kLeft, kTaken, and the XCD its workgroup runs on.
-typedef unsigned long long mark_t;
-constexpr mark_t kLeft = 1, kTaken = 3, kStateBits = 3, kMarkBits = 63;
-constexpr int kXccShift = 2;
-constexpr mark_t kTokenStep = kMarkBits + 1;
 constexpr int kMaxMarks = kMaxAttnWorkgroups * 4 / 8;   // the workspace header holds so many
 
 __device__ __forceinline__ mark_t agent_load(const mark_t *m) { return __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -57,26 +51,29 @@ __device__ __forceinline__ bool all_here(const mark_t *marks, int n, mark_t toke
     return __all(here);
 }
 
-// Looks until `seen()` says so, for at most `ticks` of the 100 MHz counter.
-template <typename F>
-__device__ __forceinline__ bool wait_until(F &&seen, int ticks) {
-    const unsigned long long start = __builtin_amdgcn_s_memrealtime();
-    for (;;) {
-        if (seen()) return true;
-        if (__builtin_amdgcn_s_memrealtime() - start >= (unsigned long long)ticks) return false;
+// A wavefront's way to the marks (handshake.h): one lane stores, all of them load.
+struct AgentMarks {
+    int lane;
+    __device__ __forceinline__ void set(mark_t *m, mark_t v) const {
+        if (lane == 0) agent_store(m, v);
     }
-}
-
-// The work of a workgroup that left, for exactly one of those who find its mark (itself included).
-__device__ __forceinline__ bool take_over(mark_t *mark, mark_t token, int lane) {
-    int mine = 0;
-    if (lane == 0) {
-        mark_t expected = token | kLeft;
-        mine = __hip_atomic_compare_exchange_strong(mark, &expected, token | kTaken, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT) ? 1 : 0;
+    __device__ __forceinline__ mark_t get(const mark_t *m) const { return agent_load(m); }
+    __device__ __forceinline__ void settle() const { wait_vmcnt<0>(); }
+    __device__ __forceinline__ bool swap(mark_t *m, mark_t from, mark_t to) const {
+        int done = 0;
+        if (lane == 0)
+            done = __hip_atomic_compare_exchange_strong(m, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1 : 0;
+        return __builtin_amdgcn_readfirstlane(done) != 0;
     }
-    return __builtin_amdgcn_readfirstlane(mine) != 0;
-}
+    template <typename F>
+    __device__ __forceinline__ bool wait_until(F &&seen, unsigned long long ticks) const {   // of the 100 MHz counter
+        const unsigned long long start = __builtin_amdgcn_s_memrealtime();
+        for (;;) {
+            if (seen()) return true;
+            if (__builtin_amdgcn_s_memrealtime() - start >= ticks) return false;
+        }
+    }
+};
 
 // 16 bytes written through to where every XCD sees them.  (The wait states: the registers may be written again behind it.)
 typedef unsigned int u32x4_agent __attribute__((ext_vector_type(4)));

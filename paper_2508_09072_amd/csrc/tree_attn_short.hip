@@ -265,13 +265,11 @@ __device__ __forceinline__ void keep_rows(const CompactParams &cp, int b, int t,
     }
 }
 
-// The sequences whose own workgroup has left, by one wavefront of a workgroup that has seen every other one land.
+// The sequences whose own workgroup has left, by one wavefront of a workgroup whose keys have landed, if it is the last.
 __device__ __forceinline__ void keep_for_others(const AttnParams &p, const Marks &marks, int lane, TailShared &sh) {
-    const AcceptParams ap = late_argument<AcceptParams, offsetof(StepParams, accept)>();
-    const CompactParams cp = late_argument<CompactParams, offsetof(StepParams, compact)>();
-#pragma unroll 1
-    for (int b = 0; b < p.B; ++b) {
-        if (agent_load(marks.keepers + b) != (marks.token | kLeft) || !take_over(marks.keepers + b, marks.token, lane)) continue;
+    act_for_those_who_left(AgentMarks{lane}, marks.keepers, p.B, marks.token, [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, [&](int b) __attribute__((always_inline)) {
+        const AcceptParams ap = late_argument<AcceptParams, offsetof(StepParams, accept)>();
+        const CompactParams cp = late_argument<CompactParams, offsetof(StepParams, compact)>();
         int bits;
         const AcceptNodes nodes = accept_stage(ap, lane, accept_load(ap, b, lane), sh.accept);
         (void)accept_choose(ap, lane, nodes, sh.accept, bits);          // (reported by the workgroup that left)
@@ -279,7 +277,7 @@ __device__ __forceinline__ void keep_for_others(const AttnParams &p, const Marks
         tail_held_t held[kTailBatch];
         keep_rows<64>(cp, b, lane, tail, sh, false, held);
         wave_lds_order();                                               // (before the next one's nodes go where these were)
-    }
+    });
 }
 
 // A workgroup that keeps one sequence's cache in a fused step: it accepts while the others attend, has the accepted rows ready,
@@ -298,15 +296,9 @@ __device__ __forceinline__ void keep_sequence(const AttnParams &p, int b, TailSh
     const bool ahead = tail.bad == 0 && tid < 2 * cp.Hkv * (cp.D / 8);
     if (ahead) tail_load(tail_column(cp, tid), sh, 0, held);
     if (tid < 64) {
-        auto seen = [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); };
-        bool go = wait_until(seen, 4 * p.wait_ticks);       // (for the longest share, and it keeps nobody from running)
-        if (!go) {
-            if (lane == 0) agent_store(marks.keepers + b, marks.token | kLeft);
-            wait_vmcnt<0>();
-            if (lane == 0) agent_store(marks.any_left, marks.token);
-            wait_vmcnt<0>();
-            go = seen() && take_over(marks.keepers + b, marks.token, lane);
-        }
+        // (four times as long as a share waits: for the longest share, and a keeper keeps nobody from running)
+        const bool go = keep(AgentMarks{lane}, marks.keepers + b, marks.any_left, marks.token,
+                             [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, 4ull * (unsigned)p.wait_ticks);
         if (lane == 0) s_append = go ? 1 : 0;
     }
     __syncthreads();
@@ -523,9 +515,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
             if (lo >= hi) __syncthreads();     // (no tile, so no barrier yet: now every wavefront has read the lengths)
             if (cw == 0) {
                 const Marks marks(p);          // (the keys of the last tile are in LDS)
-                if (lane == 0) agent_store(marks.landed + wg, marks.token);
-                wait_vmcnt<0>();
-                some_left = agent_load(marks.any_left) == marks.token;
+                some_left = arrive(AgentMarks{lane}, marks.landed + wg, marks.any_left, marks.token);
             }
         }
     }
@@ -823,13 +813,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
                     seen = agent_load(of_pair + min(lane, p.n_splits - 1));
                     return (bool)__all((seen & ~kMarkBits) == marks.token);
                 };
-                if (lane == 0) agent_store(marks.written + wg, marks.token | xcc);
-                bool complete = wait_until(look, p.wait_ticks);
-                if (!complete) {
-                    if (lane == 0) agent_store(marks.written + wg, marks.token | xcc | kLeft);
-                    wait_vmcnt<0>();
-                    complete = look();
-                }
+                const bool complete = meet(AgentMarks{lane}, marks.written + wg, marks.token | xcc, look, (unsigned)p.wait_ticks);
                 const mark_t have_left = __ballot((seen & kStateBits) == kLeft);
                 const bool here = __all((seen & (kMarkBits & ~kStateBits)) == xcc);
                 if (lane == 0) {
@@ -854,7 +838,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
         if (!whole) merge();
         if (some_left) {              // (one wavefront)
             const Marks marks(p);
-            if (all_here(marks.landed, marks.n_wg, marks.token, lane)) keep_for_others(p, marks, lane, *s_tail);
+            keep_for_others(p, marks, lane, *s_tail);
         }
     }
 }
