@@ -527,8 +527,9 @@ int reader_measure_peaks(const void *src, size_t src_bytes, void *scratch, size_
  *                               the planner takes the first at head dimension 128 and the second at 64
  *   READER_TUNE_ATTN_SHORT      0 = never the kernel for short problems, n >= 1 = always, with n shares per pair (n up
  *                               to 1024, and at most 240 tiles per share); any other override above keeps it out
- *   READER_TUNE_JOIN            0 = reader_verify_step of a short problem never waits inside a launch, n >= 1 = it waits for
- *                               (n - 1) / 100 us at most (1: whoever finds another workgroup missing leaves at once)
+ *   READER_TUNE_JOIN            0 = reader_verify_step of a short problem never waits inside a launch, n >= 1 = its workgroups
+ *                               wait for (n - 1) / 100 us at most (1: whoever finds another one missing leaves at once; never more
+ *                               than 10 ms), the one that appends four times as long
  * Returns READER_OK, or READER_EINVAL for an unknown `which`.
  */
 enum {

@@ -27,6 +27,11 @@ constexpr mark_t kLeft = 1, kTaken = 3, kStateBits = 3, kMarkBits = 63;
 constexpr int kXccShift = 2;
 constexpr mark_t kTokenStep = kMarkBits + 1;
 
+// How long a wait lasts at most, in ticks of the device's 100 MHz counter: 30 us, or what is asked for (0: one look), but never more
+// than 10 ms.  A keeper waits for the longest of all shares and keeps nobody from running: four times as long.
+constexpr long long kWaitTicks = 3000, kMostWaitTicks = 1000000, kKeeperPatience = 4;
+constexpr int wait_ticks(long long asked) { return (int)(asked < 0 ? kWaitTicks : asked > kMostWaitTicks ? kMostWaitTicks : asked); }
+
 // Workgroups that all have their part done and go on together: `here` is this one's arrival, everybody() looks at all marks.
 // True: all have arrived; false: this one has left, and its share of what comes next is done by one of those who come later,
 // who see its mark with kLeft.

@@ -11,7 +11,8 @@
 #include <utility>
 #include <vector>
 
-#include "internal.h"
+#include "internal.h"   // (brings the HIP runtime, whose qualifiers the next one needs)
+#include "handshake.h"
 
 namespace reader {
 
@@ -495,7 +496,7 @@ static void attn_join(AttnParams &p, hipStream_t stream) {
         if (hipStreamIsCapturing(stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return;
     }
     p.token = next_token();
-    p.wait_ticks = forced > 0 ? forced - 1 : 3000;       // 30 us
+    p.wait_ticks = wait_ticks(forced > 0 ? forced - 1LL : -1LL);
     const int pairs = p.B * p.Hkv;
     p.units_per_xcd = (pairs * p.n_row_chunks + kNumXCD - 1) / kNumXCD;
     p.units_per_xcd_rcp = 1.0f / (float)p.units_per_xcd;

@@ -296,9 +296,8 @@ __device__ __forceinline__ void keep_sequence(const AttnParams &p, int b, TailSh
     const bool ahead = tail.bad == 0 && tid < 2 * cp.Hkv * (cp.D / 8);
     if (ahead) tail_load(tail_column(cp, tid), sh, 0, held);
     if (tid < 64) {
-        // (four times as long as a share waits: for the longest share, and a keeper keeps nobody from running)
         const bool go = keep(AgentMarks{lane}, marks.keepers + b, marks.any_left, marks.token,
-                             [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, 4ull * (unsigned)p.wait_ticks);
+                             [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, (unsigned)p.wait_ticks * kKeeperPatience);
         if (lane == 0) s_append = go ? 1 : 0;
     }
     __syncthreads();

@@ -8,6 +8,7 @@
 // downwards, a wait may run out after any look.  Steps that nobody else can notice are taken at once, and of two runs that have seen the same
 // and left the same memory behind, which go on alike, the second is cut short.
 //   interleavings meet|keep <workgroups> <keepers> <looks until a wait runs out> <settle works: 0|1>  ->  "<runs> <violations>"
+//   interleavings ticks <asked>  ->  how long a share and a keeper wait at most
 #include <ucontext.h>
 
 #include <algorithm>
@@ -213,6 +214,11 @@ static std::string state(const Check &c) {
 }
 
 int main(int argc, char **argv) {
+    if (argc == 3 && std::string(argv[1]) == "ticks") {
+        const int ticks = wait_ticks(atoll(argv[2]));
+        std::printf("%d %lld\n", ticks, (unsigned)ticks * kKeeperPatience);
+        return 0;
+    }
     if (argc != 6) return 2;
     const bool meeting = std::string(argv[1]) == "meet";
     Check c;
