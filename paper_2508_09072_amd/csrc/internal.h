@@ -50,11 +50,6 @@ struct AttnParams {
     int32_t n_splits;        // short problems: shares every pair's key blocks are cut into (0: one of the ring kernels runs)
     float split_rcp;         // 1 / n_splits
     int32_t keep_whole;      // short problems: 1 if pairs that the ring kernels' even cut could leave whole are not cut here either
-    int32_t wait_ticks;      // ... how long a workgroup waits for others at most (100 MHz)
-    int32_t join;            // ... 1: the fused step's launch may wait inside, token permitting
-    int32_t units_per_xcd;   // ... and how many pairs' chunks of 128 rows every XCD takes (the last of some of them: none)
-    float units_per_xcd_rcp, pairs_rcp, hkv_rcp;   // 1 / units_per_xcd, 1 / (B Hkv), 1 / Hkv
-    unsigned long long token;   // short problems: what marks this launch's arrivals in the header (0: nothing waits inside the launch)
     int32_t redo_only;       // 1: second pass behind the wide kernel, only the workgroups flagged in `redo` do anything
     int32_t *status;
     int32_t B, T, Hq, Hkv, D, G, M;       // G = Hq/Hkv, M = T*G query rows per (sequence, kv head)
@@ -63,9 +58,19 @@ struct AttnParams {
     int32_t rows_per_wg;                   // attn_rows_per_wg(dims, max_seq_len)
     int32_t n_row_chunks;                  // ceil(M / rows_per_wg)
     int32_t n_ranges;                      // workgroups along the flattened (pair, tile) axis
-    int64_t num_pages;
     float g_rcp;                           // 1 / G
+    int64_t num_pages;
     float scale_log2;                      // sm_scale * log2(e)
+};
+
+// What a fused step of a short problem needs besides where it is one launch whose workgroups wait inside (arrivals.h).  Apart
+// from AttnParams, so that the other kernels' arguments stay where they are: each line of them is a trip to memory in front of
+// everything else a kernel does (with these values among them, ring kernels' step of five sequences 31.4 -> 31.9 us).
+struct JoinParams {
+    unsigned long long token;   // what marks this launch's arrivals in the header
+    int32_t wait_ticks;         // how long a workgroup waits for others at most (100 MHz)
+    int32_t units_per_xcd;      // how many pairs' chunks of 128 rows every XCD takes (the last of some of them: none)
+    float units_per_xcd_rcp, pairs_rcp, hkv_rcp;   // 1 / units_per_xcd, 1 / (B Hkv), 1 / Hkv
 };
 
 // Size of one partial record in 4-byte units: `rows` rows of D bf16 outputs (normalised by the
@@ -111,16 +116,17 @@ int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len);
 struct AcceptParams;
 struct CompactParams;
 // ev_start / ev_stop: optional events recorded around the main kernel only.  With `ap` and
-// `cp` a path per sequence is accepted and compacted too (the fused step).
+// `cp` a path per sequence is accepted and compacted too (the fused step); with `jp` as well, by the one launch of a
+// short problem.
 hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
-                                 const AcceptParams *ap = nullptr, const CompactParams *cp = nullptr);
+                                 const AcceptParams *ap = nullptr, const CompactParams *cp = nullptr, const JoinParams *jp = nullptr);
 hipError_t launch_tree_attn_scalar(const AttnParams &p, hipStream_t stream);
 // main kernel of the 256-row flavour with four wavefronts of 64 rows (tree_attn_wide.hip); no second launch
 hipError_t launch_tree_attn_wide_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
 // short problems: static grid, everything asked for at once (tree_attn_short.hip); all launches of the call
 hipError_t launch_tree_attn_short(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
-                                  const AcceptParams *ap, const CompactParams *cp);
+                                  const AcceptParams *ap, const CompactParams *cp, const JoinParams *jp);
 
 struct AcceptParams {
     const int32_t *draft, *target, *parents;

@@ -392,13 +392,14 @@ extern "C" int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, re
 
 // Argument checks and kernel parameters of the attention step (shared by reader_tree_attn and
 // reader_verify_step).  Returns READER_OK and fills `p`, or an error code; *empty is set when
-// there is nothing to do.
+// there is nothing to do, *one_launch when the fused step may be one.
 static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tree, const void *v_tree,
                         const void *k_cache, const void *v_cache, const int32_t *page_table,
                         const int32_t *seq_lens, const int32_t *parents, void *out, float *lse,
-                        int32_t max_seq_len, void *workspace, int32_t *status, AttnParams &p, bool *empty) {
+                        int32_t max_seq_len, void *workspace, int32_t *status, AttnParams &p, bool *empty, bool *one_launch = nullptr) {
     int err = 0;
     *empty = false;
+    if (one_launch) *one_launch = false;
     if (!dims_ok(dims, &err)) return err;
     if (max_seq_len < 0) return READER_EINVAL;
     if (dims->B == 0) { *empty = true; return READER_OK; }
@@ -446,9 +447,6 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.tree_in_cache = tree_in_cache ? 1 : 0;
     p.wide = attn_use_wide(*dims, p.rows_per_wg);
     p.redo_only = 0;
-    p.token = 0;
-    p.wait_ticks = p.units_per_xcd = p.join = 0;
-    p.units_per_xcd_rcp = p.pairs_rcp = p.hkv_rcp = 0.f;
     p.n_splits = 0;
     p.split_rcp = 0.f;
     p.keep_whole = 0;
@@ -458,7 +456,7 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
         p.n_row_chunks = sp.chunks;
         p.n_splits = sp.splits;
         p.split_rcp = 1.0f / (float)sp.splits;
-        p.join = sp.join;
+        if (one_launch) *one_launch = sp.join;
         p.keep_whole = sp.splits > 1 && tuning(READER_TUNE_ATTN_SHORT) < 1;   // (forced: every pair is cut as asked for)
     }
 #ifdef READER_WG_STAMPS
@@ -485,23 +483,24 @@ static unsigned long long next_token() {
     return token;
 }
 
-// Short problems: does the launch merge its records, accept and append by itself, its workgroups waiting for one another?
-// Not while the stream is being captured, whose launches would carry the same token at every replay.
-static void attn_join(AttnParams &p, hipStream_t stream) {
+// Short problems whose fused step may be one launch (it merges its records, accepts and appends by itself, its workgroups waiting
+// for one another): is it this time?  Not while the stream is being captured, whose launches would carry the same token at
+// every replay.
+static bool attn_join(const AttnParams &p, hipStream_t stream, JoinParams &j) {
     const int forced = tuning(READER_TUNE_JOIN);
-    if (forced == 0) return;
-    if (!p.join) return;
+    if (forced == 0) return false;
     if (stream) {                                        // (the null stream cannot be captured)
         hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return;
+        if (hipStreamIsCapturing(stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return false;
     }
-    p.token = next_token();
-    p.wait_ticks = wait_ticks(forced > 0 ? forced - 1LL : -1LL);
+    j.token = next_token();
+    j.wait_ticks = wait_ticks(forced > 0 ? forced - 1LL : -1LL);
     const int pairs = p.B * p.Hkv;
-    p.units_per_xcd = (pairs * p.n_row_chunks + kNumXCD - 1) / kNumXCD;
-    p.units_per_xcd_rcp = 1.0f / (float)p.units_per_xcd;
-    p.pairs_rcp = 1.0f / (float)pairs;
-    p.hkv_rcp = 1.0f / (float)p.Hkv;
+    j.units_per_xcd = (pairs * p.n_row_chunks + kNumXCD - 1) / kNumXCD;
+    j.units_per_xcd_rcp = 1.0f / (float)j.units_per_xcd;
+    j.pairs_rcp = 1.0f / (float)pairs;
+    j.hkv_rcp = 1.0f / (float)p.Hkv;
+    return true;
 }
 
 static void accept_fill(const reader_dims *dims, const int32_t *draft_tokens, const int32_t *target_tokens,
@@ -598,9 +597,9 @@ extern "C" int reader_verify_step(const reader_dims *dims, const void *q, const 
                                   int32_t *path, int32_t *bonus_token, int32_t max_seq_len, void *workspace,
                                   size_t workspace_bytes, int32_t *status, void *stream) {
     AttnParams p;
-    bool empty = false;
+    bool empty = false, one_launch = false;
     const int rc = attn_prepare(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, out, lse,
-                                max_seq_len, workspace, status, p, &empty);
+                                max_seq_len, workspace, status, p, &empty, &one_launch);
     if (rc != READER_OK || empty) return rc;
     if (!draft_tokens || !target_tokens || !accept_len || !path || !bonus_token) return READER_EINVAL;
     if (dims->variant != 0) return READER_EINVAL;   // the fused step exists for the matrix-core kernel only
@@ -612,10 +611,11 @@ extern "C" int reader_verify_step(const reader_dims *dims, const void *q, const 
     compact_fill(dims, k_tree, v_tree, path, accept_len, k_cache, v_cache, page_table, seq_lens, status, cp);
     hipEvent_t ev_a, ev_b;
     profile_next(&ev_a, &ev_b);
-    attn_join(p, (hipStream_t)stream);
+    JoinParams jp;
+    one_launch = one_launch && attn_join(p, (hipStream_t)stream, jp);
     forget_stale_error();
-    if (launch_tree_attn_mfma(p, (hipStream_t)stream, ev_a, ev_b, &ap, &cp) != hipSuccess) return READER_EHIP;
-    if (p.tree_in_cache && !p.token) {
+    if (launch_tree_attn_mfma(p, (hipStream_t)stream, ev_a, ev_b, &ap, &cp, one_launch ? &jp : nullptr) != hipSuccess) return READER_EHIP;
+    if (p.tree_in_cache && !one_launch) {
         // the tree rows are in the cache already: the accepted ones move in place (this layer's cache)
         CompactLayersParams lp;
         compact_layers_fill(dims, 1, path, accept_len, k_cache, v_cache, page_table, seq_lens, status, lp);

@@ -918,8 +918,8 @@ static hipError_t launch_tail(const AttnParams &p, hipStream_t stream, const Acc
 }
 
 hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
-                                 const AcceptParams *ap, const CompactParams *cp) {
-    if (p.n_splits > 0) return launch_tree_attn_short(p, stream, ev_start, ev_stop, ap, cp);
+                                 const AcceptParams *ap, const CompactParams *cp, const JoinParams *jp) {
+    if (p.n_splits > 0) return launch_tree_attn_short(p, stream, ev_start, ev_stop, ap, cp, jp);
     hipError_t e;
     if (p.rows_per_wg == 128) {
         e = p.D == 64 ? launch_mfma<64, 4>(p, stream, ev_start, ev_stop) : launch_mfma<128, 4>(p, stream, ev_start, ev_stop);

@@ -213,6 +213,7 @@ __device__ __forceinline__ void merge_share(const AttnParams &p, int b, int hkv,
 // The argument of the fused step's kernels, and a part of it read where it is used: read at the kernel's entry, as the compiler
 // would, what is only needed behind the main loop sits in scalar registers all the way and pushes others out.
 struct StepParams {
+    JoinParams join;           // (of the launch that waits inside)
     AttnParams attn;
     AcceptParams accept;
     CompactParams compact;
@@ -233,12 +234,12 @@ __device__ __forceinline__ T late_argument() {
 struct Marks {
     mark_t *written, *landed, *keepers, *any_left, token;
     int n_wg;
-    __device__ __forceinline__ explicit Marks(const AttnParams &p) {
+    __device__ __forceinline__ explicit Marks(const AttnParams &p, const JoinParams &j) {
         written = reinterpret_cast<mark_t *>(p.redo);
         landed = written + (p.n_splits > 1 ? kMaxMarks / 2 : 0);      // (whole pairs leave no record)
         keepers = reinterpret_cast<mark_t *>(p.pair_info);
         any_left = reinterpret_cast<mark_t *>(p.range_tiles);
-        token = p.token;
+        token = j.token;
         n_wg = p.B * p.Hkv * p.n_row_chunks * p.n_splits;
     }
 };
@@ -284,10 +285,10 @@ __device__ __forceinline__ void keep_for_others(const AttnParams &p, const Marks
 // and when every one of the others has read its keys and the lengths it appends them (a slot behind one sequence's end may
 // lie inside the prefix of another: forks of unequal length that share a partly filled page).
 constexpr int kKeeperThreads = 256;
-__device__ __forceinline__ void keep_sequence(const AttnParams &p, int b, TailShared &sh, int &s_append) {
+__device__ __forceinline__ void keep_sequence(const AttnParams &p, const JoinParams &j, int b, TailShared &sh, int &s_append) {
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid >= kKeeperThreads) return;
-    const Marks marks(p);
+    const Marks marks(p, j);
     const CompactParams cp = late_argument<CompactParams, offsetof(StepParams, compact)>();
     if (tid < 64) accept_path_wave(late_argument<AcceptParams, offsetof(StepParams, accept)>(), b, lane, sh.accept);
     __syncthreads();
@@ -297,7 +298,7 @@ __device__ __forceinline__ void keep_sequence(const AttnParams &p, int b, TailSh
     if (ahead) tail_load(tail_column(cp, tid), sh, 0, held);
     if (tid < 64) {
         const bool go = keep(AgentMarks{lane}, marks.keepers + b, marks.any_left, marks.token,
-                             [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, (unsigned)p.wait_ticks * kKeeperPatience);
+                             [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, (unsigned)j.wait_ticks * kKeeperPatience);
         if (lane == 0) s_append = go ? 1 : 0;
     }
     __syncthreads();
@@ -330,7 +331,7 @@ struct JoinShared {
 // the accepted rows wait for the next launch, as everybody reads the lengths (64 sequences of 300 to 500 tokens, 20 nodes, 40.7
 // us with acceptance in the second launch, 40.3).  Where pairs are cut the second launch merges, accepts and appends.
 template <int D, bool kStep, bool kJoin>
-__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
+__device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const JoinParams &j) {
     constexpr bool kDeep = D == 128;
     constexpr int CW = 4, kS = kShortStages;
     using G = Geometry<D, CW>;
@@ -351,17 +352,17 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
     if constexpr (kJoin) {
         // All shares of a pair's chunk get ids that are equal modulo 8: one XCD, whose L2 then holds the records to be merged.
         const int k = blockIdx.x >> 3, pairs = p.B * p.Hkv, units = pairs * p.n_row_chunks;
-        if (k >= p.units_per_xcd * p.n_splits) {
-            keep_sequence(p, blockIdx.x - kNumXCD * p.units_per_xcd * p.n_splits, *s_tail, s_join->append);
+        if (k >= j.units_per_xcd * p.n_splits) {
+            keep_sequence(p, j, blockIdx.x - kNumXCD * j.units_per_xcd * p.n_splits, *s_tail, s_join->append);
             return;
         }
         // (quotients of small numbers by way of floats: exact)
-        split = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * p.units_per_xcd_rcp));
-        const int unit = (blockIdx.x & 7) + 8 * (k - split * p.units_per_xcd);
+        split = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * j.units_per_xcd_rcp));
+        const int unit = (blockIdx.x & 7) + 8 * (k - split * j.units_per_xcd);
         if (unit >= units) return;
-        chunk = p.n_row_chunks == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)unit + 0.5f) * p.pairs_rcp));
+        chunk = p.n_row_chunks == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)unit + 0.5f) * j.pairs_rcp));
         const int pair = unit - chunk * pairs;
-        b = p.B == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)pair + 0.5f) * p.hkv_rcp));
+        b = p.B == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)pair + 0.5f) * j.hkv_rcp));
         hkv = pair - b * p.Hkv;
         wg = unit * p.n_splits + split;
     } else {
@@ -513,7 +514,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
         } else {
             if (lo >= hi) __syncthreads();     // (no tile, so no barrier yet: now every wavefront has read the lengths)
             if (cw == 0) {
-                const Marks marks(p);          // (the keys of the last tile are in LDS)
+                const Marks marks(p, j);          // (the keys of the last tile are in LDS)
                 some_left = arrive(AgentMarks{lane}, marks.landed + wg, marks.any_left, marks.token);
             }
         }
@@ -804,7 +805,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
         auto merge = [&]() __attribute__((always_inline)) {
             __syncthreads();                   // the records are written
             if (wave == 0) {
-                const Marks marks(p);
+                const Marks marks(p, j);
                 const mark_t xcc = my_xcc();
                 const mark_t *of_pair = marks.written + (wg - split);
                 mark_t seen = 0;
@@ -812,7 +813,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
                     seen = agent_load(of_pair + min(lane, p.n_splits - 1));
                     return (bool)__all((seen & ~kMarkBits) == marks.token);
                 };
-                const bool complete = meet(AgentMarks{lane}, marks.written + wg, marks.token | xcc, look, (unsigned)p.wait_ticks);
+                const bool complete = meet(AgentMarks{lane}, marks.written + wg, marks.token | xcc, look, (unsigned)j.wait_ticks);
                 const mark_t have_left = __ballot((seen & kStateBits) == kLeft);
                 const bool here = __all((seen & (kMarkBits & ~kStateBits)) == xcc);
                 if (lane == 0) {
@@ -836,7 +837,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
         };
         if (!whole) merge();
         if (some_left) {              // (one wavefront)
-            const Marks marks(p);
+            const Marks marks(p, j);
             keep_for_others(p, marks, lane, *s_tail);
         }
     }
@@ -844,15 +845,15 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p) {
 
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(AttnParams p) {
-    tree_attn_short_body<D, false, false>(p);
+    tree_attn_short_body<D, false, false>(p, JoinParams());
 }
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(StepParams p) {
-    tree_attn_short_body<D, true, false>(p.attn);
+    tree_attn_short_body<D, true, false>(p.attn, JoinParams());
 }
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_join_kernel(StepParams p) {
-    tree_attn_short_body<D, true, true>(p.attn);
+    tree_attn_short_body<D, true, true>(p.attn, p.join);
 }
 
 template <int D>
@@ -882,7 +883,7 @@ __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, Ac
 
 template <int D, bool kStep, bool kJoin>
 hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
-                       const CompactParams *cp) {
+                       const CompactParams *cp, const JoinParams *jp) {
     using G = Geometry<D, 4>;
     constexpr size_t lds = (size_t)kShortStages * G::kStageBytes + (4 * READER_MAX_T + 4 * kShortStages) * sizeof(int) +
                            (kJoin ? sizeof(JoinShared) : 0) + (kStep ? (kJoin ? sizeof(TailShared) : sizeof(AcceptShared)) : 0);
@@ -899,29 +900,29 @@ hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_st
             allowed = true;
         }
     }
-    const dim3 grid = kJoin ? dim3(kNumXCD * p.units_per_xcd * p.n_splits + p.B) : dim3(p.n_splits, p.Hkv, p.B * p.n_row_chunks);
+    const dim3 grid = kJoin ? dim3(kNumXCD * jp->units_per_xcd * p.n_splits + p.B) : dim3(p.n_splits, p.Hkv, p.B * p.n_row_chunks);
     const bool timed = ev_start && ev_stop;
     auto go = [&](auto *fn, const char *name, auto... args) {
         if (timed) hipExtLaunchKernelGGL(fn, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, args...);
         else hipLaunchKernelGGL(fn, grid, dim3(kThreads), lds, stream, args...);
         return note_hip_error(name, hipGetLastError());
     };
-    if constexpr (kJoin) return go(verify_short_join_kernel<D>, "launch verify_short_join_kernel", StepParams{p, *ap, *cp});
-    else if constexpr (kStep) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{p, *ap, *cp});
+    if constexpr (kJoin) return go(verify_short_join_kernel<D>, "launch verify_short_join_kernel", StepParams{*jp, p, *ap, *cp});
+    else if constexpr (kStep) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
     else return go(tree_attn_short_kernel<D>, "launch tree_attn_short_kernel", p);
 }
 
 template <int D>
 hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
-                      const CompactParams *cp) {
+                      const CompactParams *cp, const JoinParams *jp) {
     const bool step = ap && cp;
-    if (step && p.token) return launch_main<D, true, true>(p, stream, ev_start, ev_stop, ap, cp);
+    if (step && jp) return launch_main<D, true, true>(p, stream, ev_start, ev_stop, ap, cp, jp);
     if (step && p.n_splits == 1) {
-        const hipError_t e = launch_main<D, true, false>(p, stream, ev_start, ev_stop, ap, cp);
+        const hipError_t e = launch_main<D, true, false>(p, stream, ev_start, ev_stop, ap, cp, nullptr);
         if (e != hipSuccess || !cp->k_tree) return e;      // (in-cache layout: the rows move in a launch of their own)
         return launch_kv_compact(*cp, stream);
     }
-    const hipError_t e = launch_main<D, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr);
+    const hipError_t e = launch_main<D, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
     if (e != hipSuccess || p.n_splits == 1) return e;
     const int blocks = (p.M + 7) / 8 * (D / 64);           // of 8 rows x 8 chunks, four wavefronts
     if (step) {
@@ -935,8 +936,8 @@ hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_sta
 }  // namespace
 
 hipError_t launch_tree_attn_short(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
-                                  const AcceptParams *ap, const CompactParams *cp) {
-    return p.D == 64 ? launch_all<64>(p, stream, ev_start, ev_stop, ap, cp) : launch_all<128>(p, stream, ev_start, ev_stop, ap, cp);
+                                  const AcceptParams *ap, const CompactParams *cp, const JoinParams *jp) {
+    return p.D == 64 ? launch_all<64>(p, stream, ev_start, ev_stop, ap, cp, jp) : launch_all<128>(p, stream, ev_start, ev_stop, ap, cp, jp);
 }
 
 }  // namespace reader
