@@ -146,6 +146,12 @@ typedef struct reader_attn_plan_t {
 int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, reader_attn_plan_t *plan);
 
 /*
+ * Whether reader_verify_step of these dims is one launch (verify_short_join_kernel<D>) on a stream that is not being
+ * captured: 1 or 0, or the error reader_attn_plan would return.  Pure host function; honours reader_tuning_override.
+ */
+int reader_step_is_one_launch(const reader_dims *dims, int32_t max_seq_len);
+
+/*
  * Tree-masked attention (Section 3.2; Appendix C invariant 2).
  * For every sequence b, query head hq and tree node i:
  *     out[b,i,hq,:] = sum_j softmax_j( sm_scale * <q[b,i,hq,:], k_j> ) * v_j
@@ -530,6 +536,7 @@ int reader_measure_peaks(const void *src, size_t src_bytes, void *scratch, size_
  *   READER_TUNE_JOIN            0 = reader_verify_step of a short problem never waits inside a launch, n >= 1 = its workgroups
  *                               wait for (n - 1) / 100 us at most (1: whoever finds another one missing leaves at once; never more
  *                               than 10 ms), the one that appends four times as long
+ *   READER_TUNE_JOIN_SPREAD     1 = the shares of a pair run on different XCDs there (0 or cleared: on one)
  * Returns READER_OK, or READER_EINVAL for an unknown `which`.
  */
 enum {
@@ -541,7 +548,8 @@ enum {
     READER_TUNE_ATTN_PAIR_FRONT = 5,
     READER_TUNE_ATTN_SHORT = 6,
     READER_TUNE_JOIN = 7,
-    READER_TUNE_COUNT_ = 8
+    READER_TUNE_JOIN_SPREAD = 8,
+    READER_TUNE_COUNT_ = 9
 };
 int reader_tuning_override(int32_t which, int32_t value);
 

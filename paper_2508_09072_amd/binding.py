@@ -27,7 +27,7 @@ READER_EHIP = -4
 STATUS_BAD_TREE = 1
 STATUS_BAD_PAGE = 2
 STATUS_BAD_PATH = 4
-TUNE_ATTN_ROWS, TUNE_ATTN_RANGES, TUNE_ATTN_PAIR_COST, TUNE_ATTN_AXIS64, TUNE_ATTN_WIDE, TUNE_ATTN_PAIR_FRONT, TUNE_ATTN_SHORT, TUNE_JOIN = 0, 1, 2, 3, 4, 5, 6, 7
+TUNE_ATTN_ROWS, TUNE_ATTN_RANGES, TUNE_ATTN_PAIR_COST, TUNE_ATTN_AXIS64, TUNE_ATTN_WIDE, TUNE_ATTN_PAIR_FRONT, TUNE_ATTN_SHORT, TUNE_JOIN, TUNE_JOIN_SPREAD = 0, 1, 2, 3, 4, 5, 6, 7, 8
 
 EXPORTS = (
     "reader_version", "reader_strerror", "reader_last_error_detail", "reader_validate_tree", "reader_workspace_bytes",
@@ -37,7 +37,7 @@ EXPORTS = (
     "reader_trie_extract_tree", "reader_tree_attach_path", "reader_self_repetition", "reader_tree_prune_order",
     "reader_tree_select",
     "reader_profile_enable", "reader_profile_collect", "reader_profile_collect_each", "reader_tuning_override",
-    "reader_attn_plan", "reader_measure_peaks",
+    "reader_attn_plan", "reader_step_is_one_launch", "reader_measure_peaks",
 )
 
 
@@ -103,6 +103,8 @@ def load():
     lib.reader_measure_peaks.argtypes = [vp, ctypes.c_size_t, vp, ctypes.c_size_t] + [ctypes.POINTER(ctypes.c_double)] * 3 + [vp]
     lib.reader_attn_plan.restype = ctypes.c_int
     lib.reader_attn_plan.argtypes = [dp, i32, ctypes.POINTER(ReaderAttnPlan)]
+    lib.reader_step_is_one_launch.restype = ctypes.c_int
+    lib.reader_step_is_one_launch.argtypes = [dp, i32]
     lib.reader_tree_attn.restype = ctypes.c_int
     lib.reader_tree_attn.argtypes = [dp] + [vp] * 10 + [i32, vp, ctypes.c_size_t, vp, vp]
     lib.reader_tree_attn_noalloc.restype = ctypes.c_int
@@ -217,6 +219,14 @@ def reader_attn_plan(dims: ReaderDims, max_seq_len: int) -> dict:
     return {"kernel": ATTN_KERNEL_NAMES[int(plan.kernel)].replace("D", str(int(dims.D))), "kernel_id": int(plan.kernel),
             "rows_per_workgroup": int(plan.rows_per_workgroup), "row_chunks": int(plan.row_chunks),
             "key_ranges": int(plan.key_ranges)}
+
+
+def reader_step_is_one_launch(dims: ReaderDims, max_seq_len: int) -> bool:
+    """Whether reader_verify_step would be one launch on a stream that is not being captured (host only)."""
+    code = int(load().reader_step_is_one_launch(ctypes.byref(dims), int(max_seq_len)))
+    if code < 0:
+        _check(code, "reader_step_is_one_launch")
+    return code == 1
 
 
 def reader_measure_peaks(src, scratch) -> dict:

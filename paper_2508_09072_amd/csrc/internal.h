@@ -71,6 +71,7 @@ struct JoinParams {
     int32_t wait_ticks;         // how long a workgroup waits for others at most (100 MHz)
     int32_t units_per_xcd;      // how many pairs' chunks of 128 rows every XCD takes (the last of some of them: none)
     float units_per_xcd_rcp, pairs_rcp, hkv_rcp;   // 1 / units_per_xcd, 1 / (B Hkv), 1 / Hkv
+    int32_t spread;             // tests: 1 = a pair's shares run on different XCDs, one behind the other
 };
 
 // Size of one partial record in 4-byte units: `rows` rows of D bf16 outputs (normalised by the

@@ -19,8 +19,8 @@ namespace reader {
 static char g_error_detail[256] = "";
 
 // Planner overrides set through reader_tuning_override (tests, experiments); -1 = the planner decides.
-static std::atomic<int32_t> g_tuning[READER_TUNE_COUNT_] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
-static_assert(READER_TUNE_COUNT_ == 8, "every override starts at -1");
+static std::atomic<int32_t> g_tuning[READER_TUNE_COUNT_] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
+static_assert(READER_TUNE_COUNT_ == 9, "every override starts at -1");
 #ifdef READER_WG_STAMPS
 static std::atomic<long long *> g_wg_stamps{nullptr};
 #endif
@@ -390,6 +390,14 @@ extern "C" int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, re
     return READER_OK;
 }
 
+extern "C" int reader_step_is_one_launch(const reader_dims *dims, int32_t max_seq_len) {
+    int err = 0;
+    if (!dims_ok(dims, &err)) return err;
+    if (max_seq_len < 0) return READER_EINVAL;
+    ShortPlan sp;
+    return dims->B > 0 && tuning(READER_TUNE_JOIN) != 0 && attn_plan_short(*dims, max_seq_len, sp) && sp.join ? 1 : 0;
+}
+
 // Argument checks and kernel parameters of the attention step (shared by reader_tree_attn and
 // reader_verify_step).  Returns READER_OK and fills `p`, or an error code; *empty is set when
 // there is nothing to do, *one_launch when the fused step may be one.
@@ -500,6 +508,7 @@ static bool attn_join(const AttnParams &p, hipStream_t stream, JoinParams &j) {
     j.units_per_xcd_rcp = 1.0f / (float)j.units_per_xcd;
     j.pairs_rcp = 1.0f / (float)pairs;
     j.hkv_rcp = 1.0f / (float)p.Hkv;
+    j.spread = tuning(READER_TUNE_JOIN_SPREAD) == 1 ? 1 : 0;
     return true;
 }
 

@@ -358,7 +358,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
         }
         // (quotients of small numbers by way of floats: exact)
         split = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * j.units_per_xcd_rcp));
-        const int unit = (blockIdx.x & 7) + 8 * (k - split * j.units_per_xcd);
+        const int unit = ((blockIdx.x + j.spread * split) & 7) + 8 * (k - split * j.units_per_xcd);
         if (unit >= units) return;
         chunk = p.n_row_chunks == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(((float)unit + 0.5f) * j.pairs_rcp));
         const int pair = unit - chunk * pairs;

@@ -361,3 +361,36 @@ def test_a_short_problem_has_as_many_shares_as_the_rule_says(R, B, T, Hq, Hkv, D
     plan = R.reader_attn_plan(R.make_dims(B, T, Hq, Hkv, D, 300, 4 if T > 3 else 1, 5000), bound)
     assert plan["kernel_id"] == 4
     assert plan["key_ranges"] == B * Hkv * shares
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,one", [
+    (1, 64, 32, 8, 128, 4160, False),   # two pairs' chunks of sixteen shares fill every XCD: no place for the keeper
+    (3, 25, 32, 8, 128, 2556, True),    # three of ten shares and a keeper
+    (1, 16, 8, 8, 64, 568, True),
+    (128, 12, 8, 8, 128, 52, True), (129, 12, 8, 8, 128, 52, False),     # whole pairs: as many marks as there are, and more
+    (64, 64, 64, 8, 128, 8192, False),  # ring kernels
+    (0, 64, 64, 8, 128, 8192, False),   # nothing to do
+])
+def test_when_the_fused_step_is_one_launch(R, B, T, Hq, Hkv, D, bound, one):
+    dims = R.make_dims(B, T, Hq, Hkv, D, 600, 4, 50000)
+    assert R.reader_step_is_one_launch(dims, bound) is one
+    R.reader_tuning_override(R.TUNE_JOIN, 0)
+    try:
+        assert R.reader_step_is_one_launch(dims, bound) is False
+    finally:
+        R.reader_tuning_override(R.TUNE_JOIN, -1)
+    with pytest.raises(RuntimeError):
+        R.reader_step_is_one_launch(R.make_dims(2, 8, 8, 2, 96, 10, 4, 20), 100)
+    with pytest.raises(RuntimeError):
+        R.reader_step_is_one_launch(dims, -1)
+
+
+@pytest.mark.parametrize("D,most", [(64, 63), (128, 31)])
+def test_forced_shares_are_one_launch_as_long_as_an_xcd_holds_them_and_the_keeper(R, D, most):
+    dims = R.make_dims(1, 8, 2, 2, D, 300, 4, 5000)
+    for n, one in ((most, True), (most + 1, False)):
+        R.reader_tuning_override(R.TUNE_ATTN_SHORT, n)
+        try:
+            assert R.reader_step_is_one_launch(dims, 4096) is one
+        finally:
+            R.reader_tuning_override(R.TUNE_ATTN_SHORT, -1)
