@@ -114,8 +114,25 @@ def settle(run, torch, warmup, min_ms=SETTLE_MS):
             return ms, n
 
 
-def roofline_of(w, each):
-    """Roofline object of the attention main kernel from its per-launch times (ms, HIP events bound to the kernel)."""
+def timed_kernel(R, w, fused):
+    """Name, workgroups and rows per workgroup of the launch that the library's event pair spans: the attention main kernel, or
+    the fused step's flavour of it.  `whole_step`: merge, acceptance and compaction are in that launch too."""
+    dims = R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages)
+    bound = int(w.seq_lens.max()) + w.max_path          # (the bound the launches have, see to_device)
+    plan = R.reader_attn_plan(dims, bound)
+    res = {"kernel": plan["kernel"], "workgroups": plan["key_ranges"] * plan["row_chunks"],
+           "rows_per_workgroup": plan["rows_per_workgroup"], "whole_step": False}
+    if fused and R.reader_step_is_one_launch(dims, bound):
+        units, shares = w.B * w.Hkv * plan["row_chunks"], plan["key_ranges"] // (w.B * w.Hkv)
+        res.update(kernel="verify_short_join_kernel<%d>" % w.D, workgroups=(units + 7) // 8 * 8 * shares + w.B, whole_step=True)
+    elif fused and plan["kernel_id"] == 4 and plan["key_ranges"] == w.B * w.Hkv:
+        res["kernel"] = "verify_short_kernel<%d>" % w.D   # (whole pairs: acceptance rides along)
+    return res
+
+
+def roofline_of(w, each, fused=True):
+    """Roofline object of the attention main kernel from its per-launch times (ms, HIP events bound to the kernel).  Where that
+    launch is the whole step (`whole_step`) it does not compare with a kernel that only attends."""
     import numpy as np
     n = len(each)
     kernel_ms = float(each.sum()) / max(n, 1)
@@ -131,10 +148,8 @@ def roofline_of(w, each):
         roof = {"bound": "mfma", "achieved": tflops, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": tflops / MFMA_BF16_PEAK_TFLOPS}
     from paper_2508_09072_amd import binding as R
-    plan = R.reader_attn_plan(R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages),
-                              int(w.seq_lens.max()) + w.max_path)       # (the bound the launches have, see to_device)
-    roof.update({"kernel": plan["kernel"], "workgroups": plan["key_ranges"] * plan["row_chunks"],
-                 "rows_per_workgroup": plan["rows_per_workgroup"], "kernel_ms": kernel_ms, "launches_timed": n,
+    roof.update(timed_kernel(R, w, fused))
+    roof.update({"kernel_ms": kernel_ms, "launches_timed": n,
                  "kernel_ms_median": float(np.median(each)) if n else None,
                  "kernel_ms_min": float(each.min()) if n else None,
                  "algorithmic_bytes": alg_bytes, "algorithmic_flops": flops, "hbm_gbs": gbs,
@@ -202,7 +217,7 @@ def time_workload(R, torch, w, steps, warmup, use_graph=True, fused=True):
     torch.cuda.synchronize()
     each = R.reader_profile_collect_each()
     R.reader_profile_enable(False)
-    res["roofline"] = roofline_of(w, each)
+    res["roofline"] = roofline_of(w, each, fused)
     return res
 
 

@@ -394,3 +394,19 @@ def test_forced_shares_are_one_launch_as_long_as_an_xcd_holds_them_and_the_keepe
             assert R.reader_step_is_one_launch(dims, 4096) is one
         finally:
             R.reader_tuning_override(R.TUNE_ATTN_SHORT, -1)
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,longest,fused,kernel,whole_step,workgroups", [
+    (1, 16, 8, 8, 64, 512, True, "verify_short_join_kernel<64>", True, 8 * 10 + 1),
+    (1, 16, 8, 8, 64, 512, False, "tree_attn_short_kernel<64>", False, 8 * 10),
+    (1, 64, 32, 8, 128, 4096, True, "tree_attn_short_kernel<128>", False, 8 * 2 * 16),
+    (129, 12, 8, 8, 128, 40, True, "verify_short_kernel<128>", False, 129 * 8),
+    (64, 64, 64, 8, 128, 8192, True, "tree_attn_wide_kernel<128>", False, 256),
+])
+def test_the_bench_line_names_the_launch_that_it_times(R, B, T, Hq, Hkv, D, longest, fused, kernel, whole_step, workgroups):
+    import types
+
+    import bench
+    w = types.SimpleNamespace(B=B, T=T, Hq=Hq, Hkv=Hkv, D=D, max_pages=600, max_path=6, num_pages=50000, seq_lens=np.array([longest]))
+    got = bench.timed_kernel(R, w, fused)
+    assert (got["kernel"], got["whole_step"], got["workgroups"]) == (kernel, whole_step, workgroups)
