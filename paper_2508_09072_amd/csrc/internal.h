@@ -100,7 +100,12 @@ enum WgStamp {
     kStampLoopIssued = 12,  // ... that item asked for
     kStampTileLanded = 13,  // first key tile complete in LDS (past the barrier that says so)
     kStampTileDone = 14,    // first key tile computed by this wavefront (before the next barrier)
-    kWgStamps = 15,
+    kStampWritten = 15,     // (a launch that waits inside) this share's records are written through
+    kStampSeen = 16,        // ... the marks of all shares of the pair have been seen
+    kStampMerged = 17,      // ... this share's part of the rows is merged
+    kStampAccepted = 18,    // ... (keeper) path chosen and reported, the first rows asked for
+    kStampAppended = 19,    // ... (keeper) rows appended
+    kWgStamps = 20,
     kStampedWgs = 2048       // workgroups that note anything: the buffer holds this many
 };
 #endif

@@ -296,6 +296,7 @@ __device__ __forceinline__ void keep_sequence(const AttnParams &p, const JoinPar
     tail_held_t held[kTailBatch];
     const bool ahead = tail.bad == 0 && tid < 2 * cp.Hkv * (cp.D / 8);
     if (ahead) tail_load(tail_column(cp, tid), sh, 0, held);
+    READER_STAMP(kStampAccepted, 0);
     if (tid < 64) {
         const bool go = keep(AgentMarks{lane}, marks.keepers + b, marks.any_left, marks.token,
                              [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, (unsigned)j.wait_ticks * kKeeperPatience);
@@ -303,6 +304,7 @@ __device__ __forceinline__ void keep_sequence(const AttnParams &p, const JoinPar
     }
     __syncthreads();
     if (s_append) keep_rows<kKeeperThreads>(cp, b, tid, tail, sh, ahead, held);
+    READER_STAMP(kStampAppended, 0);
 }
 
 // What a workgroup whose launch waits inside keeps in LDS for its wavefronts.
@@ -804,6 +806,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
     if constexpr (kJoin) {
         auto merge = [&]() __attribute__((always_inline)) {
             __syncthreads();                   // the records are written
+            READER_STAMP(kStampWritten, 0);
             if (wave == 0) {
                 const Marks marks(p, j);
                 const mark_t xcc = my_xcc();
@@ -823,6 +826,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
                 }
             }
             __syncthreads();
+            READER_STAMP(kStampSeen, 0);
             if (!__builtin_amdgcn_readfirstlane(s_join->complete)) return;
             const mark_t left = s_join->left;
             const int local = __builtin_amdgcn_readfirstlane(s_join->local);
@@ -834,6 +838,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
                 if (local) merge_share<D, false>(p, b, hkv, chunk, s);
                 else merge_share<D, true>(p, b, hkv, chunk, s);
             }
+            READER_STAMP(kStampMerged, 0);
         };
         if (!whole) merge();
         if (some_left) {              // (one wavefront)

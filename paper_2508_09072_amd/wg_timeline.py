@@ -9,7 +9,11 @@ points).  This script runs one preset with it and prints, over all workgroups an
 when each point is reached (relative to the first workgroup's entry), how long a workgroup takes per
 tile in between, and how far apart the workgroups finish:
 
-    python -m paper_2508_09072_amd.wg_timeline [--config 2] [--steps 40] [--tune ATTN_PAIR_COST=3]
+    python -m paper_2508_09072_amd.wg_timeline [--config 2] [--steps 40] [--tune ATTN_PAIR_COST=3] [--step] [--shape B,Hq,Hkv,D,T,L]
+
+--step runs the fused step instead of the attention.  Where that is one launch, the time stamps go on behind "exit" (which is then a
+share's record): record written through, the marks of the pair's shares seen, rows merged, and of the workgroups that keep a
+sequence path chosen and rows appended.  --shape takes sequences of L positions instead of a preset.
 
 The stamps cost a few stores per workgroup; the kernel is otherwise the one the benchmark times, except that the
 short-problem kernel at head dimension 64 runs one workgroup per compute unit here and two there.
@@ -26,8 +30,9 @@ import numpy as np
 STAMP_NAMES = ["entry", "range known", "list written", "first two key tiles asked for", "first item in LDS",
                "first tile computed", "last tile computed", "exit", "copy constants made", "first key tile asked for",
                "iteration 8: copier at the top", "iteration 8: copier past the barrier", "iteration 8: next item asked for",
-               "first key tile in LDS", "first key tile computed (one wavefront)"]
-ORDER = [0, 1, 2, 8, 9, 3, 4, 13, 14, 5, 10, 11, 12, 6, 7]     # in the order a workgroup reaches them
+               "first key tile in LDS", "first key tile computed (one wavefront)",
+               "records written through", "marks of all shares seen", "rows merged", "keeper: path chosen", "keeper: rows appended"]
+ORDER = [0, 1, 2, 8, 9, 3, 4, 13, 14, 5, 10, 11, 12, 6, 7, 15, 16, 17, 18, 19]     # in the order a workgroup reaches them
 N_STAMPS = len(STAMP_NAMES)
 MAX_WG = 2048
 
@@ -38,6 +43,8 @@ def main():
     ap.add_argument("--steps", type=int, default=40)
     ap.add_argument("--tune", action="append", default=[], metavar="NAME=VALUE",
                     help="planner override for the run, e.g. ATTN_PAIR_COST=3 (see reader_tuning_override)")
+    ap.add_argument("--step", action="store_true", help="the fused step (reader_verify_step) instead of reader_tree_attn")
+    ap.add_argument("--shape", metavar="B,Hq,Hkv,D,T,L", help="sequences of L positions instead of a preset")
     args = ap.parse_args()
 
     import torch
@@ -54,7 +61,11 @@ def main():
         R.reader_tuning_override(getattr(R, "TUNE_" + name), int(value))
         print("planner override: %s = %s" % (name, value))
 
-    w = W.make_config(args.config)
+    if args.shape:
+        B_, Hq, Hkv, D, T, L = (int(x) for x in args.shape.split(","))
+        w = W.make_custom("shape_" + args.shape, B=B_, Hq=Hq, Hkv=Hkv, D=D, T=T, seq_lens=[L] * B_, tree="trie", depth=6, seed=5)
+    else:
+        w = W.make_config(args.config)
     dw = R.to_device(w)
     kv_bytes = 2 * w.k_cache.nbytes
     copies = int(max(1, min(8, -(-(512 << 20) // max(kv_bytes, 1)))))   # more K/V than the 256 MB Infinity Cache holds
@@ -64,7 +75,18 @@ def main():
     p = lambda t: ctypes.c_void_p(t.data_ptr())
     stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
+    lens = dw.seq_lens.clone()
+
     def attn(k):
+        if args.step:
+            dw.seq_lens.copy_(lens)
+            rc = lib.reader_verify_step(ctypes.byref(dw.dims), p(dw.q), p(dw.k_tree), p(dw.v_tree), p(kc[k % copies]), p(vc[k % copies]),
+                                        p(dw.page_table), p(dw.seq_lens), p(dw.parents), p(dw.draft_tokens), p(dw.target_tokens), p(dw.out),
+                                        None, p(dw.accept_len), p(dw.path), p(dw.bonus), dw.max_seq_len, p(dw.workspace),
+                                        dw.workspace.numel(), p(dw.status), stream)
+            if rc:
+                raise RuntimeError("reader_verify_step failed: %d" % rc)
+            return
         rc = lib.reader_tree_attn(ctypes.byref(dw.dims), p(dw.q), p(dw.k_tree), p(dw.v_tree), p(kc[k % copies]),
                                   p(vc[k % copies]), p(dw.page_table), p(dw.seq_lens), p(dw.parents), p(dw.out), None,
                                   dw.max_seq_len, p(dw.workspace), dw.workspace.numel(), p(dw.status), stream)
@@ -89,8 +111,9 @@ def main():
     ranges = dw.workspace[:256 * 4].view(torch.int32).cpu().numpy()    # tiles per range, first words of the workspace
     use = rows[len(rows) // 2:]                                          # the second half of the launches
     n_wg = int((use[0][:, 0] != 0).sum())
+    joined = args.step and R.reader_step_is_one_launch(dw.dims, dw.max_seq_len)
     print("preset %s, %s: %d workgroups with stamps, %d launches summarised; times in us from the first workgroup's entry"
-          % (w.name, plan["kernel"], n_wg, len(use)))
+          % (w.name, "verify_short_join_kernel<%d>" % w.D if joined else plan["kernel"], n_wg, len(use)))
     rel = []
     for s in use:
         live = s[s[:, 0] != 0].astype(np.float64)
@@ -117,7 +140,7 @@ def main():
         row_bytes = 2 * w.D * 2                                          # K and V row of one kv head, bf16
         print("  = %.0f GB/s while streaming, all workgroups together (64 keys x %d bytes per tile)"
               % (n_wg * 64 * row_bytes / np.median(per_tile) / 1e3, row_bytes))
-    end = rel[:, :, 7]
+    end = rel.max(axis=2) if joined else rel[:, :, 7]
     print("kernel span (first entry -> last exit): median %.2f us; last exit - median exit: %.2f us; "
           "last entry - first entry: %.2f us" % (np.median(end.max(axis=1)), np.median(end.max(axis=1) - np.median(end, axis=1)),
                                                  np.median(rel[:, :, 0].max(axis=1))))
