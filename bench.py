@@ -3,7 +3,7 @@
 
 A step is one pass of the whole hot path over one batch of synthetic input:
 attention over the draft tree, acceptance of the longest matching path, compaction of
-its rows into the cache (reader_verify_step: the three operations in two kernel launches, one where the problem is short;
+its rows into the cache (reader_verify_step: the three operations in two kernel launches, one for most short problems;
 `--separate-calls` times reader_tree_attn -> reader_accept_path -> reader_kv_compact
 instead), all on one stream, inputs resident in HBM before the clock starts.  The metric is tree tokens per
 second (B * T draft-tree nodes verified per step) together with the achieved HBM

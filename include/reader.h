@@ -40,7 +40,8 @@
  *  - Grouped-query attention: query head hq reads kv head hq / (Hq / Hkv).
  *  - Paged cache: position j of sequence b lives in physical page
  *    page_table[b][j / page_size], slot j % page_size.
- *  - Threads: the compute entry points keep no state between calls and may be called
+ *  - Threads: the compute entry points keep nothing between calls but a count of fused steps
+ *    (each of them marks its workspace with a number of its own) and may be called
  *    from several host threads, each on its own stream and with its own workspace,
  *    outputs and status word; calls that share a workspace or write the same cache
  *    pages or lengths must be ordered by the caller (one stream, or events).
@@ -303,9 +304,9 @@ int reader_kv_compact_layers(const reader_dims *dims, int32_t num_layers,
  *     reader_tree_attn -> reader_accept_path -> reader_kv_compact
  * called in that order on one stream, but in two kernel launches instead of four (three
  * where the four-wavefront kernel runs): the last launch merges the attention partials, accepts
- * a path per sequence and compacts it.  A short problem is one launch, whose workgroups wait for one
- * another (never without bound: whoever arrives last does what others have left), except on a stream
- * that is being captured: two there, with the same results.  target_tokens are an input here too
+ * a path per sequence and compacts it.  Most short problems are one launch (reader_step_is_one_launch),
+ * whose workgroups wait for one another (never without bound: whoever arrives last does what others
+ * have left), except on a stream that is being captured: two there, with the same results.  target_tokens are an input here too
  * (the base model's tokens come from outside this library), so the attention output is not
  * consulted by the acceptance.
  * k_cache, v_cache and seq_lens are read by the attention and then updated by the

@@ -10,8 +10,9 @@
 // scope), and a wavefront waits for its own stores (vmcnt 0) before the mark is set, and for the mark before it looks at another's.
 // No cache is written back or invalidated (an invalidation by every wavefront took 17 us).  What workgroups of one XCD have
 // written (their marks say where they run) is in the L2 that all its compute units share, and plain loads find it there, of
-// lines that this compute unit has not read before in the launch.  Plain stores would be there sooner too, but the launch would end with that much more to write back (one
-// prompt of 4 K tokens: 11.7 instead of 12.5 us until the last row is merged, but 19.0 instead of 17.0 for the step).
+// lines that this compute unit has not read before in the launch.  Plain stores would be there sooner too, but the launch would end with that much more to write
+// back (one prompt of 4 K tokens in 15 shares: 11.7 instead of 12.5 us until the last row is merged, but 19.0 instead of 17.0
+// for the step).
 //
 // Who waits for whom, and what happens to the work of those who leave: handshake.h.
 #pragma once

@@ -65,7 +65,7 @@ struct AttnParams {
 
 // What a fused step of a short problem needs besides where it is one launch whose workgroups wait inside (arrivals.h).  Apart
 // from AttnParams, so that the other kernels' arguments stay where they are: each line of them is a trip to memory in front of
-// everything else a kernel does (with these values among them, ring kernels' step of five sequences 31.4 -> 31.9 us).
+// everything else a kernel does (ring kernels' step of five sequences 31.6 us with these values among them, 31.2 without).
 struct JoinParams {
     unsigned long long token;   // what marks this launch's arrivals in the header
     int32_t wait_ticks;         // how long a workgroup waits for others at most (100 MHz)

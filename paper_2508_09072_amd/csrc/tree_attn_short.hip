@@ -317,12 +317,13 @@ struct JoinShared {
 
 // kStep, kJoin: the fused step in one launch.  Workgroups that keep a sequence's cache each (keep_sequence) accept meanwhile, and
 // append when everybody's keys have landed; the shares of a cut pair wait for one another and merge its rows together, on one
-// XCD.  A second launch costs 4 to 5 us, of which 2.2 are the launch.  What takes its place: 0.3 us until a share's records are
-// written through, 0.7 until their marks are seen, 2 for the merge; and an append that ends with the last share's rows.
-// Whole steps: 512 tokens 10.0 -> 8.2 us, one prompt of 4 K tokens 17.7 -> 16.3, five sequences of 100 tokens, whole pairs,
-// 12.8 -> 8.9; with the tree in the cache (three launches before) 19.7 -> 12.5.  Acceptance by the first copying wavefront of an
-// attention workgroup instead made that workgroup's first keys 0.9 us late and its append 1.7; merging inside the launches
-// of reader_tree_attn as well gains nothing (16.1 -> 15.8 us at most, 7.4 -> 8.4 on 512 tokens).
+// XCD.  A second launch costs 4 to 5 us, of which 2.2 are the launch.  What takes its place, from time stamps: 0.25 us until a
+// share's records are written through, 0.6 to 0.8 until the last one's mark is seen, 2.0 for the merge of ten shares of 24 pairs with
+// 100 rows (0.9 on 512 tokens at head dimension 64); and an append that ends before the last share's rows.
+// Whole steps: 512 tokens 10.0 -> 8.0 us, five sequences of 100 tokens, whole pairs, 12.8 -> 8.9; with the tree in the cache
+// (three launches before) 19.7 -> 12.5.  Acceptance by the first copying wavefront of an attention workgroup instead made that
+// workgroup's first keys 0.9 us late and its append 1.7; merging inside the launches of reader_tree_attn as well gained nothing
+// with an earlier merge (one prompt of 4 K tokens 16.1 -> 15.8 us, 512 tokens 7.4 -> 8.4; other shapes, and today's merge, not tried).
 //
 // Whole pairs of more sequences than run at once: the keepers, last in the grid, come to run when nobody waits for a place
 // any more (44 sequences of 237 tokens, 24 nodes, 29.8 -> 24.2 us, at head dimension 64 17.5 -> 14.0).

@@ -8,7 +8,7 @@
 // they end, not by where they begin, so that the lookups of one token (one per n-gram length) do not wait for each other.
 // Of the 17 to 18 thousand nodes of such a trie 3.4 have no child and 13.3 a single one, which its parent leads to: only
 // the children of nodes with two or more are in a table (one for all, open addressing, 8 bytes per slot).  Measured on one
-// core: one request (prompt of 4096 tokens, 64 draft trees and search paths) 226 us, 351 when every edge had a slot, 2560
+// core: one request (prompt of 4096 tokens, 64 draft trees and search paths) 222 to 227 us, 351 when every edge had a slot, 2560
 // with a hash map of edges and a vector of children per node, walked n-gram by n-gram; 65536 tokens of text that repeats
 // little inserted in 7.8 ms, 40 when every edge had a slot.
 #include <algorithm>

@@ -111,6 +111,7 @@ def test_a_workspace_serves_one_step_after_the_other(R, tune):
         for turn in range(3):
             for k, dw in zip(kinds, devs):
                 tune(R.TUNE_ATTN_SHORT, k["short"])
+                tune(R.TUNE_JOIN_SPREAD, turn & 1)         # (and what one XCD has written and read another may do next)
                 assert R.reader_workspace_bytes(dw.dims, dw.max_seq_len) <= shared.numel()
                 assert R.reader_step_is_one_launch(dw.dims, dw.max_seq_len) is (k["one"] and join != 0)
                 lens = dw.seq_lens.clone()
