@@ -268,7 +268,8 @@ __device__ __forceinline__ void keep_rows(const CompactParams &cp, int b, int t,
 
 // The sequences whose own workgroup has left, by one wavefront of a workgroup whose keys have landed, if it is the last.
 __device__ __forceinline__ void keep_for_others(const AttnParams &p, const Marks &marks, int lane, TailShared &sh) {
-    act_for_those_who_left(AgentMarks{lane}, marks.keepers, p.B, marks.token, [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); }, [&](int b) __attribute__((always_inline)) {
+    auto everybody = [&] { return all_here(marks.landed, marks.n_wg, marks.token, lane); };
+    act_for_those_who_left(AgentMarks{lane}, marks.keepers, p.B, marks.token, everybody, [&](int b) __attribute__((always_inline)) {
         const AcceptParams ap = late_argument<AcceptParams, offsetof(StepParams, accept)>();
         const CompactParams cp = late_argument<CompactParams, offsetof(StepParams, compact)>();
         int bits;
