@@ -1,0 +1,98 @@
+"""Partial records of cut pairs (at head dimension 64 fp16 in a common unit, or a row's own where its values are too large or too
+small for that), and how many of them a launch leaves."""
+import numpy as np
+import pytest
+
+from paper_2508_09072_amd import workloads as W
+from helpers import assert_close
+from test_gpu_parity import R, bf16_to_np, run_attn, tune  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def route(R, tune, kernel):
+    """Overrides that send a problem of two kv heads through one of the kernels that leave records."""
+    if kernel == "short":
+        tune(R.TUNE_ATTN_SHORT, 5)
+    else:
+        tune(R.TUNE_ATTN_SHORT, 0)
+        tune(R.TUNE_ATTN_RANGES, 9)
+        tune(R.TUNE_ATTN_ROWS, 128 if kernel == "rows128" else 256)
+        tune(R.TUNE_ATTN_WIDE, 1 if kernel == "waves4" else 0)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kernel", ["short", "rows128", "waves8", "waves4"])
+def test_outputs_of_any_size_survive_the_records(R, oracle_mod, kernel, D, tune):
+    # one kv head with values around 2^-90, one around 2^70 and one infinite value among them, one with zeros, one with
+    # values that keep the common unit for some rows only (2^-10 and less after averaging): the errors scale with them
+    route(R, tune, kernel)
+    w = W.make_custom("units_%s" % kernel, B=2, Hq=8, Hkv=4, D=D, T=33, seq_lens=[700, 333], tree="trie", depth=6, seed=530)
+    unit = np.asarray([2.0 ** -90, 2.0 ** 70, 0.0, 2.0 ** -11])
+    for name in ("v_cache", "v_tree"):
+        a = W.bf16_bits_to_f32(getattr(w, name)).astype(np.float64)
+        a *= unit[None, :, None, None] if name == "v_cache" else unit[None, None, :, None]
+        canary = np.isnan(a)
+        bits = W.to_bf16_bits(a.astype(np.float32))
+        bits[canary] = getattr(w, name)[canary]
+        setattr(w, name, bits)
+    w.v_cache[int(w.page_table[0, 3]), 1, 5, 7] = 0x7F80
+    ref, ref_lse = oracle_mod.tree_attn(w.q, w.k_tree, w.v_tree, w.k_cache, w.v_cache, w.page_table, w.seq_lens, w.parents)
+    out, lse = run_attn(R, w)
+    G = w.Hq // w.Hkv
+    assert np.isinf(ref[0, :, G:2 * G, 7]).all() and np.array_equal(out[0, :, G:2 * G, 7], ref[0, :, G:2 * G, 7])
+    out[0, :, G:2 * G, 7] = ref[0, :, G:2 * G, 7] = 0
+    assert np.isfinite(out).all()
+    for h in range(w.Hkv):
+        got, want = out[:, :, h * G:(h + 1) * G].astype(np.float64), ref[:, :, h * G:(h + 1) * G]
+        assert (np.abs(got - want) <= 2e-2 * unit[h] + 2e-2 * np.abs(want)).all(), (kernel, h)
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+
+
+@pytest.mark.parametrize("rows,T", [(128, 16), (128, 80), (256, 80)])
+def test_a_cut_pair_is_as_exact_as_a_whole_one(R, oracle_mod, rows, T, tune):
+    # bf16 weights and the final rounding leave 2.3e-3 either way; records in bf16 would add as much as the final rounding
+    # (a ratio of 1.22).  30000 roundings and more scatter by half a percent; the parts' own largest weights, which are exactly
+    # 1, move the ratio by up to three percent
+    tune(R.TUNE_ATTN_SHORT, 0)
+    tune(R.TUNE_ATTN_ROWS, rows)
+    w = W.make_custom("exact_%d_%d" % (rows, T), B=8, Hq=16, Hkv=8, D=64, T=T, seq_lens=[1200] * 8, tree="trie", depth=5, seed=531)
+    ref, _ = oracle_mod.tree_attn(w.q, w.k_tree, w.v_tree, w.k_cache, w.v_cache, w.page_table, w.seq_lens, w.parents)
+    err = []
+    for ranges in (64, 200):                     # as many as there are pairs, all alike: none is cut
+        tune(R.TUNE_ATTN_RANGES, ranges)
+        out, _ = run_attn(R, w)
+        err.append(np.linalg.norm(out - ref) / np.linalg.norm(ref))
+    print("whole %.4e, cut %.4e" % tuple(err), flush=True)
+    assert err[1] <= 1.04 * err[0]
+
+
+@pytest.mark.parametrize("B", [6, 341])
+def test_head_dim_64_with_one_and_with_two_workgroups_per_compute_unit(R, oracle_mod, B, tune):
+    # two, as planned; one, with a workspace that holds no more records, or with more sequences than two have LDS for; less than
+    # one needs is refused
+    import torch
+    tune(R.TUNE_ATTN_SHORT, 0)
+    rng = np.random.default_rng(7)
+    lens = [int(x) for x in (rng.integers(900, 4000, B) if B < 100 else rng.integers(150, 230, B))]
+    w = W.make_custom("per_cu_%d" % B, B=B, Hq=16, Hkv=8, D=64, T=20, seq_lens=lens, tree="trie", depth=6, seed=532)
+    dw = R.to_device(w)
+    bound = max(lens)
+    full = R.reader_workspace_bytes(dw.dims, bound)
+    header = -(-(256 * 4 + 2048 * 4 + B * 8 * 8) // 256) * 256
+    assert R.reader_attn_plan(dw.dims, bound)["key_ranges"] == (512 if B < 100 else 256)
+    ref, ref_lse = oracle_mod.tree_attn(w.q, w.k_tree, w.v_tree, w.k_cache, w.v_cache, w.page_table, w.seq_lens, w.parents)
+    outs = []
+    for size in (full, header + (full - header) // 2):
+        ws = torch.full((size,), 0x7F, dtype=torch.uint8, device="cuda")
+        dw.out.fill_(float("nan"))
+        R.reader_tree_attn(dw.dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
+                           dw.out, dw.lse, bound, ws, dw.status)
+        torch.cuda.synchronize()
+        outs.append(bf16_to_np(dw.out))
+        assert_close(outs[-1], ref, what="%d bytes" % size)
+        assert_close(dw.lse.cpu().numpy(), ref_lse, what="%d bytes, lse" % size)
+    assert np.array_equal(outs[0], outs[1]) == (B > 100)
+    with pytest.raises(RuntimeError):
+        R.reader_tree_attn(dw.dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
+                           dw.out, dw.lse, bound, ws[:-256], dw.status)
