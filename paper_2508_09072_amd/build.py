@@ -26,6 +26,8 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first words of a kernel's arguments arrive in scalar registers with the launch
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall",
     # the LDS-copy inline asm names m0 as clobbered on purpose
     "-Wno-inline-asm",
