@@ -361,11 +361,14 @@ struct JoinShared {
 // Whole pairs of more sequences than run at once: the keepers, last in the grid, come to run when nobody waits for a place
 // any more (44 sequences of 237 tokens, 24 nodes, 29.8 -> 24.2 us, at head dimension 64 17.5 -> 14.0).
 //
-// kStep alone: whole pairs, on a stream that is being captured or of more workgroups than there are marks for.
-// Acceptance reads tokens only and writes nothing that an attention launch reads, so the first copying wavefront of a sequence's
-// first workgroup chooses the path while the first tiles are on their way and reports it when it has no more tiles to ask for;
-// the accepted rows wait for the next launch, as everybody reads the lengths (64 sequences of 300 to 500 tokens, 20 nodes, 40.7
-// us with acceptance in the second launch, 40.3).  Where pairs are cut the second launch merges, accepts and appends.
+// kStep alone: a step of more launches than one (on a stream that is being captured, of more workgroups than there are marks for,
+// or where a pair's shares leave a keeper no place).  Acceptance reads tokens only and writes nothing that an attention launch
+// reads, so the first copying wavefront of a sequence's first workgroup does it: the tokens arrive with the page ids, and when
+// the last tile has landed it chooses the path, while the others compute that tile and write their records.  The accepted rows
+// wait for the next launch, as everybody reads the lengths.  In the second launch, where acceptance was before for pairs that are
+// cut, it stood in front of the append and made it the longest job there: one prompt of 4 K tokens 17.6 -> 16.5 us (17.15 with
+// the path chosen in front of the wait for the first tile, which that workgroup's others then wait for), 8 K 21.2 -> 20.4, 128
+// nodes 24.2 -> 22.0; whole pairs (44 sequences of 237 tokens, captured), in front of the first tile before, 32.2 -> 28.3.
 template <int D, bool kStep, bool kJoin, Form kForm>
 __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const JoinParams &j) {
     static_assert(!fine_records(D) || kForm != Form::kEither, "these records are written by kernels of their own");
@@ -451,7 +454,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
         };
         const bool early = n_table <= kPageRegs * 64 * 4;   // all the sequence can have: asked for before its length is known
         if (early) fetch_pages();
-        const bool side = kStep && !kJoin && cw == 0 && chunk == 0 && hkv == 0;
+        const bool side = kStep && !kJoin && cw == 0 && chunk == 0 && hkv == 0 && split == 0;
         AcceptTokens tok;
         if (side) tok = accept_load(late_argument<AcceptParams, offsetof(StepParams, accept)>(), b, lane);
         share();
@@ -532,8 +535,6 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             issue(lo + i);
             if (i == 0) READER_STAMP(kStampItem0Issued, 256);
         }
-        int accepted = 0, step_bits = 0;
-        if (side) accepted = accept_choose(late_argument<AcceptParams, offsetof(StepParams, accept)>(), lane, nodes, *s_accept, step_bits);
 #pragma unroll 1
         for (int t = lo; t < hi; ++t) {
             // this wavefront's part of tile t has landed once at most its copies of the tiles behind it are outstanding
@@ -545,7 +546,12 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             if (t + kS - 1 < hi) issue(t + kS - 1);
         }
         if (p.status && bad) atomicOr(p.status, bad);
-        if (side) accept_report(late_argument<AcceptParams, offsetof(StepParams, accept)>(), b, lane, accepted, step_bits, *s_accept);
+        if (side) {
+            const AcceptParams ap = late_argument<AcceptParams, offsetof(StepParams, accept)>();
+            int bits;
+            const int n = accept_choose(ap, lane, nodes, *s_accept, bits);
+            accept_report(ap, b, lane, n, bits, *s_accept);
+        }
         if constexpr (!kJoin) {
             return;
         } else {
@@ -947,6 +953,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
     tree_attn_short_body<D, false, false, form_of<D>(true)>(p, JoinParams());
 }
 template <int D>
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(StepParams p) {   // (cut pairs of a step in two launches)
+    tree_attn_short_body<D, true, false, form_of<D>(false)>(p.attn, JoinParams());
+}
+template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(StepParams p) {
     tree_attn_short_body<D, true, false, form_of<D>(true)>(p.attn, JoinParams());
 }
@@ -962,7 +972,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verif
 // What its first loads need stands in front of the other arguments, one by one: those words arrive in scalar registers with the
 // launch (members of a structure do not), and the records are not asked for a trip to memory later.  16-layer decoding step of three
 // users 259.6 -> 254.0 us.  (The same in front of the attention kernels' arguments: a step of 512 tokens 7.98 -> 8.12, one prompt of 4 K
-// tokens alike; of verify_tail_short_kernel's merge, where something else takes the time: 17.7 -> 18.5.)
+// tokens alike; in front of verify_tail_short_kernel's, whose acceptance is what takes time: 17.7 -> 18.5 us.)
 template <int D>
 __global__ __launch_bounds__(256) void merge_short_kernel(float *workspace, uint16_t *out, int32_t n_splits, int32_t M, int32_t Hkv,
                                                           int32_t n_row_chunks, int32_t T, int32_t Hq, int32_t G, float g_rcp, AttnParams p) {
@@ -971,24 +981,23 @@ __global__ __launch_bounds__(256) void merge_short_kernel(float *workspace, uint
     merge_block<D>(p, blockIdx.z, blockIdx.y, blockIdx.x);
 }
 
-// Tail of the fused step where pairs were cut: one workgroup per sequence that accepts a path and appends its rows, then the
-// merge blocks.  The jobs touch disjoint data.
+// Second launch of the fused step where pairs were cut: one workgroup per sequence that appends the rows of the path that the
+// attention launch has chosen, then the merge blocks.  The jobs touch disjoint data.
 template <int D>
-__global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks) {
+__global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, CompactParams cp, int merge_blocks) {
     if ((int)blockIdx.x >= p.B) {
         const int m = blockIdx.x - p.B, pair = m / merge_blocks, seq = pair / p.Hkv;
         merge_block<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks);
         return;
     }
-    __shared__ AcceptShared sh;
     __shared__ CompactShared cs;
+    __shared__ int s_path[READER_MAX_T];
     const int b = blockIdx.x, tid = threadIdx.x;
-    const bool append = cp.k_tree != nullptr;       // (in-cache layout: the rows move in a launch of their own)
-    if (append) kv_compact_prefetch(cp, b, tid, cs);
-    if (tid < 64) accept_path_wave(ap, b, tid, sh);
-    if (!append) return;
+    const int n = cp.accept_len[b];
+    if (tid < cp.max_path) s_path[tid] = cp.path[(size_t)b * cp.max_path + tid];   // (all of it: the next trip to memory is the rows')
+    kv_compact_prefetch(cp, b, tid, cs);
     __syncthreads();
-    kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
+    kv_compact_body(cp, b, tid, n, s_path, cs);
 }
 
 template <int D, bool kStep, bool kJoin, bool kWhole>
@@ -1002,9 +1011,10 @@ hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_st
     const void *kernel;
     if constexpr (kJoin && kOwn) kernel = reinterpret_cast<const void *>(&verify_short_join_whole_kernel<D>);
     else if constexpr (kJoin) kernel = reinterpret_cast<const void *>(&verify_short_join_kernel<D>);
-    else if constexpr (kStep) kernel = reinterpret_cast<const void *>(&verify_short_kernel<D>);
+    else if constexpr (kStep && kWhole) kernel = reinterpret_cast<const void *>(&verify_short_kernel<D>);
+    else if constexpr (kStep) kernel = reinterpret_cast<const void *>(static_cast<void (*)(StepParams)>(&tree_attn_short_kernel<D>));
     else if constexpr (kOwn) kernel = reinterpret_cast<const void *>(&tree_attn_short_whole_kernel<D>);
-    else kernel = reinterpret_cast<const void *>(&tree_attn_short_kernel<D>);
+    else kernel = reinterpret_cast<const void *>(static_cast<void (*)(AttnParams)>(&tree_attn_short_kernel<D>));
     {
         static std::mutex guard;             // host threads may call in at the same time
         static bool allowed = false;
@@ -1024,9 +1034,10 @@ hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_st
     };
     if constexpr (kJoin && kOwn) return go(verify_short_join_whole_kernel<D>, "launch verify_short_join_whole_kernel", StepParams{*jp, p, *ap, *cp});
     else if constexpr (kJoin) return go(verify_short_join_kernel<D>, "launch verify_short_join_kernel", StepParams{*jp, p, *ap, *cp});
-    else if constexpr (kStep) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
+    else if constexpr (kStep && kWhole) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
+    else if constexpr (kStep) return go(static_cast<void (*)(StepParams)>(&tree_attn_short_kernel<D>), "launch tree_attn_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
     else if constexpr (kOwn) return go(tree_attn_short_whole_kernel<D>, "launch tree_attn_short_whole_kernel", p);
-    else return go(tree_attn_short_kernel<D>, "launch tree_attn_short_kernel", p);
+    else return go(static_cast<void (*)(AttnParams)>(&tree_attn_short_kernel<D>), "launch tree_attn_short_kernel", p);
 }
 
 template <int D>
@@ -1041,12 +1052,13 @@ hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_sta
         if (e != hipSuccess || !cp->k_tree) return e;      // (in-cache layout: the rows move in a launch of their own)
         return launch_kv_compact(*cp, stream);
     }
-    const hipError_t e = whole ? launch_main<D, false, false, true>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr)
-                               : launch_main<D, false, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
+    const hipError_t e = whole  ? launch_main<D, false, false, true>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr)
+                         : step ? launch_main<D, true, false, false>(p, stream, ev_start, ev_stop, ap, cp, nullptr)
+                                : launch_main<D, false, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
     if (e != hipSuccess || whole) return e;
     const int blocks = (p.M + 7) / 8 * (D / 64);           // of 8 rows x 8 chunks, four wavefronts
-    if (step) {
-        hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * blocks), dim3(256), 0, stream, p, *ap, *cp, blocks);
+    if (step && cp->k_tree) {                              // (in-cache layout: the rows move in a launch of their own)
+        hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * blocks), dim3(256), 0, stream, p, *cp, blocks);
         return note_hip_error("launch verify_tail_short_kernel", hipGetLastError());
     }
     hipLaunchKernelGGL(merge_short_kernel<D>, dim3(blocks, p.Hkv, p.B), dim3(256), 0, stream, p.workspace, p.out, p.n_splits, p.M, p.Hkv,

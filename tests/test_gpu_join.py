@@ -173,3 +173,53 @@ def test_what_is_refused_stays_refused(R, join, fault, in_cache, splits, tune):
         assert (dw.seq_lens.cpu().numpy() - w.seq_lens).tolist() == more
     for name in NAMES if got else ():
         assert torch.equal(got[0][name].view(torch.uint8), got[1][name].view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,T,lens,splits", [
+    (1, 2, 4, 128, 65, [700], 5), (3, 2, 2, 64, 128, [700, 0, 130], 4),            # two nodes per lane; shares without tiles
+    (2, 1, 1, 128, 1, [0, 300], 3), (2, 1, 1, 64, 1, [300, 0], 3),                 # a root alone
+    (33, 8, 1, 128, 12, [200] * 33, 2), (40, 8, 1, 64, 3, [150] * 40, 1)])         # cut and whole pairs of more workgroups than run at once
+@pytest.mark.parametrize("in_cache", [False, True])
+def test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B, Hkv, G, D, T, lens, splits, in_cache, tune):
+    # every result and the cache bit for bit, as a call and as replays of a captured graph
+    import torch
+    w = W.make_custom("rides_T%d_D%d" % (T, D), B=B, Hq=Hkv * G, Hkv=Hkv, D=D, T=T, seq_lens=lens, tree="trie" if T > 1 else "chain",
+                      depth=min(9, max(1, T - 1)), p_match=0.9, max_path=T, seed=760 + T + B)
+    if in_cache:
+        put_tree_in_cache(w)
+    bound = max(lens)
+    tune(R.TUNE_ATTN_SHORT, splits)
+    tune(R.TUNE_JOIN, 0)
+
+    def step(dw):
+        kt, vt = (None, None) if in_cache else (dw.k_tree, dw.v_tree)
+        R.reader_verify_step(dw.dims, dw.q, kt, vt, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents, dw.draft_tokens,
+                             dw.target_tokens, dw.out, dw.lse, dw.accept_len, dw.path, dw.bonus, bound, dw.workspace, dw.status)
+
+    dw = R.to_device(w)
+    kt, vt = (None, None) if in_cache else (dw.k_tree, dw.v_tree)
+    R.reader_tree_attn(dw.dims, dw.q, kt, vt, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents, dw.out, dw.lse, bound,
+                       dw.workspace, dw.status)
+    R.reader_accept_path(dw.dims, dw.draft_tokens, dw.target_tokens, dw.parents, dw.accept_len, dw.path, dw.bonus, dw.status)
+    if in_cache:
+        R.reader_kv_compact_layers(dw.dims, dw.path, dw.accept_len, dw.k_cache.unsqueeze(0), dw.v_cache.unsqueeze(0), dw.page_table,
+                                   dw.seq_lens, dw.status)
+    else:
+        R.reader_kv_compact(dw.dims, kt, vt, dw.path, dw.accept_len, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.status)
+    torch.cuda.synchronize()
+    want = {n: getattr(dw, n).clone() for n in NAMES}
+    dw = R.to_device(w)
+    first = {n: getattr(dw, n).clone() for n in NAMES}
+    graph = None
+    for turn in range(4):
+        for name in NAMES:
+            getattr(dw, name).copy_(first[name])
+        if turn == 1:
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                step(dw)
+        graph.replay() if graph else step(dw)
+        torch.cuda.synchronize()
+        for name in NAMES:
+            assert torch.equal(getattr(dw, name).view(torch.uint8), want[name].view(torch.uint8)), (turn, name)
