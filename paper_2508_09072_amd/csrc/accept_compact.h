@@ -166,6 +166,21 @@ __device__ inline void kv_compact_prefetch(const CompactParams &p, int b, int ti
     }
 }
 
+// Compaction in a launch behind the one that has chosen the path, by 256 threads: the path is fetched next to what
+// kv_compact_prefetch fetches, so that the next trip to memory is the rows'.
+struct AppendShared {
+    CompactShared compact;
+    int path[READER_MAX_T];
+};
+__device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, int n, const int *path, const CompactShared &cs);
+__device__ __forceinline__ void kv_append(const CompactParams &p, int b, int tid, AppendShared &sh) {
+    const int n = p.accept_len[b];
+    if (tid < p.max_path) sh.path[tid] = p.path[(size_t)b * p.max_path + tid];
+    kv_compact_prefetch(p, b, tid, sh.compact);
+    __syncthreads();
+    kv_compact_body(p, b, tid, n, sh.path, sh.compact);
+}
+
 // Called by all 256 threads of the workgroup, after kv_compact_prefetch and a barrier.
 // n = accept_len of the sequence, path = its accepted path (global or LDS).
 __device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, int n, const int *path,

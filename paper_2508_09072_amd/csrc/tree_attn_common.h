@@ -562,6 +562,18 @@ __device__ __forceinline__ void static_for(F &&f) {
 
 // What a range workgroup knows once it has found its place: its share [lo, hi) of the tile axis, where
 // to read page ids from while the list is written, and the clamped lengths in LDS (or null).
+// A part of a kernel's arguments, kOffset bytes into them, read where it is used: read at the kernel's entry, as the compiler
+// would, what is only needed behind the main loop sits in scalar registers all the way and pushes others out.
+template <typename T, size_t kOffset>
+__device__ __forceinline__ T late_argument() {
+    typedef const __attribute__((address_space(4))) char arg_char;
+    arg_char *at = (arg_char *)__builtin_amdgcn_kernarg_segment_ptr() + kOffset;
+    asm volatile("" : "+s"(at));
+    T t;
+    __builtin_memcpy(&t, (const char *)at, sizeof(T));
+    return t;
+}
+
 struct RangeSetup {
     TilePos lo, hi;
     const int32_t *table;

@@ -78,10 +78,17 @@ namespace reader {
 #define READER_STAMP(k, who) do { } while (0)
 #endif
 
+// Where the last of the kernel's arguments lies (read late).
+struct RingArgs {
+    AttnParams p;
+    const int32_t *page_table, *seq_lens;
+    AcceptParams accept;
+};
+
 template <int D, int RB>
 __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_attn_mfma_kernel(AttnParams p,
                                                                     const int32_t *__restrict__ page_table,
-                                                                    const int32_t *__restrict__ seq_lens) {
+                                                                    const int32_t *__restrict__ seq_lens, AcceptParams) {
     constexpr bool kDma = RB == 4;
     constexpr bool kLean = kDma && D == 64;          // two workgroups per compute unit, 128 registers per lane
     constexpr int CW = kDma ? 4 : 8;
@@ -161,7 +168,30 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
     int *s_len = rs.s_len;
     const int n_tiles = hi.flat - lo.flat;
     if (chunk_id == 0 && tid == 0) p.range_tiles[range_id] = n_tiles;
-    if (n_tiles <= 0) return;
+    // The fused step: workgroup w accepts a path for sequence w (and w + grid, ...), which reads tokens only and writes nothing
+    // that an attention launch reads.  Its first copying wavefront does it when the last tile has landed, in a stage that is
+    // idle then, while the others compute that tile and write their results.  In the launch behind this one, where it was before
+    // (and still is behind the 256-row kernels, whose wavefronts all compute), it stands in front of the append and makes
+    // that the longest job there: tail 7.4 -> 6.6 us, step of 16 sequences of 1 to 4 K positions and 32 nodes 47.35 -> 46.95, 34
+    // of 6.6 K and 36 nodes 163.0 -> 162.1.
+    const bool accepts = kDma && p.accepts && wave_s == 4;
+    auto accept = [&](int b, AcceptTokens tok, char *stage) {
+        AcceptShared &sh = *reinterpret_cast<AcceptShared *>(stage);
+        for (;;) {
+            const AcceptParams ap = late_argument<AcceptParams, offsetof(RingArgs, accept)>();
+            const AcceptNodes nodes = accept_stage(ap, lane, tok, sh);
+            int bits;
+            const int n = accept_choose(ap, lane, nodes, sh, bits);
+            accept_report(ap, b, lane, n, bits, sh);
+            if ((b += gridDim.x) >= p.B) break;
+            tok = accept_load(ap, b, lane);
+        }
+    };
+    if (n_tiles <= 0) {
+        if (accepts && (int)blockIdx.x < p.B)
+            accept(blockIdx.x, accept_load(late_argument<AcceptParams, offsetof(RingArgs, accept)>(), blockIdx.x, lane), ring);
+        return;
+    }
     READER_STAMP(kStampRange, 0);
     // items of the list: the tiles, and with dedicated copy wavefronts one query unit per segment
     // (one segment per pair the range touches)
@@ -809,6 +839,8 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
         int flags_2 = desc_flags(2);        // flags of item it + 2
         int d_blk = desc_of(kS - 1)->blk[cw];                                       // of item it + kS - 1,
         int2 d_nf = *reinterpret_cast<const int2 *>(&desc_of(kS - 1)->n_valid);    // the next one to ask for
+        const bool side = accepts && (int)blockIdx.x < p.B;
+        AcceptTokens tok;
         for (int it = 0; it < n_iter; ++it) {
             // This wavefront's part of item `it` has landed once at most its copies of the items
             // after it are outstanding (copies complete in the order they were issued).
@@ -837,7 +869,10 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
                 issue_known(cl, it + kS - 1, ring_lds + ((it + kS - 1) % kS) * G::kStageBytes, c_blk, c_valid, c_flags);
             }
             if (it == 8) READER_STAMP(kStampLoopIssued, 256);
+            // (behind the last copies: they are waited for together)
+            if (side && ahead == 1) tok = accept_load(late_argument<AcceptParams, offsetof(RingArgs, accept)>(), blockIdx.x, lane);
         }
+        if (side) accept(blockIdx.x, tok, ring + ((n_iter - 2) % kS) * G::kStageBytes);
     } else if (kDma) {
         // ---------------- wavefronts that only compute (RB = 4) ----------------
         int2 d_cur = *reinterpret_cast<const int2 *>(&desc_of(0)->n_valid);
@@ -1024,11 +1059,11 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnParams p) {
     merge_body<D>(p, blockIdx.z, blockIdx.x, blockIdx.y);
 }
 
-// Tail of the fused step: one workgroup per sequence that accepts a path and appends its rows
-// to the cache, then the merge blocks.  The three jobs touch disjoint data (the merge reads
+// Tail of the fused step: one workgroup per sequence that appends the rows of its path to the cache, and chooses that first where
+// the launch in front has not, then the merge blocks.  The three jobs touch disjoint data (the merge reads
 // the workspace and writes `out`; acceptance reads tokens; compaction writes cache slots past
 // the old lengths and the lengths themselves, which the merge does not read).
-template <int D>
+template <int D, bool kAccept>
 __global__ __launch_bounds__(256) void verify_tail_kernel(AttnParams p, AcceptParams ap, CompactParams cp,
                                                            int merge_blocks_y) {
     // the per-sequence workgroups come first in the grid: theirs is the longest chain of
@@ -1038,20 +1073,25 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(AttnParams p, AcceptPa
         merge_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks_y);
         return;
     }
-    __shared__ AcceptShared sh;
-    __shared__ CompactShared cs;
     const int b = blockIdx.x, tid = threadIdx.x;
-    // (in-cache layout, no tree tensors: the in-place move of the accepted rows follows as a launch of its own)
-    const bool append = cp.k_tree != nullptr;
-    if (append) kv_compact_prefetch(cp, b, tid, cs);   // on its way while the path is being chosen
-    if (tid < 64) accept_path_wave(ap, b, tid, sh);
-    if (!append) return;
-    __syncthreads();
-    kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
+    if constexpr (!kAccept) {
+        __shared__ AppendShared sh;
+        kv_append(cp, b, tid, sh);
+    } else {
+        __shared__ AcceptShared sh;
+        __shared__ CompactShared cs;
+        // (in-cache layout, no tree tensors: the in-place move of the accepted rows follows as a launch of its own)
+        const bool append = cp.k_tree != nullptr;
+        if (append) kv_compact_prefetch(cp, b, tid, cs);   // on its way while the path is being chosen
+        if (tid < 64) accept_path_wave(ap, b, tid, sh);
+        if (!append) return;
+        __syncthreads();
+        kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
+    }
 }
 
 template <int D, int RB>
-static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams &ap = {}) {
     using G = Geometry<D, RB == 4 ? 4 : 8>;
     const size_t pref_bytes = ((size_t)(p.B + 1) * sizeof(int) + 15) & ~(size_t)15;
     const size_t main_lds = (size_t)ring_stages(RB) * G::kStageBytes +
@@ -1074,10 +1114,10 @@ static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_
     // with events: they take the kernel's own start and end time stamps
     if (ev_start && ev_stop)
         hipExtLaunchKernelGGL((tree_attn_mfma_kernel<D, RB>), dim3(p.n_ranges * p.n_row_chunks), dim3(kThreads),
-                              main_lds, stream, ev_start, ev_stop, 0, p, p.page_table, p.seq_lens);
+                              main_lds, stream, ev_start, ev_stop, 0, p, p.page_table, p.seq_lens, ap);
     else
         hipLaunchKernelGGL((tree_attn_mfma_kernel<D, RB>), dim3(p.n_ranges * p.n_row_chunks), dim3(kThreads),
-                           main_lds, stream, p, p.page_table, p.seq_lens);
+                           main_lds, stream, p, p.page_table, p.seq_lens, ap);
     return note_hip_error("launch tree_attn_mfma_kernel", hipGetLastError());
 }
 
@@ -1086,9 +1126,10 @@ template <int D>
 static hipError_t launch_tail(const AttnParams &p, hipStream_t stream, const AcceptParams *ap, const CompactParams *cp) {
     const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
     const int merge_y = p.merge_groups == 4 ? units : (units + 3) / 4;
-    if (ap && cp) {
+    if (ap && cp && (!p.accepts || cp->k_tree)) {
         const int n_merge = p.B * p.Hkv * merge_y;
-        hipLaunchKernelGGL(verify_tail_kernel<D>, dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
+        if (p.accepts) hipLaunchKernelGGL((verify_tail_kernel<D, false>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
+        else hipLaunchKernelGGL((verify_tail_kernel<D, true>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
         return note_hip_error("launch verify_tail_kernel", hipGetLastError());
     }
     hipLaunchKernelGGL(tree_attn_merge_kernel<D>, dim3(p.Hkv, merge_y, p.B), dim3(256), 0, stream, p);
@@ -1100,7 +1141,12 @@ hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEve
     if (p.n_splits > 0) return launch_tree_attn_short(p, stream, ev_start, ev_stop, ap, cp, jp);
     hipError_t e;
     if (p.rows_per_wg == 128) {
-        e = p.D == 64 ? launch_mfma<64, 4>(p, stream, ev_start, ev_stop) : launch_mfma<128, 4>(p, stream, ev_start, ev_stop);
+        AttnParams q = p;
+        q.accepts = ap && cp;
+        const AcceptParams accept = q.accepts ? *ap : AcceptParams();
+        e = p.D == 64 ? launch_mfma<64, 4>(q, stream, ev_start, ev_stop, accept) : launch_mfma<128, 4>(q, stream, ev_start, ev_stop, accept);
+        if (e != hipSuccess) return e;
+        return p.D == 64 ? launch_tail<64>(q, stream, ap, cp) : launch_tail<128>(q, stream, ap, cp);
     } else if (p.wide) {
         // Four wavefronts of 64 rows with a softmax reference that is fixed per segment; a workgroup whose
         // scores outgrew that reference says so, and the kernel that moves its reference (eight wavefronts of

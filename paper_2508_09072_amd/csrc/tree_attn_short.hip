@@ -242,24 +242,13 @@ __device__ __forceinline__ void merge_share_again(const AttnParams &p, int b, in
     for (int u = first + s * 8 + wave; u < end; u += step) merge_rows<D, true, 1, 1, true>(p, b, hkv, u, step, end);
 }
 
-// The argument of the fused step's kernels, and a part of it read where it is used: read at the kernel's entry, as the compiler
-// would, what is only needed behind the main loop sits in scalar registers all the way and pushes others out.
+// The argument of the fused step's kernels (parts of it are read where they are used: late_argument).
 struct StepParams {
     JoinParams join;           // (of the launch that waits inside)
     AttnParams attn;
     AcceptParams accept;
     CompactParams compact;
 };
-template <typename T, size_t kOffset>
-__device__ __forceinline__ T late_argument() {
-    typedef const __attribute__((address_space(4))) char arg_char;
-    arg_char *at = (arg_char *)__builtin_amdgcn_kernarg_segment_ptr() + kOffset;
-    asm volatile("" : "+s"(at));
-    T t;
-    __builtin_memcpy(&t, (const char *)at, sizeof(T));
-    return t;
-}
-
 // This launch's marks in the workspace header: of every workgroup that works on a share whether its part of the records is
 // written, and whether it reads nothing of the cache and the lengths any more; of those that keep a sequence's cache whether
 // they have left, and whether any of them has.
@@ -990,14 +979,8 @@ __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, Co
         merge_block<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks);
         return;
     }
-    __shared__ CompactShared cs;
-    __shared__ int s_path[READER_MAX_T];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int n = cp.accept_len[b];
-    if (tid < cp.max_path) s_path[tid] = cp.path[(size_t)b * cp.max_path + tid];   // (all of it: the next trip to memory is the rows')
-    kv_compact_prefetch(cp, b, tid, cs);
-    __syncthreads();
-    kv_compact_body(cp, b, tid, n, s_path, cs);
+    __shared__ AppendShared sh;
+    kv_append(cp, blockIdx.x, threadIdx.x, sh);
 }
 
 template <int D, bool kStep, bool kJoin, bool kWhole>

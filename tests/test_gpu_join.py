@@ -178,7 +178,9 @@ def test_what_is_refused_stays_refused(R, join, fault, in_cache, splits, tune):
 @pytest.mark.parametrize("B,Hkv,G,D,T,lens,splits", [
     (1, 2, 4, 128, 65, [700], 5), (3, 2, 2, 64, 128, [700, 0, 130], 4),            # two nodes per lane; shares without tiles
     (2, 1, 1, 128, 1, [0, 300], 3), (2, 1, 1, 64, 1, [300, 0], 3),                 # a root alone
-    (33, 8, 1, 128, 12, [200] * 33, 2), (40, 8, 1, 64, 3, [150] * 40, 1)])         # cut and whole pairs of more workgroups than run at once
+    (33, 8, 1, 128, 12, [200] * 33, 2), (40, 8, 1, 64, 3, [150] * 40, 1),          # cut and whole pairs of more workgroups than run at once
+    (3, 2, 4, 128, 65, [700, 0, 130], 0), (5, 1, 16, 64, 45, [900, 64, 0, 1, 65], 0),   # the ring kernels: two and six chunks of 128 rows
+    (1, 1, 1, 128, 1, [0], 0), (300, 2, 1, 64, 5, [40] * 300, 0)])                 # ranges without tiles; more sequences than workgroups
 @pytest.mark.parametrize("in_cache", [False, True])
 def test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B, Hkv, G, D, T, lens, splits, in_cache, tune):
     # every result and the cache bit for bit, as a call and as replays of a captured graph
@@ -190,6 +192,7 @@ def test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B
     bound = max(lens)
     tune(R.TUNE_ATTN_SHORT, splits)
     tune(R.TUNE_JOIN, 0)
+    assert splits > 0 or R.reader_attn_plan(R.make_dims(w.B, w.T, w.Hq, w.Hkv, w.D, w.max_pages, w.max_path, w.num_pages), bound)["rows_per_workgroup"] == 128
 
     def step(dw):
         kt, vt = (None, None) if in_cache else (dw.k_tree, dw.v_tree)
