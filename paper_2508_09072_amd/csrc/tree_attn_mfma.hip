@@ -5,7 +5,7 @@
 //   prefix tiles (paged cache, mask-free except for the ragged last one), then the
 //   tree tiles (the T tree rows, masked by ancestor-or-self bit masks held in LDS).
 //   All tiles of all pairs form one flat axis.  The grid has n_ranges workgroups per
-//   chunk of query rows, one per compute unit; a workgroup streams a contiguous range of
+//   chunk of query rows, one per compute unit (two with 128 rows at head dimension 64); a workgroup streams a contiguous range of
 //   the axis, cut so that every range costs the same (a tile counts one, the start of a
 //   pair a few more), whatever the ragged sequence lengths are.  A range may cover several
 //   whole pairs and at most one pair at each end in part.  Whole pairs are finished
