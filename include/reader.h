@@ -197,8 +197,8 @@ int reader_tree_attn(const reader_dims *dims,
  *
  *  - Dims whose reader_workspace_bytes(dims, max_seq_len) exceeds READER_NOALLOC_WORKSPACE_BYTES
  *    are refused with READER_EWORKSPACE (reader_last_error_detail says by how much).  The planner
- *    keeps key ranges x row chunks within the number of compute units (within twice that at head
- *    dimension 64), so the records never need more than 35.7 MB and the limit covers every shape with B * Hkv up to about 600,000 (the
+ *    keeps key ranges x row chunks within the number of compute units, so the records never need
+ *    more than 34.7 MB and the limit covers every shape with B * Hkv up to about 600,000 (the
  *    header holds 8 bytes per (sequence, kv head)); more ranges forced with
  *    reader_tuning_override can exceed it.
  *  - All calls on one GPU share that GPU's workspace: calls that may overlap in time (different
@@ -524,7 +524,7 @@ int reader_measure_peaks(const void *src, size_t src_bytes, void *scratch, size_
  * with a negative value.  Every choice gives the same results up to rounding; only the speed
  * and the code path differ.  Stored atomically: a call sees the old or the new value.
  *   READER_TUNE_ATTN_ROWS       128 or 256 query rows per workgroup (other values: planner decides)
- *   READER_TUNE_ATTN_RANGES     >= 1 key ranges asked for (capped at the number of compute units; at twice that with 128 rows at head dimension 64)
+ *   READER_TUNE_ATTN_RANGES     >= 1 key ranges asked for (capped at the number of compute units)
  *   READER_TUNE_ATTN_PAIR_COST  0..64 tile times booked per pair beyond its tiles
  *   READER_TUNE_ATTN_PAIR_FRONT how many of them are booked to the workgroup that starts the pair (the rest to
  *                               the one that finishes it); capped at the pair cost

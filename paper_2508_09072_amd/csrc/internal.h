@@ -34,7 +34,7 @@ struct AttnParams {
     float *lse;
     float *workspace;  // partial records, see attn_slot_floats() (behind the header, see attn_header_bytes())
     int32_t *pair_info;      // header: per (sequence, kv head) the first and the last workgroup that hold its tiles
-    int32_t *range_tiles;    // header: per range workgroup the number of tiles it holds (0: it wrote no record); with more than kNumCU of them in `redo`
+    int32_t *range_tiles;    // header: per range workgroup the number of tiles it holds (0: it wrote no record)
     int32_t *redo;           // header: per workgroup of the wide kernel 1 if its range has to be computed again (kMaxAttnWorkgroups entries)
                              // (a fused step that waits inside its launch keeps its marks in these three arrays: arrivals.h)
 #ifdef READER_WG_STAMPS
@@ -116,8 +116,9 @@ __host__ __device__ inline size_t attn_header_bytes(int B, int Hkv) {
     return ((size_t)kNumCU * 4 + (size_t)kMaxAttnWorkgroups * 4 + (size_t)B * (size_t)Hkv * 8 + 255) & ~(size_t)255;
 }
 
-// Number of range workgroups the planner picks; a pure function of the dims and the size of the workspace.
-int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len, size_t workspace_bytes);
+// Number of range workgroups the planner picks; a pure function of the dims so that
+// reader_workspace_bytes and the launch agree.
+int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len);
 
 struct AcceptParams;
 struct CompactParams;

@@ -65,12 +65,10 @@ static int rows_per_wg_by_size(const reader_dims &d, int32_t max_seq_len) {
     if (M <= 128) return 128;
     const long long tiles_per_pair = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     const long long units = (long long)d.B * d.Hkv * tiles_per_pair;
-    // (Head dimension 64: two 128-row workgroups share a compute unit and win for twice as long, 16 sequences of 2 to 8 K with 256
-    // rows 44.5 -> 42.2 us, and would for longer: 64 of 0.3 to 3 K with 512 rows 197 -> 183, 64 of 2 to 8 K 485 -> 491.)
-    return units * ((M + 127) / 128) <= (d.D == 64 ? 20000 : 10000) ? 128 : 256;
+    return units * ((M + 127) / 128) <= 10000 ? 128 : 256;
 }
 
-static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows, int per_cu);
+static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows);
 static int attn_pair_cost(const reader_dims &d, int rows_per_wg);
 
 int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
@@ -105,16 +103,16 @@ int attn_rows_per_wg(const reader_dims &d, int32_t max_seq_len) {
     const long long pairs = (long long)d.B * d.Hkv, tiles = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     const bool odd = chunks == 3 || chunks == 5;
     const bool filled = M > 320 && M <= 384;
-    const bool cut_anyway = odd && d.B == 1 && pairs * (2 + attn_pair_cost(d, 128)) <= plan_ranges(d, max_seq_len, 128, 1);
+    const bool cut_anyway = odd && d.B == 1 && pairs * (2 + attn_pair_cost(d, 128)) <= plan_ranges(d, max_seq_len, 128);
     const long long most = chunks == 5 ? (cut_anyway ? 1000000 : 2500000) : cut_anyway && filled ? 2000000 : 6000000;
     if (odd && (d.D == 64 || (filled && !cut_anyway) || pairs * tiles <= most / tiles)) return 128;
     return rows_per_wg_by_size(d, max_seq_len);
 }
 
-static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows, int per_cu) {
+static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows) {
     // One range workgroup streams a contiguous run of 64-key tiles of the flattened
     // (sequence, kv head, tile) axis.  One workgroup (8 waves, ~150 KB of LDS) occupies a
-    // compute unit, or half of one (attn_wgs_per_cu), so at most 256 or 512 ranges; short problems get fewer so that a range holds
+    // compute unit, so at most 256 ranges; short problems get fewer so that a range holds
     // at least two tiles (what a workgroup spends before its first tile arrives is worth
     // several tiles, so tiny problems want many short ranges; measured), and when the rows
     // are cut into chunks, so few that all workgroups run at once: a second round of
@@ -124,12 +122,11 @@ static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows, int 
     long long tiles_per_pair = (max_seq_len + kTile - 1) / kTile + (d.T + kTile - 1) / kTile;
     long long units = (long long)d.B * d.Hkv * tiles_per_pair;
     long long n = forced > 0 ? forced : units / 2;
-    const int most = forced > 0 ? kNumCU : per_cu * kNumCU;
-    if (n > most) n = most;
+    if (n > kNumCU) n = kNumCU;
     const int M = d.T * (d.Hq / d.Hkv);
     if (forced <= 0) {
         const int chunks = (M + rows - 1) / rows;
-        if (chunks > 1 && n > most / chunks) n = most / chunks;
+        if (chunks > 1 && n > kNumCU / chunks) n = kNumCU / chunks;
     }
     if (n > units) n = units;
     if (n < 1) n = 1;
@@ -137,31 +134,16 @@ static int plan_ranges(const reader_dims &d, int32_t max_seq_len, int rows, int 
     return (int)n;
 }
 
+int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len) {
+    return plan_ranges(d, max_seq_len, attn_rows_per_wg(d, max_seq_len));
+}
+
 // Bytes set aside for partial records.  They follow from the sizes alone, whichever kernel the planner takes, and never
 // shrink as sequences or positions are added: a workspace that was sized for a program's largest step serves every
-// smaller one, also where that one is cut into more parts.  Every plan stays within them.  per_cu: workgroups per compute unit at
-// head dimension 64, 1 for what is accepted at least.
-static size_t record_bytes(const reader_dims &d, int32_t max_seq_len, int per_cu) {
+// smaller one, also where that one is cut into more parts.  Every plan stays within them.
+static size_t record_bytes(const reader_dims &d, int32_t max_seq_len) {
     const int rows = rows_per_wg_by_size(d, max_seq_len), chunks = (d.T * (d.Hq / d.Hkv) + rows - 1) / rows;
-    return 2 * (size_t)plan_ranges(d, max_seq_len, rows, d.D == 64 ? per_cu : 1) * chunks * attn_slot_floats(d.D, rows) * sizeof(float);
-}
-static size_t workspace_bytes_for(const reader_dims &d, int32_t max_seq_len, int per_cu);
-
-// Workgroups of the 128-row ring kernel that share a compute unit: two at head dimension 64, whose ring takes half the LDS and
-// whose computing wavefronts make do with 128 registers.  With one, a single computing wavefront per SIMD issues an
-// instruction every six or seven cycles and nothing fills the gaps, however its work is ordered (as a software pipeline over
-// the tiles it gained 3 %).  24 sequences of 0.3 to 3 K positions, 360 rows, 45.1 -> 37.5 us; 64 of 0.5 to 2 K, 320 rows,
-// 146 -> 115; 16 of 5 to 30 K, 320 rows, 96 -> 84; 16 of 4 to 16 K, 128 rows (bound by the copies) 89 -> 86.
-// One with so many sequences that their lengths take too much LDS, and with a workspace of the size that one needs (`have`).
-constexpr int kMaxBatchTwoPerCu = 340;
-static int attn_wgs_per_cu(const reader_dims &d, int32_t max_seq_len, int rows, size_t have) {
-    if (d.D != 64 || rows != 128 || d.B > kMaxBatchTwoPerCu) return 1;
-    return have >= workspace_bytes_for(d, max_seq_len, 2) ? 2 : 1;
-}
-
-int attn_plan_ranges(const reader_dims &d, int32_t max_seq_len, size_t have) {
-    const int rows = attn_rows_per_wg(d, max_seq_len);
-    return plan_ranges(d, max_seq_len, rows, attn_wgs_per_cu(d, max_seq_len, rows, have));
+    return 2 * (size_t)plan_ranges(d, max_seq_len, rows) * chunks * attn_slot_floats(d.D, rows) * sizeof(float);
 }
 
 static int attn_use_wide(const reader_dims &d, int rows_per_wg) {
@@ -241,13 +223,13 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     n = n > most ? most : n;
     n = n > tiles ? tiles : n;
     // (head dimension 64 would cut some row counts into more records than the workspace holds)
-    const long long held = (long long)(record_bytes(d, max_seq_len, 1) / (attn_slot_floats(d.D, s.rows) * sizeof(float)));
+    const long long held = (long long)(record_bytes(d, max_seq_len) / (attn_slot_floats(d.D, s.rows) * sizeof(float)));
     if (n > 1 && n * units > held) n = held / units;
     n = n < 1 ? 1 : n;
     if (tiles - (tiles + n - 1) / n < (d.D == 64 ? 6 : 4)) n = 1;
     {
         const int rows = attn_rows_per_wg(d, max_seq_len);
-        if ((tiles - 1) * plan_ranges(d, max_seq_len, rows, 1) < (long long)d.B * d.Hkv * (tiles + attn_pair_cost(d, rows))) n = 1;
+        if ((tiles - 1) * plan_ranges(d, max_seq_len, rows) < (long long)d.B * d.Hkv * (tiles + attn_pair_cost(d, rows))) n = 1;
     }
     if (forced >= 1) n = forced;
     const long long per = (tiles + n - 1) / n, rounds = n == 1 ? (units + fill - 1) / fill : 1;
@@ -265,16 +247,6 @@ static bool attn_plan_short(const reader_dims &d, int32_t max_seq_len, ShortPlan
     if (forced >= 1) return true;
     if (n > 1 && d.B > 1) return per <= (d.D == 64 ? 20 : 14) - (n == 2 ? 4 : 0);
     return (n == 1 && tiles <= 16) || per * rounds <= (d.D == 64 ? 24 : 20);
-}
-
-static size_t workspace_bytes_for(const reader_dims &d, int32_t max_seq_len, int per_cu) {
-    size_t bytes = record_bytes(d, max_seq_len, per_cu);
-    ShortPlan sp;
-    if (tuning(READER_TUNE_ATTN_SHORT) >= 1 && attn_plan_short(d, max_seq_len, sp) && sp.splits > 1) {
-        const size_t forced = (size_t)d.B * d.Hkv * sp.chunks * sp.splits * attn_slot_floats(d.D, sp.rows) * sizeof(float);
-        bytes = forced > bytes ? forced : bytes;
-    }
-    return attn_header_bytes(d.B, d.Hkv) + ((bytes + 255) & ~(size_t)255);
 }
 
 // Measurement hook state: event pairs recorded around the main attention kernel.
@@ -385,7 +357,13 @@ extern "C" size_t reader_workspace_bytes(const reader_dims *dims, int32_t max_se
     int err = 0;
     if (!dims_ok(dims, &err) || max_seq_len < 0) return 0;
     if (dims->B == 0) return 256;
-    return workspace_bytes_for(*dims, max_seq_len, 2);
+    size_t bytes = record_bytes(*dims, max_seq_len);
+    ShortPlan sp;
+    if (tuning(READER_TUNE_ATTN_SHORT) >= 1 && attn_plan_short(*dims, max_seq_len, sp) && sp.splits > 1) {
+        const size_t forced = (size_t)dims->B * dims->Hkv * sp.chunks * sp.splits * attn_slot_floats(dims->D, sp.rows) * sizeof(float);
+        bytes = forced > bytes ? forced : bytes;
+    }
+    return attn_header_bytes(dims->B, dims->Hkv) + ((bytes + 255) & ~(size_t)255);
 }
 
 extern "C" int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, reader_attn_plan_t *plan) {
@@ -404,7 +382,7 @@ extern "C" int reader_attn_plan(const reader_dims *dims, int32_t max_seq_len, re
     }
     plan->rows_per_workgroup = scalar ? 0 : attn_rows_per_wg(*dims, max_seq_len);
     plan->row_chunks = scalar ? 0 : row_chunks(*dims, max_seq_len);
-    plan->key_ranges = scalar ? 0 : attn_plan_ranges(*dims, max_seq_len, (size_t)-1);
+    plan->key_ranges = scalar ? 0 : attn_plan_ranges(*dims, max_seq_len);
     plan->kernel = scalar ? READER_ATTN_KERNEL_SCALAR
                           : plan->rows_per_workgroup == 128 ? READER_ATTN_KERNEL_ROWS128
                           : attn_use_wide(*dims, plan->rows_per_workgroup) ? READER_ATTN_KERNEL_ROWS256_WAVES4
@@ -426,8 +404,7 @@ extern "C" int reader_step_is_one_launch(const reader_dims *dims, int32_t max_se
 static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tree, const void *v_tree,
                         const void *k_cache, const void *v_cache, const int32_t *page_table,
                         const int32_t *seq_lens, const int32_t *parents, void *out, float *lse,
-                        int32_t max_seq_len, void *workspace, size_t workspace_bytes, int32_t *status, AttnParams &p, bool *empty,
-                        bool *one_launch = nullptr) {
+                        int32_t max_seq_len, void *workspace, int32_t *status, AttnParams &p, bool *empty, bool *one_launch = nullptr) {
     int err = 0;
     *empty = false;
     if (one_launch) *one_launch = false;
@@ -456,7 +433,7 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.n_tree_tiles = (dims->T + kTile - 1) / kTile;
     p.rows_per_wg = attn_rows_per_wg(*dims, max_seq_len);
     p.n_row_chunks = row_chunks(*dims, max_seq_len);
-    p.n_ranges = attn_plan_ranges(*dims, max_seq_len, workspace_bytes);
+    p.n_ranges = attn_plan_ranges(*dims, max_seq_len);
     {
         const bool wide = attn_use_wide(*dims, p.rows_per_wg);
         p.pair_cost = attn_pair_cost(*dims, p.rows_per_wg);
@@ -490,8 +467,6 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
         p.split_rcp = 1.0f / (float)sp.splits;
         if (one_launch) *one_launch = sp.join;
         p.keep_whole = sp.splits > 1 && tuning(READER_TUNE_ATTN_SHORT) < 1;   // (forced: every pair is cut as asked for)
-    } else if (p.n_ranges > kNumCU) {
-        p.range_tiles = p.redo;       // (room for as many; nothing is computed again there)
     }
 #ifdef READER_WG_STAMPS
     p.stamps = g_wg_stamps.load(std::memory_order_relaxed);
@@ -577,7 +552,7 @@ extern "C" int reader_tree_attn(const reader_dims *dims, const void *q, const vo
     AttnParams p;
     bool empty = false;
     const int rc = attn_prepare(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, out, lse,
-                                max_seq_len, workspace, workspace_bytes, status, p, &empty);
+                                max_seq_len, workspace, status, p, &empty);
     if (rc != READER_OK || empty) return rc;
     hipError_t e;
     if (dims->variant == 1) {
@@ -585,7 +560,7 @@ extern "C" int reader_tree_attn(const reader_dims *dims, const void *q, const vo
         e = launch_tree_attn_scalar(p, (hipStream_t)stream);
     } else {
         if (!workspace || ((uintptr_t)workspace & 255) != 0) return READER_EWORKSPACE;
-        if (workspace_bytes < workspace_bytes_for(*dims, max_seq_len, 1)) return READER_EWORKSPACE;
+        if (workspace_bytes < reader_workspace_bytes(dims, max_seq_len)) return READER_EWORKSPACE;
         hipEvent_t ev_a, ev_b;
         profile_next(&ev_a, &ev_b);
         forget_stale_error();
@@ -603,7 +578,7 @@ extern "C" int reader_tree_attn_noalloc(const reader_dims *dims, const void *q, 
     if (!dims_ok(dims, &err)) return err;
     if (max_seq_len < 0 || dims->variant != 0) return READER_EINVAL;
     // the size check comes first: a problem that does not fit is refused whatever the device's state
-    const size_t need = dims->B == 0 ? 0 : workspace_bytes_for(*dims, max_seq_len, 1);
+    const size_t need = reader_workspace_bytes(dims, max_seq_len);
     if (need > (size_t)READER_NOALLOC_WORKSPACE_BYTES) {
         snprintf(g_error_detail, sizeof g_error_detail,
                  "reader_tree_attn_noalloc: these dims need %zu bytes of workspace, the built-in one holds %zu", need,
@@ -616,7 +591,7 @@ extern "C" int reader_tree_attn_noalloc(const reader_dims *dims, const void *q, 
     AttnParams p;
     bool empty = false;
     const int rc = attn_prepare(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, out, lse,
-                                max_seq_len, ws, (size_t)READER_NOALLOC_WORKSPACE_BYTES, status, p, &empty);
+                                max_seq_len, ws, status, p, &empty);
     if (rc != READER_OK || empty) return rc;
     // Nothing in the workspace has to start at zero: every range workgroup writes its tile count and the
     // pair table afresh before the merge reads them, and a record slot is only read when this call's
@@ -634,12 +609,12 @@ extern "C" int reader_verify_step(const reader_dims *dims, const void *q, const 
     AttnParams p;
     bool empty = false, one_launch = false;
     const int rc = attn_prepare(dims, q, k_tree, v_tree, k_cache, v_cache, page_table, seq_lens, parents, out, lse,
-                                max_seq_len, workspace, workspace_bytes, status, p, &empty, &one_launch);
+                                max_seq_len, workspace, status, p, &empty, &one_launch);
     if (rc != READER_OK || empty) return rc;
     if (!draft_tokens || !target_tokens || !accept_len || !path || !bonus_token) return READER_EINVAL;
     if (dims->variant != 0) return READER_EINVAL;   // the fused step exists for the matrix-core kernel only
     if (!workspace || ((uintptr_t)workspace & 255) != 0) return READER_EWORKSPACE;
-    if (workspace_bytes < workspace_bytes_for(*dims, max_seq_len, 1)) return READER_EWORKSPACE;
+    if (workspace_bytes < reader_workspace_bytes(dims, max_seq_len)) return READER_EWORKSPACE;
     AcceptParams ap;
     CompactParams cp;
     accept_fill(dims, draft_tokens, target_tokens, parents, accept_len, path, bonus_token, status, ap);

@@ -413,7 +413,7 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 // How a partial record holds a row's outputs, normalised by the record's own sum.  Head dimension 128: bf16.
-// Head dimension 64, where two workgroups per compute unit cut twice as many pairs: 64 times the value in fp16, which rounds
+// Head dimension 64: 64 times the value in fp16, which rounds
 // eight times finer and so leaves the result of a cut pair as exact as that of a whole one (relative error against 64 bits
 // 2.3e-3 from the bf16 weights and the final rounding; 2.9e-3 with records in bf16), at the same size.  A row whose largest
 // output fp16 would not hold that well (outside 2^-14 to 2^9) has a unit of its own, a power of two: its sum is negative in
@@ -547,7 +547,6 @@ struct MergeState {
 __device__ inline s16x4 lds_read_tr16(const char *ptr) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(ptr));
 }
-__device__ inline s16x4 lds_read_tr16_at(unsigned lds) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)lds); }
 
 // f(integral_constant<int, 0>), f(integral_constant<int, 1>), ...: a loop the compiler sees as straight-line
 // code with compile-time indices (the fixed instruction order of a tile is written with it)

@@ -5,11 +5,11 @@
 //   prefix tiles (paged cache, mask-free except for the ragged last one), then the
 //   tree tiles (the T tree rows, masked by ancestor-or-self bit masks held in LDS).
 //   All tiles of all pairs form one flat axis.  The grid has n_ranges workgroups per
-//   chunk of query rows, one per compute unit (two with 128 rows at head dimension 64); a workgroup streams a contiguous range of
+//   chunk of query rows, one per compute unit; a workgroup streams a contiguous range of
 //   the axis, cut so that every range costs the same (a tile counts one, the start of a
 //   pair a few more), whatever the ragged sequence lengths are.  A range may cover several
 //   whole pairs and at most one pair at each end in part.  Whole pairs are finished
-//   in place; a pair cut between workgroups leaves one partial record (16-bit output
+//   in place; a pair cut between workgroups leaves one partial record (bf16 output
 //   normalised by its own sum, running max, running sum) per workgroup and a second
 //   kernel merges them.  When T*G exceeds what a workgroup carries, the query rows are cut
 //   into chunks, one workgroup per (range, chunk); the chunks of a range run at the same
@@ -86,11 +86,10 @@ struct RingArgs {
 };
 
 template <int D, int RB>
-__global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_attn_mfma_kernel(AttnParams p,
+__global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
                                                                     const int32_t *__restrict__ page_table,
                                                                     const int32_t *__restrict__ seq_lens, AcceptParams) {
     constexpr bool kDma = RB == 4;
-    constexpr bool kLean = kDma && D == 64;          // two workgroups per compute unit, 128 registers per lane
     constexpr int CW = kDma ? 4 : 8;
     using G = Geometry<D, CW>;
     constexpr int kRowsPerWG = 32 * RB;
@@ -133,28 +132,13 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
     const int cw = kDma ? (wave_s & 3) : wave_s;         // index among the copying wavefronts
     const int rb = kDma ? (wave_s & 3) : wave_s;         // row block of a computing wavefront
     const int htid = kDma ? tid - 256 : tid;             // index among the helper threads, negative: none
+    const int n = lane & 31, h = lane >> 5;
     const int chunk_base = chunk_id * kRowsPerWG;
-    // This lane's query row.  (At head dimension 64 it is worked out anew wherever it is needed, out of the compiler's sight:
-    // kept through the main loop it would push others out of the 128 registers.)
-    struct Row {
-        int local, node, group, n, h;                  // row inside this workgroup's chunk; tree node and grouped head of the query row
-        bool real;
-    };
-    auto my_row = [&]() __attribute__((always_inline)) {
-        int l = threadIdx.x;
-        if constexpr (kLean) asm volatile("" : "+v"(l));
-        l &= 63;
-        Row r;
-        r.n = l & 31;
-        r.h = l >> 5;
-        r.local = rb * 32 + r.n;
-        const int m_row = chunk_base + r.local;        // query row inside the pair
-        r.real = m_row < p.M;
-        // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
-        r.node = r.real ? (int)(((float)m_row + 0.5f) * p.g_rcp) : 0;
-        r.group = r.real ? m_row - r.node * p.G : 0;
-        return r;
-    };
+    const int row_local = rb * 32 + n;             // row inside this workgroup's chunk
+    const int m_row = chunk_base + row_local;      // query row inside the pair
+    const bool row_real = m_row < p.M;
+    const int node = row_real ? m_row / p.G : 0;   // tree node of this lane's query row
+    const int group = row_real ? m_row - node * p.G : 0;
     const bool wave_active = is_computer && chunk_base + rb * 32 < p.M;
 
     // Lengths -> tile counts -> this workgroup's share [lo, hi) of the tile axis; a small page table is
@@ -221,19 +205,17 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
     // This lane's query row as the B operand of the QK product.
     bf16x8 qf[G::kKSteps];
     auto load_q = [&](int b, int hkv) {
-        const Row r = my_row();
-        const uint16_t *qrow = p.q + (((size_t)b * p.T + r.node) * p.Hq + hkv * p.G + r.group) * D;
+        const uint16_t *qrow = p.q + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D;
 #pragma unroll
         for (int kk = 0; kk < G::kKSteps; ++kk)
-            qf[kk] = __builtin_bit_cast(bf16x8, keep_if(r.real, ld16(qrow + kk * 16 + r.h * 8)));
+            qf[kk] = __builtin_bit_cast(bf16x8, keep_if(row_real, ld16(qrow + kk * 16 + h * 8)));
     };
     // RB = 8: touch the next pair's query rows one tile before they are needed, so that they
     // wait in the cache: an LDS copy of 4 bytes per lane into a scratch area nobody reads.
     auto prefetch_q = [&](int b, int hkv) {
-        const Row r = my_row();
-        const uint16_t *qrow = p.q + (((size_t)b * p.T + r.node) * p.Hq + hkv * p.G + r.group) * D;
+        const uint16_t *qrow = p.q + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D;
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off"
-                     :: "v"(qrow + (r.h * 64) % D), "s"(prefetch_lds) : "memory", "m0");
+                     :: "v"(qrow + (h * 64) % D), "s"(prefetch_lds) : "memory", "m0");
     };
     // RB = 4: a query unit.  The copying wavefronts move the pair's query rows into a ring
     // stage (rows swizzled like a K tile, rows past the last one as zeros); the computing
@@ -260,11 +242,10 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
         }
     };
     auto read_q_stage = [&](const char *stage) {
-        const Row r = my_row();
 #pragma unroll
         for (int kk = 0; kk < G::kKSteps; ++kk)
-            qf[kk] = *reinterpret_cast<const bf16x8 *>(stage + r.local * G::kRowBytes +
-                                                       (((2 * kk + r.h) ^ swizzle_k<D>(r.local)) << 4));
+            qf[kk] = *reinterpret_cast<const bf16x8 *>(stage + row_local * G::kRowBytes +
+                                                       (((2 * kk + h) ^ swizzle_k<D>(row_local)) << 4));
     };
 
     // Parent pointers of a sequence into s_par[buf] (asynchronous, copying wavefronts 0 and 1),
@@ -403,18 +384,17 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
     if (!kDma || wave_active) load_q(desc_b(0), desc_hkv(0));
 
     // per-lane LDS offsets of the matrix-core operand reads (relative to the stage)
-    const int n = lane & 31, h = lane >> 5;
-    int k_rd[kLean ? 1 : G::kKSteps];   // K fragment of k-step kk, key block 0 (kLean: of the first; the others by exclusive or)
+    int k_rd[G::kKSteps];   // K fragment of k-step kk, key block 0
 #pragma unroll
-    for (int kk = 0; kk < (kLean ? 1 : G::kKSteps); ++kk)
+    for (int kk = 0; kk < G::kKSteps; ++kk)
         k_rd[kk] = n * G::kRowBytes + (((2 * kk + h) ^ swizzle_k<D>(n)) << 4);
-    int v_rd[kLean ? 1 : G::kOBlocks];  // V fragment of output block db, keys 0..3 (+4h) of the first 16-key group
+    int v_rd[G::kOBlocks];  // V fragment of output block db, keys 0..3 (+4h) of the first 16-key group
     {
         const int i16 = lane & 15, g16 = (lane >> 4) & 1;
         const int key_lo = 4 * h + (i16 >> 2);                       // key row inside an 8-key group
         const int c_lo = 2 * g16 + ((i16 & 3) >> 1);                 // 16-byte chunk inside the 32-wide d block
 #pragma unroll
-        for (int db = 0; db < (kLean ? 1 : G::kOBlocks); ++db)
+        for (int db = 0; db < G::kOBlocks; ++db)
             v_rd[db] = G::kTileBytes + key_lo * G::kRowBytes +
                        ((((db * 4) | c_lo) ^ swizzle_v<D>(key_lo)) << 4) + (i16 & 1) * 8;
     }
@@ -510,11 +490,10 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
         if (careful) {
             // ---- masks (ragged last prefix tile, tree tiles) ----
             if (is_tree) {
-                const Row row = my_row();
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
-                    uint32_t bits = row.real ? anc[row.node * 4 + tt * 2 + kb] : 0u;
-                    bits >>= 4 * row.h;
+                    uint32_t bits = row_real ? anc[node * 4 + tt * 2 + kb] : 0u;
+                    bits >>= 4 * h;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int r = (i >> 2) * 8 + (i & 3);    // + 4h, already shifted out
@@ -580,138 +559,6 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
         }
     };
 
-    // The same at head dimension 64, where two workgroups share a compute unit and a wavefront has 128 registers: two ways
-    // through the tile that share nothing.  The fast one forgets the scores as it turns them into weights; a tile that needs care is
-    // (also if that shows only then) worked out from its keys.
-    auto compute_tile_lean = [&](unsigned stage_lds, int flags, int n_valid) {
-        const unsigned k_at = stage_lds + k_rd[0], v_at = stage_lds + v_rd[0];
-        typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
-        f32x16 sc[2];
-        uint32_t w[2][8];
-        auto scores = [&]() __attribute__((always_inline)) {
-            bf16x8 ka[G::kKSteps][2];
-#pragma unroll
-            for (int kk = 0; kk < G::kKSteps; ++kk) {
-                // (stages start at multiples of a kilobyte: a k-step flips bits of the chunk within the row)
-                const unsigned at = k_at ^ (kk << 5);
-                ka[kk][0] = *(lds_bf16x8 *)at;
-                ka[kk][1] = *(lds_bf16x8 *)(at + 32 * G::kRowBytes);
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) { sc[0][i] = 0.f; sc[1][i] = 0.f; }
-#pragma unroll
-            for (int kk = 0; kk < G::kKSteps; ++kk) {
-                sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][0], qf[kk], sc[0], 0, 0, 0);
-                sc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][1], qf[kk], sc[1], 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-            for (int j = 0; j < 2 * G::kKSteps - 4; ++j) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-        };
-        auto weights = [&]() __attribute__((always_inline)) {
-            const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
-            float lsum0 = 0.f, lsum1 = 0.f;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 16; i += 2) {
-                    const float p0 = __builtin_amdgcn_exp2f(sc[kb][i] * c2 - mc);
-                    const float p1 = __builtin_amdgcn_exp2f(sc[kb][i + 1] * c2 - mc);
-                    lsum0 += p0;
-                    lsum1 += p1;
-                    w[kb][i >> 1] = pack_bf16x2(p0, p1);
-                    asm volatile("" : "+v"(w[kb][i >> 1]));      // (packed here: put off, all 32 of them stay as floats)
-                }
-            return lsum0 + lsum1;
-        };
-        auto products = [&]() __attribute__((always_inline)) {
-            s16x4 vh[2][G::kOBlocks][2];
-            auto read_v_step = [&](int ks) {
-#pragma unroll
-                for (int db = 0; db < G::kOBlocks; ++db) {
-                    const unsigned at = (v_at ^ (db << 6)) + ks * 16 * G::kRowBytes;
-                    vh[ks & 1][db][0] = lds_read_tr16_at(at);
-                    vh[ks & 1][db][1] = lds_read_tr16_at(at + 8 * G::kRowBytes);
-                }
-            };
-            read_v_step(0);
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                if (ks + 1 < 4) read_v_step(ks + 1);
-                const int kb = ks >> 1, m2 = ks & 1;
-                u32x4 pv;
-                pv.x = w[kb][4 * m2]; pv.y = w[kb][4 * m2 + 1]; pv.z = w[kb][4 * m2 + 2]; pv.w = w[kb][4 * m2 + 3];
-#pragma unroll
-                for (int db = 0; db < G::kOBlocks; ++db) {
-                    const s16x8 a8 = __builtin_shufflevector(vh[ks & 1][db][0], vh[ks & 1][db][1], 0, 1, 2, 3, 4, 5, 6, 7);
-                    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a8), __builtin_bit_cast(bf16x8, pv), o[db], 0, 0, 0);
-                }
-            }
-        };
-        const int holes = (flags & kDescHoles) ? (flags >> 8) & 15 : 0;   // quarters of a prefix tile to skip
-        if (!((flags & (kDescTree | kDescFresh | kDescHoles)) || n_valid < kTile)) {
-            scores();
-            const float lsum = weights();
-            if (!__any(!(lsum < 0x1p40f))) {
-                l_run += lsum;
-                products();
-                return;
-            }
-        }
-        asm volatile("" ::: "memory");      // (nothing of the above is kept for what follows)
-        scores();
-        // which keys this lane's row attends to; score i of block kb is key (i / 4) * 8 + 4 h + i % 4 of the block
-        const Row row = my_row();
-        uint32_t bits[2] = {0xffffffffu, 0xffffffffu};
-        if (flags & kDescTree) {
-            const int tt = flags >> 8;
-            bits[0] = row.real ? anc[row.node * 4 + tt * 2] : 0u;
-            bits[1] = row.real ? anc[row.node * 4 + tt * 2 + 1] : 0u;
-        } else {
-            if (n_valid < kTile) {
-                bits[0] = n_valid >= 32 ? 0xffffffffu : (1u << n_valid) - 1u;
-                bits[1] = n_valid <= 32 ? 0u : (1u << (n_valid - 32)) - 1u;
-            }
-            bits[0] &= (holes & 1 ? 0xffff0000u : 0xffffffffu) & (holes & 2 ? 0x0000ffffu : 0xffffffffu);
-            bits[1] &= (holes & 4 ? 0xffff0000u : 0xffffffffu) & (holes & 8 ? 0x0000ffffu : 0xffffffffu);
-        }
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const uint32_t mine = bits[kb] >> (4 * row.h);
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (!((mine >> ((i >> 2) * 8 + (i & 3))) & 1u)) sc[kb][i] = -INFINITY;
-        }
-        float mx0 = fmaxf(sc[0][0], sc[0][1]), mx1 = fmaxf(sc[1][0], sc[1][1]);
-#pragma unroll
-        for (int i = 2; i < 16; i += 2) {
-            mx0 = fmaxf(fmaxf(mx0, sc[0][i]), sc[0][i + 1]);
-            mx1 = fmaxf(fmaxf(mx1, sc[1][i]), sc[1][i + 1]);
-        }
-        float mx = fmaxf(mx0, mx1);
-        {   // the other half of the row's keys sits in lane ^ 32
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        }
-        const bool grow = (mx - m_run) * c2 > 8.f;      // also the first finite maximum (m_run = -inf)
-        if (__any(grow)) {
-            const float alpha = grow ? __builtin_amdgcn_exp2f((m_run - mx) * c2) : 1.f;   // m_run = -inf gives 0
-            m_run = grow ? mx : m_run;
-            l_run *= alpha;
-#pragma unroll
-            for (int db = 0; db < G::kOBlocks; ++db)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
-        }
-        l_run += weights();
-        if (holes) m_run = fmaxf(m_run, -1e30f);        // (a finite reference, as above)
-        products();
-    };
-
     auto reset_state = [&](int flags) {
         seg_from_pair_start = (flags & kDescPairStart) != 0;
         m_run = -INFINITY;
@@ -727,14 +574,7 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
     // a partial record for the merge kernel.
     auto finish_segment = [&](int it, bool pair_ends) {
         const int e_b = desc_b(it), e_hkv = desc_hkv(it);
-        const Row row = my_row();
-        const int node = row.node, group = row.group, row_local = row.local, h = row.h;
-        const bool row_real = row.real;
-        float l_tot;
-        {   // the other half of the row's keys sits in lane ^ 32
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-            l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-        }
+        const float l_tot = l_run + __shfl_xor(l_run, 32);
         if (seg_from_pair_start && pair_ends) {
             // A lane holds, per 8-wide chunk of the output row, 4 values and its partner lane
             // (lane ^ 32) the other 4.  One half-wave swap per pair of chunks gives every lane
@@ -897,8 +737,7 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
                 if (t_flags & kDescMasks) { anc = s_anc + (gen_use & 1) * READER_MAX_T * 4; ++gen_use; }
             }
             if (wave_active) {
-                if constexpr (kLean) compute_tile_lean((unsigned)(size_t)(lds_char *)const_cast<char *>(stage), t_flags, t_valid);
-                else compute_tile(stage, t_flags, t_valid);
+                compute_tile(stage, t_flags, t_valid);
                 if (it == 1) READER_STAMP(kStampTileDone, 0);
                 if (last_iter) READER_STAMP(kStampLastTile, 0);
                 if (pair_ends || last_iter) finish_segment(it, pair_ends);
@@ -969,8 +808,7 @@ __global__ __launch_bounds__(kThreads, D == 64 && RB == 4 ? 4 : 2) void tree_att
             };
             if (wave_active) {
                 if (wave_s >= 4) copy_all();
-                if constexpr (kLean) compute_tile_lean((unsigned)(size_t)(lds_char *)const_cast<char *>(stage), t_flags, t_valid);
-                else compute_tile(stage, t_flags, t_valid);
+                compute_tile(stage, t_flags, t_valid);
                 if (wave_s < 4) copy_all();
                 if (last_iter) READER_STAMP(kStampLastTile, 0);
                 if (pair_ends || last_iter) finish_segment(it, pair_ends);

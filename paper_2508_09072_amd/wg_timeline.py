@@ -108,8 +108,7 @@ def main():
 
     plan = R.reader_attn_plan(dw.dims, dw.max_seq_len)
     short = plan["kernel_id"] == 4                                       # (its workgroups leave no tile counts)
-    first = 0 if plan["key_ranges"] <= 256 else 256 * 4                  # tiles per range: first words of the workspace, or the next
-    ranges = dw.workspace[first:first + 512 * 4].view(torch.int32).cpu().numpy()
+    ranges = dw.workspace[:256 * 4].view(torch.int32).cpu().numpy()    # tiles per range, first words of the workspace
     use = rows[len(rows) // 2:]                                          # the second half of the launches
     n_wg = int((use[0][:, 0] != 0).sum())
     joined = args.step and R.reader_step_is_one_launch(dw.dims, dw.max_seq_len)

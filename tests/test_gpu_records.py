@@ -1,5 +1,5 @@
 """Partial records of cut pairs (at head dimension 64 fp16 in a common unit, or a row's own where its values are too large or too
-small for that), and how many of them a launch leaves."""
+small for that)."""
 import numpy as np
 import pytest
 
@@ -65,34 +65,3 @@ def test_a_cut_pair_is_as_exact_as_a_whole_one(R, oracle_mod, rows, T, tune):
         err.append(np.linalg.norm(out - ref) / np.linalg.norm(ref))
     print("whole %.4e, cut %.4e" % tuple(err), flush=True)
     assert err[1] <= 1.04 * err[0]
-
-
-@pytest.mark.parametrize("B", [6, 341])
-def test_head_dim_64_with_one_and_with_two_workgroups_per_compute_unit(R, oracle_mod, B, tune):
-    # two, as planned; one, with a workspace that holds no more records, or with more sequences than two have LDS for; less than
-    # one needs is refused
-    import torch
-    tune(R.TUNE_ATTN_SHORT, 0)
-    rng = np.random.default_rng(7)
-    lens = [int(x) for x in (rng.integers(900, 4000, B) if B < 100 else rng.integers(150, 230, B))]
-    w = W.make_custom("per_cu_%d" % B, B=B, Hq=16, Hkv=8, D=64, T=20, seq_lens=lens, tree="trie", depth=6, seed=532)
-    dw = R.to_device(w)
-    bound = max(lens)
-    full = R.reader_workspace_bytes(dw.dims, bound)
-    header = -(-(256 * 4 + 2048 * 4 + B * 8 * 8) // 256) * 256
-    assert R.reader_attn_plan(dw.dims, bound)["key_ranges"] == (512 if B < 100 else 256)
-    ref, ref_lse = oracle_mod.tree_attn(w.q, w.k_tree, w.v_tree, w.k_cache, w.v_cache, w.page_table, w.seq_lens, w.parents)
-    outs = []
-    for size in (full, header + (full - header) // 2):
-        ws = torch.full((size,), 0x7F, dtype=torch.uint8, device="cuda")
-        dw.out.fill_(float("nan"))
-        R.reader_tree_attn(dw.dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
-                           dw.out, dw.lse, bound, ws, dw.status)
-        torch.cuda.synchronize()
-        outs.append(bf16_to_np(dw.out))
-        assert_close(outs[-1], ref, what="%d bytes" % size)
-        assert_close(dw.lse.cpu().numpy(), ref_lse, what="%d bytes, lse" % size)
-    assert np.array_equal(outs[0], outs[1]) == (B > 100)
-    with pytest.raises(RuntimeError):
-        R.reader_tree_attn(dw.dims, dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, dw.page_table, dw.seq_lens, dw.parents,
-                           dw.out, dw.lse, bound, ws[:-256], dw.status)

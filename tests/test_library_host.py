@@ -131,6 +131,21 @@ def test_records_fit_the_calls_own_workspace_on_every_route(R):
     assert {(128, 3, 2), (128, 3, 3), (64, 2, 2), (64, 2, 4)} <= met
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_one_workgroup_per_compute_unit_and_no_smaller_workspace_is_taken(R, D):
+    # the cut, and with it the bits of the result, follows from the sizes alone: not from how much workspace a call brings
+    one, lib, rng = ctypes.c_void_p(256), R.load(), np.random.default_rng(22)     # (pointers never dereferenced: the size is checked first)
+    for _ in range(300):
+        Hkv, G, T = int(rng.choice((1, 2, 4, 8))), int(rng.choice((1, 4, 8, 16))), int(rng.integers(1, 129))
+        d = R.make_dims(int(2 ** rng.uniform(0, 8)), T, G * Hkv, Hkv, D, 1 << 11, 1, 1 << 18)
+        L = int(2 ** rng.uniform(5, 14))
+        plan = R.reader_attn_plan(d, L)
+        assert plan["kernel_id"] == 4 or plan["key_ranges"] * plan["row_chunks"] <= 256, plan
+        less = R.reader_workspace_bytes(d, L) - 1
+        assert lib.reader_tree_attn(ctypes.byref(d), *[one] * 9, None, L, one, less, None, None) == R.READER_EWORKSPACE
+        assert lib.reader_verify_step(ctypes.byref(d), *[one] * 11, None, one, one, one, L, one, less, None, None) == R.READER_EWORKSPACE
+
+
 @pytest.mark.parametrize("B,T,Hq,Hkv,D,bound,short", [
     (16, 16, 32, 8, 128, 1200, True), (16, 16, 32, 8, 128, 1400, False), (16, 16, 32, 8, 128, 2400, False),   # two shares: 10 tiles, 12, 20
     (8, 16, 32, 8, 128, 3500, True), (8, 16, 32, 8, 128, 3700, False), (32, 64, 8, 2, 128, 2400, False),       # four: 14, 15; two: 20
