@@ -124,7 +124,7 @@ def timed_kernel(R, w, fused):
            "rows_per_workgroup": plan["rows_per_workgroup"], "whole_step": False}
     if fused and R.reader_step_is_one_launch(dims, bound):
         units, shares = w.B * w.Hkv * plan["row_chunks"], plan["key_ranges"] // (w.B * w.Hkv)
-        res.update(kernel="verify_short_join_%skernel<%d>" % ("whole_" if w.D == 64 and shares == 1 else "", w.D), workgroups=(units + 7) // 8 * 8 * shares + w.B, whole_step=True)
+        res.update(kernel="verify_short_join_kernel<%d>" % w.D, workgroups=(units + 7) // 8 * 8 * shares + w.B, whole_step=True)
     elif fused and plan["kernel_id"] == 4 and plan["key_ranges"] == w.B * w.Hkv:
         res["kernel"] = "verify_short_kernel<%d>" % w.D   # (whole pairs: acceptance rides along, as it does where pairs are cut, under that kernel's name)
     return res

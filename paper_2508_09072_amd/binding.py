@@ -216,10 +216,7 @@ def reader_attn_plan(dims: ReaderDims, max_seq_len: int) -> dict:
     """Kernel, rows per workgroup, row chunks and key ranges reader_tree_attn would use (host only)."""
     plan = ReaderAttnPlan()
     _check(load().reader_attn_plan(ctypes.byref(dims), int(max_seq_len), ctypes.byref(plan)), "reader_attn_plan")
-    name = ATTN_KERNEL_NAMES[int(plan.kernel)].replace("D", str(int(dims.D)))
-    if plan.kernel == 4 and dims.D == 64 and plan.key_ranges == dims.B * dims.Hkv:      # (whole pairs have a kernel of their own there)
-        name = name.replace("short", "short_whole")
-    return {"kernel": name, "kernel_id": int(plan.kernel),
+    return {"kernel": ATTN_KERNEL_NAMES[int(plan.kernel)].replace("D", str(int(dims.D))), "kernel_id": int(plan.kernel),
             "rows_per_workgroup": int(plan.rows_per_workgroup), "row_chunks": int(plan.row_chunks),
             "key_ranges": int(plan.key_ranges)}
 

@@ -75,8 +75,8 @@ struct JoinParams {
     int32_t spread;             // tests: 1 = a pair's shares run on different XCDs, one behind the other
 };
 
-// Size of one partial record in 4-byte units: `rows` rows of D bf16 outputs (fp16 at head dimension 64; normalised
-// by the record's own sum), then the rows' running maxima and running sums as fp32.
+// Size of one partial record in 4-byte units: `rows` rows of D bf16 outputs (normalised by the
+// record's own sum), then the rows' running maxima and running sums as fp32.
 __host__ __device__ constexpr size_t attn_slot_floats(int D, int rows) { return (size_t)rows * (size_t)(D / 2 + 2); }
 
 // The workspace starts with a header the main kernel leaves for the kernels after it: one int per

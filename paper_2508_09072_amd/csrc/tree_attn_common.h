@@ -412,75 +412,6 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
-// How a partial record holds a row's outputs, normalised by the record's own sum.  Head dimension 128: bf16.
-// Head dimension 64: 64 times the value in fp16, which rounds
-// eight times finer and so leaves the result of a cut pair as exact as that of a whole one (relative error against 64 bits
-// 2.3e-3 from the bf16 weights and the final rounding; 2.9e-3 with records in bf16), at the same size.  A row whose largest
-// output fp16 would not hold that well (outside 2^-14 to 2^9) has a unit of its own, a power of two: its sum is negative in
-// the record and has the unit's exponent in place of its own, which is added to the reference beside it.
-constexpr bool fine_records(int d) { return d == 64; }
-constexpr float kRecordUnit = 1.f / 64.f;
-__device__ inline bool record_row_fits(float biggest) {    // of the outputs over kRecordUnit (undefined: no)
-    return (biggest >= 0x1p-8f && biggest < 0x1p15f) || biggest == 0.f;
-}
-__device__ inline uint32_t pack_f16x2(float lo, float hi) {
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    f16x2 v;
-    v[0] = (_Float16)lo;
-    v[1] = (_Float16)hi;
-    return __builtin_bit_cast(uint32_t, v);
-}
-// (one instruction, where the compiler would first quiet both operands with two more: 96 of them at the end of every share took 0.8 us)
-__device__ inline float max_abs(float biggest, float a, float b) {
-    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(biggest) : "v"(a), "v"(b));
-    return biggest;
-}
-__device__ inline float finite_abs(float x) { return fabsf(x) < INFINITY ? fabsf(x) : 0.f; }
-// over the two lanes of a row (lane ^ 32)
-__device__ inline float max_of_row(float x) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-}
-// A row that does not fit, whose largest finite output is `biggest`: reference and sum as they go into the record.  Returns 1 over
-// the unit (the largest output becomes 2^14 to 2^15).  Over the sum it is no less than 2^-113, as the sum times the largest
-// output is a finite number.
-__device__ inline float record_row_own_unit(float biggest, bool mine, float &m, float &l) {
-    const int field = min(max(__builtin_amdgcn_frexp_expf(biggest) + 112, 1), 240);         // the unit's exponent, biased
-    const uint32_t digits = __float_as_uint(__builtin_amdgcn_frexp_mantf(l)) & 0x7fffffu;
-    m += mine ? (float)(__builtin_amdgcn_frexp_expf(l) - 1) : 0.f;
-    l = mine ? __uint_as_float(0x80000000u | ((uint32_t)field << 23) | digits) : l;
-    return __uint_as_float((uint32_t)(254 - field) << 23);
-}
-// Sums as they stand in N records, made what the rows weigh (l) and what their fp16 outputs over kRecordUnit weigh (lu).
-template <int N>
-__device__ __forceinline__ void record_sums(float (&l)[N], float (&lu)[N]) {
-    uint32_t any = 0u;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        any |= __float_as_uint(l[i]);
-        lu[i] = l[i];
-    }
-    if (__builtin_expect(__any((int)any < 0), 0)) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const uint32_t u = __float_as_uint(l[i]);
-            const float sum = __uint_as_float((u & 0x7fffffu) | 0x3f800000u), unit = __uint_as_float(u & 0x7f800000u);
-            lu[i] = (int)u < 0 ? sum * (unit / kRecordUnit) : lu[i];
-            l[i] = (int)u < 0 ? sum : l[i];
-        }
-    }
-}
-__device__ __forceinline__ void record_values(const uint4 &w, float (&v)[8]) {
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const f16x2 h = __builtin_bit_cast(f16x2, u[e]);
-        v[2 * e] = (float)h[0];
-        v[2 * e + 1] = (float)h[1];
-    }
-}
-
 // Eight output values of a query row while its partial records are merged: running maximum (exponent of two), sum of
 // weights relative to it, weighted sum of the records' outputs.
 struct MergeState {
@@ -494,22 +425,15 @@ struct MergeState {
         l = l * fa + l2 * fb;
         m = m_new;
     }
-    // a record: eight outputs normalised by the record's own sum, bf16, or fp16 (kFine) with the weight of record_sums
-    template <bool kFine>
-    __device__ __forceinline__ void fold_record(float m2, float l2, float lu2, const uint4 &w) {
+    // a record: eight bf16 outputs normalised by the record's own sum l2
+    __device__ __forceinline__ void fold_record(float m2, float l2, const uint4 &w) {
+        const uint32_t u[4] = {w.x, w.y, w.z, w.w};
         float v[8];
-        if constexpr (kFine) {
-            record_values(w, v);
-        } else {
-            const uint32_t u[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[2 * e] = __uint_as_float(u[e] << 16);
-                v[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
-            }
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = l2 * __uint_as_float(u[e] << 16);
+            v[2 * e + 1] = l2 * __uint_as_float(u[e] & 0xffff0000u);
         }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] *= lu2;
         fold(m2, l2, v);
     }
     // The states of the four wavefronts of a workgroup, folded into the first one's in their order.  All threads call this;
@@ -534,8 +458,8 @@ struct MergeState {
         }
         return true;
     }
-    __device__ __forceinline__ uint4 result(float unit) const {
-        const float inv = unit / l;                              // (> 0: every row sees its own tree node)
+    __device__ __forceinline__ uint4 result() const {
+        const float inv = 1.f / l;                               // (> 0: every row sees its own tree node)
         return make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
                           pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
     }

@@ -599,53 +599,33 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
                 p.lse[((size_t)e_b * p.Hq + e_hkv * p.G + group) * p.T + node] =
                     (m_run * c2 + __builtin_amdgcn_logf(l_tot)) * kLn2;
         } else {
-            // Partial record: the output so far, normalised by its own sum (fine_records),
+            // Partial record: the output so far, normalised by its own sum and rounded to bf16,
             // as [D / 8 chunks][rows][8 values] (the order the swapped registers hold it, so every
             // store instruction writes whole 512-byte runs), then the maxima and the sums.
             const size_t slot = ((size_t)(2 * range_id + (seg_from_pair_start ? 1 : 0)) * p.n_row_chunks + chunk_id);
             float *rec = p.workspace + slot * attn_slot_floats(D, kRowsPerWG);
             u32x4 *rec16 = reinterpret_cast<u32x4 *>(rec);
             const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;   // a row may see no key of this segment
-            float m_rec = m_run * c2, l_rec = l_tot;
-            bool mine = true;
-            auto pack = [](float lo, float hi) { return fine_records(D) ? pack_f16x2(lo, hi) : pack_bf16x2(lo, hi); };
-            auto write_rows = [&](float f) __attribute__((always_inline)) {
-                float biggest = 0.f;
 #pragma unroll
-                for (int db = 0; db < G::kOBlocks; ++db)
+            for (int db = 0; db < G::kOBlocks; ++db)
 #pragma unroll
-                    for (int i4 = 0; i4 < 4; i4 += 2) {
-                        float v[8];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) v[i] = o[db][4 * i4 + i] * f;
-#pragma unroll
-                        for (int i = 0; fine_records(D) && i < 8; i += 2) biggest = max_abs(biggest, v[i], v[i + 1]);
-                        const auto s0 = __builtin_amdgcn_permlane32_swap(pack(v[0], v[1]), pack(v[4], v[5]), false, false);
-                        const auto s1 = __builtin_amdgcn_permlane32_swap(pack(v[2], v[3]), pack(v[6], v[7]), false, false);
-                        u32x4 w;
-                        w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
-                        // (streamed past the caches: read next by the merge kernel, on other compute units; on short
-                        // launches the end of the kernel has less to write back, 0.7 us of the single-prompt step)
-                        if (mine) __builtin_nontemporal_store(w, &rec16[(size_t)(db * 4 + i4 + h) * kRowsPerWG + row_local]);
-                    }
-                return max_of_row(biggest);
-            };
-            const float largest = write_rows(fine_records(D) ? inv / kRecordUnit : inv);
-            mine = fine_records(D) && !record_row_fits(largest);
-            if (fine_records(D) && __builtin_expect(__any(mine), 0)) {    // (rows that do not fit, if there are any, once more)
-                float biggest = 0.f;
-#pragma unroll
-                for (int db = 0; db < G::kOBlocks; ++db)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) biggest = fmaxf(biggest, finite_abs(o[db][i] * inv));
-                biggest = max_of_row(biggest);
-                const float f = inv * record_row_own_unit(biggest, mine, m_rec, l_rec);
-                write_rows(f);
-            }
+                for (int i4 = 0; i4 < 4; i4 += 2) {
+                    const uint32_t a0 = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
+                    const uint32_t a1 = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
+                    const uint32_t b0 = pack_bf16x2(o[db][4 * i4 + 4] * inv, o[db][4 * i4 + 5] * inv);
+                    const uint32_t b1 = pack_bf16x2(o[db][4 * i4 + 6] * inv, o[db][4 * i4 + 7] * inv);
+                    const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+                    const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+                    u32x4 w;
+                    w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
+                    // (streamed past the caches: read next by the merge kernel, on other compute units; on short
+                    // launches the end of the kernel has less to write back, 0.7 us of the single-prompt step)
+                    __builtin_nontemporal_store(w, &rec16[(size_t)(db * 4 + i4 + h) * kRowsPerWG + row_local]);
+                }
             if (h == 0) {
                 float *ml = rec + (size_t)kRowsPerWG * (D / 2);
-                ml[row_local] = m_rec;
-                ml[kRowsPerWG + row_local] = l_rec;
+                ml[row_local] = m_run * c2;
+                ml[kRowsPerWG + row_local] = l_tot;
             }
         }
     };
@@ -824,7 +804,7 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
 }
 
 // Merge the partial records of every pair that was cut between workgroups.
-// A record holds [D / 8 chunks][rows][8 values] of output normalised by the record's own sum, then the rows' running maxima,
+// A record holds [D / 8 chunks][rows][8 bf16] of output normalised by the record's own sum, then the rows' running maxima,
 // then their running sums.  A wavefront takes 16 consecutive rows of four chunks (256 contiguous bytes per chunk and
 // load, 64 of an output row).  With few pairs and many ranges a pair is cut into dozens of parts: the four wavefronts of a
 // workgroup then take a quarter of the parts each and fold their states through LDS in the order of the ranges.
@@ -871,11 +851,9 @@ __device__ __forceinline__ void merge_body(const AttnParams &p, int b, int hkv, 
                 lw[j] = rec[rows * (D / 2 + 1) + row_local];
                 mw[j] = n_here != 0 && w0 + j <= my_last ? m_rec : -INFINITY;
             }
-            float lu[kBatch];
-            if constexpr (fine_records(D)) record_sums(lw, lu);
 #pragma unroll
             for (int j = 0; j < kBatch; ++j)
-                if (mw[j] != -INFINITY) st.fold_record<fine_records(D)>(mw[j], lw[j], fine_records(D) ? lu[j] : lw[j], v[j]);   // (else no record, or this row saw no key of that part)
+                if (mw[j] != -INFINITY) st.fold_record(mw[j], lw[j], v[j]);   // (else no record, or this row saw no key of that part)
         }
     };
     if (share > 4) take(std::integral_constant<int, 8>{});
@@ -887,7 +865,7 @@ __device__ __forceinline__ void merge_body(const AttnParams &p, int b, int hkv, 
     if (!live) return;
     // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
     const int node = (int)(((float)m_row + 0.5f) * p.g_rcp), group = m_row - node * p.G;
-    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = st.result(fine_records(D) ? kRecordUnit : 1.f);
+    *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c * 8) = st.result();
     if (p.lse && c == 0)
         p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (st.m + __builtin_amdgcn_logf(st.l)) * kLn2;
 }

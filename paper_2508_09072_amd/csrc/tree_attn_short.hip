@@ -36,7 +36,6 @@ namespace reader {
 namespace {
 
 constexpr int kShortRows = 128;
-enum class Form { kEither, kCut, kWhole };   // whether a kernel's pairs are cut into shares: known at run time, yes, no
 constexpr int kShortStages = 4;
 constexpr int kPageRegs = 4;              // page ids a copying wavefront holds: one per lane and register, i.e. 256 tiles
 
@@ -74,10 +73,9 @@ constexpr int kWavesPerSimd64 = 4;
 // 2.2; as a launch of its own, 16-layer decoding step of three users 265 -> 255 us.
 //
 // kAgent: the records are read past the caches of this XCD.  kUnits: sets of four rows and four chunks that the wavefront takes
-// together, `unit` and every `step`-th behind it below `end` (few records leave a lane room for several).  kOwnUnits: rows may have
-// units of their own; true is returned where some do that was not made for it, and then nothing has been written.
-template <int D, bool kAgent, int kUnits, int kBatch, bool kOwnUnits = false>
-__device__ __forceinline__ bool merge_rows(const AttnParams &p, int b, int hkv, int unit, int step, int end) {
+// together, `unit` and every `step`-th behind it below `end` (few records leave a lane room for several).
+template <int D, bool kAgent, int kUnits, int kBatch>
+__device__ __forceinline__ void merge_rows(const AttnParams &p, int b, int hkv, int unit, int step, int end) {
     constexpr int kQuads = D / 32;                           // sets of four chunks in a row
     constexpr size_t kRec = attn_slot_floats(D, kShortRows);   // (64 records stay below 2^32 bytes)
     const int lane = threadIdx.x & 63, g = lane >> 4, n = p.n_splits;
@@ -98,7 +96,6 @@ __device__ __forceinline__ bool merge_rows(const AttnParams &p, int b, int hkv, 
         m_at[u] = (kShortRows * (D / 2) + r) * 4;
     }
     float m[kUnits], l[kUnits], acc[kUnits][8];
-    uint32_t signs = 0u;
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) {
         m[u] = -INFINITY;
@@ -135,33 +132,21 @@ __device__ __forceinline__ bool merge_rows(const AttnParams &p, int b, int hkv, 
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[u][e] *= old;
             m[u] = m_new;
-            float lu[kBatch];
-            if constexpr (kOwnUnits) record_sums(ls[u], lu);
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) {
                 // (a share that saw no key of this row wrote no values: whatever is there is dropped, not weighted)
                 const bool none = ms[u][i] == -INFINITY;
-                const float at_ref = __builtin_amdgcn_exp2f(ms[u][i] - ref), w = none ? 0.f : ls[u][i] * at_ref;
+                const float w = none ? 0.f : ls[u][i] * __builtin_amdgcn_exp2f(ms[u][i] - ref);
                 const uint32_t x[4] = {none ? 0u : v[u][i].x, none ? 0u : v[u][i].y, none ? 0u : v[u][i].z, none ? 0u : v[u][i].w};
                 l[u] += w;
-                if constexpr (fine_records(D)) {
-                    if (!kOwnUnits) signs |= __float_as_uint(w);
-                    const float f = kOwnUnits ? (none ? 0.f : lu[i] * at_ref) : w;
-                    float h[8];
-                    record_values(make_uint4(x[0], x[1], x[2], x[3]), h);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[u][e] = __builtin_fmaf(f, h[e], acc[u][e]);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        acc[u][2 * e] = __builtin_fmaf(w, __uint_as_float(x[e] << 16), acc[u][2 * e]);
-                        acc[u][2 * e + 1] = __builtin_fmaf(w, __uint_as_float(x[e] & 0xffff0000u), acc[u][2 * e + 1]);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    acc[u][2 * e] = __builtin_fmaf(w, __uint_as_float(x[e] << 16), acc[u][2 * e]);
+                    acc[u][2 * e + 1] = __builtin_fmaf(w, __uint_as_float(x[e] & 0xffff0000u), acc[u][2 * e + 1]);
                 }
             }
         }
     }
-    if (fine_records(D) && !kOwnUnits && __any((int)signs < 0)) return true;
     // over the four groups of lanes
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) {
@@ -184,7 +169,7 @@ __device__ __forceinline__ bool merge_rows(const AttnParams &p, int b, int hkv, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[u][e] = total(acc[u][e]);
         if (m_row[u] < p.M && g == 0) {
-            const float inv = (fine_records(D) ? kRecordUnit : 1.f) / l[u];   // (> 0: every row sees its own tree node)
+            const float inv = 1.f / l[u];                    // (> 0: every row sees its own tree node)
             // m / G without an integer division: m + 0.5 is 0.5 / G away from the next multiple of G, far more than rounding
             const int node = (int)(((float)m_row[u] + 0.5f) * p.g_rcp), group = m_row[u] - node * p.G;
             *reinterpret_cast<uint4 *>(p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D + c[u] * 8) =
@@ -194,19 +179,14 @@ __device__ __forceinline__ bool merge_rows(const AttnParams &p, int b, int hkv, 
                 p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_all + __builtin_amdgcn_logf(l[u])) * kLn2;
         }
     }
-    return false;
 }
 
 // As a launch of its own: a wavefront per unit, blocks of four.
 template <int D>
 __device__ __forceinline__ void merge_block(const AttnParams &p, int b, int hkv, int block) {
     const int unit = block * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    auto rows = [&](auto batch_c) __attribute__((always_inline)) {
-        if (__builtin_expect(merge_rows<D, false, 1, decltype(batch_c)::value>(p, b, hkv, unit, 1, unit + 1), 0))
-            merge_rows<D, false, 1, 1, true>(p, b, hkv, unit, 1, unit + 1);
-    };
-    if (p.n_splits > 16) rows(std::integral_constant<int, 8>{});
-    else rows(std::integral_constant<int, 4>{});
+    if (p.n_splits > 16) merge_rows<D, false, 1, 8>(p, b, hkv, unit, 1, unit + 1);
+    else merge_rows<D, false, 1, 4>(p, b, hkv, unit, 1, unit + 1);
 }
 
 // Inside the attention launch: the rows that fall to share s of the pair's chunk, by the eight wavefronts of a workgroup.
@@ -214,32 +194,20 @@ __device__ __forceinline__ void merge_block(const AttnParams &p, int b, int hkv,
 // all of them were there, and no line of 128 bytes holds two pairs' records); others are read past it (kAgent).
 // With few shares a wavefront has several units to do, and takes up to four of them together: one trip to memory,
 // not one each (64 pairs' chunks of 128 rows, two shares each 21.2 -> 18.2 us, three 17.7 -> 16.8).
-// True: nothing has been written of some units, as rows of theirs have units of their own (merge_share_again).
 template <int D, bool kAgent>
-__device__ __forceinline__ bool merge_share(const AttnParams &p, int b, int hkv, int chunk, int s) {
+__device__ __forceinline__ void merge_share(const AttnParams &p, int b, int hkv, int chunk, int s) {
     constexpr int kQuads = D / 32;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = p.n_splits, step = n * 8;
     const int first = chunk * (kShortRows / 4) * kQuads, end = first + (min(kShortRows, p.M - chunk * kShortRows) + 7) / 8 * 2 * kQuads;
-    bool again = false;
     auto all = [&](auto units_c, auto batch_c) __attribute__((always_inline)) {
         constexpr int kUnits = decltype(units_c)::value, kBatch = decltype(batch_c)::value;
 #pragma unroll 1
-        for (int u = first + s * 8 + wave; u < end; u += step * kUnits) again |= merge_rows<D, kAgent, kUnits, kBatch>(p, b, hkv, u, step, end);
+        for (int u = first + s * 8 + wave; u < end; u += step * kUnits) merge_rows<D, kAgent, kUnits, kBatch>(p, b, hkv, u, step, end);
     };
     if (!kAgent && n <= 4) all(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
     else if (!kAgent && n <= 8) all(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
     else if (n <= 16) all(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
     else all(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
-    return again;
-}
-
-template <int D>
-__device__ __forceinline__ void merge_share_again(const AttnParams &p, int b, int hkv, int chunk, int s) {
-    constexpr int kQuads = D / 32;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), step = p.n_splits * 8;
-    const int first = chunk * (kShortRows / 4) * kQuads, end = first + (min(kShortRows, p.M - chunk * kShortRows) + 7) / 8 * 2 * kQuads;
-#pragma unroll 1
-    for (int u = first + s * 8 + wave; u < end; u += step) merge_rows<D, true, 1, 1, true>(p, b, hkv, u, step, end);
 }
 
 // The argument of the fused step's kernels (parts of it are read where they are used: late_argument).
@@ -358,9 +326,8 @@ struct JoinShared {
 // cut, it stood in front of the append and made it the longest job there: one prompt of 4 K tokens 17.6 -> 16.5 us (17.15 with
 // the path chosen in front of the wait for the first tile, which that workgroup's others then wait for), 8 K 21.2 -> 20.4, 128
 // nodes 24.2 -> 22.0; whole pairs (44 sequences of 237 tokens, captured), in front of the first tile before, 32.2 -> 28.3.
-template <int D, bool kStep, bool kJoin, Form kForm>
+template <int D, bool kStep, bool kJoin>
 __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const JoinParams &j) {
-    static_assert(!fine_records(D) || kForm != Form::kEither, "these records are written by kernels of their own");
     constexpr bool kDeep = D == 128;
     constexpr int CW = 4, kS = kShortStages;
     using G = Geometry<D, CW>;
@@ -399,14 +366,14 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
         chunk = p.n_row_chunks == 1 ? 0 : blockIdx.z / p.B, b = blockIdx.z - chunk * p.B;
     }
     const int32_t *table = p.page_table + (size_t)b * p.max_pages;
-    bool whole = kForm == Form::kEither ? p.n_splits == 1 : kForm == Form::kWhole;   // the pair's tiles are all this workgroup's (or all another one's): no record
+    bool whole = p.n_splits == 1;      // the pair's tiles are all this workgroup's (or all another one's): no record
     // this workgroup's tiles [lo, hi) of the pair (prefix tiles, then tree tiles), once the length is there
     int L, n_pre, lo, hi;
     auto share = [&]() {
         L = __builtin_amdgcn_readfirstlane(clamp_len(p, p.seq_lens, b));
         n_pre = (L + kTile - 1) / kTile;
         const int n_all = n_pre + p.n_tree_tiles;
-        if (kForm != Form::kWhole && p.keep_whole) {
+        if (p.keep_whole) {
             // The ring kernels give each of n_ranges workgroups an even share of all tiles (and pair_cost positions a
             // pair).  A pair that fits one such share may have been finished in place there, in fp32 and rounded once: it
             // is not cut here either.  Its workgroup has no more to do than one of the ring kernels'.
@@ -416,7 +383,7 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
             if ((n_all - 1) * p.n_ranges < all) {
                 lo = split == 0 ? 0 : n_all;
                 hi = n_all;
-                if (kForm == Form::kEither) whole = kJoin;   // (else its record is fp16, and what goes by it could round the other way than what does not)
+                whole = kJoin;
                 return;
             }
         }
@@ -789,90 +756,40 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
         uint16_t *orow = p.out + (((size_t)b * p.T + node) * p.Hq + hkv * p.G + group) * D;
         // A lane holds, per 8-wide chunk of the row, 4 values and its partner lane (lane ^ 32) the other 4: one half-wave
         // swap per pair of chunks gives every lane whole 16-byte chunks.  Records are [D / 8 chunks][rows][8 values].
-        float m_exp2 = m_run * c2;
-        bool mine = row_real && lo < hi;               // (of an empty share the merge looks at the maxima only)
-        float largest = 0.f;
-        auto write_rows = [&](float f) __attribute__((always_inline)) {
-            auto pack = [](float x, float y) { return kForm == Form::kWhole ? pack_bf16x2(x, y) : pack_f16x2(x, y); };
-            float biggest = 0.f;
 #pragma unroll
-            for (int db = 0; db < G::kOBlocks; ++db)
+        for (int db = 0; db < G::kOBlocks; ++db)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; i4 += 2) {
-                    float v[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) v[i] = o[db][4 * i4 + i] * f;
-#pragma unroll
-                    for (int i = 0; i < 8; i += 2) biggest = max_abs(biggest, v[i], v[i + 1]);
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(pack(v[0], v[1]), pack(v[4], v[5]), false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(pack(v[2], v[3]), pack(v[6], v[7]), false, false);
-                    u32x4 w;
-                    w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
-                    const int c = db * 4 + i4 + h;
-                    if (mine) {
-                        u32x4 *rec16 = reinterpret_cast<u32x4 *>(rec) + (size_t)c * kShortRows + row_local;
-                        if (kForm == Form::kWhole) *reinterpret_cast<u32x4 *>(orow + c * 8) = w;
-                        else if (kJoin) agent_store16(rec16, w);
-                        else __builtin_nontemporal_store(w, rec16);
-                    }
+            for (int i4 = 0; i4 < 4; i4 += 2) {
+                const uint32_t a0 = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
+                const uint32_t a1 = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
+                const uint32_t b0 = pack_bf16x2(o[db][4 * i4 + 4] * inv, o[db][4 * i4 + 5] * inv);
+                const uint32_t b1 = pack_bf16x2(o[db][4 * i4 + 6] * inv, o[db][4 * i4 + 7] * inv);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+                u32x4 w;
+                w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
+                const int c = db * 4 + i4 + h;
+                if (row_real && lo < hi) {                 // (of an empty share the merge looks at the maxima only)
+                    u32x4 *rec16 = reinterpret_cast<u32x4 *>(rec) + (size_t)c * kShortRows + row_local;
+                    if (whole) *reinterpret_cast<u32x4 *>(orow + c * 8) = w;
+                    else if (kJoin) agent_store16(rec16, w);
+                    else __builtin_nontemporal_store(w, rec16);
                 }
-            return max_of_row(biggest);
-        };
-        auto write_sums = [&]() __attribute__((always_inline)) {
-            float *m_rec = rec + kShortRows * (D / 2) + row_local, *l_rec = m_rec + kShortRows;
-            if constexpr (kJoin) {
-                agent_store(m_rec, m_exp2);
-                agent_store(l_rec, l_run);
-            } else {
-                *m_rec = m_exp2;
-                *l_rec = l_run;
             }
-        };
-        if constexpr (!fine_records(D)) {
-#pragma unroll
-            for (int db = 0; db < G::kOBlocks; ++db)
-#pragma unroll
-                for (int i4 = 0; i4 < 4; i4 += 2) {
-                    const uint32_t a0 = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
-                    const uint32_t a1 = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
-                    const uint32_t b0 = pack_bf16x2(o[db][4 * i4 + 4] * inv, o[db][4 * i4 + 5] * inv);
-                    const uint32_t b1 = pack_bf16x2(o[db][4 * i4 + 6] * inv, o[db][4 * i4 + 7] * inv);
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-                    u32x4 w;
-                    w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
-                    const int c = db * 4 + i4 + h;
-                    if (row_real && lo < hi) {                 // (of an empty share the merge looks at the maxima only)
-                        u32x4 *rec16 = reinterpret_cast<u32x4 *>(rec) + (size_t)c * kShortRows + row_local;
-                        if (whole) *reinterpret_cast<u32x4 *>(orow + c * 8) = w;
-                        else if (kJoin) agent_store16(rec16, w);
-                        else __builtin_nontemporal_store(w, rec16);
-                    }
-                }
-        } else {
-            largest = write_rows(kForm == Form::kWhole ? inv : inv / kRecordUnit);
-        }
         if (row_real && h == 0) {
+            float m_exp2 = m_run * c2;
             asm volatile("" : "+v"(m_exp2));      // (rounded here in every kernel: the lse of a whole pair has the bits of one from a record)
             if (!whole) {
-                write_sums();
+                float *m_rec = rec + kShortRows * (D / 2) + row_local, *l_rec = m_rec + kShortRows;
+                if constexpr (kJoin) {
+                    agent_store(m_rec, m_exp2);
+                    agent_store(l_rec, l_run);
+                } else {
+                    *m_rec = m_exp2;
+                    *l_rec = l_run;
+                }
             } else if (p.lse && lo < hi) {
                 p.lse[((size_t)b * p.Hq + hkv * p.G + group) * p.T + node] = (m_exp2 + __builtin_amdgcn_logf(l_run)) * kLn2;
-            }
-        }
-        if constexpr (fine_records(D) && kForm != Form::kWhole) {
-            // (looked at last, so that the stores do not wait for it) rows that do not fit, if there are any, once more
-            mine = mine && !record_row_fits(largest);
-            if (__builtin_expect(__any(mine), 0)) {
-                float biggest = 0.f;
-#pragma unroll
-                for (int db = 0; db < G::kOBlocks; ++db)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) biggest = fmaxf(biggest, finite_abs(o[db][i] * inv));
-                biggest = max_of_row(biggest);
-                const float f = inv * record_row_own_unit(biggest, mine, m_exp2, l_run);
-                write_rows(f);
-                if (mine && h == 0) write_sums();
             }
         }
         READER_STAMP(kStampExit, 0);
@@ -915,10 +832,8 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
 #pragma unroll 1
             for (int s = 0; s < p.n_splits; ++s) {
                 if (s != split && !__builtin_amdgcn_readfirstlane((int)((left >> s) & 1))) continue;
-                const bool again = local ? merge_share<D, false>(p, b, hkv, chunk, s) : merge_share<D, true>(p, b, hkv, chunk, s);
-                if constexpr (fine_records(D)) {
-                    if (__builtin_expect(again, 0)) merge_share_again<D>(p, b, hkv, chunk, s);
-                }
+                if (local) merge_share<D, false>(p, b, hkv, chunk, s);
+                else merge_share<D, true>(p, b, hkv, chunk, s);
             }
             READER_STAMP(kStampMerged, 0);
         };
@@ -930,32 +845,21 @@ __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const 
     }
 }
 
-// Head dimension 64 has kernels of their own for whole pairs, whose results are not packed like a record's: side by side in one
-// kernel the two ways cost both of them 0.3 us, instructions that come from memory at the end of every workgroup.
-template <int D> constexpr Form form_of(bool whole) { return !fine_records(D) ? Form::kEither : whole ? Form::kWhole : Form::kCut; }
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(AttnParams p) {
-    tree_attn_short_body<D, false, false, form_of<D>(false)>(p, JoinParams());
-}
-template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_whole_kernel(AttnParams p) {
-    tree_attn_short_body<D, false, false, form_of<D>(true)>(p, JoinParams());
+    tree_attn_short_body<D, false, false>(p, JoinParams());
 }
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(StepParams p) {   // (cut pairs of a step in two launches)
-    tree_attn_short_body<D, true, false, form_of<D>(false)>(p.attn, JoinParams());
+    tree_attn_short_body<D, true, false>(p.attn, JoinParams());
 }
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_kernel(StepParams p) {
-    tree_attn_short_body<D, true, false, form_of<D>(true)>(p.attn, JoinParams());
+    tree_attn_short_body<D, true, false>(p.attn, JoinParams());
 }
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_join_kernel(StepParams p) {
-    tree_attn_short_body<D, true, true, form_of<D>(false)>(p.attn, p.join);
-}
-template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verify_short_join_whole_kernel(StepParams p) {
-    tree_attn_short_body<D, true, true, form_of<D>(true)>(p.attn, p.join);
+    tree_attn_short_body<D, true, true>(p.attn, p.join);
 }
 
 // What its first loads need stands in front of the other arguments, one by one: those words arrive in scalar registers with the
@@ -983,21 +887,17 @@ __global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, Co
     kv_append(cp, blockIdx.x, threadIdx.x, sh);
 }
 
-template <int D, bool kStep, bool kJoin, bool kWhole>
+template <int D, bool kStep, bool kJoin, bool kCut = false>
 hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
                        const CompactParams *cp, const JoinParams *jp) {
     using G = Geometry<D, 4>;
     constexpr size_t lds = (size_t)kShortStages * G::kStageBytes + (4 * READER_MAX_T + 4 * kShortStages) * sizeof(int) +
                            (kJoin ? sizeof(JoinShared) : 0) + (kStep ? (kJoin ? sizeof(TailShared) : sizeof(AcceptShared)) : 0);
     static_assert(kStep || !kJoin, "only the fused step waits inside a launch");
-    constexpr bool kOwn = kWhole && fine_records(D);       // (a kernel for whole pairs)
-    const void *kernel;
-    if constexpr (kJoin && kOwn) kernel = reinterpret_cast<const void *>(&verify_short_join_whole_kernel<D>);
-    else if constexpr (kJoin) kernel = reinterpret_cast<const void *>(&verify_short_join_kernel<D>);
-    else if constexpr (kStep && kWhole) kernel = reinterpret_cast<const void *>(&verify_short_kernel<D>);
-    else if constexpr (kStep) kernel = reinterpret_cast<const void *>(static_cast<void (*)(StepParams)>(&tree_attn_short_kernel<D>));
-    else if constexpr (kOwn) kernel = reinterpret_cast<const void *>(&tree_attn_short_whole_kernel<D>);
-    else kernel = reinterpret_cast<const void *>(static_cast<void (*)(AttnParams)>(&tree_attn_short_kernel<D>));
+    const void *kernel = kJoin ? reinterpret_cast<const void *>(&verify_short_join_kernel<D>)
+                       : kCut  ? reinterpret_cast<const void *>(static_cast<void (*)(StepParams)>(&tree_attn_short_kernel<D>))
+                       : kStep ? reinterpret_cast<const void *>(&verify_short_kernel<D>)
+                               : reinterpret_cast<const void *>(static_cast<void (*)(AttnParams)>(&tree_attn_short_kernel<D>));
     {
         static std::mutex guard;             // host threads may call in at the same time
         static bool allowed = false;
@@ -1015,11 +915,9 @@ hipError_t launch_main(const AttnParams &p, hipStream_t stream, hipEvent_t ev_st
         else hipLaunchKernelGGL(fn, grid, dim3(kThreads), lds, stream, args...);
         return note_hip_error(name, hipGetLastError());
     };
-    if constexpr (kJoin && kOwn) return go(verify_short_join_whole_kernel<D>, "launch verify_short_join_whole_kernel", StepParams{*jp, p, *ap, *cp});
-    else if constexpr (kJoin) return go(verify_short_join_kernel<D>, "launch verify_short_join_kernel", StepParams{*jp, p, *ap, *cp});
-    else if constexpr (kStep && kWhole) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
-    else if constexpr (kStep) return go(static_cast<void (*)(StepParams)>(&tree_attn_short_kernel<D>), "launch tree_attn_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
-    else if constexpr (kOwn) return go(tree_attn_short_whole_kernel<D>, "launch tree_attn_short_whole_kernel", p);
+    if constexpr (kJoin) return go(verify_short_join_kernel<D>, "launch verify_short_join_kernel", StepParams{*jp, p, *ap, *cp});
+    else if constexpr (kCut) return go(static_cast<void (*)(StepParams)>(&tree_attn_short_kernel<D>), "launch tree_attn_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
+    else if constexpr (kStep) return go(verify_short_kernel<D>, "launch verify_short_kernel", StepParams{JoinParams(), p, *ap, *cp});
     else return go(static_cast<void (*)(AttnParams)>(&tree_attn_short_kernel<D>), "launch tree_attn_short_kernel", p);
 }
 
@@ -1027,18 +925,15 @@ template <int D>
 hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams *ap,
                       const CompactParams *cp, const JoinParams *jp) {
     const bool step = ap && cp;
-    const bool whole = p.n_splits == 1;
-    if (step && jp) return whole ? launch_main<D, true, true, true>(p, stream, ev_start, ev_stop, ap, cp, jp)
-                                 : launch_main<D, true, true, false>(p, stream, ev_start, ev_stop, ap, cp, jp);
-    if (step && whole) {
-        const hipError_t e = launch_main<D, true, false, true>(p, stream, ev_start, ev_stop, ap, cp, nullptr);
+    if (step && jp) return launch_main<D, true, true>(p, stream, ev_start, ev_stop, ap, cp, jp);
+    if (step && p.n_splits == 1) {
+        const hipError_t e = launch_main<D, true, false>(p, stream, ev_start, ev_stop, ap, cp, nullptr);
         if (e != hipSuccess || !cp->k_tree) return e;      // (in-cache layout: the rows move in a launch of their own)
         return launch_kv_compact(*cp, stream);
     }
-    const hipError_t e = whole  ? launch_main<D, false, false, true>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr)
-                         : step ? launch_main<D, true, false, false>(p, stream, ev_start, ev_stop, ap, cp, nullptr)
-                                : launch_main<D, false, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
-    if (e != hipSuccess || whole) return e;
+    const hipError_t e = step ? launch_main<D, true, false, true>(p, stream, ev_start, ev_stop, ap, cp, nullptr)
+                              : launch_main<D, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
+    if (e != hipSuccess || p.n_splits == 1) return e;
     const int blocks = (p.M + 7) / 8 * (D / 64);           // of 8 rows x 8 chunks, four wavefronts
     if (step && cp->k_tree) {                              // (in-cache layout: the rows move in a launch of their own)
         hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * blocks), dim3(256), 0, stream, p, *cp, blocks);

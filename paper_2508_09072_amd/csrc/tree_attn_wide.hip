@@ -614,49 +614,30 @@ __global__ __launch_bounds__(kWideThreads) void tree_attn_wide_kernel(AttnParams
             u32x4 *rec16 = reinterpret_cast<u32x4 *>(rec);
             // A lane holds, per 8-wide chunk of the output row, 4 values and its partner lane (lane ^ 32)
             // the other 4: one half-wave swap per pair of chunks gives every lane whole 16-byte chunks.
-            auto write_rows = [&](bool mine, float f, auto &&pack, auto &&store) __attribute__((always_inline)) {
-                float biggest = 0.f;
-                static_for<G::kOBlocks * 2>([&](auto cc) __attribute__((always_inline)) {
-                    constexpr int db = decltype(cc)::value / 2, i4 = (decltype(cc)::value % 2) * 2;
-                    float v[8];
-                    static_for<8>([&](auto ec) { v[decltype(ec)::value] = acc_read<Acc::o(R, db) + 4 * i4 + decltype(ec)::value>() * f; });
-#pragma unroll
-                    for (int i = 0; fine_records(D) && i < 8; i += 2) biggest = max_abs(biggest, v[i], v[i + 1]);
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(pack(v[0], v[1]), pack(v[4], v[5]), false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(pack(v[2], v[3]), pack(v[6], v[7]), false, false);
-                    u32x4 w;
-                    w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
-                    if (mine) store(db * 4 + i4 + h, w);
-                });
-                return max_of_row(biggest);
-            };
-            float m_rec = ref * c2, l_rec = l_tot;
-            if (whole) {
-                write_rows(row_real[r], inv, pack_bf16x2, [&](int c, u32x4 w) { *reinterpret_cast<u32x4 *>(orow + c * 8) = w; });
-            } else {
-                // [D / 8 chunks][rows][8 values], then the rows' references, then their sums
-                auto to_record = [&](int c, u32x4 w) { rec16[(size_t)c * kWideRows + row_local[r]] = w; };
-                if constexpr (!fine_records(D)) {
-                    write_rows(true, inv, pack_bf16x2, to_record);
-                } else if (const bool mine = !record_row_fits(write_rows(true, inv / kRecordUnit, pack_f16x2, to_record));
-                           __builtin_expect(__any(mine), 0)) {    // (rows that do not fit, if there are any, once more)
-                    float biggest = 0.f;
-                    static_for<G::kOBlocks * 16>([&](auto ec) {
-                        constexpr int e = decltype(ec)::value;
-                        biggest = fmaxf(biggest, finite_abs(acc_read<Acc::o(R, e / 16) + e % 16>() * inv));
-                    });
-                    biggest = max_of_row(biggest);
-                    const float f = inv * record_row_own_unit(biggest, mine, m_rec, l_rec);
-                    write_rows(mine, f, pack_f16x2, to_record);
+            static_for<G::kOBlocks * 2>([&](auto cc) {
+                constexpr int db = decltype(cc)::value / 2, i4 = (decltype(cc)::value % 2) * 2;
+                float v[8];
+                static_for<8>([&](auto ec) { v[decltype(ec)::value] = acc_read<Acc::o(R, db) + 4 * i4 + decltype(ec)::value>() * inv; });
+                const uint32_t a0 = pack_bf16x2(v[0], v[1]), a1 = pack_bf16x2(v[2], v[3]);
+                const uint32_t b0 = pack_bf16x2(v[4], v[5]), b1 = pack_bf16x2(v[6], v[7]);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+                u32x4 w;
+                w.x = s0[0]; w.y = s1[0]; w.z = s0[1]; w.w = s1[1];
+                if (whole) {
+                    if (row_real[r]) *reinterpret_cast<u32x4 *>(orow + db * 32 + (i4 + h) * 8) = w;
+                } else {
+                    // [D / 8 chunks][rows][8 values], then the rows' references, then their sums
+                    rec16[(size_t)(db * 4 + i4 + h) * kWideRows + row_local[r]] = w;
                 }
-            }
+            });
             if (whole) {
                 if (row_real[r] && p.lse && h == 0)
                     p.lse[((size_t)e_b * p.Hq + e_hkv * p.G + gr) * p.T + nd] = (ref * c2 + __builtin_amdgcn_logf(l_tot)) * kLn2;
             } else if (h == 0) {
                 float *ml = rec + (size_t)kWideRows * (D / 2);
-                ml[row_local[r]] = m_rec;
-                ml[kWideRows + row_local[r]] = l_rec;
+                ml[row_local[r]] = ref * c2;
+                ml[kWideRows + row_local[r]] = l_tot;
             }
         });
     };
