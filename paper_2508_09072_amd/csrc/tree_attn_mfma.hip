@@ -152,28 +152,24 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
     int *s_len = rs.s_len;
     const int n_tiles = hi.flat - lo.flat;
     if (chunk_id == 0 && tid == 0) p.range_tiles[range_id] = n_tiles;
-    // The fused step: workgroup w accepts a path for sequence w (and w + grid, ...), which reads tokens only and writes nothing
-    // that an attention launch reads.  Its first copying wavefront does it when the last tile has landed, in a stage that is
-    // idle then, while the others compute that tile and write their results.  In the launch behind this one, where it was before
-    // (and still is behind the 256-row kernels, whose wavefronts all compute), it stands in front of the append and makes
-    // that the longest job there: tail 7.4 -> 6.6 us, step of 16 sequences of 1 to 4 K positions and 32 nodes 47.35 -> 46.95, 34
-    // of 6.6 K and 36 nodes 163.0 -> 162.1.
-    const bool accepts = kDma && p.accepts && wave_s == 4;
-    auto accept = [&](int b, AcceptTokens tok, char *stage) {
+    // The fused step of no more sequences than there are workgroups: workgroup w accepts a path for
+    // sequence w, which reads tokens only and writes nothing that an attention launch reads.  Its first copying wavefront does it
+    // when the last tile has landed, in a stage that is idle then, while the others compute that tile and write their results.  In
+    // the launch behind this one, where it was before (and still is behind the 256-row kernels, whose wavefronts all compute), it
+    // stands in front of the append and makes that the longest job there: tail 8.0 -> 6.1 us, step of 16 sequences of 1 to 4 K
+    // positions and 32 nodes 47.4 -> 46.7, 34 of 6.6 K and 36 nodes 162.6 -> 161.5.  Of more sequences a workgroup would accept one
+    // behind the other: 1024 of 0.3 to 1.5 K 105.2 -> 109.8 us.
+    const bool side = kDma && p.accepts && wave_s == 4 && (int)blockIdx.x < p.B;
+    auto accept = [&](AcceptTokens tok, char *stage) {
         AcceptShared &sh = *reinterpret_cast<AcceptShared *>(stage);
-        for (;;) {
-            const AcceptParams ap = late_argument<AcceptParams, offsetof(RingArgs, accept)>();
-            const AcceptNodes nodes = accept_stage(ap, lane, tok, sh);
-            int bits;
-            const int n = accept_choose(ap, lane, nodes, sh, bits);
-            accept_report(ap, b, lane, n, bits, sh);
-            if ((b += gridDim.x) >= p.B) break;
-            tok = accept_load(ap, b, lane);
-        }
+        const AcceptParams ap = late_argument<AcceptParams, offsetof(RingArgs, accept)>();
+        const AcceptNodes nodes = accept_stage(ap, lane, tok, sh);
+        int bits;
+        const int n = accept_choose(ap, lane, nodes, sh, bits);
+        accept_report(ap, blockIdx.x, lane, n, bits, sh);
     };
     if (n_tiles <= 0) {
-        if (accepts && (int)blockIdx.x < p.B)
-            accept(blockIdx.x, accept_load(late_argument<AcceptParams, offsetof(RingArgs, accept)>(), blockIdx.x, lane), ring);
+        if (side) accept(accept_load(late_argument<AcceptParams, offsetof(RingArgs, accept)>(), blockIdx.x, lane), ring);
         return;
     }
     READER_STAMP(kStampRange, 0);
@@ -659,7 +655,6 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
         int flags_2 = desc_flags(2);        // flags of item it + 2
         int d_blk = desc_of(kS - 1)->blk[cw];                                       // of item it + kS - 1,
         int2 d_nf = *reinterpret_cast<const int2 *>(&desc_of(kS - 1)->n_valid);    // the next one to ask for
-        const bool side = accepts && (int)blockIdx.x < p.B;
         AcceptTokens tok;
         for (int it = 0; it < n_iter; ++it) {
             // This wavefront's part of item `it` has landed once at most its copies of the items
@@ -692,7 +687,7 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
             // (behind the last copies: they are waited for together)
             if (side && ahead == 1) tok = accept_load(late_argument<AcceptParams, offsetof(RingArgs, accept)>(), blockIdx.x, lane);
         }
-        if (side) accept(blockIdx.x, tok, ring + ((n_iter - 2) % kS) * G::kStageBytes);
+        if (side) accept(tok, ring + ((n_iter - 2) % kS) * G::kStageBytes);
     } else if (kDma) {
         // ---------------- wavefronts that only compute (RB = 4) ----------------
         int2 d_cur = *reinterpret_cast<const int2 *>(&desc_of(0)->n_valid);
@@ -965,7 +960,7 @@ hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEve
     hipError_t e;
     if (p.rows_per_wg == 128) {
         AttnParams q = p;
-        q.accepts = ap && cp;
+        q.accepts = ap && cp && p.B <= p.n_ranges * p.n_row_chunks;
         const AcceptParams accept = q.accepts ? *ap : AcceptParams();
         e = p.D == 64 ? launch_mfma<64, 4>(q, stream, ev_start, ev_stop, accept) : launch_mfma<128, 4>(q, stream, ev_start, ev_stop, accept);
         if (e != hipSuccess) return e;

@@ -180,7 +180,8 @@ def test_what_is_refused_stays_refused(R, join, fault, in_cache, splits, tune):
     (2, 1, 1, 128, 1, [0, 300], 3), (2, 1, 1, 64, 1, [300, 0], 3),                 # a root alone
     (33, 8, 1, 128, 12, [200] * 33, 2), (40, 8, 1, 64, 3, [150] * 40, 1),          # cut and whole pairs of more workgroups than run at once
     (3, 2, 4, 128, 65, [700, 0, 130], 0), (5, 1, 16, 64, 45, [900, 64, 0, 1, 65], 0),   # the ring kernels: two and six chunks of 128 rows
-    (1, 1, 1, 128, 1, [0], 0), (300, 2, 1, 64, 5, [40] * 300, 0)])                 # ranges without tiles; more sequences than workgroups
+    (1, 1, 1, 128, 1, [0], 0), (300, 2, 1, 64, 5, [40] * 300, 0),                  # ranges without tiles; more sequences than workgroups
+    (256, 2, 1, 64, 5, [40] * 256, 0), (257, 2, 1, 128, 5, [40] * 257, 0)])          # as many, and one more
 @pytest.mark.parametrize("in_cache", [False, True])
 def test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B, Hkv, G, D, T, lens, splits, in_cache, tune):
     # every result and the cache bit for bit, as a call and as replays of a captured graph
