@@ -85,11 +85,15 @@ struct RingArgs {
     AcceptParams accept;
 };
 
+// Whether a ring kernel can choose the paths of a fused step (see there).
+constexpr bool ring_accepts(int D, int RB) { return RB == 4 && D == 128; }
+
 template <int D, int RB>
 __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
                                                                     const int32_t *__restrict__ page_table,
                                                                     const int32_t *__restrict__ seq_lens, AcceptParams) {
     constexpr bool kDma = RB == 4;
+    constexpr bool kAccepts = ring_accepts(D, RB);
     constexpr int CW = kDma ? 4 : 8;
     using G = Geometry<D, CW>;
     constexpr int kRowsPerWG = 32 * RB;
@@ -152,14 +156,16 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
     int *s_len = rs.s_len;
     const int n_tiles = hi.flat - lo.flat;
     if (chunk_id == 0 && tid == 0) p.range_tiles[range_id] = n_tiles;
-    // The fused step of no more sequences than there are workgroups: workgroup w accepts a path for
+    // The fused step of no more sequences than there are workgroups, at head dimension 128: workgroup w accepts a path for
     // sequence w, which reads tokens only and writes nothing that an attention launch reads.  Its first copying wavefront does it
     // when the last tile has landed, in a stage that is idle then, while the others compute that tile and write their results.  In
     // the launch behind this one, where it was before (and still is behind the 256-row kernels, whose wavefronts all compute), it
     // stands in front of the append and makes that the longest job there: tail 8.0 -> 6.1 us, step of 16 sequences of 1 to 4 K
     // positions and 32 nodes 47.4 -> 46.7, 34 of 6.6 K and 36 nodes 162.6 -> 161.5.  Of more sequences a workgroup would accept one
-    // behind the other: 1024 of 0.3 to 1.5 K 105.2 -> 109.8 us.
-    const bool side = kDma && p.accepts && wave_s == 4 && (int)blockIdx.x < p.B;
+    // behind the other: 1024 of 0.3 to 1.5 K 105.2 -> 109.8 us.  At head dimension 64, whose tiles take half the time, the code in
+    // the copying wavefronts' way costs the launch 0.6 to 2.1 us of 85 (64 sequences of 2 to 24 K, 4 rows; attention alone as
+    // well), and the tail gains 0.4.
+    const bool side = kAccepts && p.accepts && wave_s == 4 && (int)blockIdx.x < p.B;
     auto accept = [&](AcceptTokens tok, char *stage) {
         AcceptShared &sh = *reinterpret_cast<AcceptShared *>(stage);
         const AcceptParams ap = late_argument<AcceptParams, offsetof(RingArgs, accept)>();
@@ -945,8 +951,13 @@ static hipError_t launch_tail(const AttnParams &p, hipStream_t stream, const Acc
     const int merge_y = p.merge_groups == 4 ? units : (units + 3) / 4;
     if (ap && cp && (!p.accepts || cp->k_tree)) {
         const int n_merge = p.B * p.Hkv * merge_y;
-        if (p.accepts) hipLaunchKernelGGL((verify_tail_kernel<D, false>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
-        else hipLaunchKernelGGL((verify_tail_kernel<D, true>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
+        if constexpr (ring_accepts(D, 4)) {
+            if (p.accepts) {
+                hipLaunchKernelGGL((verify_tail_kernel<D, false>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
+                return note_hip_error("launch verify_tail_kernel", hipGetLastError());
+            }
+        }
+        hipLaunchKernelGGL((verify_tail_kernel<D, true>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
         return note_hip_error("launch verify_tail_kernel", hipGetLastError());
     }
     hipLaunchKernelGGL(tree_attn_merge_kernel<D>, dim3(p.Hkv, merge_y, p.B), dim3(256), 0, stream, p.pair_info, p.workspace,
@@ -960,7 +971,7 @@ hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEve
     hipError_t e;
     if (p.rows_per_wg == 128) {
         AttnParams q = p;
-        q.accepts = ap && cp && p.B <= p.n_ranges * p.n_row_chunks;
+        q.accepts = ap && cp && ring_accepts(p.D, 4) && p.B <= p.n_ranges * p.n_row_chunks;
         const AcceptParams accept = q.accepts ? *ap : AcceptParams();
         e = p.D == 64 ? launch_mfma<64, 4>(q, stream, ev_start, ev_stop, accept) : launch_mfma<128, 4>(q, stream, ev_start, ev_stop, accept);
         if (e != hipSuccess) return e;
