@@ -51,7 +51,6 @@ struct AttnParams {
     float split_rcp;         // 1 / n_splits
     int32_t keep_whole;      // short problems: 1 if pairs that the ring kernels' even cut could leave whole are not cut here either
     int32_t redo_only;       // 1: second pass behind the wide kernel, only the workgroups flagged in `redo` do anything
-    int32_t accepts;         // (128-row ring kernel) 1: a fused step whose paths this launch chooses
     int32_t *status;
     int32_t B, T, Hq, Hkv, D, G, M;       // G = Hq/Hkv, M = T*G query rows per (sequence, kv head)
     int32_t max_pages, max_seq_len;

@@ -455,7 +455,6 @@ static int attn_prepare(const reader_dims *dims, const void *q, const void *k_tr
     p.tree_in_cache = tree_in_cache ? 1 : 0;
     p.wide = attn_use_wide(*dims, p.rows_per_wg);
     p.redo_only = 0;
-    p.accepts = 0;
     p.n_splits = 0;
     p.split_rcp = 0.f;
     p.keep_whole = 0;

@@ -78,22 +78,33 @@ namespace reader {
 #define READER_STAMP(k, who) do { } while (0)
 #endif
 
-// Where the last of the kernel's arguments lies (read late).
+// Where the last argument of the kernel that also accepts paths lies (read late).
 struct RingArgs {
     AttnParams p;
     const int32_t *page_table, *seq_lens;
     AcceptParams accept;
 };
 
-// Whether a ring kernel can choose the paths of a fused step (see there).
-constexpr bool ring_accepts(int D, int RB) { return RB == 4 && D == 128; }
+// Whether the attention launch of a fused step chooses its paths: the 128-row kernel of head dimension 128, one chunk of rows, and no
+// more sequences than workgroups.  Its copying wavefronts set the pace, and more code in their way is felt where that is all
+// there is to a launch, also of one that accepts nothing.  So attention alone, and a step outside this rule, take the kernel without.
+//  - Head dimension 64, whose tiles take half the time: 64 sequences of 2 to 24 K positions, 4 rows, 88.1 -> 88.7 to 90.2 us.
+//  - Several chunks of rows, which read the same tiles side by side and lose the cache's help when they drift apart: 250
+//    sequences of 10 to 20 K, 384 rows, 920 -> 942 us (attention alone too); two chunks gain as much as they lose.
+//  - More sequences, of which a workgroup would accept one behind the other: 1024 of 0.3 to 1.5 K 105.2 -> 109.8 us.
+// Within it, 16 sequences of 1 to 3 K 33.9 -> 33.0 us at 32 rows, of 1 to 4 K 47.9 -> 47.2 at 128.
+static bool ring_accepts(const AttnParams &p) {
+    return p.D == 128 && p.rows_per_wg == 128 && p.n_row_chunks == 1 && p.B <= p.n_ranges;
+}
 
-template <int D, int RB>
+// Step: nothing, or AcceptParams where the launch chooses the paths too.
+template <int D, int RB, typename... Step>
 __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
                                                                     const int32_t *__restrict__ page_table,
-                                                                    const int32_t *__restrict__ seq_lens, AcceptParams) {
+                                                                    const int32_t *__restrict__ seq_lens, Step...) {
     constexpr bool kDma = RB == 4;
-    constexpr bool kAccepts = ring_accepts(D, RB);
+    constexpr bool kAccepts = sizeof...(Step) > 0;
+    static_assert(kDma || !kAccepts, "acceptance is for a copying wavefront");
     constexpr int CW = kDma ? 4 : 8;
     using G = Geometry<D, CW>;
     constexpr int kRowsPerWG = 32 * RB;
@@ -156,16 +167,11 @@ __global__ __launch_bounds__(kThreads) void tree_attn_mfma_kernel(AttnParams p,
     int *s_len = rs.s_len;
     const int n_tiles = hi.flat - lo.flat;
     if (chunk_id == 0 && tid == 0) p.range_tiles[range_id] = n_tiles;
-    // The fused step of no more sequences than there are workgroups, at head dimension 128: workgroup w accepts a path for
-    // sequence w, which reads tokens only and writes nothing that an attention launch reads.  Its first copying wavefront does it
-    // when the last tile has landed, in a stage that is idle then, while the others compute that tile and write their results.  In
-    // the launch behind this one, where it was before (and still is behind the 256-row kernels, whose wavefronts all compute), it
-    // stands in front of the append and makes that the longest job there: tail 8.0 -> 6.1 us, step of 16 sequences of 1 to 4 K
-    // positions and 32 nodes 47.4 -> 46.7, 34 of 6.6 K and 36 nodes 162.6 -> 161.5.  Of more sequences a workgroup would accept one
-    // behind the other: 1024 of 0.3 to 1.5 K 105.2 -> 109.8 us.  At head dimension 64, whose tiles take half the time, the code in
-    // the copying wavefronts' way costs the launch 0.6 to 2.1 us of 85 (64 sequences of 2 to 24 K, 4 rows; attention alone as
-    // well), and the tail gains 0.4.
-    const bool side = kAccepts && p.accepts && wave_s == 4 && (int)blockIdx.x < p.B;
+    // Workgroup w accepts a path for sequence w, which reads tokens only and writes nothing that an attention launch reads.  Its
+    // first copying wavefront does it when the last tile has landed, in a stage that is idle then, while the others compute that
+    // tile and write their results.  In the launch behind this one it stands in front of the append and makes that the
+    // longest job there (tail 8.0 -> 6.1 us, 16 sequences of 1 to 4 K positions and 32 nodes).
+    const bool side = kAccepts && wave_s == 4 && (int)blockIdx.x < p.B;
     auto accept = [&](AcceptTokens tok, char *stage) {
         AcceptShared &sh = *reinterpret_cast<AcceptShared *>(stage);
         const AcceptParams ap = late_argument<AcceptParams, offsetof(RingArgs, accept)>();
@@ -913,8 +919,8 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(AttnParams p, AcceptPa
     }
 }
 
-template <int D, int RB>
-static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const AcceptParams &ap = {}) {
+template <int D, int RB, typename... Step>
+static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const Step &...step) {
     using G = Geometry<D, RB == 4 ? 4 : 8>;
     const size_t pref_bytes = ((size_t)(p.B + 1) * sizeof(int) + 15) & ~(size_t)15;
     const size_t main_lds = (size_t)ring_stages(RB) * G::kStageBytes +
@@ -928,7 +934,7 @@ static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_
         static size_t lds_allowed = 0;
         std::lock_guard<std::mutex> lock(guard);
         if (main_lds > lds_allowed) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_mfma_kernel<D, RB>),
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_mfma_kernel<D, RB, Step...>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)main_lds);
             if (e != hipSuccess) { (void)hipGetLastError(); return note_hip_error("hipFuncSetAttribute(attention LDS size)", e); }
             lds_allowed = main_lds;
@@ -936,23 +942,23 @@ static hipError_t launch_mfma(const AttnParams &p, hipStream_t stream, hipEvent_
     }
     // with events: they take the kernel's own start and end time stamps
     if (ev_start && ev_stop)
-        hipExtLaunchKernelGGL((tree_attn_mfma_kernel<D, RB>), dim3(p.n_ranges * p.n_row_chunks), dim3(kThreads),
-                              main_lds, stream, ev_start, ev_stop, 0, p, p.page_table, p.seq_lens, ap);
+        hipExtLaunchKernelGGL((tree_attn_mfma_kernel<D, RB, Step...>), dim3(p.n_ranges * p.n_row_chunks), dim3(kThreads),
+                              main_lds, stream, ev_start, ev_stop, 0, p, p.page_table, p.seq_lens, step...);
     else
-        hipLaunchKernelGGL((tree_attn_mfma_kernel<D, RB>), dim3(p.n_ranges * p.n_row_chunks), dim3(kThreads),
-                           main_lds, stream, p, p.page_table, p.seq_lens, ap);
+        hipLaunchKernelGGL((tree_attn_mfma_kernel<D, RB, Step...>), dim3(p.n_ranges * p.n_row_chunks), dim3(kThreads),
+                           main_lds, stream, p, p.page_table, p.seq_lens, step...);
     return note_hip_error("launch tree_attn_mfma_kernel", hipGetLastError());
 }
 
-// Second launch: merge of the partial records, and in the fused step acceptance and compaction.
+// Second launch: merge of the partial records, and in the fused step acceptance (unless the first one has `accepted`) and compaction.
 template <int D>
-static hipError_t launch_tail(const AttnParams &p, hipStream_t stream, const AcceptParams *ap, const CompactParams *cp) {
+static hipError_t launch_tail(const AttnParams &p, hipStream_t stream, const AcceptParams *ap, const CompactParams *cp, bool accepted = false) {
     const int units = (p.M + 15) / 16 * (D / 32);          // of 16 rows x 4 chunks
     const int merge_y = p.merge_groups == 4 ? units : (units + 3) / 4;
-    if (ap && cp && (!p.accepts || cp->k_tree)) {
+    if (ap && cp && (!accepted || cp->k_tree)) {
         const int n_merge = p.B * p.Hkv * merge_y;
-        if constexpr (ring_accepts(D, 4)) {
-            if (p.accepts) {
+        if constexpr (D == 128) {
+            if (accepted) {
                 hipLaunchKernelGGL((verify_tail_kernel<D, false>), dim3(p.B + n_merge), dim3(256), 0, stream, p, *ap, *cp, merge_y);
                 return note_hip_error("launch verify_tail_kernel", hipGetLastError());
             }
@@ -969,13 +975,11 @@ hipError_t launch_tree_attn_mfma(const AttnParams &p, hipStream_t stream, hipEve
                                  const AcceptParams *ap, const CompactParams *cp, const JoinParams *jp) {
     if (p.n_splits > 0) return launch_tree_attn_short(p, stream, ev_start, ev_stop, ap, cp, jp);
     hipError_t e;
-    if (p.rows_per_wg == 128) {
-        AttnParams q = p;
-        q.accepts = ap && cp && ring_accepts(p.D, 4) && p.B <= p.n_ranges * p.n_row_chunks;
-        const AcceptParams accept = q.accepts ? *ap : AcceptParams();
-        e = p.D == 64 ? launch_mfma<64, 4>(q, stream, ev_start, ev_stop, accept) : launch_mfma<128, 4>(q, stream, ev_start, ev_stop, accept);
-        if (e != hipSuccess) return e;
-        return p.D == 64 ? launch_tail<64>(q, stream, ap, cp) : launch_tail<128>(q, stream, ap, cp);
+    if (ap && cp && ring_accepts(p)) {
+        e = launch_mfma<128, 4>(p, stream, ev_start, ev_stop, *ap);
+        return e != hipSuccess ? e : launch_tail<128>(p, stream, ap, cp, true);
+    } else if (p.rows_per_wg == 128) {
+        e = p.D == 64 ? launch_mfma<64, 4>(p, stream, ev_start, ev_stop) : launch_mfma<128, 4>(p, stream, ev_start, ev_stop);
     } else if (p.wide) {
         // Four wavefronts of 64 rows with a softmax reference that is fixed per segment; a workgroup whose
         // scores outgrew that reference says so, and the kernel that moves its reference (eight wavefronts of

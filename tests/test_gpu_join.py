@@ -227,3 +227,11 @@ def test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B
         torch.cuda.synchronize()
         for name in NAMES:
             assert torch.equal(getattr(dw, name).view(torch.uint8), want[name].view(torch.uint8)), (turn, name)
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,T,lens,splits", [
+    (256, 1, 4, 128, 24, [70] * 256, 0), (257, 1, 4, 128, 24, [70] * 257, 0),      # ring kernel: as many sequences as workgroups, one more
+    (5, 2, 4, 128, 32, [900, 64, 0, 1, 65], 0), (5, 2, 4, 128, 33, [900, 64, 0, 1, 65], 0)])   # one full chunk of rows, two
+@pytest.mark.parametrize("in_cache", [False, True])
+def test_on_both_sides_of_the_rules_for_who_accepts(R, B, Hkv, G, D, T, lens, splits, in_cache, tune):
+    test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B, Hkv, G, D, T, lens, splits, in_cache, tune)
