@@ -166,21 +166,6 @@ __device__ inline void kv_compact_prefetch(const CompactParams &p, int b, int ti
     }
 }
 
-// Compaction in a launch behind the one that has chosen the path, by 256 threads: the path is fetched next to what
-// kv_compact_prefetch fetches, so that the next trip to memory is the rows'.
-struct AppendShared {
-    CompactShared compact;
-    int path[READER_MAX_T];
-};
-__device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, int n, const int *path, const CompactShared &cs);
-__device__ __forceinline__ void kv_append(const CompactParams &p, int b, int tid, AppendShared &sh) {
-    const int n = p.accept_len[b];
-    if (tid < p.max_path) sh.path[tid] = p.path[(size_t)b * p.max_path + tid];
-    kv_compact_prefetch(p, b, tid, sh.compact);
-    __syncthreads();
-    kv_compact_body(p, b, tid, n, sh.path, sh.compact);
-}
-
 // Called by all 256 threads of the workgroup, after kv_compact_prefetch and a barrier.
 // n = accept_len of the sequence, path = its accepted path (global or LDS).
 __device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, int n, const int *path,
@@ -241,6 +226,30 @@ __device__ inline void kv_compact_body(const CompactParams &p, int b, int tid, i
         }
     }
     if (tid == 0) p.seq_lens[b] = L + n + 1;
+}
+
+// The rows of a sequence's path, appended by 256 threads in the launch behind the attention; the path is chosen here too unless that
+// launch has (then it is fetched next to what kv_compact_prefetch fetches, so that the next trip to memory is the rows').
+template <bool kAccept>
+__device__ __forceinline__ void step_tail(const AcceptParams &ap, const CompactParams &cp, int b, int tid) {
+    __shared__ CompactShared cs;
+    if constexpr (kAccept) {
+        __shared__ AcceptShared sh;
+        // (in-cache layout, no tree tensors: the in-place move of the accepted rows follows as a launch of its own)
+        const bool append = cp.k_tree != nullptr;
+        if (append) kv_compact_prefetch(cp, b, tid, cs);   // on its way while the path is being chosen
+        if (tid < 64) accept_path_wave(ap, b, tid, sh);
+        if (!append) return;
+        __syncthreads();
+        kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
+    } else {
+        __shared__ int path[READER_MAX_T];
+        const int n = cp.accept_len[b];
+        if (tid < cp.max_path) path[tid] = cp.path[(size_t)b * cp.max_path + tid];
+        kv_compact_prefetch(cp, b, tid, cs);
+        __syncthreads();
+        kv_compact_body(cp, b, tid, n, path, cs);
+    }
 }
 
 // The accepted rows of a sequence, moved by wavefronts that share no barrier (inside the attention launch of a fused step).

@@ -902,21 +902,7 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(AttnParams p, AcceptPa
         merge_body<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks_y);
         return;
     }
-    const int b = blockIdx.x, tid = threadIdx.x;
-    if constexpr (!kAccept) {
-        __shared__ AppendShared sh;
-        kv_append(cp, b, tid, sh);
-    } else {
-        __shared__ AcceptShared sh;
-        __shared__ CompactShared cs;
-        // (in-cache layout, no tree tensors: the in-place move of the accepted rows follows as a launch of its own)
-        const bool append = cp.k_tree != nullptr;
-        if (append) kv_compact_prefetch(cp, b, tid, cs);   // on its way while the path is being chosen
-        if (tid < 64) accept_path_wave(ap, b, tid, sh);
-        if (!append) return;
-        __syncthreads();
-        kv_compact_body(cp, b, tid, sh.accept_len, sh.path, cs);
-    }
+    step_tail<kAccept>(ap, cp, blockIdx.x, threadIdx.x);
 }
 
 template <int D, int RB, typename... Step>

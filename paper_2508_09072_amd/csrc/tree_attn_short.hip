@@ -874,17 +874,16 @@ __global__ __launch_bounds__(256) void merge_short_kernel(float *workspace, uint
     merge_block<D>(p, blockIdx.z, blockIdx.y, blockIdx.x);
 }
 
-// Second launch of the fused step where pairs were cut: one workgroup per sequence that appends the rows of the path that the
-// attention launch has chosen, then the merge blocks.  The jobs touch disjoint data.
-template <int D>
-__global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, CompactParams cp, int merge_blocks) {
+// Second launch of the fused step where pairs were cut: one workgroup per sequence that appends the rows of its path, and chooses
+// that first where the attention launch has not, then the merge blocks.  The jobs touch disjoint data.
+template <int D, bool kAccept>
+__global__ __launch_bounds__(256) void verify_tail_short_kernel(AttnParams p, AcceptParams ap, CompactParams cp, int merge_blocks) {
     if ((int)blockIdx.x >= p.B) {
         const int m = blockIdx.x - p.B, pair = m / merge_blocks, seq = pair / p.Hkv;
         merge_block<D>(p, seq, pair - seq * p.Hkv, m - pair * merge_blocks);
         return;
     }
-    __shared__ AppendShared sh;
-    kv_append(cp, blockIdx.x, threadIdx.x, sh);
+    step_tail<kAccept>(ap, cp, blockIdx.x, threadIdx.x);
 }
 
 template <int D, bool kStep, bool kJoin, bool kCut = false>
@@ -931,12 +930,20 @@ hipError_t launch_all(const AttnParams &p, hipStream_t stream, hipEvent_t ev_sta
         if (e != hipSuccess || !cp->k_tree) return e;      // (in-cache layout: the rows move in a launch of their own)
         return launch_kv_compact(*cp, stream);
     }
-    const hipError_t e = step ? launch_main<D, true, false, true>(p, stream, ev_start, ev_stop, ap, cp, nullptr)
-                              : launch_main<D, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
+    // Who accepts where pairs are cut.  In the attention launch acceptance lengthens a copying wavefront's work; in the second one
+    // it stands in front of an append, beside the merge of B Hkv M rows.  Up to as many rows as here the append is the longer of the
+    // two, and the step 0.3 to 1.6 us shorter without acceptance in front of it (16 sequences of 8 heads, 0.2 to 0.8 K positions, 16
+    // rows, head dimension 64: 15.4 -> 14.9 us).  With more the merge is, and acceptance beside it costs nothing, in the attention launch 0.2 to
+    // 1.8 us (the same with 128 rows 20.1 -> 21.8; 32 of 4 heads at head dimension 128 24.9 -> 25.7).
+    const bool rides = step && p.B * p.Hkv * ((p.M + 7) / 8) <= 640;
+    const hipError_t e = rides ? launch_main<D, true, false, true>(p, stream, ev_start, ev_stop, ap, cp, nullptr)
+                               : launch_main<D, false, false>(p, stream, ev_start, ev_stop, nullptr, nullptr, nullptr);
     if (e != hipSuccess || p.n_splits == 1) return e;
     const int blocks = (p.M + 7) / 8 * (D / 64);           // of 8 rows x 8 chunks, four wavefronts
-    if (step && cp->k_tree) {                              // (in-cache layout: the rows move in a launch of their own)
-        hipLaunchKernelGGL(verify_tail_short_kernel<D>, dim3(p.B + p.B * p.Hkv * blocks), dim3(256), 0, stream, p, *cp, blocks);
+    if (step && (!rides || cp->k_tree)) {                  // (in-cache layout: the rows move in a launch of their own)
+        const dim3 grid(p.B + p.B * p.Hkv * blocks);
+        if (rides) hipLaunchKernelGGL((verify_tail_short_kernel<D, false>), grid, dim3(256), 0, stream, p, *ap, *cp, blocks);
+        else hipLaunchKernelGGL((verify_tail_short_kernel<D, true>), grid, dim3(256), 0, stream, p, *ap, *cp, blocks);
         return note_hip_error("launch verify_tail_short_kernel", hipGetLastError());
     }
     hipLaunchKernelGGL(merge_short_kernel<D>, dim3(blocks, p.Hkv, p.B), dim3(256), 0, stream, p.workspace, p.out, p.n_splits, p.M, p.Hkv,

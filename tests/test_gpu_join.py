@@ -231,7 +231,9 @@ def test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B
 
 @pytest.mark.parametrize("B,Hkv,G,D,T,lens,splits", [
     (256, 1, 4, 128, 24, [70] * 256, 0), (257, 1, 4, 128, 24, [70] * 257, 0),      # ring kernel: as many sequences as workgroups, one more
-    (5, 2, 4, 128, 32, [900, 64, 0, 1, 65], 0), (5, 2, 4, 128, 33, [900, 64, 0, 1, 65], 0)])   # one full chunk of rows, two
+    (5, 2, 4, 128, 32, [900, 64, 0, 1, 65], 0), (5, 2, 4, 128, 33, [900, 64, 0, 1, 65], 0),    # one full chunk of rows, two
+    (16, 8, 1, 64, 40, [200] * 16, 2), (16, 8, 1, 64, 41, [200] * 16, 2),          # short problems, cut pairs: 640 sets of eight rows to merge, 768
+    (16, 8, 1, 128, 40, [200] * 16, 2), (16, 8, 1, 128, 41, [200] * 16, 2)])
 @pytest.mark.parametrize("in_cache", [False, True])
 def test_on_both_sides_of_the_rules_for_who_accepts(R, B, Hkv, G, D, T, lens, splits, in_cache, tune):
     test_a_path_chosen_by_the_attention_launch_is_the_one_of_separate_calls(R, B, Hkv, G, D, T, lens, splits, in_cache, tune)
