@@ -483,8 +483,6 @@ __device__ __forceinline__ void static_for(F &&f) {
     static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
 }
 
-// What a range workgroup knows once it has found its place: its share [lo, hi) of the tile axis, where
-// to read page ids from while the list is written, and the clamped lengths in LDS (or null).
 // A part of a kernel's arguments, kOffset bytes into them, read where it is used: read at the kernel's entry, as the compiler
 // would, what is only needed behind the main loop sits in scalar registers all the way and pushes others out.
 template <typename T, size_t kOffset>
@@ -497,6 +495,8 @@ __device__ __forceinline__ T late_argument() {
     return t;
 }
 
+// What a range workgroup knows once it has found its place: its share [lo, hi) of the tile axis, where
+// to read page ids from while the list is written, and the clamped lengths in LDS (or null).
 struct RangeSetup {
     TilePos lo, hi;
     const int32_t *table;

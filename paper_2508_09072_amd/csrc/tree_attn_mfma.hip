@@ -878,7 +878,7 @@ __device__ __forceinline__ void merge_body(const AttnParams &p, int b, int hkv, 
 }
 
 // (What its first loads need arrives in scalar registers with the launch, as in merge_short_kernel: attention of 24 sequences of 0.3
-// to 3 K positions, head dimension 64, 38.1 -> 37.5 us.)
+// to 3 K positions, head dimension 64, 45.2 -> 45.0 us.)
 template <int D>
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(int32_t *pair_info, float *workspace, int32_t *range_tiles, uint16_t *out,
                                                               int32_t Hkv, int32_t merge_groups, int32_t M, int32_t rows_per_wg,

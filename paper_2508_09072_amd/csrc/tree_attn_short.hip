@@ -322,10 +322,11 @@ struct JoinShared {
 // or where a pair's shares leave a keeper no place).  Acceptance reads tokens only and writes nothing that an attention launch
 // reads, so the first copying wavefront of a sequence's first workgroup does it: the tokens arrive with the page ids, and when
 // the last tile has landed it chooses the path, while the others compute that tile and write their records.  The accepted rows
-// wait for the next launch, as everybody reads the lengths.  In the second launch, where acceptance was before for pairs that are
-// cut, it stood in front of the append and made it the longest job there: one prompt of 4 K tokens 17.6 -> 16.5 us (17.15 with
-// the path chosen in front of the wait for the first tile, which that workgroup's others then wait for), 8 K 21.2 -> 20.4, 128
-// nodes 24.2 -> 22.0; whole pairs (44 sequences of 237 tokens, captured), in front of the first tile before, 32.2 -> 28.3.
+// wait for the next launch, as everybody reads the lengths.  Where pairs are cut and the second launch has little to merge (the
+// rule is at the launch) acceptance stood in front of the append there and made it the longest job: one prompt of 4 K tokens 17.9 ->
+// 17.3 us (half of that with the path chosen in front of the wait for the first tile, which that workgroup's others then wait for), 8 K
+// 22.3 -> 21.5, 128 nodes 22.3 -> 21.4.  Whole pairs (44 sequences of 237 tokens, captured), chosen in front of the first tile before,
+// 30.6 -> 27.2.
 template <int D, bool kStep, bool kJoin>
 __device__ __forceinline__ void tree_attn_short_body(const AttnParams &p, const JoinParams &j) {
     constexpr bool kDeep = D == 128;
@@ -850,7 +851,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_
     tree_attn_short_body<D, false, false>(p, JoinParams());
 }
 template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(StepParams p) {   // (cut pairs of a step in two launches)
+__global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void tree_attn_short_kernel(StepParams p) {   // (cut pairs of a step whose paths it chooses; a trace tells the two apart by their argument)
     tree_attn_short_body<D, true, false>(p.attn, JoinParams());
 }
 template <int D>
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? kWavesPerSimd64 : 2) void verif
 // What its first loads need stands in front of the other arguments, one by one: those words arrive in scalar registers with the
 // launch (members of a structure do not), and the records are not asked for a trip to memory later.  16-layer decoding step of three
 // users 259.6 -> 254.0 us.  (The same in front of the attention kernels' arguments: a step of 512 tokens 7.98 -> 8.12, one prompt of 4 K
-// tokens alike; in front of verify_tail_short_kernel's, whose acceptance is what takes time: 17.7 -> 18.5 us.)
+// tokens alike; in front of verify_tail_short_kernel's, where the path and the append are what takes time: 17.7 -> 18.5 us.)
 template <int D>
 __global__ __launch_bounds__(256) void merge_short_kernel(float *workspace, uint16_t *out, int32_t n_splits, int32_t M, int32_t Hkv,
                                                           int32_t n_row_chunks, int32_t T, int32_t Hq, int32_t G, float g_rcp, AttnParams p) {
