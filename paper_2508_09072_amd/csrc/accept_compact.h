@@ -1,5 +1,6 @@
 // Device code of the acceptance and compaction steps, shared by their own kernels and by the launches of
-// reader_verify_step: the tails do both, and so do workgroups of the attention launch of short problems (or it accepts only).
+// reader_verify_step: the tails do both, and so do workgroups of the attention launch of short problems; or the attention launch
+// accepts, of short problems and in the 128-row ring kernel, and the tail appends.
 //
 // Acceptance (Algorithm 5; Appendix C invariants 2-3): one 64-lane wavefront per
 // sequence.  Each lane owns up to two tree nodes.  A node "matches" when its drafted
